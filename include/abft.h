@@ -73,7 +73,8 @@ typedef enum {
      * step (Table 1's M_t / 2) and one packed add per further B fragment.  The roundings of those
      * adds (2^-11 per add in F16, 2^-8 in BF16) widen the tolerance (abft_tolerance_half_coeff):
      * faults smaller than about an rms of C in one element go unseen.  ABFT_THREAD keeps the
-     * checksum exact instead, at twice (BF16: three times) the extra MFMAs. */
+     * checksum exact instead: the matrix unit adds the B fragments (each multiplied apart into
+     * shared checksum accumulators; I8: two digits of their sum), no vector arithmetic. */
     ABFT_THREAD_HALF = 5,
     /* Two-sided thread-level ABFT (Sec. 5.2.1, Table 1 middle column): checksums of both the A
      * fragments and the B fragments of the wavefront tile, added up in the operand type, one extra

@@ -30,9 +30,9 @@ namespace {
 // (the last term for the global scheme only).  2^-24 is the unit
 // roundoff of the fp32 accumulators; an accumulator that takes K products carries a
 // random-walk error ~ 2^-24 sqrt(K) |C_ij| / 2.4 and the errors of the entries add in
-// quadrature under the output summation.  u_chi covers the tile checksum operand of the
-// thread-level scheme, which is exact to 22 (fp16: two pieces) / 24 (bf16: three
-// pieces) bits of the fp32 column sums.  The ||.||_1 term covers a small coherent bias of the
+// quadrature under the output summation.  u_chi (thread-level schemes) is what a
+// tile checksum held in two fp16 / three bf16 pieces would be off by; the checksum the kernels
+// form is exact (the matrix unit adds the fragments), so it is headroom there.  The ||.||_1 term covers a small coherent bias of the
 // matrix unit's accumulation (measured: up to 2e-4 * 2^-24 * K per entry, same sign for all
 // entries of a tile with same-sign operands); in the thread-level scheme both sides of the
 // comparison come out of the same unit and the bias cancels.

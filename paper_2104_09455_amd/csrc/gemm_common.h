@@ -324,127 +324,34 @@ __device__ __forceinline__ i32x4 gather16(const char* base, long long stride_byt
 // Tile-local weight checksum for the thread-level scheme (Sec. 5.2.1-5.2.2): per k step the
 // checksum of the wavefront tile's B fragments,
 //   chi[k] = sum over the wave tile's columns of B[k][.],
-// goes to the matrix unit as extra B operand(s), multiplied with every A fragment.  A lane holds
-// one column of each of the TN fragments (MFMA block columns), so the vector unit adds the TN
-// fragments element by element and the matrix unit finishes the sum over the 32 columns of
-// the block: summing the checksum accumulators over their columns at the end gives
-// sum_k A[i][k] chi[k].
-//  * Plain form (TN = 1): nothing to add, the operand is the fragment itself (one block
-//    column per wavefront tile: the scheme coincides with replication, Table 1's M_t / 2 extra
-//    MMAs being all of them).
-//  * Split form (TN >= 2): the element-wise sums are handed on in exactly representable
-//    pieces, one operand and one set of accumulators per piece (below).
+// is multiplied with every A fragment; summing the checksum accumulators over their columns at
+// the end gives sum_k A[i][k] chi[k].  A lane holds one column of each of the TN fragments
+// (MFMA block columns).
+//  * fp16 / bf16: the matrix unit adds the fragments.  A . (b_0 + b_1) = A . b_0 + A . b_1, so the
+//    fragments go out one after the other, as they are, into the same checksum accumulators (two
+//    fragments share a block): exact operands and no vector arithmetic at all.  With one fragment
+//    per wavefront tile these are Table 1's M_t / 2 extra MMAs, with two as many as the sum in
+//    exactly representable pieces takes (fp16: hi + lo), with four twice (bf16: 4 / 3 of) that,
+//    but the pieces cost 14 (fp16) to 22 (bf16) vector instructions per register and k step, which
+//    four-cycle vector issue does not hide behind 32-cycle MFMAs.  Device time with pieces / so /
+//    unprotected: 3 x 3 convolution 256 -> 256 on 12544 rows, bf16 60 / 41 / 27 us; 12544 x 1024 x
+//    256 bf16 32 / 23 / 18; 3 x 3 convolution 64 -> 64 on 200704 rows, fp16 72 / 63 / 45.
+//  * int8: the sums are formed in packed 16-bit lanes and handed on in two digits, one operand
+//    and one set of accumulators per digit (below): integer accumulators that take several products
+//    could wrap where the product's own do not.
 // ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
-// Split form of the tile checksum for fp16: no cross-lane step at all.  The column sums s (fp32, one per lane and k) are handed to
-// the matrix unit as two operands, hi = fl16(s) and lo = fl16((s - hi) * 2^11), each
-// multiplied with the A fragments into its own accumulators; the checksum product is
-// sum(hi accumulators) + 2^-11 sum(lo accumulators).  Twice the checksum MFMAs of the
-// folded form, but half the vector work -- the right trade where the matrix unit idles.
-// v_fma_mix_f32 converts and accumulates a half in one instruction.
-// ---------------------------------------------------------------------------
-template <int TN>
-struct TileChecksumSplitF16 {
-    static __device__ __forceinline__ float acc_lo(int packed, float s) {
-        float r;
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(s));
-        return r;
-    }
-    static __device__ __forceinline__ float acc_hi(int packed, float s) {
-        float r;
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(s));
-        return r;
-    }
-    // s - (half `sel` of packed), exact
-    static __device__ __forceinline__ float sub_lo(int packed, float s) {
-        float r;
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(s));
-        return r;
-    }
-    static __device__ __forceinline__ float sub_hi(int packed, float s) {
-        float r;
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(s));
-        return r;
-    }
-    // weight of the low operand's products in the checksum sum
-    static constexpr double LO_SCALE = TN == 2 ? 1.0 : 1.0 / 2048.0;
-    static __device__ __forceinline__ void make(const i32x4 (&b)[TN], i32x4& hi, i32x4& lo) {
-        if constexpr (TN == 2) {
-            // two fragments: an error-free sum in packed fp16 (six instructions per register):
-            // hi = fl16(x + y) and lo = (x + y) - hi exactly, subnormal results included (the
-            // matrix unit takes fp16 subnormals as they are)
-            typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const f16x2 x = bitcast<f16x2>(b[0][d]), y = bitcast<f16x2>(b[1][d]);
-                const f16x2 s = x + y;
-                const f16x2 yy = s - x;
-                const f16x2 e = (x - (s - yy)) + (y - yy);
-                hi[d] = bitcast<int>(s);
-                lo[d] = bitcast<int>(e);
-            }
-            return;
-        }
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                s0 = acc_lo(b[j][d], s0);
-                s1 = acc_hi(b[j][d], s1);
-            }
-            // round to nearest (v_cvt_pk_f16_f32): hi is within 2^-11 of s, lo within 2^-11 of the
-            // remainder, so hi + 2^-11 lo matches s to 22 bits
-            typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-            f16x2 hp;
-            hp[0] = (_Float16)s0;
-            hp[1] = (_Float16)s1;
-            const int h = bitcast<int>(hp);
-            const float d0 = sub_lo(h, s0) * 2048.f, d1 = sub_hi(h, s1) * 2048.f;
-            f16x2 lp;
-            lp[0] = (_Float16)d0;
-            lp[1] = (_Float16)d1;
-            hi[d] = h;
-            lo[d] = bitcast<int>(lp);
-        }
-    }
-};
+// two bf16 values of a register, widened; two floats rounded to nearest even and packed
+__device__ __forceinline__ float bf16_lo(int packed) { return bitcast<float>(packed << 16); }
+__device__ __forceinline__ float bf16_hi(int packed) { return bitcast<float>((int)(packed & 0xffff0000)); }
+__device__ __forceinline__ int bf16_pack(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    bf16x2 h;
+    h[0] = (__bf16)a;
+    h[1] = (__bf16)b;
+    return bitcast<int>(h);
+}
 
-// Split form for bf16: the column sums (fp32, exact: a few bf16 values) go out as three bf16
-// operands hi + mid + lo = s exactly (3 x 8 significant bits), each multiplied with the A
-// fragments into its own accumulators.  No cross-lane step.
-template <int TN>
-struct TileChecksumSplitBF16 {
-    static __device__ __forceinline__ float lo_f(int packed) { return bitcast<float>(packed << 16); }
-    static __device__ __forceinline__ float hi_f(int packed) { return bitcast<float>((int)(packed & 0xffff0000)); }
-    static __device__ __forceinline__ int pack(float a, float b) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        bf16x2 h;
-        h[0] = (__bf16)a;  // round to nearest even
-        h[1] = (__bf16)b;
-        return bitcast<int>(h);
-    }
-    static __device__ __forceinline__ void make(const i32x4 (&b)[TN], i32x4& x0, i32x4& x1, i32x4& x2) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                s0 += lo_f(b[j][d]);
-                s1 += hi_f(b[j][d]);
-            }
-            const int h = pack(s0, s1);
-            const float r0 = s0 - lo_f(h), r1 = s1 - hi_f(h);  // exact remainders
-            const int m = pack(r0, r1);
-            const float q0 = r0 - lo_f(m), q1 = r1 - hi_f(m);
-            x0[d] = h;
-            x1[d] = m;
-            x2[d] = pack(q0, q1);
-        }
-    }
-};
-
-// Split form for int8: the column sums (at most 10 bits) are formed in packed 16-bit lanes
+// The tile checksum of int8: the column sums (at most 10 bits) are formed in packed 16-bit lanes
 // (even and odd bytes of each register apart) and go out as two operands of balanced
 // base-256 digits, s = lo + 256 hi exactly.  No cross-lane step.
 template <int TN>
@@ -465,22 +372,6 @@ struct TileChecksumSplitI8 {
             lo[d] = (bitcast<int>(le) & 0x00ff00ff) | ((bitcast<int>(lod) & 0x00ff00ff) << 8);
             hi[d] = (bitcast<int>(he) & 0x00ff00ff) | ((bitcast<int>(hod) & 0x00ff00ff) << 8);
         }
-    }
-};
-
-// The split form for any operand type: NP operands x[0..NP) whose accumulators, weighted with
-// scale(piece) (int8: 1 and 256, applied in integers by the epilogue), add up to the checksum
-// product.
-template <int DT, int TN>
-struct TileChecksumSplit {
-    static constexpr int NP = DT == DT_BF16 ? 3 : 2;
-    static __device__ __forceinline__ void make(const i32x4 (&b)[TN], i32x4 (&x)[NP]) {
-        if constexpr (DT == DT_F16) TileChecksumSplitF16<TN>::make(b, x[0], x[1]);
-        else if constexpr (DT == DT_BF16) TileChecksumSplitBF16<TN>::make(b, x[0], x[1], x[2]);
-        else TileChecksumSplitI8<TN>::make(b, x[0], x[1]);
-    }
-    static constexpr double scale(int piece) {
-        return (DT == DT_F16 && piece == 1) ? TileChecksumSplitF16<TN>::LO_SCALE : 1.0;
     }
 };
 
@@ -540,31 +431,35 @@ struct ChecksumDot {
     }
 };
 
-// Which form of the tile checksum a configuration uses, and how many checksum
-// accumulators per A fragment that takes.
+// Which form of the tile checksum a configuration uses, how many checksum accumulator blocks per
+// A fragment and how many MFMAs per A fragment and k step that takes.
 template <class CFG>
 struct ChecksumForm {
-    static constexpr bool SPLIT = CFG::TN >= 2;
-    static constexpr int NP = SPLIT ? (CFG::DT == DT_BF16 ? 3 : 2) : 1;  // checksum operands per k step
+    static constexpr bool DIGITS = CFG::DT == DT_I8 && CFG::TN >= 2;
+    static constexpr int NP = DIGITS ? 2 : (CFG::TN >= 2 ? CFG::TN / 2 : 1);
     static constexpr int NCHK = NP * CFG::TM;
+    static constexpr int MFMAS = DIGITS ? 2 : CFG::TN;
+    static_assert(CFG::TN == 1 || CFG::TN % 2 == 0, "fragments of B in pairs");
 };
 // The thread-level scheme's extra MFMAs of one k step (a: A fragments, b: B fragments).
 template <class CFG>
 __device__ __forceinline__ void thread_checksum_step(const i32x4 (&a)[CFG::TM], const i32x4 (&b)[CFG::TN],
                                                      typename Mma<CFG::DT, CFG::MI>::Acc (&chk)[ChecksumForm<CFG>::NCHK]) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
-    constexpr int TM = CFG::TM;
-    if constexpr (ChecksumForm<CFG>::SPLIT) {
-        typedef TileChecksumSplit<CFG::DT, CFG::TN> SPL;
-        i32x4 x[SPL::NP];
-        SPL::make(b, x);
+    constexpr int TM = CFG::TM, TN = CFG::TN, NP = ChecksumForm<CFG>::NP;
+    if constexpr (ChecksumForm<CFG>::DIGITS) {
+        i32x4 x[2];
+        TileChecksumSplitI8<TN>::make(b, x[0], x[1]);
 #pragma unroll
-        for (int pc = 0; pc < SPL::NP; ++pc)
+        for (int pc = 0; pc < 2; ++pc)
 #pragma unroll
             for (int i = 0; i < TM; ++i) chk[pc * TM + i] = MMA::run(a[i], x[pc], chk[pc * TM + i]);
     } else {
+        // (fragments pc and pc + NP share a block: its two MFMAs of a step are TM * NP apart)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) chk[i] = MMA::run(a[i], b[0], chk[i]);
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) chk[(j % NP) * TM + i] = MMA::run(a[i], b[j], chk[(j % NP) * TM + i]);
     }
 }
 // Redundant accumulator blocks a wavefront carries under each scheme.
@@ -587,8 +482,7 @@ __device__ __forceinline__ i32x4 add_in_operand_type(const i32x4& x, const i32x4
             typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
             out[d] = bitcast<int>((f16x2)(bitcast<f16x2>(x[d]) + bitcast<f16x2>(y[d])));
         } else {
-            typedef TileChecksumSplitBF16<2> BF;
-            out[d] = BF::pack(BF::lo_f(x[d]) + BF::lo_f(y[d]), BF::hi_f(x[d]) + BF::hi_f(y[d]));
+            out[d] = bf16_pack(bf16_lo(x[d]) + bf16_lo(y[d]), bf16_hi(x[d]) + bf16_hi(y[d]));
         }
     }
     return out;
@@ -741,12 +635,12 @@ template <class CFG, int MODE>
 __device__ __forceinline__ typename std::conditional<CFG::DT == DT_I8, long long, double>::type lane_check_sum(
     const typename Mma<CFG::DT, CFG::MI>::Acc (&chk)[(CheckRegs<CFG, MODE>::N)], int lane) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
-    constexpr int MI = CFG::MI, TM = CFG::TM, TN = CFG::TN;
-    constexpr bool SPLIT_FORM = MODE == MODE_THREAD && ChecksumForm<CFG>::SPLIT;
+    constexpr int TM = CFG::TM;
+    constexpr bool DIGITS = MODE == MODE_THREAD && ChecksumForm<CFG>::DIGITS;
     constexpr int NBLK = CheckRegs<CFG, MODE>::N;
     if constexpr (CFG::DT == DT_I8) {
         long long rsum = 0;
-        if constexpr (SPLIT_FORM) {
+        if constexpr (DIGITS) {
             // accumulators of the low-digit operand, then 256 x those of the high-digit one
 #pragma unroll
             for (int pc = 0; pc < 2; ++pc) {
@@ -775,26 +669,11 @@ __device__ __forceinline__ typename std::conditional<CFG::DT == DT_I8, long long
         return rsum;
     } else {
         double rsum = 0.0;
-        if constexpr (SPLIT_FORM) {
-            typedef TileChecksumSplit<CFG::DT, TN> SPL;
 #pragma unroll
-            for (int pc = 0; pc < SPL::NP; ++pc) {
-                double part = 0.0;
+        for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int r = 0; r < MMA::NACC; r += 4)
-                        part += (double)((chk[pc * TM + i][r] + chk[pc * TM + i][r + 1]) +
-                                         (chk[pc * TM + i][r + 2] + chk[pc * TM + i][r + 3]));
-                rsum += part * SPL::scale(pc);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NBLK; ++i)
-#pragma unroll
-                for (int r = 0; r < MMA::NACC; r += 4)
-                    rsum += (double)((chk[i][r] + chk[i][r + 1]) + (chk[i][r + 2] + chk[i][r + 3]));
-        }
+            for (int r = 0; r < MMA::NACC; r += 4)
+                rsum += (double)((chk[i][r] + chk[i][r + 1]) + (chk[i][r + 2] + chk[i][r + 3]));
         return rsum;
     }
 }

@@ -413,11 +413,13 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_fast_kernel(const GemmArgs 
                     // thread-level: the sums of the B fragments) is spread between the MFMAs
                     constexpr int NF = TM + TN;
                     constexpr int NM = TM * TN + (MDOT ? 1 : 0) +
-                                       (MODE == MODE_REPL ? TM * TN : (mode_is_wave_level(MODE) ? CheckRegs<CFG, EMODE>::N : 0));
-                    // vector instructions per MFMA slot: the exact tile checksum's pieces cost about
-                    // 14 (fp16, int8) or 22 (bf16) instructions per 16 bytes of each lane's B
-                    // fragments; sums in the operand type one (fp16) or six (bf16) per register
-                    constexpr int VSTEP = MODE == MODE_THREAD && ChecksumForm<CFG>::SPLIT ? (DT == DT_BF16 ? 22 : 14) * 4
+                                       (MODE == MODE_REPL ? TM * TN
+                                                           : (MODE == MODE_THREAD ? TM * ChecksumForm<CFG>::MFMAS
+                                                                                  : (mode_is_wave_level(MODE) ? CheckRegs<CFG, EMODE>::N : 0)));
+                    // vector instructions per MFMA slot: the digits of int8's tile checksum cost about 14
+                    // instructions per register of the lane's B fragments; sums in the operand type
+                    // one (fp16) or six (bf16)
+                    constexpr int VSTEP = MODE == MODE_THREAD && ChecksumForm<CFG>::DIGITS ? 14 * 4
                                           : (MODE == MODE_THREAD_H ? (TN - 1) * 4 * (DT == DT_BF16 ? 6 : 1)
                                              : (MODE == MODE_TWOSIDED ? (TN + TM - 2) * 4 * (DT == DT_BF16 ? 6 : 1)
                                                 : (MDOT ? 4 * TM : 0)));  // (matrix-unit dot: the selects of its operands)
