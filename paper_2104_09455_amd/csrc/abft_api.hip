@@ -109,7 +109,11 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
                             (fast_ok || !cfg_info_host(force).fast || (aligned16 && cfg_is_stream(force)));
     // (the 256 x 256 tile carries no wavefront-level scheme: a forced choice of it does not apply to those)
     if (force_fits && !((force == CFG_F256W || force == CFG_F256N || force == CFG_F256S || force == CFG_F128E) && mode == ABFT_THREAD)) return force;
-    if (M <= 16 && !aligned16) return CFG_G16;
+    // (a long k loop: the groups of the 64 x 64 tile that share it outweigh the rows of zeros: 16 x 4096 x
+    // 4095 27 against 45 us; near level at half to a quarter of that, 16 x 512 x 1023 9.9 / 10.7; 16 x 512
+    // x 300 6.4 / 5.5)
+    const long long nkt_gen = cdiv((long long)K * esize(dt), 128);
+    if (M <= 16 && !aligned16) return nkt_gen >= 32 ? CFG_G64K : CFG_G16;
     auto tiles = [&](int id) {
         CfgInfo ci = cfg_info_host(id);
         return cdiv(M, ci.bm) * cdiv(N, ci.bn);
@@ -172,6 +176,12 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
     }
     if (tiles(CFG_G128) >= 192) return CFG_G128;
     if (tiles(CFG_G64) >= 1024) return CFG_G128;
+    // Four groups sharing the k loop where at most one such tile per compute unit is there (one tile in
+    // flight per group, so four times the loads): from five k tiles on (300 x 1000 x 257 thread-level 7.0
+    // against 7.3 us, K = 400 7.1 / 8.3, 1000 x 1000 x 1000 12.9 / 21.0; three tiles 6.3 / 5.9); with two
+    // rounds of them only for long loops (400 x 4096 x 2048 38 / 40, 512 x 4096 x 4096 69 / 75; 1024 x
+    // 2048 x 1024 23.5 / 22.3).
+    if (tiles(CFG_G64) <= 256 ? nkt_gen >= 5 : (tiles(CFG_G64) <= 512 && nkt_gen >= 32)) return CFG_G64K;
     return CFG_G64;
 }
 

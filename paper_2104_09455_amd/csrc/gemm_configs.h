@@ -29,7 +29,8 @@ namespace abft {
 //    S128    64 x  64, 2 stages per wavefront                         up to about one tile per compute unit
 //  G* run the generic kernel (any alignment, layout, K):
 //    G128 128 x 128, G64 64 x 64 (32x32 MFMA shapes), G16 16 x 64 (16x16 shapes; M <= 16)
-enum CfgId { CFG_F256W = 0, CFG_F128, CFG_F128T, CFG_F64T, CFG_S32, CFG_S64, CFG_S128, CFG_G128, CFG_G64, CFG_G16, CFG_F256N, CFG_F256S, CFG_F128E, CFG_COUNT };
+//    G64K 64 x 64 with four groups of four wavefronts sharing the k tiles: at most about one tile per compute unit
+enum CfgId { CFG_F256W = 0, CFG_F128, CFG_F128T, CFG_F64T, CFG_S32, CFG_S64, CFG_S128, CFG_G128, CFG_G64, CFG_G16, CFG_F256N, CFG_F256S, CFG_F128E, CFG_G64K, CFG_COUNT };
 
 template <int DT, int ID>
 struct CfgOf;
@@ -46,11 +47,12 @@ template <int DT> struct CfgOf<DT, CFG_S64>   { typedef Cfg<DT, 32, 1, 2, 1, 1, 
 template <int DT> struct CfgOf<DT, CFG_S128>  { typedef Cfg<DT, 32, 2, 2, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 4; };
 template <int DT> struct CfgOf<DT, CFG_G128>  { typedef Cfg<DT, 32, 2, 2, 2, 2, 128> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_G64>   { typedef Cfg<DT, 32, 1, 1, 2, 2, 128> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_G64K>  { typedef Cfg<DT, 32, 1, 1, 2, 2, 128> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 4; };
 template <int DT> struct CfgOf<DT, CFG_G16>   { typedef Cfg<DT, 16, 1, 1, 1, 4, 256> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 1; };
 
 constexpr bool cfg_is_stream(int id) { return id == CFG_S32 || id == CFG_S64 || id == CFG_S128; }
 
-// threads: of one WAVES_M x WAVES_N grid of wavefronts (a streaming launch has kways times as many);
+// threads: of one WAVES_M x WAVES_N grid of wavefronts (a launch has kways times as many);
 // kway_bytes: bytes of k that one wavefront takes in turn when kways wavefronts share a tile
 struct CfgInfo {
     int bm, bn, bk_bytes, wm, wn, threads, lds_bytes, fast, kways, kway_bytes, mi;
@@ -62,8 +64,8 @@ constexpr CfgInfo cfg_info() {
     constexpr int ns = CfgOf<DT_F16, ID>::NSTAGE;
     constexpr int kw = CfgOf<DT_F16, ID>::KWAYS;
     constexpr int lds = cfg_is_stream(ID) ? kw * ns * ((C::BM + C::BN) * 128 + 768)
-                                          : (ns ? ns * ((C::BM + C::BN) * 128 + 1024) + 512 : C::LDS_BYTES);
-    return CfgInfo{C::BM, C::BN, C::BKB, C::WM, C::WN, C::THREADS, lds, ns ? 1 : 0, kw, cfg_is_stream(ID) ? 128 : 32, C::MI};
+                                          : (ns ? ns * ((C::BM + C::BN) * 128 + 1024) + 512 : kw * C::LDS_BYTES);
+    return CfgInfo{C::BM, C::BN, C::BKB, C::WM, C::WN, C::THREADS, lds, ns ? 1 : 0, kw, kw > 1 ? C::BKB : 32, C::MI};
 }
 
 inline CfgInfo cfg_info_host(int id) {
@@ -80,6 +82,7 @@ inline CfgInfo cfg_info_host(int id) {
         case CFG_S128: return cfg_info<CFG_S128>();
         case CFG_G128: return cfg_info<CFG_G128>();
         case CFG_G64: return cfg_info<CFG_G64>();
+        case CFG_G64K: return cfg_info<CFG_G64K>();
         default: return cfg_info<CFG_G16>();
     }
 }

@@ -1,19 +1,45 @@
 // Generic ABFT-protected MFMA GEMM kernel for gfx950 (MI355X): any shape, alignment,
 // weight layout, and convolutions read as an implicit im2col matrix.
 //
-// Data flow per workgroup: 16-byte (or element-wise) global loads -> registers -> LDS
-// (double buffered, padded rows) -> ds_read_b128 MFMA fragments -> accumulators ->
-// checksum epilogue -> C.
+// Data flow per workgroup: global loads -> registers -> LDS (double buffered, padded rows) ->
+// ds_read_b128 MFMA fragments -> accumulators -> checksum epilogue -> C.  Rows that are contiguous
+// along k are read 16 bytes at a time whatever their alignment (the last chunk of a row from the
+// last 16 bytes of the row, shifted down); weights stored K x N are read four bytes of a row at a
+// time, eight rows of k per thread, and turned in registers on the way to LDS.  Only convolutions
+// whose channels fill no chunk, and rows of less than 16 bytes, are gathered by the element.
+// Bound: the latency of a k tile's loads (one tile in flight per group of wavefronts), so where
+// the chip has room KG groups of wavefronts share a tile along k.  Thread-level, with element gathers
+// and one group / so: 511 x 1000 x 2047 fp16, weights K x N, 92 / 21 us; 256 x 4096 x 4096 129 / 36;
+// 2048 x 4096 x 4096 445 / 161 (unprotected 267 / 120); 16 x 4096 x 4095, weights N x K, 114 / 27.
 #pragma once
 #include "gemm_common.h"
 
 namespace abft {
 
+// 16 / 4 bytes at any address (global memory takes unaligned vector loads)
+__device__ __forceinline__ i32x4 ld16u(const char* p) {
+    i32x4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+__device__ __forceinline__ int ld4u(const char* p) {
+    int v;
+    __builtin_memcpy(&v, p, 4);
+    return v;
+}
+// 16 bytes shifted down by `bytes` (0 .. 15), zeros at the top
+__device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
+    unsigned __int128 u = bitcast<unsigned __int128>(v);
+    return bitcast<i32x4>(u >> (8 * bytes));
+}
+
 // ---------------------------------------------------------------------------
-// The kernel
+// The kernel.  KG groups of CFG::THREADS threads each own the whole workgroup tile and take the k
+// tiles t with t % KG == group, each with LDS buffers of its own; at the end the groups' partial
+// tiles (and redundant accumulators) are added in group order and group 0 checks and stores.
 // ---------------------------------------------------------------------------
-template <class CFG, int MODE, bool INJ, bool CONV, bool GENERIC>
-__global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
+template <class CFG, int MODE, bool INJ, bool CONV, int KG>
+__global__ __launch_bounds__(CFG::THREADS * KG) void gemm_kernel(const GemmArgs p) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
     typedef typename MMA::Acc Acc;
     typedef typename MMA::AccT AccT;
@@ -26,9 +52,11 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
     constexpr int NGRP = 64 / MI;  // k-groups per fragment (2 or 4)
     constexpr bool IS_INT = CFG::DT == DT_I8;
 
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+    extern __shared__ __attribute__((aligned(16))) char smem_all[];
 
-    const int tid = threadIdx.x;
+    const int grp = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / CFG::THREADS) : 0;
+    const int tid = KG > 1 ? (int)threadIdx.x - grp * CFG::THREADS : (int)threadIdx.x;
+    char* const smem = smem_all + grp * CFG::LDS_BYTES;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wave_m = wave / CFG::WAVES_N, wave_n = wave % CFG::WAVES_N;
@@ -64,7 +92,7 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
             a_ih0[t] = oh * p.stride - p.pad;
             a_iw0[t] = ow * p.stride - p.pad;
         }
-        int k = kc * EPC;
+        int k = grp * BK + kc * EPC;
         int tap = k / p.Cin;
         tap_c = k - tap * p.Cin;
         tap_kh = tap / p.KW;
@@ -75,10 +103,29 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
         a_iw0[0] = 0;
     }
 
+    // rows read 16 bytes at a time at any alignment: a chunk that K cuts short is read as the last 16
+    // bytes of its row and shifted down when it goes to LDS
+    const bool a_row = !CONV && !p.a_vec && K >= EPC;
+    const bool b_row = !p.b_vec && p.b_sk == 1 && K >= EPC;
+    // weights stored K x N: units of eight k times four bytes of n (four bytes of a row end inside it)
+    constexpr int NPD = 4 / ESIZE;                     // columns per four bytes
+    constexpr int NGN = BN / NPD;                      // such groups per row of the tile
+    constexpr int UNITS = NB / 2;                      // units per thread
+    static_assert(NB % 2 == 0 && CFG::THREADS * UNITS == NGN * (BK / 8), "units of the transposing loader");
+    const bool b_turn = !p.b_vec && !b_row && p.b_sn == 1 && N >= NPD;
     auto load_a = [&](int kt, i32x4(&regs)[NA]) {
         const int k0 = kt * BK + kc * EPC;  // first k of this thread's chunk
         if constexpr (!CONV) {
-            if (!GENERIC || p.a_vec) {
+            if (a_row) {
+                const int ks = k0 + EPC <= K ? k0 : K - EPC;
+#pragma unroll
+                for (int t = 0; t < NA; ++t) {
+                    const int m = bm0 + r0 + t * RPP;
+                    i32x4 v = {0, 0, 0, 0};
+                    if (m < M && k0 < K) v = ld16u(p.A + ((long long)m * p.lda + ks) * ESIZE);
+                    regs[t] = v;
+                }
+            } else if (p.a_vec) {
 #pragma unroll
                 for (int t = 0; t < NA; ++t) {
                     int m = bm0 + r0 + t * RPP;
@@ -95,7 +142,7 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
                 }
             }
         } else {
-        if (!GENERIC || p.a_vec) {
+        if (p.a_vec) {
             // a chunk never straddles a filter tap (Cin is a multiple of the chunk length)
 #pragma unroll
             for (int t = 0; t < NA; ++t) {
@@ -151,10 +198,10 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
         }
         }
     };
-    // advance this thread's filter-tap decomposition by one k-tile
+    // advance this thread's filter-tap decomposition to its group's next k-tile
     auto advance_taps = [&]() {
         if constexpr (CONV) {
-            tap_c += BK;
+            tap_c += KG * BK;
             while (tap_c >= p.Cin) {
                 tap_c -= p.Cin;
                 if (++tap_kw == p.KW) {
@@ -166,7 +213,28 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
     };
     auto load_b = [&](int kt, i32x4(&regs)[NB]) {
         const int k0 = kt * BK + kc * EPC;
-        if (!GENERIC || p.b_vec) {
+        if (b_row) {
+            const int ks = k0 + EPC <= K ? k0 : K - EPC;
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+                const int n = bn0 + r0 + t * RPP;
+                i32x4 v = {0, 0, 0, 0};
+                if (n < N && k0 < K) v = ld16u(p.B + ((long long)n * p.ldb + ks) * ESIZE);
+                regs[t] = v;
+            }
+        } else if (b_turn) {
+            // (rows past K and columns past N read valid elements, dropped on the way to LDS)
+#pragma unroll
+            for (int t = 0; t < UNITS; ++t) {
+                const int u = tid + t * CFG::THREADS, n = bn0 + (u % NGN) * NPD;
+                const char* src = p.B + (long long)(n + NPD <= N ? n : N - NPD) * ESIZE;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int k = kt * BK + (u / NGN) * 8 + e;
+                    regs[2 * t + (e >> 2)][e & 3] = ld4u(src + (long long)(k < K ? k : K - 1) * p.ldb * ESIZE);
+                }
+            }
+        } else if (p.b_vec) {
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 int n = bn0 + r0 + t * RPP;
@@ -184,15 +252,73 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
             }
         }
     };
-    auto store_tiles = [&](int buf, const i32x4(&ra)[NA], const i32x4(&rb)[NB]) {
+    auto store_tiles = [&](int buf, int kt, const i32x4(&ra)[NA], const i32x4(&rb)[NB]) {
         char* as = smem + buf * CFG::STAGE_BYTES;
         char* bs = as + BM * STRIDE;
+        // (bytes by which a chunk that K cuts short was read early; a whole chunk: 0)
+        const int k0 = kt * BK + kc * EPC;
+        const int early = k0 < K && k0 + EPC > K ? (k0 + EPC - K) * ESIZE : 0;
+        const bool cut = (kt + 1) * BK > K;
+        if (a_row && cut) {
 #pragma unroll
-        for (int t = 0; t < NA; ++t)
-            *reinterpret_cast<i32x4*>(as + (r0 + t * RPP) * STRIDE + kc * 16) = ra[t];
+            for (int t = 0; t < NA; ++t)
+                *reinterpret_cast<i32x4*>(as + (r0 + t * RPP) * STRIDE + kc * 16) = shift_down(ra[t], early);
+        } else {
 #pragma unroll
-        for (int t = 0; t < NB; ++t)
-            *reinterpret_cast<i32x4*>(bs + (r0 + t * RPP) * STRIDE + kc * 16) = rb[t];
+            for (int t = 0; t < NA; ++t)
+                *reinterpret_cast<i32x4*>(as + (r0 + t * RPP) * STRIDE + kc * 16) = ra[t];
+        }
+        if (b_turn) {
+            const bool edge = cut || bn0 + BN > N;
+#pragma unroll
+            for (int t = 0; t < UNITS; ++t) {
+                const int u = tid + t * CFG::THREADS, nl = (u % NGN) * NPD, kl = (u / NGN) * 8;
+                unsigned d[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) d[e] = (unsigned)rb[2 * t + (e >> 2)][e & 3];
+                if (edge) {
+                    const int over = bn0 + nl + NPD - N;   // columns of the group beyond N (read early by as many)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if (over > 0) d[e] = over >= NPD ? 0u : d[e] >> (8 * ESIZE * over);
+                        if (kt * BK + kl + e >= K) d[e] = 0u;
+                    }
+                }
+                if constexpr (ESIZE == 2) {
+                    i32x4 c0, c1;   // eight k of column nl, of column nl + 1
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        c0[q] = (int)__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u);
+                        c1[q] = (int)__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u);
+                    }
+                    *reinterpret_cast<i32x4*>(bs + nl * STRIDE + kl * 2) = c0;
+                    *reinterpret_cast<i32x4*>(bs + (nl + 1) * STRIDE + kl * 2) = c1;
+                } else {
+                    i32x2 c[4];     // eight k of each of four columns
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const unsigned x01 = __builtin_amdgcn_perm(d[4 * h + 1], d[4 * h], 0x05010400u);
+                        const unsigned x23 = __builtin_amdgcn_perm(d[4 * h + 3], d[4 * h + 2], 0x05010400u);
+                        const unsigned y01 = __builtin_amdgcn_perm(d[4 * h + 1], d[4 * h], 0x07030602u);
+                        const unsigned y23 = __builtin_amdgcn_perm(d[4 * h + 3], d[4 * h + 2], 0x07030602u);
+                        c[0][h] = (int)__builtin_amdgcn_perm(x23, x01, 0x05040100u);
+                        c[1][h] = (int)__builtin_amdgcn_perm(x23, x01, 0x07060302u);
+                        c[2][h] = (int)__builtin_amdgcn_perm(y23, y01, 0x05040100u);
+                        c[3][h] = (int)__builtin_amdgcn_perm(y23, y01, 0x07060302u);
+                    }
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) *reinterpret_cast<i32x2*>(bs + (nl + n) * STRIDE + kl) = c[n];
+                }
+            }
+        } else if (b_row && cut) {
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+                *reinterpret_cast<i32x4*>(bs + (r0 + t * RPP) * STRIDE + kc * 16) = shift_down(rb[t], early);
+        } else {
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+                *reinterpret_cast<i32x4*>(bs + (r0 + t * RPP) * STRIDE + kc * 16) = rb[t];
+        }
     };
 
     Acc acc[TM][TN];
@@ -210,48 +336,98 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_kernel(const GemmArgs p) {
         for (int r = 0; r < MMA::NACC; ++r) chk[i][r] = 0;
 
     i32x4 ra[NA], rb[NB];
-    load_a(0, ra);
-    load_b(0, rb);
-    store_tiles(0, ra, rb);
+    // (every group goes through the same number of steps: they share the workgroup's barrier)
+    const int nsteps = (nkt + KG - 1) / KG;
+    if (grp < nkt) {
+        load_a(grp, ra);
+        load_b(grp, rb);
+        store_tiles(0, grp, ra, rb);
+    }
     __syncthreads();
 
-    for (int kt = 0; kt < nkt; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nkt;
+    for (int s = 0; s < nsteps; ++s) {
+        const int kt = s * KG + grp;   // this group's k tile of the step (none: >= nkt)
+        const int cur = s & 1;
+        const bool more = kt + KG < nkt;
         if (more) {
             advance_taps();
-            load_a(kt + 1, ra);
-            load_b(kt + 1, rb);
+            load_a(kt + KG, ra);
+            load_b(kt + KG, rb);
         }
-        const char* as = smem + cur * CFG::STAGE_BYTES + (wave_m * CFG::WM + lrow) * STRIDE + lgrp * 16;
-        const char* bs = smem + cur * CFG::STAGE_BYTES + BM * STRIDE + (wave_n * CFG::WN + lrow) * STRIDE + lgrp * 16;
+        if (KG == 1 || kt < nkt) {
+            const char* as = smem + cur * CFG::STAGE_BYTES + (wave_m * CFG::WM + lrow) * STRIDE + lgrp * 16;
+            const char* bs = smem + cur * CFG::STAGE_BYTES + BM * STRIDE + (wave_n * CFG::WN + lrow) * STRIDE + lgrp * 16;
 #pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) {
-            i32x4 a[TM], b[TN];
+            for (int kk = 0; kk < KSTEPS; ++kk) {
+                i32x4 a[TM], b[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                a[i] = *reinterpret_cast<const i32x4*>(as + i * MI * STRIDE + kk * MMA::KBYTES);
+                for (int i = 0; i < TM; ++i)
+                    a[i] = *reinterpret_cast<const i32x4*>(as + i * MI * STRIDE + kk * MMA::KBYTES);
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                b[j] = *reinterpret_cast<const i32x4*>(bs + j * MI * STRIDE + kk * MMA::KBYTES);
+                for (int j = 0; j < TN; ++j)
+                    b[j] = *reinterpret_cast<const i32x4*>(bs + j * MI * STRIDE + kk * MMA::KBYTES);
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = MMA::run(a[i], b[j], acc[i][j]);
-            if constexpr (mode_is_wave_level(MODE)) check_step<CFG, MODE>(a, b, chk);
+                    for (int j = 0; j < TN; ++j) acc[i][j] = MMA::run(a[i], b[j], acc[i][j]);
+                if constexpr (mode_is_wave_level(MODE)) check_step<CFG, MODE>(a, b, chk);
+            }
         }
-        if (more) store_tiles(cur ^ 1, ra, rb);
+        if (more) store_tiles(cur ^ 1, kt + KG, ra, rb);
         __syncthreads();
         if constexpr (INJ) {
-            if (kt == p.f_kt) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n));
+            if (kt == p.f_kt) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n, wave));
         }
     }
     if constexpr (INJ) {
-        if (p.f_kt < 0) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n));
+        // a fault in a finished accumulator: that of the group holding the last k tile
+        if (p.f_kt == -1 && (KG == 1 || grp == (nkt - 1) % KG)) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n, wave));
+    }
+    if constexpr (KG > 1) {
+        // the other groups leave their accumulators in LDS (every buffer is free: the loop ended with a
+        // barrier), group 0 adds them in group order; the checks see the added-up tile and the
+        // added-up redundant accumulators (checksum products of partial products add up to the
+        // checksum product of the whole, Sec. 5.2.2)
+        constexpr int NCHK_OUT = mode_is_wave_level(MODE) ? NCHK : 0;
+        constexpr int NV = (TM * TN + NCHK_OUT) * MMA::NACC;     // values per lane
+        static_assert((KG - 1) * NV * CFG::THREADS * 4 <= KG * CFG::LDS_BYTES, "LDS for the final sum");
+        AccT* red = reinterpret_cast<AccT*>(smem_all);
+        if (grp > 0) {
+            AccT* out = red + ((long long)(grp - 1) * NV) * CFG::THREADS + tid;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < MMA::NACC; ++r) out[((i * TN + j) * MMA::NACC + r) * CFG::THREADS] = acc[i][j][r];
+#pragma unroll
+            for (int i = 0; i < NCHK_OUT; ++i)
+#pragma unroll
+                for (int r = 0; r < MMA::NACC; ++r) out[((TM * TN + i) * MMA::NACC + r) * CFG::THREADS] = chk[i][r];
+        }
+        __syncthreads();
+        if (grp > 0) return;
+#pragma unroll
+        for (int g = 1; g < KG; ++g) {
+            const AccT* in = red + ((long long)(g - 1) * NV) * CFG::THREADS + tid;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < MMA::NACC; ++r) acc[i][j][r] += in[((i * TN + j) * MMA::NACC + r) * CFG::THREADS];
+#pragma unroll
+            for (int i = 0; i < NCHK_OUT; ++i)
+#pragma unroll
+                for (int r = 0; r < MMA::NACC; ++r) chk[i][r] += in[((TM * TN + i) * MMA::NACC + r) * CFG::THREADS];
+        }
+        if constexpr (INJ) {
+            if (p.f_kt == -2) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n, wave));
+        }
     }
     (void)NGRP;
 
-    epilogue<CFG, MODE>(acc, chk, p, tile_m, tile_n, smem);
+    epilogue<CFG, MODE>(acc, chk, p, tile_m, tile_n, smem, true, wave);
 }
 
 }  // namespace abft

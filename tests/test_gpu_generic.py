@@ -1,0 +1,64 @@
+"""The generic kernel's loaders (16-byte reads of rows at any alignment, the turning loader of weights stored
+K x N, element gathers where neither applies) and its groups of wavefronts that share a tile along k, at the sizes
+where their edges lie."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import DT, c_close, run_gemm
+from paper_2104_09455_amd import binding as B
+from paper_2104_09455_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): rows shorter than 16 bytes, exactly 16 bytes, one element more; a k tile less / plus one; one, two and three
+# columns (a group of four bytes is two fp16 or four int8 columns) and tile edges; few rows; the first k loops that groups
+# share (five k tiles) with a whole and a cut last tile, and one whose last step leaves groups without a tile
+EDGES = [(5, 9, 7), (9, 70, 4100), (33, 1, 8), (64, 2, 9), (17, 3, 15), (65, 4, 17), (31, 63, 63), (64, 64, 65), (70, 65, 127),
+         (96, 130, 129), (66, 127, 257), (66, 127, 449), (40, 66, 513), (130, 70, 1025), (64, 200, 1100)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("layout", [B.B_NK, B.B_KN])
+@pytest.mark.parametrize("shape", EDGES)
+def test_edges_of_the_generic_loaders(shape, layout, dtype):
+    M, N, K = shape
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M * 131 + N * 17 + K, dist_a="normal", dist_b="normal")
+    C_ref = oracle.gemm(A, Bm, dtype)
+    for mode in (B.NONE, B.GLOBAL, B.THREAD):
+        # (pads and an odd start move every row to another alignment)
+        for pads in ((0, 0, 0, 0), (3, 1, 5, 1)):
+            print("case", shape, layout, dtype, mode, pads, flush=True)
+            r = run_gemm(A, Bm, dtype, mode, layout=layout, lda_pad=pads[0], ldb_pad=pads[1], ldc_pad=pads[2], misalign=pads[3],
+                         use_beta=mode == B.GLOBAL)
+            assert c_close(r.C, C_ref, dtype), (mode, pads)
+            assert r.flag == 0, (mode, pads, r.report.worst_ratio)
+            if mode != B.NONE:
+                assert r.report.worst_ratio < 0.5
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("mode", [B.GLOBAL, B.THREAD, B.TWOSIDED])
+def test_faults_where_groups_share_a_tile_along_k(mode, dtype):
+    """511-like odd sizes on the four-group tile: a fault in a group's running or finished partial accumulator, or in
+    the added-up value, is seen, and C carries exactly that flip (int8)."""
+    M, N, K = 75, 133, 1301
+    dt = DT[dtype]
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=77, dist_a="normal", dist_b="normal")
+    C_ref = oracle.gemm(A, Bm, dtype)
+    assert B.abft_k_ways(M, N, K, dt, mode, False)[0] == 4
+    ks = B.abft_tile_shape(M, N, K, dt, False)[2]
+    parts = B.abft_k_parts(M, N, K, dt, mode, False)
+    assert sorted(k for p in parts for k in p) == list(range(K))
+    for t, k_after in enumerate([-1, -2, ks, 3 * ks, 4 * ks, (K - 1) // ks * ks]):
+        i, j, bit = (13 * t + 5) % M, (29 * t + 60) % N, 30
+        print("case", mode, dtype, k_after, i, j, flush=True)
+        r = run_gemm(A, Bm, dtype, mode, layout=B.B_KN, inject=B.Fault(i, j, bit, k_after), want_report=False)
+        assert r.flag == 1, k_after
+        if dtype == "i8":
+            if k_after == -2:
+                bad = oracle.inject(A, Bm, C_ref, dtype, i, j, bit)
+            else:
+                bad = oracle.inject(A, Bm, C_ref, dtype, i, j, bit, k_after=k_after,
+                                    k_set=parts[oracle.part_of(parts, (K if k_after < 0 else k_after) - 1)])
+            assert np.array_equal(r.C, ((bad + 2 ** 31) % 2 ** 32) - 2 ** 31), k_after
