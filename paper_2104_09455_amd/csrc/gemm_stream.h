@@ -81,9 +81,10 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
     const char* aptr[NQA];
     const char* bptr[NQB];
     unsigned a_valid = 0, b_valid = 0;
-    long long a_img[CONV ? NQA : 1];
+    // (convolutions: see the direct-to-LDS kernel: aptr is a row's top-left input pixel)
     int a_ih0[CONV ? NQA : 1], a_iw0[CONV ? NQA : 1];
     int tap_c[2] = {0, 0}, tap_kh[2] = {0, 0}, tap_kw[2] = {0, 0};  // per chunk column (q parity)
+    long long tap_off[2] = {0, 0};
     // (row pointers: one 64-bit product each for A and B, then uniform steps of 8 rows)
     const char* const b_row0 = p.B + ((long long)(bn0 + crow) * p.ldb + (long long)wave * BK) * ESIZE;
     const long long b_step = 8 * p.ldb * ESIZE;
@@ -107,10 +108,9 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
             const int img = mm / (p.OH * p.OW);
             const int rem = mm - img * (p.OH * p.OW);
             const int oh = rem / p.OW, ow = rem - oh * p.OW;
-            a_img[q] = (long long)img * p.imgpitch;
             a_ih0[q] = oh * p.stride - p.pad;
             a_iw0[q] = ow * p.stride - p.pad;
-            aptr[q] = zero;
+            aptr[q] = p.A + ((long long)img * p.imgpitch + a_ih0[q] * p.rowpitch + (long long)a_iw0[q] * p.pix) * ESIZE;
         }
     }
     // weight checksums of this tile's column block: lane l copies bytes 4l .. 4l+3 of the k tile's
@@ -142,6 +142,7 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
             tap_c[h] = k - tap * p.Cin;
             tap_kh[h] = tap / p.KW;
             tap_kw[h] = tap - tap_kh[h] * p.KW;
+            tap_off[h] = (tap_kh[h] * p.rowpitch + (long long)tap_kw[h] * p.pix + tap_c[h]) * ESIZE;
         }
     }
 
@@ -158,10 +159,9 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
             const char* src = aptr[q];
             if constexpr (CONV) {
                 // a chunk never straddles a filter tap (Cin is a multiple of the chunk length)
-                const int ih = a_ih0[q] + tap_kh[q & 1], iw = a_iw0[q] + tap_kw[q & 1];
-                const bool ok = ((a_valid >> q) & 1u) && ih >= 0 && ih < p.H && iw >= 0 && iw < p.W;
-                src = ok ? p.A + (a_img[q] + (long long)ih * p.rowpitch + (long long)iw * p.pix + tap_c[q & 1]) * ESIZE
-                         : g_zero_chunk + ckc[q & 1] * 16;
+                const bool ok = ((a_valid >> q) & 1u) && (unsigned)(a_ih0[q] + tap_kh[q & 1]) < (unsigned)p.H &&
+                                (unsigned)(a_iw0[q] + tap_kw[q & 1]) < (unsigned)p.W;
+                src = ok ? aptr[q] + tap_off[q & 1] : g_zero_chunk + ckc[q & 1] * 16;
             }
             if (cut[q & 1]) src = g_zero_chunk + ckc[q & 1] * 16;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
@@ -214,11 +214,14 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 tap_c[h] += KW * BK;
+                tap_off[h] += KW * BKB;
                 while (tap_c[h] >= p.Cin) {
                     tap_c[h] -= p.Cin;
+                    tap_off[h] += (p.pix - p.Cin) * ESIZE;
                     if (++tap_kw[h] == p.KW) {
                         tap_kw[h] = 0;
                         ++tap_kh[h];
+                        tap_off[h] += (p.rowpitch - (long long)p.KW * p.pix) * ESIZE;
                     }
                 }
             }
