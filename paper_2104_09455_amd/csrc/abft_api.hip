@@ -108,7 +108,12 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
     const bool force_fits = force >= 0 && force < CFG_COUNT &&
                             (fast_ok || !cfg_info_host(force).fast || (aligned16 && cfg_is_stream(force)));
     // (the 256 x 256 tile carries no wavefront-level scheme: a forced choice of it does not apply to those)
-    if (force_fits && !((force == CFG_F256W || force == CFG_F256N || force == CFG_F256S || force == CFG_F128E) && mode == ABFT_THREAD)) return force;
+    // the row-streaming kernel: 16-bit types, no scheme that compares across wavefronts, the weights within
+    // LDS (one column block of 64 and up to twenty k tiles, or a single k tile and up to twenty column blocks)
+    const bool rows_fit = fast_ok && dt != ABFT_I8 && mode != ABFT_GLOBAL &&
+                          (N <= 64 || (long long)K * esize(dt) == 128) && cdiv(N, 64) * cdiv((long long)K * esize(dt), 128) <= 20;
+    if (force == CFG_R64 && rows_fit) return force;
+    if (force_fits && force != CFG_R64 && !((force == CFG_F256W || force == CFG_F256N || force == CFG_F256S || force == CFG_F128E) && mode == ABFT_THREAD)) return force;
     // (a long k loop: the groups of the 64 x 64 tile that share it outweigh the rows of zeros: 16 x 4096 x
     // 4095 27 against 45 us; near level at half to a quarter of that, 16 x 512 x 1023 9.9 / 10.7; 16 x 512
     // x 300 6.4 / 5.5)
@@ -146,6 +151,12 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
         if (fast_ok && mode != ABFT_THREAD && N <= 64 && N > 32 && M >= 65536 &&
             (nkt_all >= 6 || (nkt_all == 1 && mode == ABFT_GLOBAL)))
             return CFG_F256S;
+        // Very many rows whose weights fit in LDS: the row-streaming kernel, from two 32-row tiles per wavefront
+        // of the chip on (thread-level / unprotected against 128 x 128 tiles: 3 x 3 convolution 64 -> 64 on 200704
+        // rows 41 / 35 us against 60 / 45, 200704 x 256 x 64 40 / 38 against 50 / 42, stem on 802816 rows 85 /
+        // 74 against 115 / 96; at 70000 to 100000 rows level: 70000 x 64 x 256 19 / 13 against 18 / 15, stem 25 /
+        // 23 against 24 / 21; at 50176 rows the loads into an empty pipeline lose, 18.6 / 16.9 against 18 / 13.5).
+        if (rows_fit && M >= 131072) return CFG_R64;
         const bool fills128 = tiles(CFG_F128) >= 128;
         if (fast_ok && fills128 && N < 128) return CFG_F128T;  // narrow outputs: every wavefront spans all columns
         // Few tiles: the time is the latency of a workgroup's k loop and the rate at which one
@@ -498,13 +509,18 @@ __global__ __launch_bounds__(256) void conv_pad_kernel(const char* x, char* out,
     constexpr int EPC = 16 / ESIZE;
     const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
     if (t >= total_chunks) return;
-    const long long row = t / chunks_per_row;
+    // (32-bit divisions where they do: the 64-bit ones cost more than the copy)
+    const bool small = total_chunks <= 0x7fffffffLL;
+    const long long row = small ? (long long)((unsigned)t / (unsigned)chunks_per_row) : t / chunks_per_row;
     const long long e0 = (t - row * chunks_per_row) * EPC;
-    const long long img = row / Hp;
+    const long long img = small ? (long long)((unsigned)row / (unsigned)Hp) : row / Hp;
     const int ih = (int)(row - img * Hp) - pad;
     i32x4 v = {0, 0, 0, 0};
     if (ih >= 0 && ih < H) {
         const char* src = x + ((img * H + ih) * (long long)WC) * ESIZE;
+        // chunks inside the input row in one read at whatever alignment, those at its ends by the element
+        if (e0 >= padC && e0 + EPC - padC <= WC) v = ld16u(src + (e0 - padC) * ESIZE);
+        else
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             const long long xe = e0 + e - padC;

@@ -292,6 +292,20 @@ struct Cfg {
 };
 
 __device__ __forceinline__ i32x4 ld16(const char* p) { return *reinterpret_cast<const i32x4*>(p); }
+// 16 / 4 bytes at any address (global memory takes unaligned vector loads); as global loads also
+// where the address is a choice between an operand and the block of zeros, which the compiler takes
+// for a generic address (generic loads count as LDS operations too and are waited for all at once)
+template <typename T>
+__device__ __forceinline__ T load_global_unaligned(const char* p) {
+    struct __attribute__((packed)) Any { T v; };
+    return reinterpret_cast<const __attribute__((address_space(1))) Any*>(
+        (const __attribute__((address_space(1))) char*)p)->v;
+}
+__device__ __forceinline__ i32x4 ld16u(const char* p) { return load_global_unaligned<i32x4>(p); }
+__device__ __forceinline__ int ld4u(const char* p) { return load_global_unaligned<int>(p); }
+__device__ __forceinline__ i32x4 ld16g(const char* p) {
+    return *(const __attribute__((address_space(1))) i32x4*)(const __attribute__((address_space(1))) char*)p;
+}
 
 // 16 bytes gathered element by element: element e of the chunk is at base + e*stride
 // (bytes) and is taken only while e < n_valid.  Every load reads an element of the run (the

@@ -16,17 +16,6 @@
 
 namespace abft {
 
-// 16 / 4 bytes at any address (global memory takes unaligned vector loads)
-__device__ __forceinline__ i32x4 ld16u(const char* p) {
-    i32x4 v;
-    __builtin_memcpy(&v, p, 16);
-    return v;
-}
-__device__ __forceinline__ int ld4u(const char* p) {
-    int v;
-    __builtin_memcpy(&v, p, 4);
-    return v;
-}
 // 16 bytes shifted down by `bytes` (0 .. 15), zeros at the top
 __device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
     unsigned __int128 u = bitcast<unsigned __int128>(v);

@@ -1,0 +1,126 @@
+"""The row-streaming kernel (very many rows, weights resident in LDS; unprotected and wavefront-level schemes) at
+the edges of its range: one and several k tiles, fewer k tiles than are loaded ahead and more, one and several column
+blocks, rows and columns that fill no tile, leading dimensions that rule out wide stores, convolutions whose rows
+wrap over several images."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import DT, DeviceConv, DeviceGemm, c_close, run_gemm, sample_rows
+from paper_2104_09455_amd import binding as B
+from paper_2104_09455_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+WAVE = [B.NONE, B.THREAD, B.REPLICA, B.THREAD_HALF, B.TWOSIDED]
+# (M, N, K): a single k tile with 1, 4 and 20 (all of LDS) column blocks; 2, 3, 4 (as many as are loaded ahead), 5, 9
+# and 20 k tiles; ragged rows and columns
+SHAPES = [(131072, 64, 64), (131105, 256, 64), (131104, 1280, 64), (131536, 64, 128), (131072, 40, 192),
+          (131081, 64, 256), (131072, 64, 320), (131072, 64, 576), (131103, 33, 1280)]
+
+
+def _huge_flip(A, Bm, dtype, i, j, k_after):
+    """The exponent bit whose flip makes the accumulator of (i, j) astronomically large."""
+    real = wl.bf16_bits_to_f32 if dtype == "bf16" else (lambda x: x.astype(np.float64))
+    k = A.shape[1] if k_after < 0 else k_after
+    return 30 if abs(float(real(A[i, :k]) @ real(Bm[:k, j]))) < 2 else 29
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_products_of_very_many_rows(shape, dtype):
+    M, N, K = shape
+    d = DeviceGemm(M, N, K, dtype, seed=M + N + K)
+    assert (d.tm, d.tn, d.k_step) == (32, 64, 64)
+    rows = sample_rows(M, 3000)
+    C_ref = oracle.gemm(d.A[rows], d.Bm, dtype)
+    rng = np.random.default_rng(K)
+    for mode in WAVE:
+        print("case", shape, dtype, mode, flush=True)
+        d.dC.fill_(7.0)
+        flag, rep = d.run(mode)
+        assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        if mode == B.NONE:
+            continue
+        if mode == B.THREAD:
+            whole = d.dC.clone()
+        assert d.dC.equal(whole)     # (every wavefront-level scheme stores the same product)
+        assert rep.worst_ratio < 0.5 and rep.tiles == -(-M // 32) * -(-N // 64)
+        # a fault anywhere in a finished or running accumulator is seen: first and last tile, a tile in between
+        for i, j, k_after in [(0, 0, -1), (M - 1, N - 1, -1), (int(rng.integers(M)), int(rng.integers(N)), -2),
+                              (int(rng.integers(M)), int(rng.integers(N)), (K - 1) // 64 * 64 or -1)]:
+            bit = _huge_flip(d.A, d.Bm, dtype, i, j, k_after)
+            flag, _ = d.run(mode, inject=B.Fault(i, j, bit, k_after), want_report=False)
+            assert flag == 1, (mode, i, j, bit, k_after)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_leading_dimensions_without_wide_stores(dtype):
+    A, Bm = wl.gemm_operands(131084, 64, 128, dtype, seed=5, dist_a="normal", dist_b="normal")
+    C_ref = oracle.gemm(A, Bm, dtype)
+    for mode in (B.NONE, B.THREAD):
+        r = run_gemm(A, Bm, dtype, mode, lda_pad=8, ldb_pad=16, ldc_pad=1)
+        assert c_close(r.C, C_ref, dtype) and r.flag == 0
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("conv", [
+    wl.Conv(12, 106, 105, 64, 64, 3, 3, 1, 1),     # nine k tiles, padding taps, rows that end inside a tile
+    wl.Conv(2700, 7, 7, 64, 64, 3, 3, 1, 1),       # a step of rows spans several images
+    wl.Conv(36, 123, 121, 32, 64, 2, 2, 2, 0),     # two taps per k tile, stride 2
+    wl.Conv(12, 215, 214, 3, 64, 7, 7, 2, 3),      # three channels: lowered to row segments, three k tiles
+], ids=str)
+def test_convolutions_of_very_many_rows(conv, dtype):
+    d = DeviceConv(conv, dtype, seed=31)
+    A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
+    assert d.M >= 131072
+    rows = sample_rows(d.M, 3000)
+    C_ref = oracle.gemm(A[rows], d.Wm, dtype)
+    for mode in (B.NONE, B.THREAD, B.TWOSIDED):
+        print("case", conv, dtype, mode, flush=True)
+        flag, rep = d.run(mode)
+        assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        if mode == B.THREAD:
+            whole = d.dC.clone()
+        if mode != B.NONE:
+            assert d.dC.equal(whole) and rep.worst_ratio < 0.5
+            bit = _huge_flip(A, d.Wm, dtype, d.M - 3, 5, -1)
+            flag, _ = d.run(mode, inject=B.Fault(d.M - 3, 5, bit, -1), want_report=False)
+            assert flag == 1
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_activation_and_sums_left_for_the_next_layer(dtype):
+    """A thread-level layer on this kernel applies ReLU, and leaves the column sums of what it stores to a layer under
+    the global scheme, whose comparison they enter."""
+    import torch
+    from gpu_util import DEV, c_to_host, to_dev
+    M, dt = 131072 + 32, DT[dtype]
+    widths = [64, 128, 128]
+    x = wl.random_matrix((M, widths[0]), dtype, "uniform_01", 3)
+    ws = [wl.random_matrix((widths[i], widths[i + 1]), dtype, "weights", 10 + i) for i in range(2)]
+    dws = [to_dev(np.ascontiguousarray(w.T), dtype) for w in ws]
+    layers = [B.Layer(M, widths[i + 1], widths[i], dt, B.B_NK, 0, B.Conv(), dws[i].data_ptr(), widths[i]) for i in range(2)]
+    plan = B.abft_plan_create(layers)
+    B.abft_plan_set_mode(plan, 0, B.THREAD)
+    B.abft_plan_set_mode(plan, 1, B.GLOBAL)
+    B.abft_plan_set_activation(plan, 0, B.ACT_RELU)
+    t = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    dx = to_dev(x, dtype)
+    outs = [torch.zeros((M, w), dtype=t, device=DEV) for w in widths[1:]]
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    before = B.abft_handover_launches()
+    B.abft_plan_run_chain(plan, 0, 2, dx, widths[0], outs, widths[1:], flag)
+    torch.cuda.synchronize()
+    assert B.abft_handover_launches() == before + 1
+    assert int(flag.item()) == 0
+    ref = np.maximum(oracle.gemm(x, ws[0], dtype), 0)
+    assert c_close(c_to_host(outs[0], dtype), ref, dtype)
+    stored = outs[0].double().cpu().numpy()
+    w1 = dws[1].double().cpu().numpy().T
+    assert c_close(c_to_host(outs[1], dtype), stored @ w1, dtype)
+    B.abft_plan_set_diagnostics(plan, 1, None, B.Fault(M - 5, 77, 30, -1))
+    B.abft_plan_run_chain(plan, 0, 2, dx, widths[0], outs, widths[1:], flag)
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 1
+    B.abft_plan_destroy(plan)
