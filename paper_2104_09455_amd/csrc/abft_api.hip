@@ -167,7 +167,12 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
         // the idle wavefronts of a short loop cost more than the barriers they save; 3000 x 384 x
         // 384 takes 9.9 us on 282 such tiles, 8.2 us on 64 x 128 tiles).  (On the 32 x 32 tile the thread-level
         // scheme's checksum operand is the B fragment itself: no vector work at all.)
-        if (tiles(CFG_S32) <= 256) return CFG_S32;
+        // Fewer than a quarter of the compute units in use and a long k loop: eight wavefronts per tile, two per
+        // SIMD, so that one's copies and address work run under the other's products (3 x 3 convolutions at batch
+        // 1: 512 -> 512 on 49 rows, 32 tiles of 72 k tiles, 10.3 against 11.7 us thread-level, 256 -> 256 on 196
+        // rows 7.5 / 8.1; 49 x 512 x 4608 7.9 / 8.1).  More tiles: level for products (256 x 512 x 2048 5.9 / 5.9,
+        // 16 x 4096 x 4096 8.9 / 8.7).
+        if (tiles(CFG_S32) <= 256) return nkt_all >= 32 && tiles(CFG_S32) < 64 ? CFG_S32W : CFG_S32;
         if (tiles(CFG_S64) <= 256) return CFG_S64;
         if (tiles(CFG_S128) <= 256 ? nkt_all >= 4 : (tiles(CFG_S128) <= 512 && nkt_all >= (mode == ABFT_THREAD ? 8 : 16))) return CFG_S128;
         if (fast_ok) {
@@ -1088,6 +1093,9 @@ struct abft_plan {
 
 namespace {
 
+// (layers that would run on 32 x 32 tiles by themselves, however many wavefronts share one)
+bool chain_cfg(int cfg) { return cfg == CFG_S32 || cfg == CFG_S32W; }
+
 // Can this layer run inside the chain kernel?  Fully connected, fp16 / bf16, weights with k
 // contiguous and 16-byte aligned rows, K whole k tiles of 128 bytes.
 bool chain_layer_ok(const abft_layer_t& d) {
@@ -1510,7 +1518,7 @@ int abft_plan_run_chain(abft_plan_t* plan, int first, int count, const void* A, 
         const int64_t lda_i = i == 0 ? lda : ldc[i - 1];
         // (layers small enough that a launch of their own would run on 32 x 32 tiles too)
         one_launch = L.chain_beta != nullptr && d.dtype == d0.dtype && d.M == d0.M &&
-                     pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode) == CFG_S32 && !L.report && !L.has_fault &&
+                     chain_cfg(pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode)) && !L.report && !L.has_fault &&
                      (L.mode == ABFT_NONE || L.mode == ABFT_GLOBAL || L.mode == ABFT_THREAD) && C[i] != nullptr &&
                      aligned16(a_i) && (lda_i * 2) % 16 == 0 && lda_i >= d.K && ldc[i] >= d.N &&
                      (i == 0 || d.K == plan->layers[first + i - 1].desc.N);

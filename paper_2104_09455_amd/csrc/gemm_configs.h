@@ -26,6 +26,7 @@ namespace abft {
 //  S* run the streaming kernel (same alignment, K any multiple of 16 bytes; four wavefronts split the k tiles of one
 //  register tile between them, each with its own LDS stages, no barrier in the k loop):
 //    S32     32 x  32, 4 stages per wavefront                         a few tiles only: latency-bound layers
+//    S32W    32 x  32, eight wavefronts with 2 stages each             the same with long k loops
 //    S64     32 x  64, 3 stages per wavefront
 //    S128    64 x  64, 2 stages per wavefront                         up to about one tile per compute unit
 //  R64 runs the row-streaming kernel (same alignment as F*; 16-bit types, unprotected or wavefront-level):
@@ -33,7 +34,7 @@ namespace abft {
 //  G* run the generic kernel (any alignment, layout, K):
 //    G128 128 x 128, G64 64 x 64 (32x32 MFMA shapes), G16 16 x 64 (16x16 shapes; M <= 16)
 //    G64K 64 x 64 with four groups of four wavefronts sharing the k tiles: at most about one tile per compute unit
-enum CfgId { CFG_F256W = 0, CFG_F128, CFG_F128T, CFG_F64T, CFG_S32, CFG_S64, CFG_S128, CFG_G128, CFG_G64, CFG_G16, CFG_F256N, CFG_F256S, CFG_F128E, CFG_G64K, CFG_R64, CFG_COUNT };
+enum CfgId { CFG_F256W = 0, CFG_F128, CFG_F128T, CFG_F64T, CFG_S32, CFG_S64, CFG_S128, CFG_G128, CFG_G64, CFG_G16, CFG_F256N, CFG_F256S, CFG_F128E, CFG_G64K, CFG_R64, CFG_S32W, CFG_COUNT };
 
 template <int DT, int ID>
 struct CfgOf;
@@ -46,6 +47,7 @@ template <int DT> struct CfgOf<DT, CFG_F256N> { typedef Cfg<DT, 16, 4, 4, 4, 2, 
 template <int DT> struct CfgOf<DT, CFG_F256S> { typedef Cfg<DT, 16, 2, 4, 8, 1, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_F128E> { typedef Cfg<DT, 16, 2, 4, 4, 2, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_S32>   { typedef Cfg<DT, 32, 1, 1, 1, 1, 128> type; static constexpr int NSTAGE = 4; static constexpr int KWAYS = 4; };
+template <int DT> struct CfgOf<DT, CFG_S32W>  { typedef Cfg<DT, 32, 1, 1, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 8; };
 template <int DT> struct CfgOf<DT, CFG_S64>   { typedef Cfg<DT, 32, 1, 2, 1, 1, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 4; };
 template <int DT> struct CfgOf<DT, CFG_S128>  { typedef Cfg<DT, 32, 2, 2, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 4; };
 template <int DT> struct CfgOf<DT, CFG_R64>   { typedef Cfg<DT, 32, 1, 2, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
@@ -55,7 +57,7 @@ template <int DT> struct CfgOf<DT, CFG_G64K>  { typedef Cfg<DT, 32, 1, 1, 2, 2, 
 template <int DT> struct CfgOf<DT, CFG_G16>   { typedef Cfg<DT, 16, 1, 1, 1, 4, 256> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 1; };
 
 constexpr bool cfg_is_rows(int id) { return id == CFG_R64; }
-constexpr bool cfg_is_stream(int id) { return id == CFG_S32 || id == CFG_S64 || id == CFG_S128; }
+constexpr bool cfg_is_stream(int id) { return id == CFG_S32 || id == CFG_S32W || id == CFG_S64 || id == CFG_S128; }
 
 // threads: of one WAVES_M x WAVES_N grid of wavefronts (a launch has kways times as many);
 // kway_bytes: bytes of k that one wavefront takes in turn when kways wavefronts share a tile
@@ -83,6 +85,7 @@ inline CfgInfo cfg_info_host(int id) {
         case CFG_F256S: return cfg_info<CFG_F256S>();
         case CFG_F128E: return cfg_info<CFG_F128E>();
         case CFG_S32: return cfg_info<CFG_S32>();
+        case CFG_S32W: return cfg_info<CFG_S32W>();
         case CFG_S64: return cfg_info<CFG_S64>();
         case CFG_S128: return cfg_info<CFG_S128>();
         case CFG_R64: return cfg_info<CFG_R64>();

@@ -2,13 +2,13 @@
 // tiles, whose time is the latency of one workgroup's k loop rather than bandwidth or MFMA
 // rate (small-batch MLP layers, batch-1 convolutions).
 //
-// Workgroup tile (32 TM) x (32 TN), four wavefronts that ALL own the whole tile and split
-// the k loop between them: wavefront w multiplies the k tiles t with t % 4 == w (a k tile is
+// Workgroup tile (32 TM) x (32 TN), four (long k loops of few tiles: eight) wavefronts that ALL own the
+// whole tile and split the k loop between them: wavefront w multiplies the k tiles t with t % 4 == w (a k tile is
 // 128 bytes of k).  Each wavefront streams its own k tiles from HBM straight into its own
 // ring of LDS stages (global_load_lds_dwordx4) and reads them back as MFMA fragments, so the
 // k loop has no workgroup barrier at all: a wavefront only ever waits for its own copies.
-// The four partial tiles are added through LDS in wavefront order, every wavefront adding and
-// storing a quarter of the tile; every protected scheme makes its comparison on the added-up
+// The partial tiles are added through LDS in wavefront order, four wavefronts adding and storing a
+// quarter of the tile each; every protected scheme makes its comparison on the added-up
 // tile (one per tile), so the final addition is inside the check as well.
 //
 // Same alignment requirements and LDS row swizzle as the direct-to-LDS kernel, but K may be any
@@ -19,25 +19,26 @@
 
 namespace abft {
 
-template <class CFG, int NST>
+template <class CFG, int NST, int KW_>
 struct StreamLayout {
-    static constexpr int KW = 4;                                 // wavefronts per workgroup
+    static constexpr int KW = KW_;                               // wavefronts per workgroup
     static constexpr int AB_STAGE = (CFG::BM + CFG::BN) * 128;
     static constexpr int WSTAGE = AB_STAGE + 768;                // one wavefront's stage: A, B, weight checksums (six planes of 128 bytes)
     static constexpr int LDS_BYTES = KW * NST * WSTAGE;
     static constexpr int NQA = CFG::BM / 8, NQB = CFG::BN / 8;   // 1 KB copies per k tile
     static_assert(CFG::WAVES_M == 1 && CFG::WAVES_N == 1 && CFG::MI == 32 && CFG::BKB == 128, "one register tile");
+    static_assert(KW == 4 || KW == 8, "four of them add and store");
     static_assert((NST - 1) * (NQA + NQB + 1) <= 63, "vmcnt range");
     static_assert(LDS_BYTES >= KW * CFG::TM * CFG::TN * 16 * 64 * 4, "LDS for the final sum");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
 };
 
-// One output tile, by all 256 threads of the workgroup (uniform call: it holds workgroup barriers).
+// One output tile, by all 64 KW threads of the workgroup (uniform call: it holds workgroup barriers).
 // FRESH_A: the A operand was written earlier in the same launch by other compute units of this
 // die (a chain of layers in one kernel): its copies go past the compute unit's own cache.
-template <class CFG, int NST, int MODE, bool INJ, bool CONV, bool RAGGED, bool FRESH_A>
+template <class CFG, int NST, int KWAYS, int MODE, bool INJ, bool CONV, bool RAGGED, bool FRESH_A>
 __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int tile_n, char* smem) {
-    typedef StreamLayout<CFG, NST> LAY;
+    typedef StreamLayout<CFG, NST, KWAYS> LAY;
     constexpr int DT = CFG::DT;
     typedef Mma<DT, 32> MMA;
     typedef typename MMA::Acc Acc;
@@ -403,6 +404,8 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
             }
         }
     }
+    // (of eight wavefronts the first four add and store; all leave their redundant accumulators' sums)
+    if (KW == 4 || wave < 4) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -482,6 +485,7 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
                 }
             }
         }
+    }
     if constexpr (WGT) {
         // ---- three comparisons for this tile (Sec. 2.4, last paragraph): the plain one, one with
         // the rows weighted, one with the columns weighted.  Checksum side, from the extra result
@@ -669,12 +673,12 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
 
 // RAGGED: K is a whole number of 16-byte chunks but not of k tiles (an instance of its own, so that
 // products of whole k tiles pay nothing for the short last tile)
-template <class CFG, int NST, int MODE, bool INJ, bool CONV, bool RAGGED = false>
-__global__ __launch_bounds__(256) void gemm_stream_kernel(const GemmArgs p) {
+template <class CFG, int NST, int KWAYS, int MODE, bool INJ, bool CONV, bool RAGGED = false>
+__global__ __launch_bounds__(64 * KWAYS) void gemm_stream_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tile_m, tile_n;
     tile_of_block((int)blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    stream_tile<CFG, NST, MODE, INJ, CONV, RAGGED, false>(p, tile_m, tile_n, smem);
+    stream_tile<CFG, NST, KWAYS, MODE, INJ, CONV, RAGGED, false>(p, tile_m, tile_n, smem);
 }
 
 }  // namespace abft

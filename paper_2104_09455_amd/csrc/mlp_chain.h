@@ -141,9 +141,9 @@ __global__ __launch_bounds__(256) void mlp_chain_kernel(const ChainArgs a) {
             const int tile_m = tm0 + t / g.tiles_n, tile_n = t % g.tiles_n;
             __syncthreads();                         // the previous tile is done with the LDS
             // (inputs written by other compute units in this launch: read past this one's cache)
-            if (L.mode == MODE_GLOBAL) stream_tile<CFG, NST, MODE_GLOBAL, false, false, false, true>(g, tile_m, tile_n, smem);
-            else if (L.mode == MODE_THREAD) stream_tile<CFG, NST, MODE_THREAD, false, false, false, true>(g, tile_m, tile_n, smem);
-            else stream_tile<CFG, NST, MODE_NONE, false, false, false, true>(g, tile_m, tile_n, smem);
+            if (L.mode == MODE_GLOBAL) stream_tile<CFG, NST, 4, MODE_GLOBAL, false, false, false, true>(g, tile_m, tile_n, smem);
+            else if (L.mode == MODE_THREAD) stream_tile<CFG, NST, 4, MODE_THREAD, false, false, false, true>(g, tile_m, tile_n, smem);
+            else stream_tile<CFG, NST, 4, MODE_NONE, false, false, false, true>(g, tile_m, tile_n, smem);
         }
         // this workgroup's stores of C have reached the L2; then its flag of the layer flips
         __builtin_amdgcn_s_waitcnt(0);               // vmcnt(0), expcnt(0), lgkmcnt(0)
