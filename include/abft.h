@@ -55,8 +55,12 @@ extern "C" {
  * comparison.  For 16-byte aligned operands the product kernel forms that dot product
  * itself from the A tiles it loads (one kernel in all); otherwise, and for very large
  * products, an activation-checksum kernel runs first.  THREAD: the paper's one-sided
- * thread-level scheme (Sec. 5.2.2), carried out per wavefront register tile.  AUTO:
- * whatever abft_select returns (intensity-guided ABFT, Sec. 5.3). */
+ * thread-level scheme (Sec. 5.2.2), carried out per wavefront register tile, with an exact tile
+ * checksum of B_t.  F16 / BF16: the matrix unit adds the fragments of B_t, A.(b_0 + b_1) = A.b_0 +
+ * A.b_1, each product into checksum accumulators of its own: the MFMAs of replication (Sec. 5.1),
+ * and a checksum side that rounds exactly as the product does.  I8: the sums are formed on the
+ * vector unit and handed on in two digits, two MFMAs per A fragment.  AUTO: whatever abft_select
+ * returns (intensity-guided ABFT, Sec. 5.3). */
 typedef enum {
     ABFT_NONE = 0,
     ABFT_GLOBAL = 1,   /* global ABFT, one comparison per workgroup tile (Sec. 2.4, 2.5) */
@@ -65,16 +69,19 @@ typedef enum {
     /* Thread-level replication with single accumulation (Sec. 5.1), the baseline the paper weighs
      * one-sided ABFT against: every MFMA of the product is issued a second time, all those of one A
      * fragment into one accumulator block, whose sum must equal the sum of the wavefront tile.
-     * Same tiles, comparisons, tolerance, report and k partition as ABFT_THREAD; never chosen by
-     * ABFT_AUTO or by a plan's profile. */
+     * Same tiles, comparisons, tolerance, report and k partition as ABFT_THREAD, and for F16 / BF16 the
+     * same MFMAs (tiles with one B fragment: the same computation); what differs is that a block takes
+     * the products of several fragments and rounds otherwise than the product's own.  Under operands
+     * that are constant over a tile that difference passes the tolerance (F16, 1024^3, all 0.1: 2.4
+     * times): clean products of such operands can be flagged.  Never chosen by ABFT_AUTO or by a
+     * plan's profile. */
     ABFT_REPLICA = 4,
     /* One-sided thread-level ABFT with the tile checksum of B_t added up in the operand type, as the
      * paper does it (Sec. 5.2.2: packed half-precision adds): one extra MFMA per A fragment and k
      * step (Table 1's M_t / 2) and one packed add per further B fragment.  The roundings of those
      * adds (2^-11 per add in F16, 2^-8 in BF16) widen the tolerance (abft_tolerance_half_coeff):
-     * faults smaller than about an rms of C in one element go unseen.  ABFT_THREAD keeps the
-     * checksum exact instead: the matrix unit adds the B fragments (each multiplied apart into
-     * shared checksum accumulators; I8: two digits of their sum), no vector arithmetic. */
+     * faults smaller than about an rms of C in one element go unseen, which ABFT_THREAD's exact
+     * checksum sees, at one extra MFMA per B fragment. */
     ABFT_THREAD_HALF = 5,
     /* Two-sided thread-level ABFT (Sec. 5.2.1, Table 1 middle column): checksums of both the A
      * fragments and the B fragments of the wavefront tile, added up in the operand type, one extra

@@ -279,18 +279,17 @@ def frob(C, r0=0, r1=None, c0=0, c1=None) -> float:
         return float(np.sqrt(np.sum(blk * blk)))
 
 
-# Precision of the tile checksum operand in the thread-level scheme: the checksum of
-# B_t is formed in binary32 and handed to the matrix unit as two fp16 pieces (22 bits)
-# or three bf16 pieces (24 bits), so it adds a relative 2^-22 / 2^-23 on top of the
-# accumulation noise.  The global scheme keeps its checksums in fp64 and adds nothing.
+# Thread-level schemes: the relative error of a tile checksum of B_t that is held in two fp16 pieces (22
+# bits) or three bf16 pieces (24 bits).  The checksums that are compared are exact (the matrix unit adds the
+# fragments), so the term is headroom.  The global scheme keeps its checksums in fp64 and adds nothing.
 U_CHI = {F16: 2.0 ** -22, BF16: 2.0 ** -23}
 
 # Global scheme only: the accelerator's binary32 accumulation is not perfectly unbiased;
 # measured on MI355X, every entry of C carries a same-sign error of up to about
 # 2e-4 * 2^-24 * K * |C_ij| when the operands have the same sign, which adds coherently
-# under the output summation.  C_BIAS = 1e-3 covers it five times over.  (In the
-# thread-level scheme both sides of the comparison are accumulated the same way and
-# the bias cancels.)
+# under the output summation.  C_BIAS = 1e-3 covers it five times over.  (In the one-sided
+# thread-level scheme every checksum accumulator goes through the same operations as an
+# accumulator of the product, and the bias cancels.)
 C_BIAS = 1.0e-3
 
 

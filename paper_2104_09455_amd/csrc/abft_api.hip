@@ -30,12 +30,15 @@ namespace {
 // (the last term for the global scheme only).  2^-24 is the unit
 // roundoff of the fp32 accumulators; an accumulator that takes K products carries a
 // random-walk error ~ 2^-24 sqrt(K) |C_ij| / 2.4 and the errors of the entries add in
-// quadrature under the output summation.  u_chi (thread-level schemes) is what a
-// tile checksum held in two fp16 / three bf16 pieces would be off by; the checksum the kernels
-// form is exact (the matrix unit adds the fragments), so it is headroom there.  The ||.||_1 term covers a small coherent bias of the
+// quadrature under the output summation.  The ||.||_1 term covers a small coherent bias of the
 // matrix unit's accumulation (measured: up to 2e-4 * 2^-24 * K per entry, same sign for all
-// entries of a tile with same-sign operands); in the thread-level scheme both sides of the
-// comparison come out of the same unit and the bias cancels.
+// entries of a tile with same-sign operands).  Under ABFT_THREAD (fp16, bf16) every checksum
+// accumulator goes through the MFMAs of a product accumulator in their order, so both sides carry the
+// same errors, bias and all, and differ only where a tile is the sum of several wavefronts'
+// partial tiles, by the roundings of that addition.  (ABFT_REPLICA's blocks take the products of
+// several fragments, twice to four times as many at as many times the magnitude, and neither walk nor
+// bias cancels: 0.43 tau on 2048 x 2048 x 65536 operands of one sign.)  u_chi (thread-level schemes) is
+// the error of a tile checksum cut into two fp16 / three bf16 pieces, which no scheme here forms: headroom.
 constexpr double C_TOL = 8.0;
 constexpr double C_BIAS = 1.0e-3;
 constexpr double U_ACC = 5.9604644775390625e-08;  // 2^-24
@@ -91,8 +94,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // ------------------------------------------------------------------------- //
 // tile configuration choice (host logic)
 // ------------------------------------------------------------------------- //
-// mode: the scheme the product will run with (thread-level prefers wavefront tiles that are
-// wide in N: one checksum MFMA per TN real ones); force >= 0 pins a configuration (tuning aid,
+// mode: the scheme the product will run with; force >= 0 pins a configuration (tuning aid,
 // environment variable ABFT_FORCE_CFG).
 int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
     // (every wavefront-level scheme is checked per wavefront tile: the same tiles)

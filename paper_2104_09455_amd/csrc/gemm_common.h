@@ -342,17 +342,22 @@ __device__ __forceinline__ i32x4 gather16(const char* base, long long stride_byt
 // the end gives sum_k A[i][k] chi[k].  A lane holds one column of each of the TN fragments
 // (MFMA block columns).
 //  * fp16 / bf16: the matrix unit adds the fragments.  A . (b_0 + b_1) = A . b_0 + A . b_1, so the
-//    fragments go out one after the other, as they are, into the same checksum accumulators (two
-//    fragments share a block): exact operands and no vector arithmetic at all.  With one fragment
-//    per wavefront tile these are Table 1's M_t / 2 extra MMAs, with two as many as the sum in
-//    exactly representable pieces takes (fp16: hi + lo), with four twice (bf16: 4 / 3 of) that,
-//    but the pieces cost 14 (fp16) to 22 (bf16) vector instructions per register and k step, which
-//    four-cycle vector issue does not hide behind 32-cycle MFMAs.  Device time with pieces / so /
-//    unprotected: 3 x 3 convolution 256 -> 256 on 12544 rows, bf16 60 / 41 / 27 us; 12544 x 1024 x
-//    256 bf16 32 / 23 / 18; 3 x 3 convolution 64 -> 64 on 200704 rows, fp16 72 / 63 / 45.
+//    fragments go out one after the other, as they are, each into checksum accumulators of its own:
+//    exact operands and no vector arithmetic, and the checksum accumulators go through the very
+//    roundings of the product's, so that whatever the operands the two sides of a clean comparison are
+//    equal (streaming kernel: up to the final addition of the wavefronts' partial tiles).  Fragments that
+//    share accumulators round differently from the product: with constant operands, where every
+//    element of the tile errs alike, that alone is several times the tolerance (1024^3 fp16, all
+//    operands 0.1: 2.4; 4096^3: 6.6).  In matrix instructions the scheme is then replication (Sec.
+//    5.1) with accumulators of its own per product block: it doubles the MFMAs.  Table 1's M_t / 2
+//    would take the sums of the fragments: cut into exactly representable pieces those cost 14 (fp16)
+//    to 22 (bf16) vector instructions per register and k step, which four-cycle vector issue does not
+//    hide behind 32-cycle MFMAs.  Device time with pieces / so / unprotected: 3 x 3 convolution 256 -> 256
+//    on 12544 rows, bf16 60 / 35 / 26 us; 12544 x 1024 x 256 bf16 32 / 22 / 19; 3 x 3 convolution 64 -> 64
+//    on 200704 rows, fp16, 128 x 128 tiles 72 / 57 / 47.  (Accumulators shared by two fragments: 35, 22-23, 56;
+//    on the row-streaming kernel's short tiles the stem of 64 images took 86 us, so 88.)
 //  * int8: the sums are formed in packed 16-bit lanes and handed on in two digits, one operand
-//    and one set of accumulators per digit (below): integer accumulators that take several products
-//    could wrap where the product's own do not.
+//    and one set of accumulators per digit (below).
 // ---------------------------------------------------------------------------
 // two bf16 values of a register, widened; two floats rounded to nearest even and packed
 __device__ __forceinline__ float bf16_lo(int packed) { return bitcast<float>(packed << 16); }
@@ -445,22 +450,20 @@ struct ChecksumDot {
     }
 };
 
-// Which form of the tile checksum a configuration uses, how many checksum accumulator blocks per
-// A fragment and how many MFMAs per A fragment and k step that takes.
+// Which form of the tile checksum a configuration uses, how many checksum accumulator blocks
+// (and MFMAs a k step) that takes per A fragment.
 template <class CFG>
 struct ChecksumForm {
     static constexpr bool DIGITS = CFG::DT == DT_I8 && CFG::TN >= 2;
-    static constexpr int NP = DIGITS ? 2 : (CFG::TN >= 2 ? CFG::TN / 2 : 1);
+    static constexpr int NP = DIGITS ? 2 : CFG::TN;
     static constexpr int NCHK = NP * CFG::TM;
-    static constexpr int MFMAS = DIGITS ? 2 : CFG::TN;
-    static_assert(CFG::TN == 1 || CFG::TN % 2 == 0, "fragments of B in pairs");
 };
 // The thread-level scheme's extra MFMAs of one k step (a: A fragments, b: B fragments).
 template <class CFG>
 __device__ __forceinline__ void thread_checksum_step(const i32x4 (&a)[CFG::TM], const i32x4 (&b)[CFG::TN],
                                                      typename Mma<CFG::DT, CFG::MI>::Acc (&chk)[ChecksumForm<CFG>::NCHK]) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
-    constexpr int TM = CFG::TM, TN = CFG::TN, NP = ChecksumForm<CFG>::NP;
+    constexpr int TM = CFG::TM, TN = CFG::TN;
     if constexpr (ChecksumForm<CFG>::DIGITS) {
         i32x4 x[2];
         TileChecksumSplitI8<TN>::make(b, x[0], x[1]);
@@ -469,11 +472,10 @@ __device__ __forceinline__ void thread_checksum_step(const i32x4 (&a)[CFG::TM], 
 #pragma unroll
             for (int i = 0; i < TM; ++i) chk[pc * TM + i] = MMA::run(a[i], x[pc], chk[pc * TM + i]);
     } else {
-        // (fragments pc and pc + NP share a block: its two MFMAs of a step are TM * NP apart)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int i = 0; i < TM; ++i) chk[(j % NP) * TM + i] = MMA::run(a[i], b[j], chk[(j % NP) * TM + i]);
+            for (int j = 0; j < TN; ++j) chk[i * TN + j] = MMA::run(a[i], b[j], chk[i * TN + j]);
     }
 }
 // Redundant accumulator blocks a wavefront carries under each scheme.
@@ -482,6 +484,27 @@ struct CheckRegs {
     static constexpr int N = MODE == MODE_THREAD ? ChecksumForm<CFG>::NCHK
                              : ((MODE == MODE_REPL || MODE == MODE_THREAD_H) ? CFG::TM : 1);
 };
+// Zeros into the redundant accumulator blocks.  APART (where the k steps follow without a loop between):
+// the first register of each takes a zero whose value the compiler does not see, since a block that
+// is to take the product's own operands would otherwise be the product's block to it, and be merged
+// with it as far as the two agree.
+template <class CFG, int MODE, bool APART = false>
+__device__ __forceinline__ void clear_check(typename Mma<CFG::DT, CFG::MI>::Acc (&chk)[(CheckRegs<CFG, MODE>::N)]) {
+    typedef Mma<CFG::DT, CFG::MI> MMA;
+    typename MMA::AccT zero = 0;
+    if constexpr (APART && mode_is_wave_level(MODE)) asm("" : "+v"(zero));
+#pragma unroll
+    for (int i = 0; i < CheckRegs<CFG, MODE>::N; ++i)
+#pragma unroll
+        for (int r = 0; r < MMA::NACC; ++r) chk[i][r] = r == 0 ? zero : 0;
+}
+// Wavefronts per SIMD that a kernel of four wavefronts has to leave registers for.  With checksum
+// accumulators for each of its four product blocks a wavefront takes 128 accumulator registers; a few
+// vector registers less let two workgroups share a compute unit as they do under the other schemes.
+template <class CFG, int MODE>
+constexpr int min_waves_per_simd() {
+    return MODE == MODE_THREAD && CFG::THREADS == 256 && CFG::MI == 32 && CFG::TM * CFG::TN == 4 && !ChecksumForm<CFG>::DIGITS ? 2 : 1;
+}
 
 // Element-wise sum of two fragments in the operand type (fp16: one packed add per register;
 // bf16: widened, added and rounded to nearest even).  int8 sums do not fit the operand type:

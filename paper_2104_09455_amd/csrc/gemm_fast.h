@@ -77,7 +77,8 @@ struct FastLayout {
 };
 
 template <class CFG, int NSTAGE, int MODE, bool INJ, bool CONV>
-__global__ __launch_bounds__(CFG::THREADS) void gemm_fast_kernel(const GemmArgs p) {
+__global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(INJ ? 1 : min_waves_per_simd<CFG, MODE>())))
+void gemm_fast_kernel(const GemmArgs p) {
     typedef FastLayout<CFG, NSTAGE> LAY;
     constexpr int DT = CFG::DT;
     constexpr int MI = CFG::MI;
@@ -280,10 +281,7 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_fast_kernel(const GemmArgs 
             for (int r = 0; r < MMA::NACC; ++r) acc[i][j][r] = 0;
     constexpr int NCHK = CheckRegs<CFG, MODE>::N;
     Acc chk[NCHK];
-#pragma unroll
-    for (int i = 0; i < NCHK; ++i)
-#pragma unroll
-        for (int r = 0; r < MMA::NACC; ++r) chk[i][r] = 0;
+    clear_check<CFG, MODE>(chk);
 
     // ---- fragment reads: lane l reads row l%32 of a 32-row block, k chunk 2*kk + l/32,
     // stored at position chunk ^ ((row >> 1) & 7), which is (l >> 1) & 7 for every block
@@ -420,9 +418,7 @@ __global__ __launch_bounds__(CFG::THREADS) void gemm_fast_kernel(const GemmArgs 
                     // thread-level: the sums of the B fragments) is spread between the MFMAs
                     constexpr int NF = TM + TN;
                     constexpr int NM = TM * TN + (MDOT ? 1 : 0) +
-                                       (MODE == MODE_REPL ? TM * TN
-                                                           : (MODE == MODE_THREAD ? TM * ChecksumForm<CFG>::MFMAS
-                                                                                  : (mode_is_wave_level(MODE) ? CheckRegs<CFG, EMODE>::N : 0)));
+                                       (MODE == MODE_REPL ? TM * TN : (mode_is_wave_level(MODE) ? CheckRegs<CFG, EMODE>::N : 0));
                     // vector instructions per MFMA slot: the digits of int8's tile checksum cost about 14
                     // instructions per register of the lane's B fragments; sums in the operand type
                     // one (fp16) or six (bf16)

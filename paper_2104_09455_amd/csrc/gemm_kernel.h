@@ -28,7 +28,8 @@ __device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
 // tiles (and redundant accumulators) are added in group order and group 0 checks and stores.
 // ---------------------------------------------------------------------------
 template <class CFG, int MODE, bool INJ, bool CONV, int KG>
-__global__ __launch_bounds__(CFG::THREADS * KG) void gemm_kernel(const GemmArgs p) {
+__global__ __launch_bounds__(CFG::THREADS * KG) __attribute__((amdgpu_waves_per_eu(INJ || KG > 1 ? 1 : min_waves_per_simd<CFG, MODE>())))
+void gemm_kernel(const GemmArgs p) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
     typedef typename MMA::Acc Acc;
     typedef typename MMA::AccT AccT;
@@ -319,10 +320,7 @@ __global__ __launch_bounds__(CFG::THREADS * KG) void gemm_kernel(const GemmArgs 
             for (int r = 0; r < MMA::NACC; ++r) acc[i][j][r] = 0;
     constexpr int NCHK = CheckRegs<CFG, MODE>::N;
     Acc chk[NCHK];
-#pragma unroll
-    for (int i = 0; i < NCHK; ++i)
-#pragma unroll
-        for (int r = 0; r < MMA::NACC; ++r) chk[i][r] = 0;
+    clear_check<CFG, MODE>(chk);
 
     i32x4 ra[NA], rb[NB];
     // (every group goes through the same number of steps: they share the workgroup's barrier)

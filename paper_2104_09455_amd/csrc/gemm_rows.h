@@ -225,10 +225,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[0][j][r] = 0;
-#pragma unroll
-        for (int i = 0; i < NCHK; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) chk[i][r] = 0;
+        clear_check<CFG, MODE, true>(chk);
     };
     clear();
     int kt = 0, tile_m = t_lo + wave;

@@ -248,10 +248,7 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& p, int tile_m, int t
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
     constexpr int NCHK = CheckRegs<CFG, MODE>::N;
     Acc chk[NCHK];
-#pragma unroll
-    for (int i = 0; i < NCHK; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) chk[i][r] = 0;
+    clear_check<CFG, MODE>(chk);
 
     // ---- fragment reads: lane l reads row l%32 of a 32-row block, k chunk 2*kk + l/32, stored
     // at position chunk ^ ((row >> 1) & 7)
