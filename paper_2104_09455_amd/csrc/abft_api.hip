@@ -1095,9 +1095,6 @@ struct abft_plan {
 
 namespace {
 
-// (layers that would run on 32 x 32 tiles by themselves, however many wavefronts share one)
-bool chain_cfg(int cfg) { return cfg == CFG_S32 || cfg == CFG_S32W; }
-
 // Can this layer run inside the chain kernel?  Fully connected, fp16 / bf16, weights with k
 // contiguous and 16-byte aligned rows, K whole k tiles of 128 bytes.
 bool chain_layer_ok(const abft_layer_t& d) {
@@ -1518,9 +1515,12 @@ int abft_plan_run_chain(abft_plan_t* plan, int first, int count, const void* A, 
         const abft_layer_t& d = L.desc;
         const void* a_i = i == 0 ? A : C[i - 1];
         const int64_t lda_i = i == 0 ? lda : ldc[i - 1];
-        // (layers small enough that a launch of their own would run on 32 x 32 tiles too)
+        // (layers small enough that a launch of their own would run on 32 x 32 tiles too, and in the same four
+        // shares of the k loop: the chain's results are the layers'.  Eight shares in two sets of accumulators
+        // per wavefront gave those results in one launch as well, in 46 us for 16 x 4096 -> 1024 -> 4096 -> 1024
+        // thread-level, where three launches take 20)
         one_launch = L.chain_beta != nullptr && d.dtype == d0.dtype && d.M == d0.M &&
-                     chain_cfg(pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode)) && !L.report && !L.has_fault &&
+                     pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode) == CFG_S32 && !L.report && !L.has_fault &&
                      (L.mode == ABFT_NONE || L.mode == ABFT_GLOBAL || L.mode == ABFT_THREAD) && C[i] != nullptr &&
                      aligned16(a_i) && (lda_i * 2) % 16 == 0 && lda_i >= d.K && ldc[i] >= d.N &&
                      (i == 0 || d.K == plan->layers[first + i - 1].desc.N);

@@ -16,7 +16,8 @@
 // be cleared between launches.
 //
 // Each tile is computed by the streaming kernel's tile routine: same arithmetic, same checks, same
-// fault flag as a launch per layer.
+// fault flag as a launch per layer (only layers that a launch of their own would give four wavefronts to
+// a tile come here).
 #pragma once
 #include "gemm_configs.h"
 #include "gemm_stream.h"

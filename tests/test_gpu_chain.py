@@ -98,6 +98,36 @@ def test_chain_in_one_launch_matches_the_oracle(M, widths, kind, dtype):
         ch.close()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("kind", ["none", "global", "thread", "mixed"])
+@pytest.mark.parametrize("M,widths", [(16, [2048, 1024, 96]), (49, [4160, 256, 2112, 64]), (1, [8192, 32])])
+def test_chain_with_long_k_loops_stores_what_the_layers_store(M, widths, kind, dtype):
+    """Chains with layers whose launches of their own put eight wavefronts on a tile (few tiles, k loops of 32 tiles and
+    more, among them loops that leave some of the eight shares a tile less), between layers with four: bit for bit the
+    results of the per-layer calls."""
+    import torch
+    nl = len(widths) - 1
+    ch = Chain(M, widths, dtype, seed=800 + M, modes=_modes(kind, nl))
+    try:
+        ways = [B.abft_k_ways(M, widths[l + 1], widths[l], DT[dtype], m)[0] for l, m in enumerate(_modes(kind, nl))]
+        assert set(ways) <= {4, 8} and 8 in ways
+        x, dx = ch.input(seed=900 + M)
+        print(f"case chain M={M} widths={widths} modes={kind} dtype={dtype}", flush=True)
+        ch.run(dx)
+        torch.cuda.synchronize()
+        assert B.abft_plan_chain_status(ch.plan) == 0 and int(ch.flag.item()) == 0
+        ch.check(x)
+        chained = [c.clone() for c in ch.Cs]
+        for l in range(nl):
+            a = dx if l == 0 else chained[l - 1]
+            B.abft_plan_run(ch.plan, l, a, widths[l], ch.Cs[l], widths[l + 1], ch.flag)
+            torch.cuda.synchronize()
+            assert ch.Cs[l].equal(chained[l]), l
+        assert int(ch.flag.item()) == 0
+    finally:
+        ch.close()
+
+
 def test_chain_under_graph_replay():
     import torch
     ch = Chain(256, TOP, "f16", seed=700, modes=_modes("mixed", 5))
