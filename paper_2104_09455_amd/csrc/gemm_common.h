@@ -975,7 +975,7 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
         }
         // wavefront tiles that lie wholly inside C: 8-byte stores of four columns per lane
         const int wrow0 = tc.bm0 + tc.wave_m * CFG::WM, wcol0 = tc.bn0 + tc.wave_n * CFG::WN;
-        const bool whole = wrow0 + CFG::WM <= M && wcol0 + CFG::WN <= N && (p.ldc & 3) == 0 &&
+        const bool whole = CFG::WM <= M - wrow0 && CFG::WN <= N - wcol0 && (p.ldc & 3) == 0 &&
                            (reinterpret_cast<uintptr_t>(p.C) & 7u) == 0;
         if (whole) {
             const long long ldcb = p.ldc * 2;
@@ -993,7 +993,7 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
     if constexpr (CFG::CSIZE == 2 && MI == 32) {
         // wavefront tiles that lie wholly inside C: 8-byte stores of four columns per lane
         const int wrow0 = tc.bm0 + tc.wave_m * CFG::WM, wcol0 = tc.bn0 + tc.wave_n * CFG::WN;
-        const bool whole = wrow0 + CFG::WM <= M && wcol0 + CFG::WN <= N && (p.ldc & 3) == 0 &&
+        const bool whole = CFG::WM <= M - wrow0 && CFG::WN <= N - wcol0 && (p.ldc & 3) == 0 &&
                            (reinterpret_cast<uintptr_t>(p.C) & 7u) == 0;
         if (whole) {
             const long long ldcb = p.ldc * 2;

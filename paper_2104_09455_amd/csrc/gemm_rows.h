@@ -79,9 +79,10 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) pos[kk] = frow * ROWB + ((4 * fgrp + kk) ^ fx) * 16;
 
-    // this lane's row of the tile whose loads go out next (they run AHEAD k tiles before the product)
-    int m_next = (t_lo + wave) * BM + frow;
-    const int m_end = t_hi * BM < M ? t_hi * BM : M;
+    // this lane's row of the tile whose loads go out next (they run AHEAD k tiles before the product;
+    // unsigned: up to AHEAD steps of rows past M, which may be close to 2^31)
+    unsigned m_next = (unsigned)(t_lo + wave) * BM + frow;
+    const unsigned m_end = (unsigned)t_hi * BM < (unsigned)M ? (unsigned)t_hi * BM : (unsigned)M;
     const char* aptr = p.A;            // its first chunk; convolutions: its top-left input pixel, possibly outside
     int a_ih0 = 0, a_iw0 = 0;
     // filter taps: one wavefront-uniform tap where all chunks of a k tile lie in it, else one per chunk
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
         d_ptr = (d_ih * p.rowpitch + (long long)d_iw * p.pix) * ESIZE;
         d_row = (p.stride * p.rowpitch - (long long)p.OW * p.stride * p.pix) * ESIZE;
         d_img = (p.imgpitch - (long long)p.OH * p.stride * p.rowpitch) * ESIZE;
-        const int m = m_next < M ? m_next : 0;
+        const int m = m_next < (unsigned)M ? (int)m_next : 0;
         const int img = m / (p.OH * p.OW);
         const int rem = m - img * (p.OH * p.OW);
         const int oh = rem / p.OW, ow = rem - oh * p.OW;

@@ -124,3 +124,36 @@ def test_activation_and_sums_left_for_the_next_layer(dtype):
     torch.cuda.synchronize()
     assert int(flag.item()) == 1
     B.abft_plan_destroy(plan)
+
+
+def test_rows_up_to_the_largest_count():
+    """2^31 - 128 rows (a 1 x 8 filter over 128 images of one very long line): the loads that run ahead of the last
+    tiles count rows past 2^31, and must neither read there nor take those rows for rows of C."""
+    import torch
+    from gpu_util import DEV
+    batch, ow, cin, kw = 128, 2 ** 24 - 1, 8, 8
+    W, M, K = ow + kw - 1, batch * ow, kw * cin
+    assert M == 2 ** 31 - 128 and B.abft_tile_shape(M, 1, K, B.F16)[:2] == (32, 64)
+    x = torch.empty(batch * W * cin, dtype=torch.float16, device=DEV)
+    n = 1 << 22
+    x[:n].normal_(generator=torch.Generator(device=DEV).manual_seed(1))
+    while n < x.numel():
+        m = min(n, x.numel() - n)
+        x[n:n + m] = x[:m]
+        n += m
+    w = torch.randn(K, device=DEV, generator=torch.Generator(device=DEV).manual_seed(2)).half()
+    C = torch.full((M,), 7.0, dtype=torch.float16, device=DEV)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    conv = B.Conv(batch, 1, W, cin, 1, kw, 1, 0)
+    print("case", M, 1, K, flush=True)
+    B.abft_conv(conv, 1, x, w, K, B.B_NK, C, 1, B.F16, B.THREAD, fault_flag=flag)
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 0
+    rows = torch.cat([torch.arange(0, 4096), torch.arange(M // 2, M // 2 + 4096), torch.arange(M - 16384, M)]).to(DEV)
+    at = (rows // ow) * (W * cin) + (rows % ow) * cin
+    ref = torch.empty(rows.numel(), dtype=torch.float64, device=DEV)
+    for i in range(0, rows.numel(), 4096):
+        ref[i:i + 4096] = (x[at[i:i + 4096, None] + torch.arange(K, device=DEV)].double() * w.double()).sum(1)
+    assert c_close(C[rows].double().cpu().numpy(), ref.cpu().numpy(), "f16")
+    del x, C
+    torch.cuda.empty_cache()
