@@ -138,8 +138,9 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
             if constexpr (ONE_TAP) {
                 const bool ok = m_next < m_end && (unsigned)(a_ih0 + u_kh) < (unsigned)p.H && (unsigned)(a_iw0 + u_kw) < (unsigned)p.W;
                 const char* src = ok ? aptr + u_off + fgrp * 64 : g_zero_chunk;
+                // (a lowered row's segment can be a whole k tile; it starts at a multiple of four bytes)
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) f[kk] = ld16g(src + kk * 16);
+                for (int kk = 0; kk < 4; ++kk) f[kk] = ld16u(src + kk * 16);
             } else {
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {

@@ -157,3 +157,32 @@ def test_rows_up_to_the_largest_count():
     assert c_close(C[rows].double().cpu().numpy(), ref.cpu().numpy(), "f16")
     del x, C
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("conv", [
+    wl.Conv(44, 111, 109, 9, 64, 7, 7, 2, 3),      # lowered to segments of a whole k tile that start at multiples of four bytes
+    wl.Conv(44, 112, 110, 64, 256, 1, 1, 2, 0),    # one tap, stride 2, four column blocks
+    wl.Conv(44, 55, 56, 64, 33, 3, 3, 1, 1),       # one tap per k tile, nine of them
+    wl.Conv(44, 55, 56, 32, 64, 3, 3, 1, 1),       # two taps per k tile and half a tile left: not on this kernel
+], ids=str)
+def test_convolutions_with_one_tap_per_k_tile(conv, dtype):
+    d = DeviceConv(conv, dtype, seed=41)
+    A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
+    assert d.M >= 131072
+    rows = sample_rows(d.M, 3000)
+    C_ref = oracle.gemm(A[rows], d.Wm, dtype)
+    for mode in (B.NONE, B.THREAD, B.THREAD_HALF):
+        print("case", conv, dtype, mode, flush=True)
+        d.dC.fill_(7.0)
+        flag, rep = d.run(mode)
+        assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        if mode != B.THREAD:
+            continue
+        # finished and running accumulators, first and last rows and columns
+        for i, j, k_after in [(0, conv.Cout - 1, -1), (d.M - 1, 0, -1), (d.M // 3, 5, 64), (d.M - 2, 32, (d.K - 1) // 64 * 64)]:
+            if not 0 < k_after < d.K:
+                k_after = -1
+            bit = _huge_flip(A, d.Wm, dtype, i, j, k_after)
+            flag, _ = d.run(mode, inject=B.Fault(i, j, bit, k_after), want_report=False)
+            assert flag == 1, (i, j, bit, k_after)
