@@ -296,6 +296,10 @@ int abft_region_shape(int M, int N, int K, int dtype, int aligned, int *region_m
  * comparison on the added-up tile, so the split only matters for where an injected fault
  * lands (abft_fault_t).  ways = 1: not split. */
 int abft_k_ways(int M, int N, int K, int dtype, int aligned, int mode, int *ways, int *step);
+/* Name of the tile configuration a product runs on under `mode` (diagnostics; NULL: a value out of
+ * range).  conv != 0: a convolution that is read as an implicit M x K matrix; unprotected ones can
+ * run on another configuration than a product of their size. */
+const char *abft_kernel_name(int M, int N, int K, int dtype, int aligned, int mode, int conv);
 
 /* Comparison tolerance (the paper states none; Sec. 2.4 step 4 says "compare").  A comparison
  * covers a region C_S of C -- one workgroup tile (abft_region_shape) for GLOBAL, one wavefront

@@ -60,7 +60,7 @@ EXPORTS = [
     "abft_plan_run_all", "abft_plan_set_mode", "abft_k_ways", "abft_beta_bytes", "abft_conv_workspace_bytes",
     "abft_plan_set_activation", "abft_plan_activation", "abft_gemm_static", "abft_static_scratch_bytes",
     "abft_tolerance_half_coeff", "abft_plan_run_chain", "abft_plan_chain_status", "abft_plan_chain_reset",
-    "abft_plan_set_diagnostics", "abft_handover_launches", "abft_mfma_probe", "abft_mfma_probe_bytes",
+    "abft_plan_set_diagnostics", "abft_kernel_name", "abft_handover_launches", "abft_mfma_probe", "abft_mfma_probe_bytes",
 ]
 
 _lib = None
@@ -128,6 +128,8 @@ def lib() -> ctypes.CDLL:
     L.abft_plan_chain_status.argtypes = [vp, ctypes.POINTER(ctypes.c_uint32), vp]
     L.abft_plan_chain_reset.restype = ci
     L.abft_plan_chain_reset.argtypes = [vp, ci, vp]
+    L.abft_kernel_name.restype = ctypes.c_char_p
+    L.abft_kernel_name.argtypes = [ctypes.c_int] * 7
     L.abft_handover_launches.restype = ctypes.c_longlong
     L.abft_handover_launches.argtypes = []
     L.abft_mfma_probe_bytes.restype = ctypes.c_size_t
@@ -230,6 +232,12 @@ def abft_k_ways(M, N, K, dtype, mode, aligned=True):
     w, st = ctypes.c_int(), ctypes.c_int()
     _check(lib().abft_k_ways(M, N, K, dtype, 1 if aligned else 0, mode, ctypes.byref(w), ctypes.byref(st)))
     return w.value, st.value
+
+
+def abft_kernel_name(M, N, K, dtype, mode, aligned=True, conv=False):
+    """Name of the tile configuration a product (conv: of a convolution) runs on under `mode`."""
+    name = lib().abft_kernel_name(M, N, K, dtype, 1 if aligned else 0, mode, 1 if conv else 0)
+    return name.decode() if name else None
 
 
 def abft_k_parts(M, N, K, dtype, mode, aligned=True):

@@ -95,8 +95,9 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // tile configuration choice (host logic)
 // ------------------------------------------------------------------------- //
 // mode: the scheme the product will run with; force >= 0 pins a configuration (tuning aid,
-// environment variable ABFT_FORCE_CFG).
-int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
+// environment variable ABFT_FORCE_CFG).  conv: the product of a convolution read as an implicit
+// matrix (unprotected products only: what is reported of the other schemes' tiles has no such word).
+int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode, bool conv = false) {
     // (every wavefront-level scheme is checked per wavefront tile: the same tiles)
     if (mode == ABFT_REPLICA || mode == ABFT_THREAD_HALF || mode == ABFT_TWOSIDED) mode = ABFT_THREAD;
     if (mode == ABFT_GLOBAL_WEIGHTED) mode = ABFT_GLOBAL;
@@ -146,19 +147,28 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode) {
         // k loop of four tiles: level).  Its wavefront tiles carry no wavefront-level scheme.
         const long long t256n = tiles(CFG_F256N);
         if (fast_ok && mode != ABFT_THREAD && N >= 128 && nkt_all >= 6 && t256n >= 144 && t256n <= 256) return CFG_F256N;
+        // Very many rows whose weights fit in LDS: the row-streaming kernel, from two 32-row tiles per wavefront
+        // of the chip on (below, the loads into an empty pipeline lose: 50176 x 64 x 256 18.6 / 16.9 us thread-level
+        // / unprotected against 18 / 13.5 on 128 x 128 tiles, 70000 rows 19 / 13 against 18 / 15).
+        // Unprotected: every convolution, whose neighbouring rows share their input (against the better of 128
+        // x 128 and 256 x 64 tiles: 3 x 3 64 -> 64 on 131712 rows 27 / 30, on 200704 bf16 35 / 39; 128 -> 64 44 /
+        // 47; stem on 802816 rows 71 / 90; 1 x 1, stride 2, 64 -> 64 16 / 17); products of two to four k tiles
+        // (180000 x 64 x 128 18 / 19, 262144 x 16 x 192 28 / 31; five k tiles level, 180000 x 16 x 320 32 / 31, twenty
+        // 82 / 75) and of one with more than 128 columns (262144 x 192 x 64 35 / 43, 131072 x 1280 x 64 90 / 112; 128
+        // columns 17 / 16, 64 columns 12 / 11).
+        // Wavefront-level: whatever fits (thread-level 131072 x 64 x 1280 85 / 87, 200000 x 64 x 256 35 / 41; 3 x 3
+        // 64 -> 64 on 200704 rows 39 / 56) but for one k tile with 65 to 128 columns (400000 x 128 x 64 50 / 47) and
+        // more than eighteen k tiles with at most 32 columns (131072 x 32 x 1280 81 / 77).
+        const bool rows_pay = mode == ABFT_THREAD ? (nkt_all == 1 ? N <= 64 || N > 128 : nkt_all <= 18 || N > 32)
+                                                  : conv || (nkt_all == 1 ? N > 128 : nkt_all <= 4);
+        if (rows_fit && M >= 131072 && rows_pay) return CFG_R64;
         // Outputs of at most 64 columns and very many rows (ResNet-50's first stage at batch 64: 200704
-        // rows): 256 x 64 tiles with three stages.  3 x 3 convolution 64 -> 64: 46 us against 52 us
-        // unprotected, 52 against 63 global; K = 64: 17 against 23 us global, level unprotected; k loops
-        // of two to five tiles: slower unprotected (33 against 30 us at K = 256).
+        // rows) otherwise: 256 x 64 tiles with three stages.  3 x 3 convolution 64 -> 64: 52 us against 63 on 128 x 128
+        // tiles, global; K = 64: 17 against 23 us global, level unprotected; k loops of two to five
+        // tiles: slower unprotected (33 against 30 us at K = 256).
         if (fast_ok && mode != ABFT_THREAD && N <= 64 && N > 32 && M >= 65536 &&
             (nkt_all >= 6 || (nkt_all == 1 && mode == ABFT_GLOBAL)))
             return CFG_F256S;
-        // Very many rows whose weights fit in LDS: the row-streaming kernel, from two 32-row tiles per wavefront
-        // of the chip on (thread-level / unprotected against 128 x 128 tiles: 3 x 3 convolution 64 -> 64 on 200704
-        // rows 41 / 35 us against 60 / 45, 200704 x 256 x 64 40 / 38 against 50 / 42, stem on 802816 rows 85 /
-        // 74 against 115 / 96; at 70000 to 100000 rows level: 70000 x 64 x 256 19 / 13 against 18 / 15, stem 25 /
-        // 23 against 24 / 21; at 50176 rows the loads into an empty pipeline lose, 18.6 / 16.9 against 18 / 13.5).
-        if (rows_fit && M >= 131072) return CFG_R64;
         const bool fills128 = tiles(CFG_F128) >= 128;
         if (fast_ok && fills128 && N < 128) return CFG_F128T;  // narrow outputs: every wavefront spans all columns
         // Few tiles: the time is the latency of a workgroup's k loop and the rate at which one
@@ -790,7 +800,7 @@ int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, 
 
     const bool avec = a_vectorisable(pr), bvec = b_vectorisable(pr);
     const bool all16 = avec && bvec;
-    const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, all16, mode);
+    const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, all16, mode, pr.conv);
     const CfgInfo ci = cfg_info_host(cfg);
     const int bk = ci.bk_bytes / esize(pr.dtype);
 
@@ -1218,6 +1228,12 @@ int abft_k_ways(int M, int N, int K, int dtype, int aligned, int mode, int* ways
     if (ways) *ways = ci.kways;
     if (step) *step = ci.kway_bytes / esize(dtype);
     return ABFT_OK;
+}
+
+const char* abft_kernel_name(int M, int N, int K, int dtype, int aligned, int mode, int conv) {
+    if (!valid_dtype(dtype) || M <= 0 || N <= 0 || K <= 0 || mode < ABFT_NONE || mode > ABFT_GLOBAL_WEIGHTED) return nullptr;
+    if (mode == ABFT_AUTO) mode = select_mode(M, N, K, dtype);
+    return cfg_name(pick_cfg(M, N, K, dtype, aligned != 0, mode, conv != 0));
 }
 
 double abft_arithmetic_intensity(int M, int N, int K, int dtype) {

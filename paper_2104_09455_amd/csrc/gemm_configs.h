@@ -36,6 +36,12 @@ namespace abft {
 //    G64K 64 x 64 with four groups of four wavefronts sharing the k tiles: at most about one tile per compute unit
 enum CfgId { CFG_F256W = 0, CFG_F128, CFG_F128T, CFG_F64T, CFG_S32, CFG_S64, CFG_S128, CFG_G128, CFG_G64, CFG_G16, CFG_F256N, CFG_F256S, CFG_F128E, CFG_G64K, CFG_R64, CFG_S32W, CFG_COUNT };
 
+inline const char* cfg_name(int id) {
+    static const char* const names[CFG_COUNT] = {"F256W", "F128", "F128T", "F64T", "S32", "S64", "S128", "G128", "G64", "G16",
+                                                 "F256N", "F256S", "F128E", "G64K", "R64", "S32W"};
+    return id >= 0 && id < CFG_COUNT ? names[id] : nullptr;
+}
+
 template <int DT, int ID>
 struct CfgOf;
 //                                             MI TM TN WM WN BKB

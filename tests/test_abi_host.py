@@ -192,3 +192,25 @@ def test_tile_choice_for_few_tiles(lib):
     # streaming tiles split k over four wavefronts
     assert B.abft_k_ways(256, 1024, 1024, B.F16, B.THREAD)[0] == 4
     assert B.abft_k_ways(8192, 8192, 8192, B.F16, B.THREAD)[0] == 1
+
+
+def test_row_streaming_kernel_runs_where_its_rule_says(lib):
+    """Which kernel products of very many rows run on: under every scheme that the row-streaming kernel carries, and
+    where it was measured to be the slower one, not."""
+    name = B.abft_kernel_name
+    for dt in (B.F16, B.BF16):
+        # the first stage's 3 x 3 convolution, unprotected and wavefront-level; its product from 256 x 64 tiles unprotected
+        for mode in (B.NONE, B.THREAD, B.REPLICA, B.THREAD_HALF, B.TWOSIDED):
+            assert name(200704, 64, 576, dt, mode, conv=True) == "R64"
+            assert name(131072, 64, 1280, dt, mode, conv=True) == "R64"
+            assert name(131071, 64, 576, dt, mode, conv=True) != "R64"
+            assert name(131072, 64, 1344, dt, mode, conv=True) != "R64"      # weights beyond LDS
+            assert name(131072, 64, 576, dt, mode, aligned=False, conv=True) != "R64"
+        assert name(200704, 64, 576, dt, B.NONE) == "F256S"
+        assert [name(200704, 64, 64 * t, dt, B.NONE) == "R64" for t in range(1, 6)] == [False, True, True, True, False]
+        assert [name(200704, n, 64, dt, B.NONE) == "R64" for n in (64, 128, 129, 1280, 1281)] == [False, False, True, True, False]
+        assert [name(200704, n, 64, dt, B.THREAD) == "R64" for n in (64, 65, 128, 129, 1280, 1281)] == [True, False, False, True, True, False]
+        assert [name(200704, n, k, dt, B.THREAD) == "R64" for n, k in ((32, 1152), (32, 1216), (33, 1216))] == [True, False, True]
+        assert name(200704, 64, 576, dt, B.GLOBAL) == "F256S"
+    assert name(200704, 64, 1024, B.I8, B.THREAD) != "R64"
+    assert name(0, 64, 64, B.F16, B.NONE) is None and name(64, 64, 64, B.F16, 99) is None

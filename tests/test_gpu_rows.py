@@ -17,6 +17,8 @@ WAVE = [B.NONE, B.THREAD, B.REPLICA, B.THREAD_HALF, B.TWOSIDED]
 # and 20 k tiles; ragged rows and columns
 SHAPES = [(131072, 64, 64), (131105, 256, 64), (131104, 1280, 64), (131536, 64, 128), (131072, 40, 192),
           (131081, 64, 256), (131072, 64, 320), (131072, 64, 576), (131103, 33, 1280)]
+# those of them that run on it unprotected too
+UNPROTECTED = [(131105, 256, 64), (131104, 1280, 64), (131536, 64, 128), (131072, 40, 192), (131081, 64, 256)]
 
 
 def _huge_flip(A, Bm, dtype, i, j, k_after):
@@ -40,8 +42,11 @@ def test_products_of_very_many_rows(shape, dtype):
         d.dC.fill_(7.0)
         flag, rep = d.run(mode)
         assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        kernel = B.abft_kernel_name(M, N, K, d.dt, mode)
         if mode == B.NONE:
+            assert (kernel == "R64") == (shape in UNPROTECTED)
             continue
+        assert kernel == "R64"
         if mode == B.THREAD:
             whole = d.dC.clone()
         assert d.dC.equal(whole)     # (every wavefront-level scheme stores the same product)
@@ -74,9 +79,11 @@ def test_convolutions_of_very_many_rows(conv, dtype):
     d = DeviceConv(conv, dtype, seed=31)
     A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
     assert d.M >= 131072
+    K = d.K if conv.Cin % 8 == 0 else 192     # (lowered: seven segments of 24, filled up to whole k tiles)
     rows = sample_rows(d.M, 3000)
     C_ref = oracle.gemm(A[rows], d.Wm, dtype)
     for mode in (B.NONE, B.THREAD, B.TWOSIDED):
+        assert B.abft_kernel_name(d.M, d.N, K, d.dt, mode, conv=True) == "R64"
         print("case", conv, dtype, mode, flush=True)
         flag, rep = d.run(mode)
         assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
