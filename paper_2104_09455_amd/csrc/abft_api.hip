@@ -117,15 +117,17 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode, bool conv = 
                           (N <= 64 || (long long)K * esize(dt) == 128) && cdiv(N, 64) * cdiv((long long)K * esize(dt), 128) <= 20;
     if (force == CFG_R64 && rows_fit) return force;
     if (force_fits && force != CFG_R64 && !((force == CFG_F256W || force == CFG_F256N || force == CFG_F256S || force == CFG_F128E) && mode == ABFT_THREAD)) return force;
-    // (a long k loop: the groups of the 64 x 64 tile that share it outweigh the rows of zeros: 16 x 4096 x
-    // 4095 27 against 45 us; near level at half to a quarter of that, 16 x 512 x 1023 9.9 / 10.7; 16 x 512
-    // x 300 6.4 / 5.5)
     const long long nkt_gen = cdiv((long long)K * esize(dt), 128);
-    if (M <= 16 && !aligned16) return nkt_gen >= 32 ? CFG_G64K : CFG_G16;
     auto tiles = [&](int id) {
         CfgInfo ci = cfg_info_host(id);
         return cdiv(M, ci.bm) * cdiv(N, ci.bn);
     };
+    // (few rows, a long k loop, at most one 64 x 64 tile per compute unit: the groups that share the tile's k
+    // loop outweigh its rows of zeros: 16 x 4096 x 4095 27 against 45 us, 16 x 16384 x 2049 18 / 26, 16384 x 4096 K
+    // x N 35 / 53; near level at half to a quarter of that k loop, 16 x 512 x 1023 9.9 / 10.7; 16 x 512 x 300
+    // 6.4 / 5.5.  A second round of workgroups that fill a compute unit each costs more than it gives: 1 x 32000
+    // x 4095 71 / 59, 8 x 128000 x 2049 153 / 121)
+    if (M <= 16 && !aligned16) return nkt_gen >= 32 && tiles(CFG_G64K) <= 256 ? CFG_G64K : CFG_G16;
     if (aligned16) {
         // fill the 256 compute units before growing the tile
         // (thread-level: the 128 x 128 tile of wide wavefront tiles; the 256 x 256 one would spill)

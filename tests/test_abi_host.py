@@ -214,3 +214,15 @@ def test_row_streaming_kernel_runs_where_its_rule_says(lib):
         assert name(200704, 64, 576, dt, B.GLOBAL) == "F256S"
     assert name(200704, 64, 1024, B.I8, B.THREAD) != "R64"
     assert name(0, 64, 64, B.F16, B.NONE) is None and name(64, 64, 64, B.F16, 99) is None
+
+
+def test_few_unaligned_rows_share_the_k_loop_only_in_one_round(lib):
+    """Up to sixteen rows, unaligned: four groups of wavefronts on a 64 x 64 tile where the k loop is long and each tile
+    has a compute unit; wider outputs stay on 16 x 64 tiles."""
+    name = B.abft_kernel_name
+    for dt, k in ((B.F16, 2047), (B.BF16, 4095), (B.I8, 8001)):
+        for mode in (B.NONE, B.GLOBAL, B.THREAD):
+            for m in (1, 16):
+                assert name(m, 256 * 64, k, dt, mode, aligned=False) == "G64K"
+                assert name(m, 256 * 64 + 1, k, dt, mode, aligned=False) == "G16"
+    assert name(16, 512, 1983, B.F16, B.THREAD, aligned=False) == "G16"
