@@ -184,9 +184,16 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode, bool conv = 
         // Fewer than a quarter of the compute units in use and a long k loop: eight wavefronts per tile, two per
         // SIMD, so that one's copies and address work run under the other's products (3 x 3 convolutions at batch
         // 1: 512 -> 512 on 49 rows, 32 tiles of 72 k tiles, 10.3 against 11.7 us thread-level, 256 -> 256 on 196
-        // rows 7.5 / 8.1; 49 x 512 x 4608 7.9 / 8.1).  More tiles: level for products (256 x 512 x 2048 5.9 / 5.9,
-        // 16 x 4096 x 4096 8.9 / 8.7).
-        if (tiles(CFG_S32) <= 256) return nkt_all >= 32 && tiles(CFG_S32) < 64 ? CFG_S32W : CFG_S32;
+        // rows 7.6 / 8.2; 16 x 512 x 8192 10.9 / 11.9; global 16 x 2016 x 8192 13.8 / 16.9).  More tiles: level for
+        // products (256 x 512 x 2048 5.9 / 5.9, 16 x 4096 x 4096 8.9 / 8.7).  Unprotected there is little to run
+        // under, and four wavefronts with twice the stages each stream long loops better: eight up to 128 k
+        // tiles (4 tiles of 128: 9.8 / 10.2, of 256: 18.8 / 18.0) and nine of them per compute unit of the chip (49 x
+        // 512 x 4608 6.9 / 7.2, 16 x 1024 x 4096 6.5 / 6.7; 16 x 1280 x 4096 7.4 / 7.2, 16 x 2016 x 16384 20.6 / 19.0).
+        if (tiles(CFG_S32) <= 256) {
+            const bool eight = nkt_all >= 32 && tiles(CFG_S32) < 64 &&
+                               (mode != ABFT_NONE || (nkt_all <= 128 && tiles(CFG_S32) * nkt_all <= 9 * 256));
+            return eight ? CFG_S32W : CFG_S32;
+        }
         if (tiles(CFG_S64) <= 256) return CFG_S64;
         if (tiles(CFG_S128) <= 256 ? nkt_all >= 4 : (tiles(CFG_S128) <= 512 && nkt_all >= (mode == ABFT_THREAD ? 8 : 16))) return CFG_S128;
         if (fast_ok) {

@@ -226,3 +226,16 @@ def test_few_unaligned_rows_share_the_k_loop_only_in_one_round(lib):
                 assert name(m, 256 * 64, k, dt, mode, aligned=False) == "G64K"
                 assert name(m, 256 * 64 + 1, k, dt, mode, aligned=False) == "G16"
     assert name(16, 512, 1983, B.F16, B.THREAD, aligned=False) == "G16"
+
+
+def test_eight_wavefronts_per_tile_where_they_pay(lib):
+    """Few 32 x 32 tiles with long k loops: eight wavefronts each under every scheme, unprotected only up to so much
+    work (a loop of 128 k tiles, nine k tiles per compute unit)."""
+    name = B.abft_kernel_name
+    for dt, tile in ((B.F16, 64), (B.BF16, 64), (B.I8, 128)):
+        for mode in (B.GLOBAL, B.THREAD, B.REPLICA):
+            assert name(16, 63 * 32, 256 * tile, dt, mode) == "S32W" and name(16, 64 * 32, 32 * tile, dt, mode) == "S32"
+            assert name(16, 32, 32 * tile, dt, mode) == "S32W" and name(16, 32, 31 * tile, dt, mode) == "S32"
+        for tiles, k_tiles, eight in ((18, 128, True), (18, 129, False), (19, 128, False), (1, 129, False), (63, 36, True),
+                                      (63, 37, False), (32, 72, True), (1, 31, False), (64, 32, False)):
+            assert (name(16, 32 * tiles, k_tiles * tile, dt, B.NONE) == "S32W") == eight, (tiles, k_tiles)
