@@ -130,7 +130,7 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode, bool conv = 
     if (M <= 16 && !aligned16) return nkt_gen >= 32 && tiles(CFG_G64K) <= 256 ? CFG_G64K : CFG_G16;
     if (aligned16) {
         // fill the 256 compute units before growing the tile
-        // (thread-level: the 128 x 128 tile of wide wavefront tiles; the 256 x 256 one would spill)
+        // (wavefront-level: the 128 x 128 tile of wide wavefront tiles; the 256 x 256 one would spill)
         // (a single k tile: the 128 x 128 tile, of which several fit a compute unit at once)
         const long long nkt_all = cdiv((long long)K * esize(dt), 128);
         // The 256 x 256 tile runs one workgroup per compute unit, in rounds of 256: it is taken when
@@ -177,10 +177,12 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode, bool conv = 
         // compute unit can stream its operands, so the streaming configurations take over (no
         // barriers in the k loop, four wavefronts sharing the k tiles): the smallest tile that
         // still fits the chip in one round of workgroups, 64 x 64 for up to two rounds (that one
-        // only with a k loop of at least one tile per wavefront, sixteen tiles (thread-level: eight) for a second round:
+        // only with a k loop of at least one tile per wavefront, sixteen tiles for a second round:
         // the idle wavefronts of a short loop cost more than the barriers they save; 3000 x 384 x
-        // 384 takes 9.9 us on 282 such tiles, 8.2 us on 64 x 128 tiles).  (On the 32 x 32 tile the thread-level
-        // scheme's checksum operand is the B fragment itself: no vector work at all.)
+        // 384 takes 9.9 us on 282 such tiles, 8.2 us on 64 x 128 tiles; thread-level, fp16, 2048 x 1024 x 512 12.3
+        // against 10.5, K = 768 14.7 / 13.5, K = 1024 16.7 / 16.3, K = 2048 23.3 / 25.6).  Wavefront-level bf16 and
+        // int8 from eight: their checksums cost vector work, more of it on the 64 x 128 tile's wide wavefront
+        // tiles (K = 512 bf16, half-precision sums, 11.9 / 13.3, exact 12.8 / 10.8; int8 K = 1024 14.6 / 17.5).
         // Fewer than a quarter of the compute units in use and a long k loop: eight wavefronts per tile, two per
         // SIMD, so that one's copies and address work run under the other's products (3 x 3 convolutions at batch
         // 1: 512 -> 512 on 49 rows, 32 tiles of 72 k tiles, 10.3 against 11.7 us thread-level, 256 -> 256 on 196
@@ -195,11 +197,12 @@ int pick_cfg(int M, int N, int K, int dt, bool aligned16, int mode, bool conv = 
             return eight ? CFG_S32W : CFG_S32;
         }
         if (tiles(CFG_S64) <= 256) return CFG_S64;
-        if (tiles(CFG_S128) <= 256 ? nkt_all >= 4 : (tiles(CFG_S128) <= 512 && nkt_all >= (mode == ABFT_THREAD ? 8 : 16))) return CFG_S128;
+        if (tiles(CFG_S128) <= 256 ? nkt_all >= 4 : (tiles(CFG_S128) <= 512 && nkt_all >= (mode == ABFT_THREAD && dt != ABFT_F16 ? 8 : 16))) return CFG_S128;
         if (fast_ok) {
-            // (thread-level: the wide wavefront tiles pay off once two workgroups share a compute unit;
-            // with at most one per unit the 64 x 64 wavefront tiles' cheaper checksum wins: 1536 x 2048 x
-            // 2048 takes 37 us against 42 us, 640 x 5120 x 1280 26 us against 30 us)
+            // (wavefront-level: 64 x 64 wavefront tiles with at most one workgroup per compute unit, 32 x 128 ones once
+            // two share it.  The exact scheme issues the same MFMAs on both and is level, the wide tiles 0 to 3 %
+            // behind: 1536 x 2048 x 2048 33.1 / 33.8 us, 4096^3 222 / 226; fp16 half-precision sums take an extra MFMA
+            // per A fragment, of which the wide tiles have half: 3072 x 2048 x 2048 49.2 / 45.8, 4096^3 193 / 183)
             // At most one 128 x 128 tile per compute unit (one round): eight wavefronts of 32 x 64 on the
             // 16x16x32 shapes with three stages instead of four wavefronts of 64 x 64 with two: the second
             // wavefront per SIMD and the deeper pipeline hide what a second workgroup would (1024 x 4096 x

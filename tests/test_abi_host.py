@@ -239,3 +239,14 @@ def test_eight_wavefronts_per_tile_where_they_pay(lib):
         for tiles, k_tiles, eight in ((18, 128, True), (18, 129, False), (19, 128, False), (1, 129, False), (63, 36, True),
                                       (63, 37, False), (32, 72, True), (1, 31, False), (64, 32, False)):
             assert (name(16, 32 * tiles, k_tiles * tile, dt, B.NONE) == "S32W") == eight, (tiles, k_tiles)
+
+
+def test_second_round_of_streaming_tiles_needs_a_k_loop(lib):
+    """257 to 512 tiles of 64 x 64: the streaming kernel from sixteen k tiles on; wavefront-level bf16 and int8, whose
+    checksums cost vector work, from eight."""
+    name = B.abft_kernel_name
+    for dt, tile, thread_from in ((B.F16, 64, 16), (B.BF16, 64, 8), (B.I8, 128, 8)):
+        for k_tiles in (7, 8, 15, 16):
+            assert (name(2048, 1024, k_tiles * tile, dt, B.THREAD) == "S128") == (k_tiles >= thread_from)
+            assert (name(2048, 1024, k_tiles * tile, dt, B.GLOBAL) == "S128") == (k_tiles >= 16)
+        assert name(1024, 1024, 4 * tile, dt, B.THREAD) == "S128"
