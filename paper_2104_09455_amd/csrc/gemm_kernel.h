@@ -26,8 +26,11 @@ __device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
 // The kernel.  KG groups of CFG::THREADS threads each own the whole workgroup tile and take the k
 // tiles t with t % KG == group, each with LDS buffers of its own; at the end the groups' partial
 // tiles (and redundant accumulators) are added in group order and group 0 checks and stores.
+// VEC: both operands are read in aligned 16-byte chunks (a_vec and b_vec); an instance of its own, since the
+// other loaders' registers and branches cost such products a fifth (4000 x 4000 x 1000 fp16 unprotected 74 us, so
+// 59; int8 thread-level, K = 4016, 283 / 199; 5 x 5 convolution 40 -> 120 on 100352 rows 76 / 53).
 // ---------------------------------------------------------------------------
-template <class CFG, int MODE, bool INJ, bool CONV, int KG>
+template <class CFG, int MODE, bool INJ, bool CONV, int KG, bool VEC>
 __global__ __launch_bounds__(CFG::THREADS * KG) __attribute__((amdgpu_waves_per_eu(INJ || KG > 1 ? 1 : min_waves_per_simd<CFG, MODE>())))
 void gemm_kernel(const GemmArgs p) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
@@ -95,14 +98,15 @@ void gemm_kernel(const GemmArgs p) {
 
     // rows read 16 bytes at a time at any alignment: a chunk that K cuts short is read as the last 16
     // bytes of its row and shifted down when it goes to LDS
-    const bool a_row = !CONV && !p.a_vec && K >= EPC;
-    const bool b_row = !p.b_vec && p.b_sk == 1 && K >= EPC;
+    const bool a_vec = VEC || p.a_vec, b_vec = VEC || p.b_vec;
+    const bool a_row = !CONV && !a_vec && K >= EPC;
+    const bool b_row = !b_vec && p.b_sk == 1 && K >= EPC;
     // weights stored K x N: units of eight k times four bytes of n (four bytes of a row end inside it)
     constexpr int NPD = 4 / ESIZE;                     // columns per four bytes
     constexpr int NGN = BN / NPD;                      // such groups per row of the tile
     constexpr int UNITS = NB / 2;                      // units per thread
     static_assert(NB % 2 == 0 && CFG::THREADS * UNITS == NGN * (BK / 8), "units of the transposing loader");
-    const bool b_turn = !p.b_vec && !b_row && p.b_sn == 1 && N >= NPD;
+    const bool b_turn = !b_vec && !b_row && p.b_sn == 1 && N >= NPD;
     auto load_a = [&](int kt, i32x4(&regs)[NA]) {
         const int k0 = kt * BK + kc * EPC;  // first k of this thread's chunk
         if constexpr (!CONV) {
@@ -115,7 +119,7 @@ void gemm_kernel(const GemmArgs p) {
                     if (m < M && k0 < K) v = ld16u(p.A + ((long long)m * p.lda + ks) * ESIZE);
                     regs[t] = v;
                 }
-            } else if (p.a_vec) {
+            } else if (a_vec) {
 #pragma unroll
                 for (int t = 0; t < NA; ++t) {
                     int m = bm0 + r0 + t * RPP;
@@ -132,7 +136,7 @@ void gemm_kernel(const GemmArgs p) {
                 }
             }
         } else {
-        if (p.a_vec) {
+        if (a_vec) {
             // a chunk never straddles a filter tap (Cin is a multiple of the chunk length)
 #pragma unroll
             for (int t = 0; t < NA; ++t) {
@@ -224,7 +228,7 @@ void gemm_kernel(const GemmArgs p) {
                     regs[2 * t + (e >> 2)][e & 3] = ld4u(src + (long long)(k < K ? k : K - 1) * p.ldb * ESIZE);
                 }
             }
-        } else if (p.b_vec) {
+        } else if (b_vec) {
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 int n = bn0 + r0 + t * RPP;

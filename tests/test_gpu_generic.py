@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import DT, c_close, run_gemm
+from gpu_util import DT, DeviceConv, c_close, run_gemm, sample_rows
 from paper_2104_09455_amd import binding as B
 from paper_2104_09455_amd import workloads as wl
 
@@ -62,3 +62,45 @@ def test_faults_where_groups_share_a_tile_along_k(mode, dtype):
                 bad = oracle.inject(A, Bm, C_ref, dtype, i, j, bit, k_after=k_after,
                                     k_set=parts[oracle.part_of(parts, (K if k_after < 0 else k_after) - 1)])
             assert np.array_equal(r.C, ((bad + 2 ** 31) % 2 ** 32) - 2 ** 31), k_after
+
+
+# 64 x 64 and 128 x 128 tiles; k loops of whole 16-byte chunks that end inside a k tile (one chunk into it, one short of
+# it), ragged rows and columns
+ALIGNED = [(1900, 1100, 200, "G64"), (1900, 1100, 376, "G64"), (3000, 1000, 72, "G128"), (2997, 1003, 248, "G128")]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("case", ALIGNED, ids=str)
+def test_aligned_operands_take_the_general_path_s_results(case, dtype):
+    """Aligned operands whose k loop is no whole number of k tiles have instances of the kernel of their own: bit for
+    bit what the general ones store, and right."""
+    M, N, K, kernel = case
+    K = 2 * K if dtype == "i8" else K
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + K, dist_a="normal", dist_b="normal")
+    rows = sample_rows(M, 400)
+    C_ref = oracle.gemm(A[rows], Bm, dtype)
+    for mode in (B.NONE, B.GLOBAL, B.THREAD, B.REPLICA, B.THREAD_HALF, B.TWOSIDED):
+        print("case", case, dtype, mode, flush=True)
+        assert {B.abft_kernel_name(M, N, K, DT[dtype], mode, al) for al in (True, False)} == {kernel}
+        a = run_gemm(A, Bm, dtype, mode, use_beta=mode == B.GLOBAL)
+        u = run_gemm(A, Bm, dtype, mode, misalign=1, use_beta=mode == B.GLOBAL)
+        assert np.array_equal(a.C, u.C) and c_close(a.C[rows], C_ref, dtype), mode
+        assert a.flag == 0 and u.flag == 0
+        assert mode == B.NONE or (a.report.worst_ratio < 0.5 and a.report.tiles == u.report.tiles)
+
+
+@pytest.mark.parametrize("dtype,conv,kernel", [
+    ("f16", wl.Conv(8, 64, 63, 24, 48, 3, 3, 1, 1), "G128"), ("bf16", wl.Conv(20, 50, 44, 40, 150, 5, 5, 2, 2), "G64"),
+    ("i8", wl.Conv(16, 28, 28, 96, 96, 3, 3, 1, 1), "G64")], ids=str)
+def test_convolutions_of_whole_chunks(dtype, conv, kernel):
+    """Channels that fill chunks but no k tiles: every scheme against the oracle."""
+    d = DeviceConv(conv, dtype, seed=3)
+    A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
+    rows = sample_rows(d.M, 1500)
+    C_ref = oracle.gemm(A[rows], d.Wm, dtype)
+    for mode in (B.NONE, B.GLOBAL, B.THREAD, B.TWOSIDED):
+        print("case", conv, dtype, mode, flush=True)
+        assert B.abft_kernel_name(d.M, d.N, d.K, d.dt, mode, conv=True) == kernel
+        flag, rep = d.run(mode)
+        assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        assert mode == B.NONE or rep.worst_ratio < 0.5
