@@ -81,6 +81,16 @@ class Hip:
 # --------------------------------------------------------------------------- #
 # one protected layer with its device buffers
 # --------------------------------------------------------------------------- #
+def _values(shape, dist, gen, dev):
+    if dist == "constant":
+        return torch.full(shape, 0.1, device=dev)
+    if dist in ("normal", "weights"):
+        x = torch.randn(shape, generator=gen, device=dev)
+        return x * 0.02 if dist == "weights" else x
+    x = torch.rand(shape, generator=gen, device=dev)
+    return {"uniform_01": x, "uniform_pm1": x * 2 - 1}[dist]
+
+
 class LayerRun:
     def __init__(self, layer: wl.Layer, dtype: str, gen: torch.Generator, dist_a="uniform_01", dist_b="weights"):
         self.layer, self.dtype = layer, dtype
@@ -92,13 +102,8 @@ class LayerRun:
             self.A = torch.randint(-128, 128, a_shape, generator=gen, device=dev, dtype=torch.int32).to(torch.int8)
             self.B = torch.randint(-128, 128, (N, K), generator=gen, device=dev, dtype=torch.int32).to(torch.int8)
         else:
-            a = torch.rand(a_shape, generator=gen, device=dev) if dist_a == "uniform_01" else (
-                torch.randn(a_shape, generator=gen, device=dev) if dist_a == "normal" else
-                torch.rand(a_shape, generator=gen, device=dev) * 2 - 1)
-            b = torch.randn((N, K), generator=gen, device=dev)
-            if dist_b == "weights":
-                b = b * 0.02
-            self.A, self.B = a.to(TORCH_IN[dtype]), b.to(TORCH_IN[dtype])  # B stored N x K (ABFT_B_NK)
+            self.A = _values(a_shape, dist_a, gen, dev).to(TORCH_IN[dtype])
+            self.B = _values((N, K), dist_b, gen, dev).to(TORCH_IN[dtype])  # B stored N x K (ABFT_B_NK)
         self.C = torch.zeros((M, N), dtype=TORCH_OUT[dtype], device=dev)
         self.flag = torch.zeros(1, dtype=torch.int32, device=dev)
         es = ESIZE[dtype]
@@ -672,12 +677,13 @@ def noise_study(gen):
     u = 2.0 ** -24
     out = []
     shapes = ((256, 256, 64), (256, 256, 1024), (1024, 1024, 1024), (1024, 1024, 8192), (4096, 4096, 4096),
-              (2048, 2048, 16384), (8192, 8192, 8192))
-    dists = (("normal", "normal"), ("uniform_pm1", "uniform_pm1"), ("uniform_01", "weights"), ("uniform_01", "uniform_01"))
+              (2048, 2048, 16384), (8192, 8192, 8192), (2048, 2048, 65536))
+    dists = (("normal", "normal"), ("uniform_pm1", "uniform_pm1"), ("uniform_01", "weights"), ("uniform_01", "uniform_01"),
+             ("constant", "constant"))
     for dtype in ("f16", "bf16"):
         for da, db in dists:
             for (M, N, K) in shapes:
-                seeds = 2 if M >= 4096 else 6
+                seeds = 1 if da == "constant" else (2 if M * N * K >= 1 << 35 else 6)
                 for mode in (B.GLOBAL, B.THREAD):
                     walk = drift = ratio = 0.0
                     flags = 0
