@@ -498,12 +498,12 @@ __device__ __forceinline__ void clear_check(typename Mma<CFG::DT, CFG::MI>::Acc 
 #pragma unroll
         for (int r = 0; r < MMA::NACC; ++r) chk[i][r] = r == 0 ? zero : 0;
 }
-// Wavefronts per SIMD that a kernel of four wavefronts has to leave registers for.  With checksum
+// Wavefronts per SIMD that a kernel of at most four wavefronts has to leave registers for.  With checksum
 // accumulators for each of its four product blocks a wavefront takes 128 accumulator registers; a few
 // vector registers less let two workgroups share a compute unit as they do under the other schemes.
 template <class CFG, int MODE>
 constexpr int min_waves_per_simd() {
-    return MODE == MODE_THREAD && CFG::THREADS == 256 && CFG::MI == 32 && CFG::TM * CFG::TN == 4 && !ChecksumForm<CFG>::DIGITS ? 2 : 1;
+    return MODE == MODE_THREAD && CFG::THREADS <= 256 && CFG::MI == 32 && CFG::TM * CFG::TN == 4 && !ChecksumForm<CFG>::DIGITS ? 2 : 1;
 }
 
 // Element-wise sum of two fragments in the operand type (fp16: one packed add per register;

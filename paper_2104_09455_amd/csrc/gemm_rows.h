@@ -10,9 +10,9 @@
 // the workgroup; rings of two LDS stages beside 72 KB of weights took 50 us where this form takes
 // 41.)  Bound: HBM (the rows in, C out) and, for 3 x 3 convolutions, the rate at which the vector
 // memory path serves fragments of 32 rows at a time.  Thread-level, fp16, against 128 x 128 tiles:
-// 200704 x 64 x 256 34-38 us (3.4-3.8 TB/s) against 42, 200704 x 256 x 64 38-40 against 48-50, 3 x 3
-// convolution 64 -> 64 on 200704 rows 41 against 60 (unprotected 35 / 45), stem (7 x 7, lowered to K = 192)
-// on 802816 rows with its padded copy 84 against 115.
+// 200704 x 64 x 256 35 us (3.7 TB/s) against 41, 200704 x 256 x 64 40 against 46-50, 3 x 3 convolution 64 -> 64
+// on 200704 rows 39-41 against 56 (unprotected 35, on 256 x 64 tiles 39), stem (7 x 7, lowered to K = 192)
+// on 802816 rows with its padded copy 86-88 against 112.
 #pragma once
 #include "gemm_fast.h"
 
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
                 }
             }
             // (whatever path was taken: the count of loads stays the same; before the last of the tile's
-            // checks and stores, which take as long as the loads: behind them the stem took 100 us, so 84)
+            // checks and stores, which take as long as the loads: behind them the stem took 100 us, so 86)
             load(fa[u]);
             if (last) {
                 finish(ncb - 1);
