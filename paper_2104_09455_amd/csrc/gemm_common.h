@@ -825,9 +825,26 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
             }
         } else {
             // groups of four accumulators are summed in fp32 (three roundings), everything
-            // above that in fp64, so the summation adds nothing visible to the comparison
+            // above that in fp64, so the summation adds nothing visible to the comparison.  (Exact
+            // thread-level scheme without a report: the blocks' differences, which are zeros on a clean tile
+            // and a fault's change otherwise, need neither)
+            constexpr bool TWIN = MODE == MODE_THREAD;
             double s = 0.0;
-            float f2 = 0.f, l1 = 0.f;
+            float f2 = 0.f, l1 = 0.f, diff = 0.f;
+            if (TWIN && !p.report) {
+                if constexpr (TWIN) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int r = 0; r < MMA::NACC; ++r) {
+                                const float v = acc[i][j][r];
+                                f2 += v * v;
+                                diff += v - chk[i * TN + j][r];
+                            }
+                }
+            } else {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -840,6 +857,7 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
                         if constexpr (MODE == MODE_GLOBAL)
                             l1 += (__builtin_fabsf(v0) + __builtin_fabsf(v1)) + (__builtin_fabsf(v2) + __builtin_fabsf(v3));
                     }
+            }
             // cross-lane sums: the norms of the tolerance in fp32; the two sides of the comparison in
             // fp64, as one sum of their per-lane difference unless the report wants them apart
             const double F2 = (double)wave_sum(f2);
@@ -892,11 +910,14 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
                     }
                 }
             } else {
-                double rsum = lane_check_sum<CFG, MODE>(chk, lane);
+                double rsum = 0.0;
                 if (p.report) {
                     s = wave_sum(s);
-                    rsum = wave_sum(rsum);
+                    rsum = wave_sum(lane_check_sum<CFG, MODE>(chk, lane));
+                } else if constexpr (TWIN) {
+                    s = (double)wave_sum(diff);
                 } else {
+                    rsum = lane_check_sum<CFG, MODE>(chk, lane);
                     s = wave_sum(s - rsum);
                     rsum = 0.0;
                 }
