@@ -351,6 +351,9 @@ int abft_plan_run(abft_plan_t *plan, int layer, const void *A, int64_t lda, void
  * device pointers / leading dimensions) are layer i's input and output.  A layer whose input is
  * the output of the layer before it (A[i] == C[i - 1], lda[i] == ldc[i - 1]) is chained to it and
  * takes its activation checksums from that layer's epilogue where abft_plan_run_chain would.
+ * Results are those of the layers one behind the other; layers that do not wait for one another (none
+ * writes what another reads or writes: A, B and C of every layer are compared) and run on the same
+ * latency-bound tiling may share a kernel launch.
  * event_layer selects the one layer whose product kernel the abft_set_kernel_events hook brackets
  * (-1: none). */
 int abft_plan_run_all(abft_plan_t *plan, const void *const *A, const int64_t *lda, void *const *C,
@@ -397,6 +400,8 @@ int abft_plan_set_diagnostics(abft_plan_t *plan, int layer, abft_report_t *repor
 /* How many product launches of this process so far took their activation checksums from the
  * layer before (abft_plan_run_chain, layer by layer); lets a caller see that a chain qualified. */
 long long abft_handover_launches(void);
+/* How many launches of this process so far carried several layers of an abft_plan_run_all pass. */
+long long abft_shared_launches(void);
 /* Override the scheme of a layer (abft_mode_t; ABFT_AUTO re-applies abft_select). */
 int abft_plan_set_mode(abft_plan_t *plan, int layer, int mode);
 /* Activation function of a layer (abft_act_t; ABFT_ACT_NONE at creation), fused into the store

@@ -18,6 +18,7 @@
 #include "../../include/abft.h"
 #include "gemm_configs.h"
 #include "mlp_chain.h"
+#include "gemm_group.h"
 
 using namespace abft;
 
@@ -801,8 +802,17 @@ bool fused_global(const Problem& pr, const CfgInfo& ci) {
     return in_loop * t_gemm < t_pre;
 }
 
-int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, size_t ws_bytes, uint32_t* flag,
-                abft_report_t* report, const abft_fault_t* inject, hipStream_t st) {
+// A product ready to be launched
+struct Prepared {
+    GemmArgs g;
+    int cfg, kmode, dtype;   // kmode: the kernels' scheme index
+    bool inj;
+};
+
+// Everything of a product up to its kernel's launch: checks, tiling, kernel arguments, and the launches that
+// come before it (weight checksums that were not handed in, a pass over A of its own).
+int prepare_problem(const Problem& pr, int mode, const void* beta, void* workspace, size_t ws_bytes, uint32_t* flag,
+                    abft_report_t* report, const abft_fault_t* inject, hipStream_t st, Prepared& out) {
     int rc = validate_common(pr, mode, flag);
     if (rc != ABFT_OK) return rc;
     if (mode == ABFT_AUTO) mode = select_mode(pr.M, pr.N, pr.K, pr.dtype);
@@ -816,7 +826,7 @@ int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, 
     const CfgInfo ci = cfg_info_host(cfg);
     const int bk = ci.bk_bytes / esize(pr.dtype);
 
-    GemmArgs g;
+    GemmArgs& g = out.g;
     std::memset(&g, 0, sizeof g);
     g.A = reinterpret_cast<const char*>(pr.A);
     g.B = reinterpret_cast<const char*>(pr.B);
@@ -908,11 +918,23 @@ int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, 
         }
     }
 
+    out.cfg = cfg;
+    out.kmode = kmode;
+    out.dtype = pr.dtype;
+    out.inj = inj;
+    return ABFT_OK;
+}
+
+int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, size_t ws_bytes, uint32_t* flag,
+                abft_report_t* report, const abft_fault_t* inject, hipStream_t st) {
+    Prepared w;
+    const int rc = prepare_problem(pr, mode, beta, workspace, ws_bytes, flag, report, inject, st, w);
+    if (rc != ABFT_OK) return rc;
     hipError_t e;
     if (g_ev_start && hipEventRecord(g_ev_start, st) != hipSuccess) return ABFT_E_HIP;
-    if (pr.dtype == ABFT_F16) e = launch_gemm_f16(cfg, kmode, inj, g, st);
-    else if (pr.dtype == ABFT_BF16) e = launch_gemm_bf16(cfg, kmode, inj, g, st);
-    else e = launch_gemm_i8(cfg, kmode, inj, g, st);
+    if (w.dtype == ABFT_F16) e = launch_gemm_f16(w.cfg, w.kmode, w.inj, w.g, st);
+    else if (w.dtype == ABFT_BF16) e = launch_gemm_bf16(w.cfg, w.kmode, w.inj, w.g, st);
+    else e = launch_gemm_i8(w.cfg, w.kmode, w.inj, w.g, st);
     if (e != hipSuccess) return ABFT_E_HIP;
     if (g_ev_stop && hipEventRecord(g_ev_stop, st) != hipSuccess) return ABFT_E_HIP;
 
@@ -1460,14 +1482,9 @@ float* handover_target(const abft_plan_t* plan, int next, const void* a_next, in
     return (ci.fast && ci.kways == 1 && cfg != CFG_F128E) ? nx.alpha32 : nullptr;
 }
 
-// One layer of a plan.  alpha_out (may be null): where to leave the activation checksums of the
-// layer that follows (leading dimension ld_alpha_out), *alpha_emitted set when the kernel that ran
-// could; alpha_in (may be null): those the layer before left for this layer's input.
-int plan_run_layer(abft_plan_t* plan, int layer, const void* A, int64_t lda, void* C, int64_t ldc, uint32_t* fault_flag,
-                   void* stream, float* alpha_out, long long ld_alpha_out, bool* alpha_emitted, const float* alpha_in) {
-    abft_plan::Layer& L = plan->layers[layer];
+// The product a layer stands for on these buffers.
+int layer_problem(const abft_plan::Layer& L, const void* A, int64_t lda, void* C, int64_t ldc, Problem& pr) {
     const abft_layer_t& d = L.desc;
-    Problem pr;
     std::memset(&pr, 0, sizeof pr);
     if (d.has_conv) {
         int rc = conv_problem(&d.conv, d.N, pr);
@@ -1478,11 +1495,26 @@ int plan_run_layer(abft_plan_t* plan, int layer, const void* A, int64_t lda, voi
     pr.dtype = d.dtype; pr.b_layout = d.b_layout;
     pr.A = A; pr.B = d.B; pr.ldb = d.ldb; pr.C = C; pr.ldc = ldc;
     pr.act = L.act;
-    pr.alpha_out = alpha_out; pr.ld_alpha_out = ld_alpha_out; pr.alpha_emitted = alpha_emitted; pr.alpha_in = alpha_in;
-    // the offline checksums fit the tiling chosen for aligned activations; an input that
-    // forces another tiling gets them recomputed into the workspace
+    return ABFT_OK;
+}
+// the layer's offline weight checksums where they fit the tiling chosen for this input (an input that
+// forces another tiling gets them recomputed into the workspace), else null
+const void* layer_beta(const abft_plan::Layer& L, const Problem& pr) {
     const int bn_now = cfg_info_host(pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), ABFT_GLOBAL)).bn;
-    const void* beta = bn_now == L.beta_block_n ? L.beta : nullptr;
+    return bn_now == L.beta_block_n ? L.beta : nullptr;
+}
+
+// One layer of a plan.  alpha_out (may be null): where to leave the activation checksums of the
+// layer that follows (leading dimension ld_alpha_out), *alpha_emitted set when the kernel that ran
+// could; alpha_in (may be null): those the layer before left for this layer's input.
+int plan_run_layer(abft_plan_t* plan, int layer, const void* A, int64_t lda, void* C, int64_t ldc, uint32_t* fault_flag,
+                   void* stream, float* alpha_out, long long ld_alpha_out, bool* alpha_emitted, const float* alpha_in) {
+    abft_plan::Layer& L = plan->layers[layer];
+    Problem pr;
+    const int rc = layer_problem(L, A, lda, C, ldc, pr);
+    if (rc != ABFT_OK) return rc;
+    pr.alpha_out = alpha_out; pr.ld_alpha_out = ld_alpha_out; pr.alpha_emitted = alpha_emitted; pr.alpha_in = alpha_in;
+    const void* beta = layer_beta(L, pr);
     const abft_fault_t* fault = L.has_fault ? &L.fault : nullptr;
     if (pr.conv) {
         const LoweredWeights pre = {L.lowered_B, L.lowered_beta, L.lowered_block_n};
@@ -1492,6 +1524,190 @@ int plan_run_layer(abft_plan_t* plan, int layer, const void* A, int64_t lda, voi
     return run_problem(pr, L.mode, beta, L.workspace, L.ws_bytes, fault_flag, L.report, fault,
                        reinterpret_cast<hipStream_t>(stream));
 }
+
+// ------------------------------------------------------------------------- //
+// A pass over a plan's layers (abft_plan_run_all).  Layers that do not wait for one another may share a
+// launch: the pass is looked at in windows of up to 64 layers; a layer's depth is one more than that of the
+// deepest earlier layer it has to wait for (that one writes what it reads, or either writes what the
+// other touches), layers of one depth and kind share a launch, and the launches go out by depth.
+// Results are those of the layers one behind the other.
+// ------------------------------------------------------------------------- //
+// product launches so far that carried several layers of a pass (diagnostics)
+std::atomic<long long> g_shared_launches{0};
+
+struct PassWindow {
+    static constexpr int MAX_LAYERS = 64;
+    struct Range {
+        uintptr_t lo, hi;
+        bool meets(const Range& o) const { return lo < o.hi && o.lo < hi; }
+    };
+    struct Entry {
+        int layer, depth;
+        Range in, weights, out;
+    };
+    struct Slot {
+        int depth;
+        int cfg, kmode, dtype;    // of a launch that can take more layers; cfg < 0: one layer, by itself
+        int count;
+        int entry[GROUP_MAX];
+    };
+    abft_plan_t* plan;
+    const void* const* A;
+    const int64_t* lda;
+    void* const* C;
+    const int64_t* ldc;
+    uint32_t* flag;
+    void* stream;
+    int n_entries = 0, n_slots = 0;
+    Entry entries[MAX_LAYERS];
+    Slot slots[MAX_LAYERS];
+    // activation checksums that a layer's epilogue left for the layer behind it (alpha[i - base] for layer i; the
+    // window's layers are base, base + 1, ...)
+    int base = 0;
+    const float* alpha[MAX_LAYERS + 1] = {nullptr};
+
+    PassWindow(abft_plan_t* p, const void* const* A_, const int64_t* lda_, void* const* C_, const int64_t* ldc_, uint32_t* f, void* s)
+        : plan(p), A(A_), lda(lda_), C(C_), ldc(ldc_), flag(f), stream(s) {}
+
+    // layer i by itself, here and now
+    int run_now(int i) {
+        // a layer whose input IS the output of the layer before it (same pointer and leading
+        // dimension) is chained to it: it can take its activation checksums from that layer's epilogue
+        const bool next_chained = i + 1 < (int)plan->layers.size() && A[i + 1] == C[i] && lda[i + 1] == ldc[i];
+        float* alpha_out = next_chained ? handover_target(plan, i + 1, C[i], ldc[i]) : nullptr;
+        bool emitted = false;
+        const int rc = plan_run_layer(plan, i, A[i], lda[i], C[i], ldc[i], flag, stream, alpha_out,
+                                      alpha_out ? plan->layers[i + 1].desc.K : 0, &emitted, alpha[i - base]);
+        alpha[i - base + 1] = emitted ? alpha_out : nullptr;
+        return rc;
+    }
+
+    int add(int i) {
+        const abft_plan::Layer& L = plan->layers[i];
+        const abft_layer_t& d = L.desc;
+        Problem pr;
+        int rc = layer_problem(L, A[i], lda[i], C[i], ldc[i], pr);
+        if (rc == ABFT_OK) rc = validate_common(pr, L.mode, flag);
+        if (rc != ABFT_OK) return rc;
+        int mode = L.mode;
+        if (mode == ABFT_AUTO) mode = select_mode(pr.M, pr.N, pr.K, pr.dtype);
+        // (diagnostics, planted faults and the schemes that are never chosen: in order, by themselves)
+        if (L.report || L.has_fault || (mode != ABFT_NONE && mode != ABFT_GLOBAL && mode != ABFT_THREAD)) {
+            return in_place(i);
+        }
+        if (n_entries == MAX_LAYERS) {
+            rc = flush();
+            if (rc != ABFT_OK) return rc;
+        }
+        const long long es = esize(d.dtype), cs = csize(d.dtype);
+        Entry& e = entries[n_entries];
+        e.layer = i;
+        auto range = [](const void* p, long long bytes) { return Range{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + (uintptr_t)bytes}; };
+        e.in = range(pr.A, es * (d.has_conv ? (long long)d.conv.batch * d.conv.H * d.conv.W * d.conv.Cin : (pr.M - 1) * pr.lda + pr.K));
+        e.weights = range(pr.B, es * (pr.b_layout == ABFT_B_NK ? (pr.N - 1) * pr.ldb + pr.K : (pr.K - 1) * pr.ldb + pr.N));
+        e.out = range(pr.C, cs * ((pr.M - 1) * pr.ldc + pr.N));
+        e.depth = 0;
+        for (int j = 0; j < n_entries; ++j) {
+            const Entry& o = entries[j];
+            if (o.depth >= e.depth && (e.in.meets(o.out) || e.out.meets(o.out) || e.out.meets(o.in) || e.weights.meets(o.out) || e.out.meets(o.weights)))
+                e.depth = o.depth + 1;
+        }
+        const int cfg = shared_cfg(L, pr, mode);
+        int s = n_slots;
+        if (cfg >= 0) {
+            s = 0;
+            while (s < n_slots && !(slots[s].depth == e.depth && slots[s].cfg == cfg && slots[s].kmode == mode && slots[s].dtype == d.dtype &&
+                                    slots[s].count < GROUP_MAX))
+                ++s;
+        }
+        if (s == n_slots) slots[n_slots++] = Slot{e.depth, cfg, mode, d.dtype, 0, {}};
+        slots[s].entry[slots[s].count++] = n_entries;
+        ++n_entries;
+        return ABFT_OK;
+    }
+
+    // the configuration under which a layer can share a launch, or -1: the streaming kernel on whole
+    // k tiles, with nothing to launch ahead of it
+    static int shared_cfg(const abft_plan::Layer& L, const Problem& pr, int mode) {
+        if (!a_vectorisable(pr) || !b_vectorisable(pr) || ((long long)pr.K * esize(pr.dtype)) % 128 != 0) return -1;
+        if (pr.conv && conv_lowering(pr).ok) return -1;
+        const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, true, mode, pr.conv);
+        if (!cfg_is_stream(cfg) || (mode == ABFT_GLOBAL && !layer_beta(L, pr))) return -1;
+        return cfg;
+    }
+
+    int launch_shared(const Slot& slot) {
+        // longest k loops first, so that the last workgroups to start are short ones
+        int order[GROUP_MAX];
+        for (int q = 0; q < slot.count; ++q) {
+            int at = q;
+            while (at > 0 && plan->layers[entries[order[at - 1]].layer].desc.K < plan->layers[entries[slot.entry[q]].layer].desc.K) {
+                order[at] = order[at - 1];
+                --at;
+            }
+            order[at] = slot.entry[q];
+        }
+        GroupArgs a;
+        std::memset(&a, 0, sizeof a);
+        int blocks = 0;
+        for (int q = 0; q < slot.count; ++q) {
+            const int i = entries[order[q]].layer;
+            abft_plan::Layer& L = plan->layers[i];
+            Problem pr;
+            Prepared w;
+            int rc = layer_problem(L, A[i], lda[i], C[i], ldc[i], pr);
+            if (rc == ABFT_OK)
+                rc = prepare_problem(pr, L.mode, slot.kmode == ABFT_GLOBAL ? layer_beta(L, pr) : nullptr, L.workspace, L.ws_bytes, flag, nullptr, nullptr,
+                                     reinterpret_cast<hipStream_t>(stream), w);
+            if (rc != ABFT_OK) return rc;
+            const GemmArgs& g = w.g;
+            GroupItem& it = a.item[q];
+            it.A = g.A; it.B = g.B; it.C = g.C; it.beta_k = g.beta_k; it.beta_p = g.beta_p;
+            it.lda = g.lda; it.ldb = g.ldb; it.ldc = g.ldc; it.imgpitch = g.imgpitch; it.rowpitch = g.rowpitch;
+            it.tol_coeff = g.tol_coeff; it.tol_l1 = g.tol_l1;
+            it.M = g.M; it.N = g.N; it.K = g.K; it.tiles_m = g.tiles_m; it.tiles_n = g.tiles_n; it.act = g.act;
+            it.conv = g.conv; it.H = g.H; it.W = g.W; it.Cin = g.Cin; it.KH = g.KH; it.KW = g.KW;
+            it.stride = g.stride; it.pad = g.pad; it.OH = g.OH; it.OW = g.OW; it.pix = g.pix;
+            a.first[q] = blocks;
+            blocks += g.tiles_m * g.tiles_n;
+        }
+        for (int q = slot.count; q < GROUP_MAX; ++q) a.first[q] = 0x7fffffff;
+        a.flag = flag;
+        g_shared_launches.fetch_add(1, std::memory_order_relaxed);
+        hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+        const hipError_t e = slot.dtype == ABFT_F16    ? launch_group_f16(slot.cfg, slot.kmode, blocks, a, st)
+                             : slot.dtype == ABFT_BF16 ? launch_group_bf16(slot.cfg, slot.kmode, blocks, a, st)
+                                                       : launch_group_i8(slot.cfg, slot.kmode, blocks, a, st);
+        return e == hipSuccess ? ABFT_OK : ABFT_E_HIP;
+    }
+
+    // what has been added so far goes out; the window is empty again and starts behind it
+    int flush() {
+        int rc = ABFT_OK;
+        for (int depth = 0, left = n_slots; left > 0 && rc == ABFT_OK; ++depth)
+            for (int s = 0; s < n_slots && rc == ABFT_OK; ++s)
+                if (slots[s].depth == depth) {
+                    --left;
+                    rc = slots[s].count > 1 ? launch_shared(slots[s]) : run_now(entries[slots[s].entry[0]].layer);
+                }
+        advance(n_entries);
+        n_entries = n_slots = 0;
+        return rc;
+    }
+    // a layer that keeps to its place: behind everything before it, ahead of everything after it
+    int in_place(int i) {
+        int rc = flush();
+        if (rc == ABFT_OK) rc = run_now(i);
+        advance(1);
+        return rc;
+    }
+    void advance(int layers) {
+        const float* carried = alpha[layers];
+        for (int q = 0; q <= layers; ++q) alpha[q] = nullptr;
+        alpha[0] = carried;
+        base += layers;
+    }
+};
 
 }  // namespace
 
@@ -1508,22 +1724,26 @@ int abft_plan_run_all(abft_plan_t* plan, const void* const* A, const int64_t* ld
     if (!plan) return ABFT_E_PLAN;
     if (!A || !lda || !C || !ldc) return ABFT_E_NULL;
     const hipEvent_t ev0 = g_ev_start, ev1 = g_ev_stop;
-    int rc = ABFT_OK;
     const int n = (int)plan->layers.size();
-    const float* alpha_in = nullptr;
+    PassWindow w(plan, A, lda, C, ldc, fault_flag, stream);
+    g_ev_start = g_ev_stop = nullptr;
+    int rc = ABFT_OK;
     for (int i = 0; i < n && rc == ABFT_OK; ++i) {
         // the measurement hook, if set, brackets the product kernel of one layer only
-        g_ev_start = i == event_layer ? ev0 : nullptr;
-        g_ev_stop = i == event_layer ? ev1 : nullptr;
-        // a layer whose input IS the output of the layer before it (same pointer and leading
-        // dimension) is chained to it: it can take its activation checksums from that layer's epilogue
-        const bool next_chained = i + 1 < n && A[i + 1] == C[i] && lda[i + 1] == ldc[i];
-        float* alpha_out = next_chained ? handover_target(plan, i + 1, C[i], ldc[i]) : nullptr;
-        bool emitted = false;
-        rc = plan_run_layer(plan, i, A[i], lda[i], C[i], ldc[i], fault_flag, stream, alpha_out,
-                            alpha_out ? plan->layers[i + 1].desc.K : 0, &emitted, alpha_in);
-        alpha_in = emitted ? alpha_out : nullptr;
+        const bool hooked = i == event_layer && (ev0 || ev1);
+        if (!hooked) {
+            rc = w.add(i);
+            continue;
+        }
+        rc = w.flush();
+        if (rc != ABFT_OK) break;
+        g_ev_start = ev0;
+        g_ev_stop = ev1;
+        rc = w.in_place(i);
+        g_ev_start = g_ev_stop = nullptr;
     }
+    const int rest = w.flush();   // (a call that is refused: the layers before it have run, as ever)
+    if (rc == ABFT_OK) rc = rest;
     g_ev_start = ev0;
     g_ev_stop = ev1;
     return rc;
@@ -1625,6 +1845,7 @@ int abft_plan_chain_reset(abft_plan_t* plan, int spin_limit, void* stream) {
 }
 
 long long abft_handover_launches(void) { return g_handover_launches.load(std::memory_order_relaxed); }
+long long abft_shared_launches(void) { return g_shared_launches.load(std::memory_order_relaxed); }
 
 int abft_plan_set_diagnostics(abft_plan_t* plan, int layer, abft_report_t* report, const abft_fault_t* inject) {
     if (!plan || layer < 0 || layer >= (int)plan->layers.size()) return ABFT_E_PLAN;

@@ -1,0 +1,80 @@
+// Several independent products in ONE launch of the streaming kernel for gfx950 (MI355X): the layers
+// of a network that do not wait for one another (the two MLPs of a recommendation model, the
+// downsampling and the first convolution of a block, blocks whose inputs are all at hand).
+//
+// A latency-bound layer occupies the chip for the 3 to 10 us of one workgroup's k loop, whatever its
+// number of workgroups, so layers launched one behind the other leave most of the compute units
+// idle most of the time.  Here every workgroup looks up which product it belongs to and runs the
+// streaming kernel's own tile routine on it: results, checks and flag are those of the layer's own launch.
+// Where all workgroups fit the chip in one round they get the stages of a launch of their own; else
+// fewer, so that two to four workgroups share a compute unit and one's copies run under another's
+// products and epilogue.
+#pragma once
+#include "gemm_configs.h"
+#include "gemm_stream.h"
+
+namespace abft {
+
+constexpr int GROUP_MAX = 16;   // products per launch: 2.8 KB of kernel arguments
+
+// what the tile routine needs of GemmArgs
+struct GroupItem {
+    const char* A;
+    const char* B;
+    char* C;
+    const char* beta_k;
+    const char* beta_p;
+    long long lda, ldb, ldc, imgpitch, rowpitch;
+    double tol_coeff, tol_l1;
+    int M, N, K, tiles_m, tiles_n, act;
+    int conv, H, W, Cin, KH, KW, stride, pad, OH, OW, pix;
+};
+
+struct GroupArgs {
+    int first[GROUP_MAX];   // first workgroup of each product; unused entries: INT_MAX
+    unsigned* flag;
+    GroupItem item[GROUP_MAX];
+};
+static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments");
+
+template <int DT, int ID, int NST, int MODE>
+__global__ __launch_bounds__((64 * CfgOf<DT, ID>::KWAYS)) void gemm_group_kernel(const GroupArgs a) {
+    typedef typename CfgOf<DT, ID>::type CFG;
+    constexpr int KWAYS = CfgOf<DT, ID>::KWAYS;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bid = (int)blockIdx.x;
+    int i = 0;
+#pragma unroll
+    for (int q = 1; q < GROUP_MAX; ++q) i += bid >= a.first[q] ? 1 : 0;
+    const GroupItem& L = a.item[i];
+
+    GemmArgs g;
+    g.A = L.A; g.B = L.B; g.C = L.C;
+    g.M = L.M; g.N = L.N; g.K = L.K;
+    g.lda = L.lda; g.ldb = L.ldb; g.ldc = L.ldc;
+    g.b_sn = L.ldb; g.b_sk = 1;
+    g.a_vec = g.b_vec = 1;
+    g.conv = L.conv;
+    g.H = L.H; g.W = L.W; g.Cin = L.Cin; g.KH = L.KH; g.KW = L.KW;
+    g.stride = L.stride; g.pad = L.pad; g.OH = L.OH; g.OW = L.OW;
+    g.imgpitch = L.imgpitch; g.rowpitch = L.rowpitch; g.pix = L.pix;
+    g.beta_k = L.beta_k; g.beta_p = L.beta_p; g.beta_r = nullptr;
+    g.partial_dots = nullptr; g.n_parts = 0;
+    g.tol_l1 = L.tol_l1; g.tol_coeff = L.tol_coeff;
+    g.flag = a.flag; g.report = nullptr;
+    g.f_row = g.f_col = -1; g.f_bit = 0; g.f_kt = -1;
+    g.tiles_m = L.tiles_m; g.tiles_n = L.tiles_n;
+    g.act = L.act;
+    g.alpha_out = nullptr; g.ld_alpha_out = 0; g.alpha_in = nullptr;
+    int tile_m, tile_n;
+    tile_of_block(bid - a.first[i], g.tiles_m, g.tiles_n, tile_m, tile_n);
+    if (g.conv) stream_tile<CFG, NST, KWAYS, MODE, false, true, false, false>(g, tile_m, tile_n, smem);
+    else stream_tile<CFG, NST, KWAYS, MODE, false, false, false, false>(g, tile_m, tile_n, smem);
+}
+
+// blocks: workgroups of all products together; mode: MODE_NONE, MODE_GLOBAL or MODE_THREAD
+hipError_t launch_group_f16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+hipError_t launch_group_bf16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+hipError_t launch_group_i8(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+
+}  // namespace abft

@@ -1,0 +1,4 @@
+// Launches of several independent products, bf16 operands.
+#define ABFT_DT abft::DT_BF16
+#define ABFT_GROUP_NAME launch_group_bf16
+#include "gemm_group.inc"
