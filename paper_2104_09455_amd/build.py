@@ -22,8 +22,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # keep the compiler from emitting packed-fp32 VALU forms
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 FLAGS += os.environ.get("ABFT_EXTRA_HIPCC_FLAGS", "").split()   # e.g. -D switches of tuning experiments
-SOURCES = ["gemm_f16.hip", "gemm_bf16.hip", "gemm_i8.hip", "gemm_group_f16.hip", "gemm_group_bf16.hip", "gemm_group_i8.hip",
-           "abft_api.hip"]
+# (the ones that take longest first)
+SOURCES = [f"gemm_{family}_{dt}.hip" for family in ("fast", "generic", "stream", "group") for dt in ("f16", "bf16", "i8")] + ["abft_api.hip"]
 
 
 def _compile(src: str) -> str:
@@ -38,7 +38,7 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build(verbose: bool = False, jobs: int = 7) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, SOURCES))

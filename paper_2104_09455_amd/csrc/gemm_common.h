@@ -307,6 +307,9 @@ __device__ __forceinline__ i32x4 ld16g(const char* p) {
     return *(const __attribute__((address_space(1))) i32x4*)(const __attribute__((address_space(1))) char*)p;
 }
 
+// zeros that stand in for rows beyond the matrix edge and for convolution padding
+__device__ __attribute__((aligned(256))) static const char g_zero_chunk[256] = {0};
+
 // 16 bytes gathered element by element: element e of the chunk is at base + e*stride
 // (bytes) and is taken only while e < n_valid.  Every load reads an element of the run (the
 // index is clamped to the last valid one, the value dropped afterwards), so that the loads

@@ -64,6 +64,7 @@ template <int DT> struct CfgOf<DT, CFG_G16>   { typedef Cfg<DT, 16, 1, 1, 1, 4, 
 
 constexpr bool cfg_is_rows(int id) { return id == CFG_R64; }
 constexpr bool cfg_is_stream(int id) { return id == CFG_S32 || id == CFG_S32W || id == CFG_S64 || id == CFG_S128; }
+constexpr bool cfg_is_generic(int id) { return id == CFG_G128 || id == CFG_G64 || id == CFG_G64K || id == CFG_G16; }
 
 // threads: of one WAVES_M x WAVES_N grid of wavefronts (a launch has kways times as many);
 // kway_bytes: bytes of k that one wavefront takes in turn when kways wavefronts share a tile
@@ -102,9 +103,19 @@ inline CfgInfo cfg_info_host(int id) {
     }
 }
 
-// implemented once per dtype in gemm_f16.hip / gemm_bf16.hip / gemm_i8.hip
-hipError_t launch_gemm_f16(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);
-hipError_t launch_gemm_bf16(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);
-hipError_t launch_gemm_i8(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);
+// implemented once per dtype and family of configurations in gemm_<family>_<dtype>.hip
+#define ABFT_DECLARE_LAUNCHES(dt)                                                                                  \
+    hipError_t launch_fast_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);    \
+    hipError_t launch_stream_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);  \
+    hipError_t launch_generic_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream); \
+    inline hipError_t launch_gemm_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream) { \
+        if (cfg_is_stream(cfg)) return launch_stream_##dt(cfg, mode, inject, args, stream);                   \
+        if (cfg_is_generic(cfg)) return launch_generic_##dt(cfg, mode, inject, args, stream);                 \
+        return launch_fast_##dt(cfg, mode, inject, args, stream);                                             \
+    }
+ABFT_DECLARE_LAUNCHES(f16)
+ABFT_DECLARE_LAUNCHES(bf16)
+ABFT_DECLARE_LAUNCHES(i8)
+#undef ABFT_DECLARE_LAUNCHES
 
 }  // namespace abft

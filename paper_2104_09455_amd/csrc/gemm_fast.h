@@ -25,9 +25,6 @@
 
 namespace abft {
 
-// zeros that stand in for rows beyond the matrix edge and for convolution padding
-__device__ __attribute__((aligned(256))) static const char g_zero_chunk[256] = {0};
-
 // Workgroup index -> output tile.  Workgroups are dealt round-robin to the 8 XCDs, each
 // with its own L2; the remap hands every XCD a contiguous run of tiles and walks those in
 // bands of 8 tile rows, so that the tiles resident on an XCD at one time share A row

@@ -7,10 +7,11 @@
 // last 16 bytes of the row, shifted down); weights stored K x N are read four bytes of a row at a
 // time, eight rows of k per thread, and turned in registers on the way to LDS.  Only convolutions
 // whose channels fill no chunk, and rows of less than 16 bytes, are gathered by the element.
-// Bound: the latency of a k tile's loads (one tile in flight per group of wavefronts), so where
-// the chip has room KG groups of wavefronts share a tile along k.  Thread-level, with element gathers
-// and one group / so: 511 x 1000 x 2047 fp16, weights K x N, 92 / 21 us; 256 x 4096 x 4096 129 / 36;
-// 2048 x 4096 x 4096 445 / 161 (unprotected 267 / 120); 16 x 4096 x 4095, weights N x K, 114 / 27.
+// Bound: LDS traffic and the latency of a k tile's loads (one tile in registers on its way, one in LDS, per
+// group of wavefronts), so where the chip has room KG groups of wavefronts share a tile along k.  Loaders chosen
+// at run time with a condition per lane / at compile time without one, unprotected: 511 x 1000 x 2047
+// fp16, weights K x N, 19.3 / 16.4 us (thread-level 21.4 / 18.3), N x K 19.1 / 16.2; 2048 x 2048 x 2047 65 / 38;
+// 2048 x 4096 x 4096, weights K x N, 117 / 107, int8 77 / 69 (thread-level 175 / 131); 1 x 512 x 13 3.1 / 2.5.
 #pragma once
 #include "gemm_common.h"
 
@@ -26,11 +27,14 @@ __device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
 // The kernel.  KG groups of CFG::THREADS threads each own the whole workgroup tile and take the k
 // tiles t with t % KG == group, each with LDS buffers of its own; at the end the groups' partial
 // tiles (and redundant accumulators) are added in group order and group 0 checks and stores.
-// VEC: both operands are read in aligned 16-byte chunks (a_vec and b_vec); an instance of its own, since the
-// other loaders' registers and branches cost such products a fifth (4000 x 4000 x 1000 fp16 unprotected 74 us, so
-// 59; int8 thread-level, K = 4016, 283 / 199; 5 x 5 convolution 40 -> 120 on 100352 rows 76 / 53).
+// LD: how the operands are read.  VEC: both in aligned 16-byte chunks (a_vec and b_vec); an instance of its own,
+// since the other loaders' registers and branches cost such products a fifth (4000 x 4000 x 1000 fp16
+// unprotected 74 us, so 59; int8 thread-level, K = 4016, 283 / 199; 5 x 5 convolution 40 -> 120 on 100352 rows 76 / 53).
+// ROWS: both contiguous along k, at any alignment; TURN: A so, weights K x N.  These two know their loaders at compile
+// time, and load without a condition per lane (rows outside read the zeros).
 // ---------------------------------------------------------------------------
-template <class CFG, int MODE, bool INJ, bool CONV, int KG, bool VEC>
+enum { LD_ANY = 0, LD_VEC = 1, LD_ROWS = 2, LD_TURN = 3 };
+template <class CFG, int MODE, bool INJ, bool CONV, int KG, int LD>
 __global__ __launch_bounds__(CFG::THREADS * KG) __attribute__((amdgpu_waves_per_eu(INJ || KG > 1 ? 1 : min_waves_per_simd<CFG, MODE>())))
 void gemm_kernel(const GemmArgs p) {
     typedef Mma<CFG::DT, CFG::MI> MMA;
@@ -98,15 +102,17 @@ void gemm_kernel(const GemmArgs p) {
 
     // rows read 16 bytes at a time at any alignment: a chunk that K cuts short is read as the last 16
     // bytes of its row and shifted down when it goes to LDS
-    const bool a_vec = VEC || p.a_vec, b_vec = VEC || p.b_vec;
-    const bool a_row = !CONV && !a_vec && K >= EPC;
-    const bool b_row = !b_vec && p.b_sk == 1 && K >= EPC;
+    constexpr bool VEC = LD == LD_VEC, STREAM = LD >= LD_ROWS;
+    static_assert(!STREAM || !CONV, "matrices only");
+    const bool a_vec = VEC || (!STREAM && p.a_vec), b_vec = VEC || (!STREAM && p.b_vec);
+    const bool a_row = STREAM || (!CONV && !a_vec && K >= EPC);
+    const bool b_row = LD == LD_ROWS || (LD != LD_TURN && !b_vec && p.b_sk == 1 && K >= EPC);
     // weights stored K x N: units of eight k times four bytes of n (four bytes of a row end inside it)
     constexpr int NPD = 4 / ESIZE;                     // columns per four bytes
     constexpr int NGN = BN / NPD;                      // such groups per row of the tile
     constexpr int UNITS = NB / 2;                      // units per thread
     static_assert(NB % 2 == 0 && CFG::THREADS * UNITS == NGN * (BK / 8), "units of the transposing loader");
-    const bool b_turn = !b_vec && !b_row && p.b_sn == 1 && N >= NPD;
+    const bool b_turn = LD == LD_TURN || (!STREAM && !b_vec && !b_row && p.b_sn == 1 && N >= NPD);
     auto load_a = [&](int kt, i32x4(&regs)[NA]) {
         const int k0 = kt * BK + kc * EPC;  // first k of this thread's chunk
         if constexpr (!CONV) {
@@ -115,9 +121,13 @@ void gemm_kernel(const GemmArgs p) {
 #pragma unroll
                 for (int t = 0; t < NA; ++t) {
                     const int m = bm0 + r0 + t * RPP;
-                    i32x4 v = {0, 0, 0, 0};
-                    if (m < M && k0 < K) v = ld16u(p.A + ((long long)m * p.lda + ks) * ESIZE);
-                    regs[t] = v;
+                    if constexpr (STREAM) {
+                        regs[t] = ld16u(m < M && k0 < K ? p.A + ((long long)m * p.lda + ks) * ESIZE : g_zero_chunk);
+                    } else {
+                        i32x4 v = {0, 0, 0, 0};
+                        if (m < M && k0 < K) v = ld16u(p.A + ((long long)m * p.lda + ks) * ESIZE);
+                        regs[t] = v;
+                    }
                 }
             } else if (a_vec) {
 #pragma unroll
@@ -212,9 +222,13 @@ void gemm_kernel(const GemmArgs p) {
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 const int n = bn0 + r0 + t * RPP;
-                i32x4 v = {0, 0, 0, 0};
-                if (n < N && k0 < K) v = ld16u(p.B + ((long long)n * p.ldb + ks) * ESIZE);
-                regs[t] = v;
+                if constexpr (STREAM) {
+                    regs[t] = ld16u(n < N && k0 < K ? p.B + ((long long)n * p.ldb + ks) * ESIZE : g_zero_chunk);
+                } else {
+                    i32x4 v = {0, 0, 0, 0};
+                    if (n < N && k0 < K) v = ld16u(p.B + ((long long)n * p.ldb + ks) * ESIZE);
+                    regs[t] = v;
+                }
             }
         } else if (b_turn) {
             // (rows past K and columns past N read valid elements, dropped on the way to LDS)
@@ -326,6 +340,26 @@ void gemm_kernel(const GemmArgs p) {
     Acc chk[NCHK];
     clear_check<CFG, MODE>(chk);
 
+    // the products of one k tile, from LDS buffer `cur`
+    auto multiply = [&](int cur) {
+        const char* as = smem + cur * CFG::STAGE_BYTES + (wave_m * CFG::WM + lrow) * STRIDE + lgrp * 16;
+        const char* bs = smem + cur * CFG::STAGE_BYTES + BM * STRIDE + (wave_n * CFG::WN + lrow) * STRIDE + lgrp * 16;
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            i32x4 a[TM], b[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                a[i] = *reinterpret_cast<const i32x4*>(as + i * MI * STRIDE + kk * MMA::KBYTES);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                b[j] = *reinterpret_cast<const i32x4*>(bs + j * MI * STRIDE + kk * MMA::KBYTES);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = MMA::run(a[i], b[j], acc[i][j]);
+            if constexpr (mode_is_wave_level(MODE)) check_step<CFG, MODE>(a, b, chk);
+        }
+    };
     i32x4 ra[NA], rb[NB];
     // (every group goes through the same number of steps: they share the workgroup's barrier)
     const int nsteps = (nkt + KG - 1) / KG;
@@ -334,40 +368,43 @@ void gemm_kernel(const GemmArgs p) {
         load_b(grp, rb);
         store_tiles(0, grp, ra, rb);
     }
-    __syncthreads();
-
-    for (int s = 0; s < nsteps; ++s) {
-        const int kt = s * KG + grp;   // this group's k tile of the step (none: >= nkt)
-        const int cur = s & 1;
-        const bool more = kt + KG < nkt;
-        if (more) {
-            advance_taps();
-            load_a(kt + KG, ra);
-            load_b(kt + KG, rb);
+    if constexpr (STREAM) {
+        static_assert(!INJ, "injected faults go through the other loaders");
+        // step s: the products of the group's tile s (LDS buffer s % 2); tile s + 1 moves from registers to LDS, and the
+        // loads of tile s + 2 go out, a step and a half before they are waited for
+        if (grp + KG < nkt) {
+            load_a(grp + KG, ra);
+            load_b(grp + KG, rb);
         }
-        if (KG == 1 || kt < nkt) {
-            const char* as = smem + cur * CFG::STAGE_BYTES + (wave_m * CFG::WM + lrow) * STRIDE + lgrp * 16;
-            const char* bs = smem + cur * CFG::STAGE_BYTES + BM * STRIDE + (wave_n * CFG::WN + lrow) * STRIDE + lgrp * 16;
-#pragma unroll
-            for (int kk = 0; kk < KSTEPS; ++kk) {
-                i32x4 a[TM], b[TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    a[i] = *reinterpret_cast<const i32x4*>(as + i * MI * STRIDE + kk * MMA::KBYTES);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    b[j] = *reinterpret_cast<const i32x4*>(bs + j * MI * STRIDE + kk * MMA::KBYTES);
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = MMA::run(a[i], b[j], acc[i][j]);
-                if constexpr (mode_is_wave_level(MODE)) check_step<CFG, MODE>(a, b, chk);
-            }
-        }
-        if (more) store_tiles(cur ^ 1, kt + KG, ra, rb);
         __syncthreads();
-        if constexpr (INJ) {
-            if (kt == p.f_kt) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n, wave));
+        for (int s = 0; s < nsteps; ++s) {
+            const int kt = s * KG + grp;
+            if (KG == 1 || kt < nkt) multiply(s & 1);
+            if (kt + KG < nkt) store_tiles((s & 1) ^ 1, kt + KG, ra, rb);
+            if (kt + 2 * KG < nkt) {
+                load_a(kt + 2 * KG, ra);
+                load_b(kt + 2 * KG, rb);
+            }
+            __syncthreads();
+        }
+    } else {
+        __syncthreads();
+
+        for (int s = 0; s < nsteps; ++s) {
+            const int kt = s * KG + grp;   // this group's k tile of the step (none: >= nkt)
+            const int cur = s & 1;
+            const bool more = kt + KG < nkt;
+            if (more) {
+                advance_taps();
+                load_a(kt + KG, ra);
+                load_b(kt + KG, rb);
+            }
+            if (KG == 1 || kt < nkt) multiply(cur);
+            if (more) store_tiles(cur ^ 1, kt + KG, ra, rb);
+            __syncthreads();
+            if constexpr (INJ) {
+                if (kt == p.f_kt) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n, wave));
+            }
         }
     }
     if constexpr (INJ) {

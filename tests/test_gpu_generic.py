@@ -104,3 +104,33 @@ def test_convolutions_of_whole_chunks(dtype, conv, kernel):
         flag, rep = d.run(mode)
         assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
         assert mode == B.NONE or rep.worst_ratio < 0.5
+
+
+# (M, N, K) on the 16 x 64 tile, the 64 x 64 tile alone and in four groups, the 128 x 128 tile: one k tile and less,
+# a chunk's length, k loops that leave groups without a tile, and long ones
+UNALIGNED = [(5, 70, 8), (16, 130, 63), (3, 300, 130), (9, 200, 2100), (70, 65, 16), (130, 66, 129), (66, 100, 257), (200, 300, 321),
+             (511, 130, 1023), (2000, 1700, 77), (1900, 1701, 200)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("layout", [B.B_NK, B.B_KN], ids=["nk", "kn"])
+@pytest.mark.parametrize("shape", UNALIGNED, ids=str)
+def test_unaligned_operands_take_the_general_path_s_results(shape, layout, dtype):
+    """Operands whose rows are contiguous have instances of the kernel with loaders of their own: bit for bit what the
+    general one, which a planted fault goes through, stores everywhere but at the fault."""
+    M, N, K = shape
+    K = 2 * K if dtype == "i8" and K > 16 else K
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N + K, dist_a="normal", dist_b="normal")
+    rows = sample_rows(M, 300)
+    C_ref = oracle.gemm(A[rows], Bm, dtype)
+    i, j = M // 2, N - 1
+    for mode in (B.NONE, B.GLOBAL, B.THREAD, B.REPLICA):
+        print("case", shape, layout, dtype, mode, flush=True)
+        for pads in (dict(misalign=1), dict(lda_pad=3, ldb_pad=1, ldc_pad=2)):
+            r = run_gemm(A, Bm, dtype, mode, layout=layout, **pads)
+            assert c_close(r.C[rows], C_ref, dtype) and r.flag == 0, mode
+            assert mode == B.NONE or r.report.worst_ratio < 0.5
+            bad = run_gemm(A, Bm, dtype, mode, layout=layout, inject=B.Fault(i, j, 30, -1), **pads)
+            same = bad.C == r.C
+            same[i, j] = True
+            assert same.all() and bad.flag == (mode != B.NONE), mode
