@@ -280,11 +280,11 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
     for (int e = 0; e < EPC; ++e) s[e] = 0;
 
     __shared__ Wide alpha_s[32 * EPC];
-    // Rows whose chunks cannot be read whole (K or the leading dimension is no multiple of a
-    // chunk): one element per thread and row instead.  Thread t takes column t % kb of the kb
+    // Matrices (those whose rows are shorter than a chunk; the others have the kernel below): one element
+    // per thread and row instead.  Thread t takes column t % kb of the kb
     // columns of a pass and every nrg-th row, so that adjacent lanes read adjacent elements of a
     // row and the loads of one thread do not wait for each other.
-    const bool by_element = !p.conv && !p.vec;
+    const bool by_element = !p.conv;
     if (by_element) {
         const int kbase = blockIdx.x * 32 * EPC;
         const int kb_all = min(32 * EPC, p.K - kbase);   // columns of this block
@@ -339,10 +339,7 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
             const int m = m0 + 8 * u;
             if (m >= row_end || k0 >= p.K) continue;
             i32x4 v = {0, 0, 0, 0};
-            if (!p.conv) {
-                const char* src = p.A + ((long long)m * p.lda + k0) * ESIZE;
-                v = p.vec ? ld16(src) : gather16<ESIZE>(src, ESIZE, p.K - k0);
-            } else {
+            {
                 int img = m / (p.OH * p.OW);
                 int rem = m - img * (p.OH * p.OW);
                 int oh = rem / p.OW, ow = rem - oh * p.OW;
@@ -434,6 +431,133 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
             Wide tot = 0;
             for (int y = 0; y < 8; ++y) tot += red2[y * 32 + tx];
             pout[(long long)j * n_parts] = tot;
+        }
+    }
+}
+
+// The same for matrices whose rows are contiguous (at any alignment): the pass over A of the global scheme.  A chunk
+// that K cuts short is read as the last 16 bytes of its row and shifted down.  Four rows per thread are on their
+// way while four are added, and the first weight checksums of the block's k range before any of them; registers for
+// four workgroups per compute unit.  Bound: HBM (A once); with few row blocks, the trip for A.
+// With the weight checksums / this pass of the kernel above, global over unprotected: 511 x 1000 x 2047 fp16 +9.2 / +6.4 us,
+// 2048 x 2048 x 2047 int8 +15.7 / +8, 700 x 128 x 1000 int8, K x N, +14.4 / +7.7 (rows that are no whole chunks went by
+// the element there), 256 x 4096 x 4096, K x N, +10.2 / +6.9, 8192 x 4096 x 4096 bf16 +18 / +14; 8192^3 level (+28).
+template <int DT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == DT_I8 ? 2 : 4)))
+void act_checksum_rows_kernel(const PreArgs p) {
+    constexpr int ESIZE = DT == DT_I8 ? 1 : 2;
+    constexpr int EPC = 16 / ESIZE;
+    constexpr int KB = 32 * EPC;   // values of k per workgroup
+    constexpr int NR = 4;          // rows per set of loads
+    constexpr int NBV = 16;        // weight checksums per batch
+    typedef typename std::conditional<DT == DT_I8, long long, double>::type Wide;
+    __shared__ Wide red[8][32][EPC];
+    __shared__ Wide alpha_s[KB];
+    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+    const int kbase = blockIdx.x * KB, k0 = kbase + tx * EPC;
+    const int subs = p.rows_per_slab / p.rows_per_block;
+    const int slab = blockIdx.y / subs, sub = blockIdx.y - slab * subs;
+    const int row_begin = slab * p.rows_per_slab + sub * p.rows_per_block;
+    const int row_end = min(p.M, row_begin + p.rows_per_block);
+    const int kcount = min(KB, p.K - kbase);
+
+    // this lane's column block, sixteen values of k at a time (out of range: a valid value, multiplied with a
+    // zero or dropped)
+    Wide bv[NBV];
+    auto load_beta = [&](int jb, int batch) {
+        const Wide* bj = reinterpret_cast<const Wide*>(p.beta) + (long long)kbase * p.nb + (jb + tx < p.nb ? jb + tx : p.nb - 1);
+#pragma unroll
+        for (int u = 0; u < NBV; ++u) {
+            const int k = ty + 8 * (batch * NBV + u);
+            bv[u] = bj[(long long)(k < kcount ? k : 0) * p.nb];
+        }
+    };
+    if (p.partial_dots) load_beta(0, 0);
+
+    Wide s[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) s[e] = 0;
+    if (row_begin < row_end) {
+        const int early = k0 < p.K && k0 + EPC > p.K ? (k0 + EPC - p.K) * ESIZE : 0;
+        const char* const src = p.A + (long long)(k0 + EPC <= p.K ? k0 : p.K - EPC) * ESIZE;
+        // set `it`: rows ty, ty + 8, .. of 8 NR rows
+        auto load = [&](int it, i32x4(&v)[NR]) {
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const int m = row_begin + ty + 8 * (NR * it + u);
+                v[u] = ld16u(src + (long long)(m < row_end ? m : row_end - 1) * p.lda * ESIZE);
+            }
+        };
+        // values are widened and added in fp64 one by one (int8: a set in int32 first, exactly), so that the
+        // checksum side carries no rounding that could show up in the comparison
+        auto add = [&](int it, const i32x4(&v)[NR]) {
+            int f[DT == DT_I8 ? EPC : 1] = {0};
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                i32x4 x = v[u];
+                if (early) x = shift_down(x, early);
+                if (row_begin + ty + 8 * (NR * it + u) >= row_end || k0 >= p.K) x = i32x4{0, 0, 0, 0};
+                if constexpr (DT == DT_F16) {
+                    const f16x8 h = bitcast<f16x8>(x);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s[e] += (double)(float)h[e];
+                } else if constexpr (DT == DT_BF16) {
+                    const bf16x8 h = bitcast<bf16x8>(x);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s[e] += (double)(float)h[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) f[e] += (int)(signed char)(x[e >> 2] >> (8 * (e & 3)));
+                }
+            }
+            if constexpr (DT == DT_I8) {
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) s[e] += (Wide)f[e];
+            }
+        };
+        const int n_it = (row_end - row_begin + 8 * NR - 1) / (8 * NR);
+        i32x4 va[NR], vb[NR];
+        load(0, va);
+#pragma nounroll
+        for (int it = 0; it < n_it; it += 2) {
+            if (it + 1 < n_it) load(it + 1, vb);
+            add(it, va);
+            if (it + 2 < n_it) load(it + 2, va);
+            if (it + 1 < n_it) add(it + 1, vb);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) red[ty][tx][e] = s[e];
+    __syncthreads();
+    Wide* out = reinterpret_cast<Wide*>(p.alpha_out);
+    for (int k = tid; k < KB; k += 256) {
+        Wide a = 0;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) a += (&red[y][0][0])[k];
+        alpha_s[k] = a;                                   // (zero beyond K)
+        if (out && kbase + k < p.K) out[kbase + k] = a;
+    }
+    if (!p.partial_dots) return;
+    // Sec. 2.4 step 2: this block's share of the checksum dot products, as in the kernel above
+    __syncthreads();
+    Wide* red2 = &red[0][0][0];  // reuse: 8 x 32 values
+    const int n_parts = subs * gridDim.x;
+    Wide* pout = reinterpret_cast<Wide*>(p.partial_dots) + (long long)slab * p.nb * n_parts + sub * gridDim.x + blockIdx.x;
+    for (int jb = 0; jb < p.nb; jb += 32) {
+        Wide acc = 0;
+#pragma nounroll
+        for (int batch = 0; batch < KB / 8 / NBV; ++batch) {
+            if (batch > 0 || jb > 0) load_beta(jb, batch);
+#pragma unroll
+            for (int u = 0; u < NBV; ++u) acc += alpha_s[ty + 8 * (batch * NBV + u)] * bv[u];
+        }
+        __syncthreads();
+        red2[ty * 32 + tx] = acc;
+        __syncthreads();
+        if (ty == 0 && jb + tx < p.nb) {
+            Wide tot = 0;
+            for (int y = 0; y < 8; ++y) tot += red2[y * 32 + tx];
+            pout[(long long)(jb + tx) * n_parts] = tot;
         }
     }
 }
@@ -760,6 +884,12 @@ hipError_t launch_act_checksum(const Problem& pr, void* alpha_out, int rows_per_
     a.partial_dots = partial_dots;
     const int subs = a.rows_per_slab / a.rows_per_block;
     dim3 grid((unsigned)pre_grid_x(pr.K, pr.dtype), (unsigned)(cdiv(pr.M, rows_per_slab) * subs)), block(256);
+    if (!pr.conv && pr.K >= 16 / esize(pr.dtype)) {
+        if (pr.dtype == ABFT_F16) hipLaunchKernelGGL(act_checksum_rows_kernel<DT_F16>, grid, block, 0, st, a);
+        else if (pr.dtype == ABFT_BF16) hipLaunchKernelGGL(act_checksum_rows_kernel<DT_BF16>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(act_checksum_rows_kernel<DT_I8>, grid, block, 0, st, a);
+        return hipGetLastError();
+    }
     if (pr.dtype == ABFT_F16) hipLaunchKernelGGL(act_checksum_kernel<DT_F16>, grid, block, 0, st, a);
     else if (pr.dtype == ABFT_BF16) hipLaunchKernelGGL(act_checksum_kernel<DT_BF16>, grid, block, 0, st, a);
     else hipLaunchKernelGGL(act_checksum_kernel<DT_I8>, grid, block, 0, st, a);
