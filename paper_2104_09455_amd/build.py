@@ -23,7 +23,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 FLAGS += os.environ.get("ABFT_EXTRA_HIPCC_FLAGS", "").split()   # e.g. -D switches of tuning experiments
 # (the ones that take longest first)
-SOURCES = [f"gemm_{family}_{dt}.hip" for family in ("fast", "generic", "stream", "group") for dt in ("f16", "bf16", "i8")] + ["abft_api.hip"]
+SOURCES = [f"gemm_{family}_{dt}.hip" for family in ("fast", "generic", "stream", "group") for dt in ("f16", "bf16", "i8")]
+SOURCES += ["gemm_strip_f16.hip", "gemm_strip_bf16.hip", "abft_api.hip"]
 
 
 def _compile(src: str) -> str:

@@ -726,6 +726,7 @@ struct Problem {
     long long imgpitch, rowpitch;  // conv: input element (img, ih, iw, c) at img*imgpitch + ih*rowpitch + iw*pix + c
     int pix;
     int tol_K;                     // K the tolerance is taken for (differs from K for a lowered convolution)
+    int run_seg;                   // lowered weights on the input as it is (strip kernel): elements of a filter row's run, else 0
     int act;                       // abft_act_t applied to the stored values
     // chains of layers (Sec. 2.4 step 4): where this layer's epilogue leaves the activation checksums
     // of the NEXT layer (per 32-row block, leading dimension ld_alpha_out; see GemmArgs), whether it
@@ -740,6 +741,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 bool a_vectorisable(const Problem& pr) {
     const int es = esize(pr.dtype);
+    if (pr.run_seg) return true;
     if (!aligned16(pr.A)) return false;
     // (a lowered convolution reads chunks at 4-byte aligned addresses: 16-byte loads still apply)
     if (pr.conv) return (pr.cg.Cin * es) % 16 == 0;
@@ -932,6 +934,31 @@ bool fused_global(const Problem& pr, const CfgInfo& ci) {
     return in_loop * t_gemm < t_pre;
 }
 
+// The strip kernel's share of LDS for a convolution on its input as it is (see gemm_strip.h): the
+// input rows under them beside the weights.  Kp: k as the weights hold it; segp: elements of a filter row's run in
+// them, 0: a pixel's channels are one k tile.  Whether it fits.
+bool strip_fits(const Problem& pr, int Kp, int segp, int& rows, int& pitch) {
+    if (!pr.conv || esize(pr.dtype) != 2 || pr.N > 64) return false;
+    const abft_conv_t& c = pr.cg;
+    const long long pixB = 2ll * c.Cin, WB = c.W * pixB;
+    if (segp == 0 && pixB != 128) return false;
+    if (segp != 0 && (pixB * c.stride % 4 != 0 || WB < 16)) return false;
+    const long long Hv = (long long)(pr.OH - 1) * c.stride + c.KH;
+    // output rows that a strip's consecutive rows of C can meet, ends of images among them, and their input rows
+    const int form = segp ? STRIP_RUNS : STRIP_TAPS;
+    const long long nr = cdiv(32 * strip_waves(form) - 1, pr.OW) + 1, ends = cdiv(nr - 1, pr.OH);
+    const long long r = (nr - 1) * c.stride + c.KH + ends * std::max(0, c.KH - c.stride);
+    const long long w = segp ? std::max(WB + 2 * c.pad * pixB, (pr.OW - 1) * c.stride * pixB + 2ll * segp) : WB + 2 * c.pad * pixB;
+    if (w > 65536 || r > STRIP_ROWS_MAX || r > Hv || pr.OW < 2 || (long long)r * WB > 0x3fffffff || std::llabs(Hv - c.H) * WB > 0x3fffffff) return false;
+    const long long nkt = cdiv(2ll * Kp, 128), p16 = (long long)align_up((size_t)w, 16);
+    if (nkt > 20 || r * p16 > strip_max_bytes(form) || strip_lds_bytes(form, (int)nkt, (int)r, (int)p16) > 160 * 1024)
+        return false;
+    if ((c.batch + 1) * Hv > 0x3fffffff) return false;
+    rows = (int)r;
+    pitch = (int)p16;
+    return true;
+}
+
 // A product ready to be launched
 struct Prepared {
     GemmArgs g;
@@ -975,6 +1002,7 @@ int prepare_problem(const Problem& pr, int mode, const void* beta, void* workspa
     // (they ride in spare columns of the streaming kernel's extra matrix operand: latency-bound
     // products with fp16 or int8 operands)
     if (weighted && (!cfg_is_stream(cfg) || pr.dtype == ABFT_BF16)) return ABFT_E_UNSUPPORTED;
+    if (cfg == CFG_R64 && strip_fits(pr, pr.K, pr.run_seg, g.strip_rows, g.strip_pitch)) g.strip_seg = pr.run_seg;
     g.tiles_m = (int)cdiv(pr.M, ci.bm);
     g.tiles_n = (int)cdiv(pr.N, ci.bn);
     g.flag = flag;
@@ -1200,6 +1228,20 @@ int run_conv(const Problem& pr, int mode, const void* beta, void* workspace, siz
     const size_t inner = align_up(plain_workspace_bytes(pr.M, pr.N, lw.Kp, pr.dtype, mode), 256);
     char* xp = reinterpret_cast<char*>(workspace) + inner;
     char* bp = xp + lw.xp_bytes;
+    // where the row-streaming tiles would run and the input rows under 256 rows of C fit LDS: the lowered weights on
+    // the input as it is, without the padded copy
+    int rows, pitch;
+    if (mode != ABFT_GLOBAL && mode != ABFT_GLOBAL_WEIGHTED && strip_fits(pr, lw.Kp, lw.segp, rows, pitch) &&
+        pick_cfg(pr.M, pr.N, lw.Kp, pr.dtype, true, mode, true) == CFG_R64) {
+        if (!pre && launch_conv_weights(pr, lw, bp, st) != hipSuccess) return ABFT_E_HIP;
+        Problem q = pr;
+        q.B = pre ? pre->bp : bp;
+        q.b_layout = ABFT_B_NK;
+        q.ldb = q.K = q.lda = lw.Kp;
+        q.tol_K = pr.K;
+        q.run_seg = lw.segp;
+        return run_problem(q, mode, nullptr, workspace, inner, flag, report, inject, st);
+    }
     {
         const long long chunks_per_row = lw.rowp / (16 / es);
         const long long total = (long long)c.batch * lw.Hp * chunks_per_row;

@@ -148,6 +148,9 @@ struct GemmArgs {
     long long ld_alpha_out;
     // MODE_GLOBAL_FED: the same from the layer before, for this layer's A: alpha_in[b * K + k]
     const float* alpha_in;
+    // strip kernel (strip_pitch != 0): bytes of an input row and rows it keeps in LDS; elements of a filter
+    // row's run in B where the channels fill no k tile (A is the input as it is, B and K are in that order)
+    int strip_pitch, strip_rows, strip_seg;
 };
 
 template <typename To, typename Ti>
@@ -736,6 +739,15 @@ __device__ __forceinline__ bool cross_wave_last(char* epi, int lane, int wave) {
     return __builtin_amdgcn_readfirstlane(seen) == (unsigned)(CFG::WAVES_M * CFG::WAVES_N - 1);
 }
 
+// max(x, 0), 0 where x is no number.  (One instruction: from the comparison the compiler makes two, the first of them
+// to quiet a signalling NaN, which no matrix instruction leaves)
+__device__ __forceinline__ int relu(int x) { return x > 0 ? x : 0; }
+__device__ __forceinline__ float relu(float x) {
+    float r;
+    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
 // Checksum epilogue (taken from the accumulators, before down-conversion) and store of C.
 //  GLOBAL: fused output summation (Sec. 2.5) of the workgroup tile, compared right here with
 //          the tile's checksum dot product (Sec. 2.4 steps 3-4).  lane_dot (a double, or a
@@ -947,7 +959,7 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int r = 0; r < MMA::NACC; ++r) acc[i][j][r] = acc[i][j][r] > 0 ? acc[i][j][r] : 0;
+                for (int r = 0; r < MMA::NACC; ++r) acc[i][j][r] = relu(acc[i][j][r]);
     }
     // ---- activation checksums for the next layer: per 32-row block and column, the sum of the
     // values as they are stored (a lane holds 16 rows of one column of each MFMA block, the

@@ -31,6 +31,7 @@ namespace abft {
 //    S128    64 x  64, 2 stages per wavefront                         up to about one tile per compute unit
 //  R64 runs the row-streaming kernel (same alignment as F*; 16-bit types, unprotected or wavefront-level):
 //    R64     32 x  64 per wavefront, weights resident in LDS         very many rows, 64 columns or a single k tile
+//                                                                    (convolutions whose input rows fit beside them: the strip kernel)
 //  G* run the generic kernel (any alignment, layout, K):
 //    G128 128 x 128, G64 64 x 64 (32x32 MFMA shapes), G16 16 x 64 (16x16 shapes; M <= 16)
 //    G64K 64 x 64 with four groups of four wavefronts sharing the k tiles: at most about one tile per compute unit
@@ -103,12 +104,29 @@ inline CfgInfo cfg_info_host(int id) {
     }
 }
 
+// the strip kernel (16-bit types; gemm_strip_<dtype>.hip)
+hipError_t launch_strip_f16(int mode, bool inject, const GemmArgs& args, hipStream_t stream);
+hipError_t launch_strip_bf16(int mode, bool inject, const GemmArgs& args, hipStream_t stream);
+inline hipError_t launch_strip_i8(int, bool, const GemmArgs&, hipStream_t) { return hipErrorInvalidValue; }  // (never picked)
+// Its two forms (see gemm_strip.h): wavefronts (three, resp. two, per SIMD), strips held at a time, and the bytes of one strip
+// (3 resp. 10 chunks of the next one per thread)
+enum { STRIP_RUNS = 0, STRIP_TAPS = 1 };
+constexpr int strip_waves(int form) { return form == STRIP_RUNS ? 12 : 8; }
+constexpr int strip_buffers(int form) { return form == STRIP_RUNS ? 2 : 1; }
+constexpr int strip_max_bytes(int form) { return (form == STRIP_RUNS ? 3 : 10) * 64 * strip_waves(form) * 16; }
+constexpr int STRIP_ROWS_MAX = 128;
+// what it keeps in LDS: the weights, the strips, where each chunk of k starts
+constexpr int strip_lds_bytes(int form, int nkt, int rows, int pitch) {
+    return nkt * 64 * 128 + strip_buffers(form) * rows * pitch + nkt * 32;
+}
+
 // implemented once per dtype and family of configurations in gemm_<family>_<dtype>.hip
 #define ABFT_DECLARE_LAUNCHES(dt)                                                                                  \
     hipError_t launch_fast_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);    \
     hipError_t launch_stream_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream);  \
     hipError_t launch_generic_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream); \
     inline hipError_t launch_gemm_##dt(int cfg, int mode, bool inject, const GemmArgs& args, hipStream_t stream) { \
+        if (args.strip_pitch) return launch_strip_##dt(mode, inject, args, stream);                           \
         if (cfg_is_stream(cfg)) return launch_stream_##dt(cfg, mode, inject, args, stream);                   \
         if (cfg_is_generic(cfg)) return launch_generic_##dt(cfg, mode, inject, args, stream);                 \
         return launch_fast_##dt(cfg, mode, inject, args, stream);                                             \

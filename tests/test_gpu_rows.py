@@ -97,6 +97,40 @@ def test_convolutions_of_very_many_rows(conv, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("conv", [
+    wl.Conv(45, 54, 55, 64, 64, 3, 3, 1, 1),       # a pixel is a k tile: strips that meet two images, last tile short
+    wl.Conv(45, 109, 56, 64, 40, 2, 2, 1, 0),      # no border, fewer columns than the tile
+    wl.Conv(20, 211, 70, 64, 64, 1, 3, 1, 1),      # a filter of one row, a border above it
+    wl.Conv(14, 225, 161, 3, 64, 7, 7, 2, 3),      # rows of an odd number of elements, both ends cut chunks; 21 chunks of k
+    wl.Conv(24, 107, 105, 4, 64, 3, 3, 1, 0),      # no border: rows start whole, end cut; an even number of chunks
+    wl.Conv(40, 118, 121, 1, 33, 5, 5, 2, 2),      # one channel, one k tile; columns that rule out wide stores
+    wl.Conv(9, 242, 246, 3, 64, 3, 3, 2, 1),       # short windows
+], ids=str)
+def test_convolutions_whose_input_rows_stay_in_lds(conv, dtype):
+    """The strip kernel: every tap read from input rows that were copied into LDS once, with their border."""
+    if conv.batch * conv.OH * conv.OW < 131072:
+        conv = wl.Conv(-(-131072 // (conv.OH * conv.OW)), *[getattr(conv, f) for f in
+                       ("H", "W", "Cin", "Cout", "KH", "KW", "stride", "pad")])
+    d = DeviceConv(conv, dtype, seed=37)
+    A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
+    rows = np.unique(np.concatenate([sample_rows(d.M, 3000), np.arange(d.M - 40, d.M)]))
+    C_ref = oracle.gemm(A[rows], d.Wm, dtype)
+    for mode in WAVE:
+        print("case", conv, dtype, mode, flush=True)
+        d.dC.fill_(7.0)
+        flag, rep = d.run(mode)
+        assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        if mode == B.NONE:
+            continue
+        if mode == B.THREAD:
+            whole = d.dC.clone()
+        assert d.dC.equal(whole) and rep.worst_ratio < 0.5 and rep.tiles == -(-d.M // 32)
+        for i, j in [(0, 0), (d.M - 1, d.N - 1), (d.M // 2, 7)]:
+            flag, _ = d.run(mode, inject=B.Fault(i, j, _huge_flip(A, d.Wm, dtype, i, j, -1), -1), want_report=False)
+            assert flag == 1, (mode, i, j)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_activation_and_sums_left_for_the_next_layer(dtype):
     """A thread-level layer on this kernel applies ReLU, and leaves the column sums of what it stores to a layer under
     the global scheme, whose comparison they enter."""
