@@ -271,8 +271,15 @@ __device__ __forceinline__ T wave_sum(T v) {
 // ---------------------------------------------------------------------------
 // Tile configuration
 // ---------------------------------------------------------------------------
-template <int DT_, int MI_, int TM_, int TN_, int WAVES_M_, int WAVES_N_, int BKB_>
+// INTERLEAVED: which column of a wavefront tile's TN MI columns lane l of MFMA block j holds: TN l + j, so that a lane
+// holds TN adjacent columns of its rows and a store of them is a run of whole cache lines over the lanes; else
+// MI j + l.  The kernel that copies B into LDS decides it, by the row that it puts where (b_row_of).
+// (Storing four columns of one row per lane, exchanged inside quads of lanes, wrote four rows from each quad: 103 MB
+// of 128-byte rows at 3.9 TB/s, with lanes along the rows at 5.5.)
+template <int DT_, int MI_, int TM_, int TN_, int WAVES_M_, int WAVES_N_, int BKB_, bool INTERLEAVED_ = false>
 struct Cfg {
+    static constexpr bool INTERLEAVED = INTERLEAVED_;
+    static_assert(!INTERLEAVED_ || TN_ == 2 || TN_ == 4, "two or four adjacent columns");
     static constexpr int DT = DT_, MI = MI_, TM = TM_, TN = TN_;
     static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, BKB = BKB_;
     static constexpr int ESIZE = (DT_ == DT_I8) ? 1 : 2;  // bytes per input element
@@ -289,6 +296,10 @@ struct Cfg {
     static constexpr int NB = BN / ROWS_PER_PASS;
     static constexpr int STAGE_BYTES = (BM + BN) * LDS_STRIDE;
     static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
+    // the column (from the workgroup tile's first) that row r of the B tile in LDS holds
+    static constexpr __host__ __device__ int b_row_of(int r) {
+        return INTERLEAVED ? r / WN * WN + r % MI * TN + r % WN / MI : r;
+    }
     static_assert(THREADS % CPR == 0, "threads must cover whole tile rows");
     static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "tile rows vs threads");
     static_assert(BKB_ % Mma<DT_, MI_>::KBYTES == 0, "k tile vs MFMA depth");
@@ -587,7 +598,9 @@ struct TileCoords {
         int in_tile = (CFG::MI == 32) ? (8 * (r >> 2) + 4 * lgrp + (r & 3)) : (4 * lgrp + r);
         return bm0 + wave_m * CFG::WM + i * CFG::MI + in_tile;
     }
-    __device__ __forceinline__ int col(int j) const { return bn0 + wave_n * CFG::WN + j * CFG::MI + lrow; }
+    __device__ __forceinline__ int col(int j) const {
+        return bn0 + wave_n * CFG::WN + (CFG::INTERLEAVED ? lrow * CFG::TN + j : j * CFG::MI + lrow);
+    }
 };
 
 // Fault injection (test hook): flips bit f_bit of the accumulator that holds element
@@ -603,7 +616,7 @@ __device__ __forceinline__ void inject_fault(typename Mma<CFG::DT, CFG::MI>::Acc
     const int cc = p.f_col - (tc.bn0 + tc.wave_n * CFG::WN);
     if (rr >= 0 && rr < CFG::WM && cc >= 0 && cc < CFG::WN) {
         const int i = rr / MI, in_tile = rr % MI;
-        const int j = cc / MI, own_col = cc % MI;
+        const int j = CFG::INTERLEAVED ? cc % TN : cc / MI, own_col = CFG::INTERLEAVED ? cc / TN : cc % MI;
         int r, own_grp;
         if (MI == 32) {
             r = (in_tile >> 3) * 4 + (in_tile & 3);
@@ -1009,24 +1022,46 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
                     if (lane < 16 && col < N && blk * 32 < M) p.alpha_out[(long long)blk * p.ld_alpha_out + col] = cs;
                 }
         }
-        // wavefront tiles that lie wholly inside C: 8-byte stores of four columns per lane
-        const int wrow0 = tc.bm0 + tc.wave_m * CFG::WM, wcol0 = tc.bn0 + tc.wave_n * CFG::WN;
-        const bool whole = CFG::WM <= M - wrow0 && CFG::WN <= N - wcol0 && (p.ldc & 3) == 0 &&
-                           (reinterpret_cast<uintptr_t>(p.C) & 7u) == 0;
+    }
+    // ---- store C (rounded to the output type)
+    if constexpr (CFG::INTERLEAVED) {
+        // wavefront tiles that lie wholly inside C: a lane's TN adjacent columns at once (the bound on ldc: a lane's
+        // offset, up to twelve rows, in 32 bits beside a base that the wavefront shares)
+        typedef int IntN __attribute__((ext_vector_type(TN)));
+        typedef int HalfN __attribute__((ext_vector_type(TN / 2)));
+        const int wave_row0 = __builtin_amdgcn_readfirstlane(tc.bm0 + tc.wave_m * CFG::WM);
+        const int wave_col0 = __builtin_amdgcn_readfirstlane(tc.bn0 + tc.wave_n * CFG::WN);
+        const bool whole = CFG::WM <= M - wave_row0 && CFG::WN <= N - wave_col0 && p.ldc % TN == 0 && p.ldc < (1 << 26) &&
+                           (reinterpret_cast<uintptr_t>(p.C) & (TN * CFG::CSIZE - 1)) == 0;
         if (whole) {
-            const long long ldcb = p.ldc * 2;
-            char* base = p.C + ((long long)(wrow0 + 4 * tc.lgrp + (lane & 3)) * p.ldc + wcol0 + (tc.lrow & ~3)) * 2;
+            const long long ldcb = p.ldc * CFG::CSIZE;
+            char* const base = p.C + wave_row0 * ldcb + (long long)wave_col0 * CFG::CSIZE;
+            const unsigned mine = (unsigned)(4 * tc.lgrp) * (unsigned)ldcb + (unsigned)(tc.lrow * TN * CFG::CSIZE);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    store_quad_rows<CFG::DT>(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3],
-                                             base + (i * 16) * ldcb + j * 32, lane);
+                for (int r = 0; r < MMA::NACC; ++r) {
+                    char* const dst = base + (i * MI + 8 * (r >> 2) + (r & 3)) * ldcb;
+                    if constexpr (CFG::CSIZE == 2) {
+                        HalfN out;
+#pragma unroll
+                        for (int j = 0; j < TN / 2; ++j) {
+                            const int pk = pack_out16<CFG::DT>(acc[i][2 * j][r], acc[i][2 * j + 1][r]);
+                            if constexpr (TN == 2) out = pk;
+                            else out[j] = pk;
+                        }
+                        *reinterpret_cast<HalfN*>(dst + mine) = out;
+                    } else {
+                        IntN out;
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) out[j] = acc[i][j][r];
+                        *reinterpret_cast<IntN*>(dst + mine) = out;
+                    }
+                }
             return;
         }
     }
-    // ---- store C (rounded to the output type)
-    if constexpr (CFG::CSIZE == 2 && MI == 32) {
+    if constexpr (CFG::CSIZE == 2 && MI == 32 && !CFG::INTERLEAVED) {
         // wavefront tiles that lie wholly inside C: 8-byte stores of four columns per lane
         const int wrow0 = tc.bm0 + tc.wave_m * CFG::WM, wcol0 = tc.bn0 + tc.wave_n * CFG::WN;
         const bool whole = CFG::WM <= M - wrow0 && CFG::WN <= N - wcol0 && (p.ldc & 3) == 0 &&

@@ -46,18 +46,18 @@ inline const char* cfg_name(int id) {
 template <int DT, int ID>
 struct CfgOf;
 //                                             MI TM TN WM WN BKB
-template <int DT> struct CfgOf<DT, CFG_F128>  { typedef Cfg<DT, 32, 2, 2, 2, 2, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
-template <int DT> struct CfgOf<DT, CFG_F128T> { typedef Cfg<DT, 32, 1, 4, 4, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
-template <int DT> struct CfgOf<DT, CFG_F64T>  { typedef Cfg<DT, 32, 1, 4, 2, 1, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
-template <int DT> struct CfgOf<DT, CFG_F256W> { typedef Cfg<DT, 16, 8, 4, 2, 4, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
-template <int DT> struct CfgOf<DT, CFG_F256N> { typedef Cfg<DT, 16, 4, 4, 4, 2, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
-template <int DT> struct CfgOf<DT, CFG_F256S> { typedef Cfg<DT, 16, 2, 4, 8, 1, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
-template <int DT> struct CfgOf<DT, CFG_F128E> { typedef Cfg<DT, 16, 2, 4, 4, 2, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F128>  { typedef Cfg<DT, 32, 2, 2, 2, 2, 128, true> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F128T> { typedef Cfg<DT, 32, 1, 4, 4, 1, 128, true> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F64T>  { typedef Cfg<DT, 32, 1, 4, 2, 1, 128, true> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F256W> { typedef Cfg<DT, 16, 8, 4, 2, 4, 128, true> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F256N> { typedef Cfg<DT, 16, 4, 4, 4, 2, 128, true> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F256S> { typedef Cfg<DT, 16, 2, 4, 8, 1, 128, true> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_F128E> { typedef Cfg<DT, 16, 2, 4, 4, 2, 128, true> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_S32>   { typedef Cfg<DT, 32, 1, 1, 1, 1, 128> type; static constexpr int NSTAGE = 4; static constexpr int KWAYS = 4; };
 template <int DT> struct CfgOf<DT, CFG_S32W>  { typedef Cfg<DT, 32, 1, 1, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 8; };
 template <int DT> struct CfgOf<DT, CFG_S64>   { typedef Cfg<DT, 32, 1, 2, 1, 1, 128> type; static constexpr int NSTAGE = 3; static constexpr int KWAYS = 4; };
 template <int DT> struct CfgOf<DT, CFG_S128>  { typedef Cfg<DT, 32, 2, 2, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 4; };
-template <int DT> struct CfgOf<DT, CFG_R64>   { typedef Cfg<DT, 32, 1, 2, 1, 1, 128> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
+template <int DT> struct CfgOf<DT, CFG_R64>   { typedef Cfg<DT, 32, 1, 2, 1, 1, 128, true> type; static constexpr int NSTAGE = 2; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_G128>  { typedef Cfg<DT, 32, 2, 2, 2, 2, 128> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_G64>   { typedef Cfg<DT, 32, 1, 1, 2, 2, 128> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 1; };
 template <int DT> struct CfgOf<DT, CFG_G64K>  { typedef Cfg<DT, 32, 1, 1, 2, 2, 128> type; static constexpr int NSTAGE = 0; static constexpr int KWAYS = 4; };

@@ -151,7 +151,7 @@ void gemm_fast_kernel(const GemmArgs p) {
     (void)NQ;
 #pragma unroll
     for (int q = 0; q < NQB; ++q) {
-        const int n = bn0 + (q * WAVES + wave) * 8 + crow;
+        const int n = bn0 + CFG::b_row_of((q * WAVES + wave) * 8 + crow);
         if (n < N) b_valid |= 1u << q;
         bptr[q] = n < N ? p.B + (long long)n * p.ldb * ESIZE + ckc * 16 : zero;
     }

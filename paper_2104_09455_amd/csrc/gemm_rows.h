@@ -62,7 +62,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
     for (int i = wave; i < b_tiles * (BN / 8); i += WAVES) {
         const int tile = i / (BN / 8), q = i - tile * (BN / 8);
         const int c = tile / nkt, t = tile - c * nkt;
-        const int n = c * BN + q * 8 + (lane >> 3), ck = (lane & 7) ^ ((lane >> 4) + 4 * (q & 1));
+        const int n = c * BN + CFG::b_row_of(q * 8 + (lane >> 3)), ck = (lane & 7) ^ ((lane >> 4) + 4 * (q & 1));
         const char* src = n < N ? p.B + ((long long)n * p.ldb + (long long)t * BK) * ESIZE + ck * 16 : g_zero_chunk + ck * 16;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                          (__attribute__((address_space(3))) void*)(smem + i * 1024), 16, 0, 0);

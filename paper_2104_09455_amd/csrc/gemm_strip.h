@@ -58,7 +58,7 @@ __global__ __launch_bounds__(StripLayout<FORM>::THREADS, StripLayout<FORM>::WAVE
     // ---- the weights, once (the row-streaming kernel's layout)
     for (int i = wave; i < nkt * (BN / 8); i += WAVES) {
         const int t = i / (BN / 8), q = i - t * (BN / 8);
-        const int n = q * 8 + (lane >> 3), ck = (lane & 7) ^ ((lane >> 4) + 4 * (q & 1));
+        const int n = CFG::b_row_of(q * 8 + (lane >> 3)), ck = (lane & 7) ^ ((lane >> 4) + 4 * (q & 1));
         const char* src = n < N ? p.B + ((long long)n * p.ldb + (long long)t * BK) * ESIZE + ck * 16 : g_zero_chunk + ck * 16;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                          (__attribute__((address_space(3))) void*)(smem + i * 1024), 16, 0, 0);

@@ -1,0 +1,58 @@
+"""C's edges and leading dimensions on the tiles whose lanes hold adjacent columns: wavefront tiles that lie wholly inside C
+are stored two or four columns per lane where C's rows start at a multiple of those, all others by the element; nothing
+outside C is written, and a fault lands in the element it names."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import DEV, DT, c_close, c_to_host, to_dev
+from paper_2104_09455_amd import binding as B
+from paper_2104_09455_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+# (M, N, K) on each tile: columns that end inside a wavefront tile and at its edge
+CASES = {
+    "F256W": (3585, 4097, 128), "F256N": (2049, 2240, 512), "F256S": (65571, 60, 512), "F128E": (1150, 2056, 512),
+    "F128": (2300, 2190, 256), "F128T": (16400, 100, 128), "F64T": (3000, 390, 384), "R64": (131105, 130, 64),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_edges_and_leading_dimensions(name, dtype):
+    M, N, K = CASES[name]
+    dt = DT[dtype]
+    K = 2 * K if dtype == "i8" else K    # (the same bytes)
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N, dist_a="int8" if dtype == "i8" else "normal",
+                             dist_b="int8" if dtype == "i8" else "normal")
+    dA, dB = to_dev(A, dtype), to_dev(np.ascontiguousarray(Bm.T), dtype)
+    rows = np.unique(np.r_[0:40, 120:136, M // 2:M // 2 + 70, M - 70:M])
+    C_ref = oracle.gemm(A[rows], Bm, dtype)
+    t = {"f16": torch.float16, "bf16": torch.bfloat16, "i8": torch.int32}[dtype]
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    seen = set()
+    for mode in (B.NONE, B.THREAD):
+        seen.add(B.abft_kernel_name(M, N, K, dt, mode))
+        for pad, shift in ((0, 0), (1, 0), (2, 0), (4, 0), (8, 1), (8, 2), (8, 4)):
+            print("case", name, dtype, mode, pad, shift, flush=True)
+            ldc = -(-N // 8) * 8 + pad
+            buf = torch.full((M * ldc + 16,), 77, dtype=t, device=DEV)
+            C = buf[shift:shift + M * ldc].view(M, ldc)
+            B.abft_gemm(M, N, K, dA, K, dB, K, B.B_NK, C, ldc, dt, mode, fault_flag=flag)
+            torch.cuda.synchronize()
+            got = C[torch.as_tensor(rows, device=DEV)][:, :N].contiguous()
+            assert c_close(c_to_host(got, dtype), C_ref, dtype), (mode, pad, shift)
+            assert bool((C[:, N:] == 77).all()) and bool((buf[:shift] == 77).all()) and bool((buf[shift + M * ldc:] == 77).all())
+            assert int(flag.item()) == 0
+            if pad == 0 and shift == 0:
+                whole = C[:, :N].clone()
+            assert C[:, :N].equal(whole)
+    # a flipped top bit of a finished accumulator changes that element and no other
+    for i, j in ((0, 1), (M - 1, N - 1), (M // 2, N // 3)):
+        C = torch.zeros((M, N), dtype=t, device=DEV)
+        B.abft_gemm(M, N, K, dA, K, dB, K, B.B_NK, C, N, dt, B.THREAD, fault_flag=flag, inject=B.Fault(i, j, 31, -1))
+        torch.cuda.synchronize()
+        assert [tuple(x) for x in (C != whole).nonzero().tolist()] == [(i, j)]
+    print("tiles", name, seen, flush=True)
+    assert name in seen or (dtype == "i8" and name == "R64")
