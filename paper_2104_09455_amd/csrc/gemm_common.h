@@ -855,12 +855,14 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
             // groups of four accumulators are summed in fp32 (three roundings), everything
             // above that in fp64, so the summation adds nothing visible to the comparison.  (Exact
             // thread-level scheme without a report: the blocks' differences, which are zeros on a clean tile
-            // and a fault's change otherwise, need neither)
+            // and a fault's change otherwise, need neither; and where every pair is the same bit for bit, they
+            // need not be added up at all)
             constexpr bool TWIN = MODE == MODE_THREAD;
             double s = 0.0;
             float f2 = 0.f, l1 = 0.f, diff = 0.f;
             if (TWIN && !p.report) {
                 if constexpr (TWIN) {
+                    int differ = 0;
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -869,8 +871,18 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
                             for (int r = 0; r < MMA::NACC; ++r) {
                                 const float v = acc[i][j][r];
                                 f2 += v * v;
-                                diff += v - chk[i * TN + j][r];
+                                // (one instruction: differ | (v ^ twin), the table of three inputs 0xF0, 0xCC, 0xAA)
+                                differ = __builtin_amdgcn_bitop3_b32(bitcast<int>(v), bitcast<int>((float)chk[i * TN + j][r]), differ, 0xBE);
                             }
+                    if (__any(differ)) {
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                                for (int r = 0; r < MMA::NACC; ++r) diff += acc[i][j][r] - chk[i * TN + j][r];
+                        diff = wave_sum(diff);
+                    }
                 }
             } else {
 #pragma unroll
@@ -943,7 +955,7 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
                     s = wave_sum(s);
                     rsum = wave_sum(lane_check_sum<CFG, MODE>(chk, lane));
                 } else if constexpr (TWIN) {
-                    s = (double)wave_sum(diff);
+                    s = (double)diff;
                 } else {
                     rsum = lane_check_sum<CFG, MODE>(chk, lane);
                     s = wave_sum(s - rsum);

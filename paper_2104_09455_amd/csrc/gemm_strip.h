@@ -128,6 +128,13 @@ __global__ __launch_bounds__(StripLayout<FORM>::THREADS, StripLayout<FORM>::WAVE
         const int ihp0 = c_oh * p.stride;
         v_pre = c_img * Hv + ihp0;
         const char* const base = p.A + ((long long)c_img * p.H + ihp0 - p.pad) * WB;
+        if (ihp0 >= p.pad && ihp0 - p.pad + n_rows <= p.H) {
+            // all of it inside one image (most strips): rows and their chunks lie in order
+            const unsigned end = (unsigned)(n_rows * WB);
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) pre[u] = ld16u((unsigned)from[u] < end ? base + from[u] : g_zero_chunk);
+            if (ends) pre_end = ld16u((unsigned)e_from < end ? base + e_from : g_zero_chunk);
+        } else {
         const int over = Hv - ihp0, skip = (Hv - p.H) * WB;   // first row of the next image
         auto source = [&](int sl, int fr) {
             const bool next = sl >= over;
@@ -138,6 +145,7 @@ __global__ __launch_bounds__(StripLayout<FORM>::THREADS, StripLayout<FORM>::WAVE
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) pre[u] = ld16u(source(slot[u], from[u]));
         if (ends) pre_end = ld16u(source(e_slot, e_from));
+        }
         // on to the next strip's first row of C
         c_ow += d_ow;
         c_oh += d_oh;
