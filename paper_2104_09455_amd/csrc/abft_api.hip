@@ -979,7 +979,7 @@ int prepare_problem(const Problem& pr, int mode, const void* beta, void* workspa
 
     const bool avec = a_vectorisable(pr), bvec = b_vectorisable(pr);
     const bool all16 = avec && bvec;
-    const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, all16, mode, pr.conv);
+    const int cfg = pr.run_seg ? (int)CFG_R64 : pick_cfg(pr.M, pr.N, pr.K, pr.dtype, all16, mode, pr.conv);
     const CfgInfo ci = cfg_info_host(cfg);
     const int bk = ci.bk_bytes / esize(pr.dtype);
 
@@ -1210,6 +1210,19 @@ Problem lowered_problem(const Problem& pr, const ConvLowering& lw, const void* x
     return q;
 }
 
+// Does the strip kernel take a lowered convolution?  Where its input rows fit LDS: under the schemes whose other tiles
+// check C in the same pieces, so that what is reported of them stays (32 rows by all of at most 64 columns: the row-streaming
+// kernel, and the 64 x 128 and 128 x 128 tiles of 32 x 128 per wavefront; sums in the operand type have a tolerance by
+// the nominal tile and stay on those), and unprotected wherever the product fills more than streaming tiles.
+bool lowered_on_strips(const Problem& pr, const ConvLowering& lw, int mode) {
+    int rows, pitch;
+    if (mode == ABFT_GLOBAL || mode == ABFT_GLOBAL_WEIGHTED || !strip_fits(pr, lw.Kp, lw.segp, rows, pitch)) return false;
+    const int cfg = pick_cfg(pr.M, pr.N, lw.Kp, pr.dtype, true, mode, true);
+    if (cfg == CFG_R64) return true;
+    if (mode == ABFT_NONE) return !cfg_is_stream(cfg) && !cfg_is_generic(cfg);
+    return (mode == ABFT_THREAD || mode == ABFT_REPLICA) && (cfg == CFG_F64T || cfg == CFG_F128T);
+}
+
 // a convolution: lowered to row segments when it qualifies and the workspace has the room.
 // A fault planted in a running accumulator (k_after >= 0) counts k in the order of abft_conv_t,
 // which the lowered product does not keep: such a call runs unlowered.
@@ -1228,11 +1241,8 @@ int run_conv(const Problem& pr, int mode, const void* beta, void* workspace, siz
     const size_t inner = align_up(plain_workspace_bytes(pr.M, pr.N, lw.Kp, pr.dtype, mode), 256);
     char* xp = reinterpret_cast<char*>(workspace) + inner;
     char* bp = xp + lw.xp_bytes;
-    // where the row-streaming tiles would run and the input rows under 256 rows of C fit LDS: the lowered weights on
-    // the input as it is, without the padded copy
-    int rows, pitch;
-    if (mode != ABFT_GLOBAL && mode != ABFT_GLOBAL_WEIGHTED && strip_fits(pr, lw.Kp, lw.segp, rows, pitch) &&
-        pick_cfg(pr.M, pr.N, lw.Kp, pr.dtype, true, mode, true) == CFG_R64) {
+    if (lowered_on_strips(pr, lw, mode)) {
+        // the lowered weights on the input as it is, without the padded copy
         if (!pre && launch_conv_weights(pr, lw, bp, st) != hipSuccess) return ABFT_E_HIP;
         Problem q = pr;
         q.B = pre ? pre->bp : bp;
