@@ -2,17 +2,17 @@
 // whole weight matrix fits in LDS (a CNN's first stage: 64 input or output channels), unprotected
 // or under a wavefront-level scheme.
 //
-// One workgroup of eight wavefronts per compute unit copies the weights into LDS once and stays.
-// After that no wavefront waits for another: each walks its own 32-row tiles of C (32 x 64 at a
-// time) and loads the k tiles (128 bytes of k) of its rows of A straight into MFMA fragments, four
-// k tiles ahead and across tile boundaries, so that the next rows are on their way while this tile
+// One workgroup per compute unit copies the weights into LDS once and stays.  After that no
+// wavefront waits for another: each walks its own 32-row tiles of C (32 x 64 at a
+// time) and loads the k tiles (128 bytes of k) of its rows of A straight into MFMA fragments, two to
+// four k tiles ahead and across tile boundaries, so that the next rows are on their way while this tile
 // is checked and stored.  (A wavefront tile of 32 rows meets no other reader of its rows of A in
-// the workgroup; rings of two LDS stages beside 72 KB of weights took 50 us where this form takes
-// 41.)  Bound: HBM (the rows in, C out) and, for 3 x 3 convolutions, the rate at which the vector
-// memory path serves fragments of 32 rows at a time.  Thread-level, fp16, against 128 x 128 tiles:
-// 200704 x 64 x 256 35 us (3.7 TB/s) against 41, 200704 x 256 x 64 40 against 46-50, 3 x 3 convolution 64 -> 64
-// on 200704 rows 39-41 against 56 (unprotected 35, on 256 x 64 tiles 39), stem (7 x 7, lowered to K = 192)
-// on 802816 rows with its padded copy 86-88 against 112.
+// the workgroup; rings of two LDS stages beside 72 KB of weights took 50 us where this form takes 41.)
+// Matrices: twelve wavefronts, three per SIMD, with two k tiles ahead, so that checks and stores run under
+// the others' loads: thread-level fp16 200704 x 256 x 64 33 -> 31 us, 131104 x 1280 x 64 87 -> 83 (eight with four
+// ahead before; sixteen: registers spill, 38 and 92); unprotected level (27 and 74).  Bound: HBM (the rows in, C
+// out; 200704 x 64 x 256 thread-level 31 us, 4.1 TB/s) and, for convolutions whose input rows do not fit LDS (else:
+// the strip kernel), the rate at which the vector memory path serves fragments of 32 rows at a time.
 #pragma once
 #include "gemm_fast.h"
 
@@ -20,7 +20,6 @@ namespace abft {
 
 template <class CFG>
 struct RowsLayout {
-    static constexpr int WAVES = 8;
     static constexpr int B_TILE = CFG::BN * 128;              // one k tile of 64 columns
     static constexpr int LDS_MAX = 160 * 1024;
     static constexpr int MAX_B_TILES = LDS_MAX / B_TILE;
@@ -31,14 +30,15 @@ struct RowsLayout {
 // K is whole k tiles; one column block of 64 (p.tiles_n == 1), or several with a single k tile.
 // Grid: any number of workgroups.  FORM: how a row of A is read.
 enum { ROWS_MATRIX = 0, ROWS_CONV = 1, ROWS_CONV_ONE_TAP = 2 };  // (one tap: Cin a multiple of the k tile)
+constexpr int rows_waves(int form) { return form == ROWS_MATRIX ? 12 : 8; }
 template <class CFG, int MODE, bool INJ, int FORM>
-__global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs p) {
+__global__ __launch_bounds__((64 * rows_waves(FORM))) void gemm_rows_kernel(const GemmArgs p) {
     typedef RowsLayout<CFG> LAY;
     constexpr int DT = CFG::DT;
     typedef Mma<DT, 32> MMA;
     typedef typename MMA::Acc Acc;
     constexpr int TN = CFG::TN, BM = CFG::BM, BN = CFG::BN, BK = CFG::BK, ESIZE = CFG::ESIZE, EPC = CFG::EPC;
-    constexpr int ROWB = 128, WAVES = LAY::WAVES, AHEAD = 4;
+    constexpr int ROWB = 128, WAVES = rows_waves(FORM), AHEAD = FORM == ROWS_MATRIX ? 2 : 4;
     constexpr bool CONV = FORM != ROWS_MATRIX, ONE_TAP = FORM == ROWS_CONV_ONE_TAP;
     static_assert(MODE == MODE_NONE || mode_is_wave_level(MODE), "no scheme that compares across wavefronts");
     static_assert(CFG::CSIZE == 2, "16-bit outputs");
