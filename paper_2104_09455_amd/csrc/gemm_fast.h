@@ -25,24 +25,6 @@
 
 namespace abft {
 
-// Workgroup index -> output tile.  Workgroups are dealt round-robin to the 8 XCDs, each
-// with its own L2; the remap hands every XCD a contiguous run of tiles and walks those in
-// bands of 8 tile rows, so that the tiles resident on an XCD at one time share A row
-// blocks and B column blocks in its L2.
-__device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int total = tiles_m * tiles_n;
-    int lin = bid;
-    if ((total & 7) == 0) lin = (bid & 7) * (total >> 3) + (bid >> 3);
-    constexpr int GM = 8;
-    const int per_group = GM * tiles_n;
-    const int group = lin / per_group;
-    const int first_m = group * GM;
-    const int gsz = min(tiles_m - first_m, GM);
-    const int in_group = lin - group * per_group;
-    tn = in_group / gsz;
-    tm = first_m + (in_group - tn * gsz);
-}
-
 // vmcnt(n) with expcnt / lgkmcnt left open (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 

@@ -12,8 +12,9 @@
 //     MFMAs (eight: 64 us, twelve 57), and two strips in LDS, one barrier per strip.  The padded copy that the
 //     row-streaming kernel needs, 14 us, is gone.
 //   STRIP_TAPS: nine k tiles of weights leave LDS for one strip; eight wavefronts, four steps' fragments read ahead.
-// Thread-level fp16: stem of 64 images (802816 x 64, 7 x 7 x 3) 88 -> 57 us with its copy; 3 x 3 convolution 64 -> 64 on
-// 200704 rows 43 -> 38.  Bound: vector work (580 instructions of 32 x 64 stem tile, the epilogue's half of them), the store of C.
+// Thread-level fp16: stem of 64 images (802816 x 64, 7 x 7 x 3) 88 -> 47-50 us, its padded copy among them; 3 x 3 convolution
+// 64 -> 64 on 200704 rows 46 -> 38.  Bound: vector work (500 instructions a 32 x 64 stem tile, the epilogue's half of them),
+// then the store of C.
 #pragma once
 #include "gemm_configs.h"
 

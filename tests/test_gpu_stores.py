@@ -56,3 +56,23 @@ def test_edges_and_leading_dimensions(name, dtype):
         assert [tuple(x) for x in (C != whole).nonzero().tolist()] == [(i, j)]
     print("tiles", name, seen, flush=True)
     assert name in seen or (dtype == "i8" and name == "R64")
+
+
+@pytest.mark.parametrize("shape", [(250, 4000, 256), (70, 3000, 256), (1, 1500, 512), (1900, 2500, 256), (2500, 1900, 256),
+                                   (300, 1100, 257), (1100, 300, 257), (5, 1000, 131), (2100, 2200, 130), (2200, 2100, 130)], ids=str)
+@pytest.mark.parametrize("layout", [B.B_NK, B.B_KN])
+def test_every_tile_once_whatever_their_number(shape, layout):
+    """Numbers of tiles that 8 does and does not divide, more tile columns than rows and the reverse: all of C is written,
+    exactly (int8)."""
+    M, N, K = shape
+    A, Bm = wl.gemm_operands(M, N, K, "i8", seed=M + N, dist_a="int8", dist_b="int8")
+    W = np.ascontiguousarray(Bm.T) if layout == B.B_NK else Bm
+    dA, dB = to_dev(A, "i8"), to_dev(W, "i8")
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    C_ref = oracle.gemm(A, Bm, "i8")
+    for mode in (B.NONE, B.THREAD):
+        print("case", shape, layout, mode, flush=True)
+        C = torch.full((M, N), -7, dtype=torch.int32, device=DEV)
+        B.abft_gemm(M, N, K, dA, K, dB, W.shape[1], layout, C, N, B.I8, mode, fault_flag=flag)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), C_ref) and int(flag.item()) == 0
