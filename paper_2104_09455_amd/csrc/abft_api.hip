@@ -940,6 +940,8 @@ bool fused_global(const Problem& pr, const CfgInfo& ci) {
 bool strip_fits(const Problem& pr, int Kp, int segp, int& rows, int& pitch) {
     if (!pr.conv || esize(pr.dtype) != 2 || pr.N > 64) return false;
     const abft_conv_t& c = pr.cg;
+    // (the padded copy of a lowered convolution has pitches of its own, also where a run is a whole k tile)
+    if (pr.pix != c.Cin || pr.rowpitch != (long long)c.W * c.Cin || pr.imgpitch != pr.rowpitch * c.H) return false;
     const long long pixB = 2ll * c.Cin, WB = c.W * pixB;
     if (segp == 0 && pixB != 128) return false;
     if (segp != 0 && (pixB * c.stride % 4 != 0 || WB < 16)) return false;

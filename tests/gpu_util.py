@@ -111,6 +111,18 @@ def sample_rows(M, n, band=256, seed=0):
     return np.array(sorted(rows))
 
 
+def edge_rows(c, n=24000):
+    """Rows of a convolution's C in the first and last output row of its images: of all images, or of so many of
+    the first and last ones as have about n such rows."""
+    per = 2 * c.OW
+    images = np.arange(c.batch)
+    if c.batch * per > n:
+        half = max(1, n // per // 2)
+        images = np.r_[images[:half], images[-half:]]
+    first = images[:, None] * c.OH * c.OW + np.arange(c.OW)
+    return np.unique(np.r_[first.ravel(), (first + (c.OH - 1) * c.OW).ravel()])
+
+
 class DeviceGemm:
     """Device-resident operands of one product (weights stored N x K), reused over many calls."""
 

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import DT, DeviceConv, DeviceGemm, c_close, run_gemm, sample_rows
+from gpu_util import DT, DeviceConv, DeviceGemm, c_close, edge_rows, run_gemm, sample_rows
 from paper_2104_09455_amd import binding as B
 from paper_2104_09455_amd import workloads as wl
 
@@ -128,6 +128,32 @@ def test_convolutions_whose_input_rows_stay_in_lds(conv, dtype):
         for i, j in [(0, 0), (d.M - 1, d.N - 1), (d.M // 2, 7)]:
             flag, _ = d.run(mode, inject=B.Fault(i, j, _huge_flip(A, d.Wm, dtype, i, j, -1), -1), want_report=False)
             assert flag == 1, (mode, i, j)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("conv", [
+    wl.Conv(328, 20, 20, 20, 64, 3, 3, 1, 1),      # runs of 60 elements
+    wl.Conv(330, 22, 19, 12, 33, 5, 5, 1, 2),
+    wl.Conv(35, 63, 63, 30, 64, 2, 2, 1, 0),       # two filter rows
+], ids=str)
+def test_padded_copies_whose_runs_are_a_whole_k_tile(conv, dtype):
+    """Lowered convolutions whose strips do not fit LDS: their product reads the padded copy, whose rows and pixels have
+    pitches of their own, although a run is as long as the pixels that the strip kernel takes."""
+    d = DeviceConv(conv, dtype, seed=43)
+    assert d.M >= 131072 and B.abft_kernel_name(d.M, d.N, 64 * conv.KH, d.dt, B.THREAD, conv=True) == "R64"
+    A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
+    rows = np.union1d(sample_rows(d.M, 3000), edge_rows(conv))
+    C_ref = oracle.gemm(A[rows], d.Wm, dtype)
+    for mode in WAVE:
+        print("case", conv, dtype, mode, flush=True)
+        d.dC.fill_(7.0)
+        flag, rep = d.run(mode)
+        assert c_close(d.C(rows), C_ref, dtype) and flag == 0, mode
+        if mode == B.NONE:
+            continue
+        if mode == B.THREAD:
+            whole = d.dC.clone()
+        assert d.dC.equal(whole) and rep.worst_ratio < 0.5 and rep.tiles == -(-d.M // 32)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
