@@ -129,8 +129,9 @@ __global__ __launch_bounds__(StripLayout<FORM>::THREADS, StripLayout<FORM>::WAVE
         const int ihp0 = c_oh * p.stride;
         v_pre = c_img * Hv + ihp0;
         const char* const base = p.A + ((long long)c_img * p.H + ihp0 - p.pad) * WB;
-        if (ihp0 >= p.pad && ihp0 - p.pad + n_rows <= p.H) {
-            // all of it inside one image (most strips): rows and their chunks lie in order
+        if (c_oh + down < p.OH && ihp0 >= p.pad && ihp0 - p.pad + n_rows <= p.H) {
+            // all of it inside one image (most strips): rows and their chunks lie in order.  (The rows alone do not tell:
+            // at an image's foot there can be as many that no window reaches as the next image's first windows need)
             const unsigned end = (unsigned)(n_rows * WB);
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) pre[u] = ld16u((unsigned)from[u] < end ? base + from[u] : g_zero_chunk);

@@ -105,6 +105,9 @@ def test_convolutions_of_very_many_rows(conv, dtype):
     wl.Conv(24, 107, 105, 4, 64, 3, 3, 1, 0),      # no border: rows start whole, end cut; an even number of chunks
     wl.Conv(40, 118, 121, 1, 33, 5, 5, 2, 2),      # one channel, one k tile; columns that rule out wide stores
     wl.Conv(9, 242, 246, 3, 64, 3, 3, 2, 1),       # short windows
+    # strides that leave rows at an image's foot unread, as many as the next image's first windows reach, and (odd height) none
+    wl.Conv(15, 200, 200, 4, 64, 1, 1, 2, 0), wl.Conv(15, 201, 200, 4, 64, 1, 1, 2, 0), wl.Conv(16, 227, 227, 2, 64, 3, 3, 5, 0),
+    wl.Conv(15, 190, 204, 4, 64, 1, 3, 2, 0), wl.Conv(10, 202, 150, 4, 48, 2, 3, 6, 1),
 ], ids=str)
 def test_convolutions_whose_input_rows_stay_in_lds(conv, dtype):
     """The strip kernel: every tap read from input rows that were copied into LDS once, with their border."""
@@ -113,7 +116,7 @@ def test_convolutions_whose_input_rows_stay_in_lds(conv, dtype):
                        ("H", "W", "Cin", "Cout", "KH", "KW", "stride", "pad")])
     d = DeviceConv(conv, dtype, seed=37)
     A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
-    rows = np.unique(np.concatenate([sample_rows(d.M, 3000), np.arange(d.M - 40, d.M)]))
+    rows = np.unique(np.concatenate([sample_rows(d.M, 3000), edge_rows(conv)]))
     C_ref = oracle.gemm(A[rows], d.Wm, dtype)
     for mode in WAVE:
         print("case", conv, dtype, mode, flush=True)
@@ -128,6 +131,24 @@ def test_convolutions_whose_input_rows_stay_in_lds(conv, dtype):
         for i, j in [(0, 0), (d.M - 1, d.N - 1), (d.M // 2, 7)]:
             flag, _ = d.run(mode, inject=B.Fault(i, j, _huge_flip(A, d.Wm, dtype, i, j, -1), -1), want_report=False)
             assert flag == 1, (mode, i, j)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("conv", [
+    wl.Conv(37, 64, 64, 3, 64, 1, 1, 2, 0), wl.Conv(40, 120, 120, 3, 64, 1, 1, 2, 0), wl.Conv(16, 227, 227, 2, 64, 3, 3, 5, 0),
+    wl.Conv(64, 65, 70, 3, 40, 3, 3, 2, 1),
+], ids=str)
+def test_lowered_convolutions_of_fewer_rows_on_strips(conv, dtype):
+    """All of C, where a strip's rows of C come from two images and its stride leaves input rows unread."""
+    d = DeviceConv(conv, dtype, seed=47)
+    A = oracle.im2col(d.x, dtype, conv.KH, conv.KW, conv.stride, conv.pad)
+    C_ref = oracle.gemm(A, d.Wm, dtype)
+    for mode in (B.NONE, B.THREAD, B.REPLICA):
+        print("case", conv, dtype, mode, flush=True)
+        d.dC.fill_(7.0)
+        flag, rep = d.run(mode)
+        assert c_close(d.C(), C_ref, dtype) and flag == 0, mode
+        assert mode == B.NONE or (rep.worst_ratio < 0.5 and rep.tiles == -(-d.M // 32))
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
