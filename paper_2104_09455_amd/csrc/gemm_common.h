@@ -775,14 +775,12 @@ __device__ __forceinline__ bool cross_wave_last(char* epi, int lane, int wave) {
     return __builtin_amdgcn_readfirstlane(seen) == (unsigned)(CFG::WAVES_M * CFG::WAVES_N - 1);
 }
 
-// max(x, 0), 0 where x is no number.  (One instruction: from the comparison the compiler makes two, the first of them
-// to quiet a signalling NaN, which no matrix instruction leaves)
+// max(x, 0), 0 where x is no number.  Floats are stored in 16 bits: the median of x, the largest float and 0 is one
+// instruction, which the compiler keeps as far behind the matrix instruction that writes x as the hardware asks (the
+// comparison takes two: 2 % of a stem).  Infinity comes out as the largest float, which both types round to
+// infinity; every other one of the 2^32 patterns, signalling NaN among them, as from the comparison.
 __device__ __forceinline__ int relu(int x) { return x > 0 ? x : 0; }
-__device__ __forceinline__ float relu(float x) {
-    float r;
-    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
+__device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 3.402823466e+38f, 0.f); }
 
 // Checksum epilogue (taken from the accumulators, before down-conversion) and store of C.
 //  GLOBAL: fused output summation (Sec. 2.5) of the workgroup tile, compared right here with

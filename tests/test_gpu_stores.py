@@ -1,4 +1,4 @@
-"""C's edges and leading dimensions on the tiles whose lanes hold adjacent columns: wavefront tiles that lie wholly inside C
+"""C's edges, activation and leading dimensions on the tiles whose lanes hold adjacent columns: wavefront tiles that lie wholly inside C
 are stored two or four columns per lane where C's rows start at a multiple of those, all others by the element; nothing
 outside C is written, and a fault lands in the element it names."""
 import numpy as np
@@ -76,3 +76,61 @@ def test_every_tile_once_whatever_their_number(shape, layout):
         B.abft_gemm(M, N, K, dA, K, dB, W.shape[1], layout, C, N, B.I8, mode, fault_flag=flag)
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy(), C_ref) and int(flag.item()) == 0
+
+
+CONVS = {
+    "R64 one tap": wl.Conv(2700, 7, 7, 64, 64, 3, 3, 1, 1), "R64 taps": wl.Conv(36, 123, 121, 32, 64, 2, 2, 2, 0),
+    "strips of pixels": wl.Conv(45, 54, 55, 64, 64, 3, 3, 1, 1), "strips of runs": wl.Conv(12, 215, 214, 3, 64, 7, 7, 2, 3),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("name", sorted(CASES) + sorted(CONVS))
+def test_relu_of_every_tile(name, dtype):
+    """ReLU as C is stored: what is stored without it, and zeros for its negative values, bit for bit, with and without checks
+    (the checks read the accumulators before; without them the activation is the first to).  A signalling NaN (the top exponent bit
+    of a value between 1 and 1.5 flipped) stores 0, as any NaN."""
+    dt = DT[dtype]
+    t = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    if name in CASES:
+        M, N, K = CASES[name]
+        c, geo = None, B.Conv()
+        x, w = wl.random_matrix((M, K), dtype, "normal", 5), wl.random_matrix((N, K), dtype, "normal", 6)
+    else:
+        c = CONVS[name]
+        geo = B.Conv(c.batch, c.H, c.W, c.Cin, c.KH, c.KW, c.stride, c.pad)
+        M, N, K = c.batch * c.OH * c.OW, c.Cout, c.KH * c.KW * c.Cin
+        x, w = wl.random_matrix((c.batch * c.H * c.W, c.Cin), dtype, "normal", 5), wl.random_matrix((N, K), dtype, "normal", 6)
+    dx, dw = to_dev(x, dtype), to_dev(w, dtype)
+    plan = B.abft_plan_create([B.Layer(M, N, K, dt, B.B_NK, 0 if c is None else 1, geo, dw.data_ptr(), K)])
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+
+    def run(mode, act, fault=None):
+        C = torch.full((M, N), 77, dtype=t, device=DEV)
+        flag.zero_()
+        B.abft_plan_set_mode(plan, 0, mode)
+        B.abft_plan_set_activation(plan, 0, act)
+        B.abft_plan_set_diagnostics(plan, 0, None, fault)
+        B.abft_plan_run(plan, 0, dx, K, C, N, flag)
+        torch.cuda.synchronize()
+        return C, int(flag.item())
+
+    for mode in (B.NONE, B.THREAD, B.GLOBAL):
+        print("case", name, dtype, mode, flush=True)
+        plain, f0 = run(mode, B.ACT_NONE)
+        act, f1 = run(mode, B.ACT_RELU)
+        assert f0 == 0 and f1 == 0 and bool((plain < 0).any())
+        assert act.equal(torch.where(plain > 0, plain, torch.zeros_like(plain)))
+        i, j = ((plain > 1.02) & (plain < 1.48)).nonzero()[7].tolist()
+        bad, f = run(mode, B.ACT_RELU, B.Fault(i, j, 30, -1))
+        assert f == (mode != B.NONE) and float(bad[i, j]) == 0
+        bad[i, j] = act[i, j]
+        assert bad.equal(act)
+    # sums beyond the range of the output type, and (bf16) of the accumulators, of either sign
+    dx[0] = 0
+    dx[0, 0] = 60000.0 if dtype == "f16" else 3.0e38
+    plain, _ = run(B.NONE, B.ACT_NONE)
+    act, _ = run(B.NONE, B.ACT_RELU)
+    assert bool((plain == float("inf")).any()) and bool((plain == -float("inf")).any())
+    assert act.equal(torch.where(plain > 0, plain, torch.zeros_like(plain)))
+    B.abft_plan_destroy(plan)
