@@ -1058,41 +1058,94 @@ __device__ __forceinline__ void epilogue(typename Mma<CFG::DT, CFG::MI>::Acc (&a
     }
     // ---- store C (rounded to the output type)
     if constexpr (CFG::INTERLEAVED) {
-        // wavefront tiles that lie wholly inside C: a lane's TN adjacent columns at once (the bound on ldc: a lane's
-        // offset, up to twelve rows, in 32 bits beside a base that the wavefront shares)
+        // A lane's TN adjacent columns at once, at whatever address its run of them starts, fewer where N cuts them.  By the
+        // element, TN columns apart from lane to lane, tiles that C cuts and rows at odd addresses wrote a line in pieces (by the
+        // element / so, us; with adjacent lanes on adjacent columns): 4096 x 4001 x 1024 fp16 unprotected 42.5 / 32.7 (36.5), int8, K =
+        // 2048, 49.5 / 35.8 (37.4); ldc = 4097 42.2 / 33.0 (36.7), int8 50 / 36.6 (39.0); thread-level 100352 x 64 x 256 23.6 /
+        // 20.1 (21.4), x 576 38.2 / 34.3 (34.2); 65571 x 60 x 512 21.1 / 18.2 (19.7); 3000 x 390 x 384 9.8 / 9.3 (9.5).  Whole tiles
+        // keep a branch of their own (without it 4096 x 4096 x 1024 32.6 -> 33.4).
         typedef int IntN __attribute__((ext_vector_type(TN)));
+        typedef int Int2 __attribute__((ext_vector_type(2)));
         typedef int HalfN __attribute__((ext_vector_type(TN / 2)));
+        typedef typename std::conditional<CFG::CSIZE == 2, HalfN, IntN>::type Run;
+        typedef typename std::conditional<CFG::CSIZE == 2, int, Int2>::type Pair;
+        typedef typename std::conditional<CFG::CSIZE == 2, short, int>::type One;
+        struct __attribute__((packed, aligned(CFG::CSIZE))) AnyRun { Run v; };
+        struct __attribute__((packed, aligned(CFG::CSIZE))) AnyPair { Pair v; };
+        auto pair = [&](int i, int j, int r) -> Pair {
+            if constexpr (CFG::CSIZE == 2) return pack_out16<CFG::DT>(acc[i][j][r], acc[i][j + 1][r]);
+            else return Int2{acc[i][j][r], acc[i][j + 1][r]};
+        };
+        auto store_run = [&](char* dst, int i, int r) {
+            Run out;
+            if constexpr (CFG::CSIZE == 2) {
+#pragma unroll
+                for (int j = 0; j < TN / 2; ++j) {
+                    if constexpr (TN == 2) out = pair(i, 0, r);
+                    else out[j] = pair(i, 2 * j, r);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) out[j] = acc[i][j][r];
+            }
+            reinterpret_cast<AnyRun*>(dst)->v = out;
+        };
+        // wavefront tiles that lie wholly inside C (the bound on ldc: a lane's offset, up to twelve rows, in 32 bits beside
+        // a base that the wavefront shares)
         const int wave_row0 = __builtin_amdgcn_readfirstlane(tc.bm0 + tc.wave_m * CFG::WM);
         const int wave_col0 = __builtin_amdgcn_readfirstlane(tc.bn0 + tc.wave_n * CFG::WN);
-        const bool whole = CFG::WM <= M - wave_row0 && CFG::WN <= N - wave_col0 && p.ldc % TN == 0 && p.ldc < (1 << 26) &&
-                           (reinterpret_cast<uintptr_t>(p.C) & (TN * CFG::CSIZE - 1)) == 0;
-        if (whole) {
+        const bool rows_whole = CFG::WM <= M - wave_row0 && p.ldc < (1 << 26);
+        auto store_rows = [&]() {
             const long long ldcb = p.ldc * CFG::CSIZE;
             char* const base = p.C + wave_row0 * ldcb + (long long)wave_col0 * CFG::CSIZE;
             const unsigned mine = (unsigned)(4 * tc.lgrp) * (unsigned)ldcb + (unsigned)(tc.lrow * TN * CFG::CSIZE);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int r = 0; r < MMA::NACC; ++r) {
-                    char* const dst = base + (i * MI + 8 * (r >> 2) + (r & 3)) * ldcb;
-                    if constexpr (CFG::CSIZE == 2) {
-                        HalfN out;
-#pragma unroll
-                        for (int j = 0; j < TN / 2; ++j) {
-                            const int pk = pack_out16<CFG::DT>(acc[i][2 * j][r], acc[i][2 * j + 1][r]);
-                            if constexpr (TN == 2) out = pk;
-                            else out[j] = pk;
-                        }
-                        *reinterpret_cast<HalfN*>(dst + mine) = out;
-                    } else {
-                        IntN out;
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) out[j] = acc[i][j][r];
-                        *reinterpret_cast<IntN*>(dst + mine) = out;
-                    }
-                }
+                for (int r = 0; r < MMA::NACC; ++r) store_run(base + (i * MI + 8 * (r >> 2) + (r & 3)) * ldcb + mine, i, r);
+        };
+        if (__builtin_expect(rows_whole && CFG::WN <= N - wave_col0, 1)) {
+            store_rows();
             return;
         }
+        // those that C cuts: the lanes whose columns lie inside C the same way
+        const int left = N - acc_col(0);
+        if (left >= TN) {
+            if (rows_whole) {
+                store_rows();
+            } else {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int r = 0; r < MMA::NACC; ++r) {
+                        const int row = acc_row(i, r);
+                        if (row < M) store_run(p.C + ((long long)row * p.ldc + acc_col(0)) * CFG::CSIZE, i, r);
+                    }
+            }
+        } else if (left > 0) {
+            // N cuts this lane's run: two columns, if there are, and the last of an odd number
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < MMA::NACC; ++r) {
+                    const int row = acc_row(i, r);
+                    if (row >= M) continue;
+                    char* const dst = p.C + ((long long)row * p.ldc + acc_col(0)) * CFG::CSIZE;
+                    Pair last = pair(i, 0, r);
+                    if constexpr (TN == 4) {
+                        if (left & 2) {
+                            reinterpret_cast<AnyPair*>(dst)->v = last;
+                            last = pair(i, 2, r);
+                        }
+                    }
+                    if (left & 1) {
+                        One* const end = reinterpret_cast<One*>(dst) + (left - 1);
+                        if constexpr (CFG::CSIZE == 2) *end = (short)last;
+                        else *end = last[0];
+                    }
+                }
+        }
+        return;
     }
     if constexpr (CFG::CSIZE == 2 && MI == 32 && !CFG::INTERLEAVED) {
         // wavefront tiles that lie wholly inside C: 8-byte stores of four columns per lane

@@ -1,6 +1,6 @@
-"""C's edges, activation and leading dimensions on the tiles whose lanes hold adjacent columns: wavefront tiles that lie wholly inside C
-are stored two or four columns per lane where C's rows start at a multiple of those, all others by the element; nothing
-outside C is written, and a fault lands in the element it names."""
+"""C's edges, activation and leading dimensions on the tiles whose lanes hold adjacent columns: two or four columns per lane
+are stored at once wherever C's rows start, fewer where N cuts them; nothing outside C is written, and a fault lands in the
+element it names."""
 import numpy as np
 import pytest
 import torch
@@ -56,6 +56,39 @@ def test_edges_and_leading_dimensions(name, dtype):
         assert [tuple(x) for x in (C != whole).nonzero().tolist()] == [(i, j)]
     print("tiles", name, seen, flush=True)
     assert name in seen or (dtype == "i8" and name == "R64")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_columns_that_cut_a_lane_s_run(name, dtype):
+    """One, two or three of the columns that a lane holds inside C, rows that end inside its rows, at any alignment of C's
+    rows: what the larger product has there, bit for bit, and nothing written beside it."""
+    M, N, K = CASES[name]
+    N += 4 if name == "R64" else 0    # (more than 128 columns, also when cut)
+    dt = DT[dtype]
+    K = 2 * K if dtype == "i8" else K
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N, dist_a="int8" if dtype == "i8" else "normal",
+                             dist_b="int8" if dtype == "i8" else "normal")
+    dA, dB = to_dev(A, dtype), to_dev(np.ascontiguousarray(Bm.T), dtype)
+    t = {"f16": torch.float16, "bf16": torch.bfloat16, "i8": torch.int32}[dtype]
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    seen = set()
+    for mode in (B.NONE, B.THREAD):
+        ref = torch.zeros((M, N), dtype=t, device=DEV)
+        B.abft_gemm(M, N, K, dA, K, dB, K, B.B_NK, ref, N, dt, mode, fault_flag=flag)
+        for cut, pad, shift in ((1, 0, 0), (2, 3, 1), (3, 0, 3), (3, 6, 2)):
+            m, n = M - 5 * cut, N - cut
+            ldc = n + pad
+            print("case", name, dtype, mode, m, n, K, ldc, shift, flush=True)
+            assert B.abft_kernel_name(m, n, K, dt, mode) == B.abft_kernel_name(M, N, K, dt, mode)
+            seen.add(B.abft_kernel_name(m, n, K, dt, mode))
+            buf = torch.full((m * ldc + 16,), 77, dtype=t, device=DEV)
+            C = buf[shift:shift + m * ldc].view(m, ldc)
+            B.abft_gemm(m, n, K, dA, K, dB, K, B.B_NK, C, ldc, dt, mode, fault_flag=flag)
+            torch.cuda.synchronize()
+            assert C[:, :n].equal(ref[:m, :n]), (mode, cut)
+            assert bool((C[:, n:] == 77).all()) and bool((buf[:shift] == 77).all()) and bool((buf[shift + m * ldc:] == 77).all())
+    assert int(flag.item()) == 0 and (name in seen or (dtype == "i8" and name == "R64"))
 
 
 @pytest.mark.parametrize("shape", [(250, 4000, 256), (70, 3000, 256), (1, 1500, 512), (1900, 2500, 256), (2500, 1900, 256),
