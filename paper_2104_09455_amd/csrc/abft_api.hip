@@ -246,7 +246,8 @@ struct PreArgs {
 };
 
 // Activation checksum alpha_s[k] = sum over the rows m of slab s of A[m][k] (Sec. 2.4
-// step 1), one slab per row block of the product's workgroup tiling.
+// step 1), one slab per row block of the product's workgroup tiling: convolutions, and matrices whose rows are shorter
+// than a 16-byte chunk (the others have the kernel below).
 // Block = 32 chunk columns x 8 row lanes.
 template <int DT>
 __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
@@ -254,6 +255,7 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
     constexpr int EPC = 16 / ESIZE;
     typedef typename std::conditional<DT == DT_I8, long long, double>::type Wide;
     __shared__ Wide red[8][32][EPC];
+    __shared__ Wide alpha_s[32 * EPC];
 
     const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
     const int k0 = (blockIdx.x * 32 + tx) * EPC;
@@ -261,10 +263,46 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
     const int slab = blockIdx.y / subs, sub = blockIdx.y - slab * subs;
     const int row_begin = slab * p.rows_per_slab + sub * p.rows_per_block;
     const int row_end = min(p.M, row_begin + p.rows_per_block);
+    Wide* out = reinterpret_cast<Wide*>(p.alpha_out);
 
-    // per-element filter tap for the implicit-GEMM view (k is fixed per thread)
-    int e_off[EPC], e_kh[EPC], e_kw[EPC];
-    if (p.conv) {
+    if (!p.conv) {
+        // one element per thread and row: thread t takes column t % K and every nrg-th row, so that adjacent lanes
+        // read adjacent elements and the loads of one thread do not wait for each other
+        const int kb = p.K, nrg = 256 / kb, col = tid % kb, rg = tid / kb;
+        Wide* part = &red[0][0][0];
+        Wide acc = 0;
+        if (rg < nrg) {
+            const char* src = p.A + (long long)col * ESIZE;
+            for (int m0 = row_begin + rg; m0 < row_end; m0 += 8 * nrg) {
+                Wide v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int m = m0 + u * nrg;
+                    const int mc = m < row_end ? m : m0;   // a valid row; its value is dropped below
+                    const char* q = src + (long long)mc * p.lda * ESIZE;
+                    Wide x;
+                    if constexpr (DT == DT_F16) x = (double)(float)*reinterpret_cast<const _Float16*>(q);
+                    else if constexpr (DT == DT_BF16) x = (double)(float)*reinterpret_cast<const __bf16*>(q);
+                    else x = (long long)*reinterpret_cast<const signed char*>(q);
+                    v[u] = m < row_end ? x : (Wide)0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc += v[u];
+            }
+        }
+        part[tid] = acc;
+        __syncthreads();
+        for (int k = tid; k < 32 * EPC; k += 256) {
+            Wide a = 0;
+            if (k < kb) {
+                for (int g = 0; g < nrg; ++g) a += part[g * kb + k];
+                if (out) out[k] = a;
+            }
+            alpha_s[k] = a;
+        }
+    } else {
+        // per-element filter tap for the implicit-GEMM view (k is fixed per thread)
+        int e_off[EPC], e_kh[EPC], e_kw[EPC];
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             int k = k0 + e;
@@ -273,73 +311,21 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
             e_kh[e] = tap / p.KW;
             e_kw[e] = tap - e_kh[e] * p.KW;
         }
-    }
-
-    Wide s[EPC];
+        Wide s[EPC];
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) s[e] = 0;
-
-    __shared__ Wide alpha_s[32 * EPC];
-    // Matrices (those whose rows are shorter than a chunk; the others have the kernel below): one element
-    // per thread and row instead.  Thread t takes column t % kb of the kb
-    // columns of a pass and every nrg-th row, so that adjacent lanes read adjacent elements of a
-    // row and the loads of one thread do not wait for each other.
-    const bool by_element = !p.conv;
-    if (by_element) {
-        const int kbase = blockIdx.x * 32 * EPC;
-        const int kb_all = min(32 * EPC, p.K - kbase);   // columns of this block
-        Wide* part = &red[0][0][0];
-        Wide* out = reinterpret_cast<Wide*>(p.alpha_out);
-        for (int c0 = 0; c0 < 32 * EPC; c0 += 256) {     // (int8 blocks span 512 columns: two passes)
-            const int kb = min(256, kb_all - c0);        // columns of this pass; none left: <= 0
-            Wide acc = 0;
-            if (kb > 0) {
-                const int nrg = 256 / kb, col = tid % kb, rg = tid / kb;
-                if (rg < nrg) {
-                    const char* src = p.A + (long long)(kbase + c0 + col) * ESIZE;
-                    for (int m0 = row_begin + rg; m0 < row_end; m0 += 8 * nrg) {
-                        Wide v[8];
+        for (int e = 0; e < EPC; ++e) s[e] = 0;
+        for (int m0 = row_begin + ty; m0 < row_end; m0 += 64) {
+            // int8: up to eight rows are summed in int32 first (exact); fp16 / bf16 values are
+            // widened and added in fp64 one by one, so the checksum side carries no rounding
+            // that could show up in the comparison
+            typename std::conditional<DT == DT_I8, int, double>::type f[EPC];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const int m = m0 + u * nrg;
-                            const int mc = m < row_end ? m : m0;   // a valid row; its value is dropped below
-                            const char* q = src + (long long)mc * p.lda * ESIZE;
-                            Wide x;
-                            if constexpr (DT == DT_F16) x = (double)(float)*reinterpret_cast<const _Float16*>(q);
-                            else if constexpr (DT == DT_BF16) x = (double)(float)*reinterpret_cast<const __bf16*>(q);
-                            else x = (long long)*reinterpret_cast<const signed char*>(q);
-                            v[u] = m < row_end ? x : (Wide)0;
-                        }
+            for (int e = 0; e < EPC; ++e) f[e] = 0;
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) acc += v[u];
-                    }
-                }
-            }
-            part[tid] = acc;
-            __syncthreads();
-            Wide a = 0;
-            if (tid < kb) {
-                const int nrg = 256 / kb;
-                for (int g = 0; g < nrg; ++g) a += part[g * kb + tid];
-                if (out) out[kbase + c0 + tid] = a;
-            }
-            alpha_s[c0 + tid] = a;
-            __syncthreads();
-        }
-    }
-    for (int m0 = row_begin + ty; m0 < row_end && !by_element; m0 += 64) {
-        // int8: up to eight rows are summed in int32 first (exact); fp16 / bf16 values are
-        // widened and added in fp64 one by one, so the checksum side carries no rounding
-        // that could show up in the comparison
-        typename std::conditional<DT == DT_I8, int, double>::type f[EPC];
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) f[e] = 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int m = m0 + 8 * u;
-            if (m >= row_end || k0 >= p.K) continue;
-            i32x4 v = {0, 0, 0, 0};
-            {
+            for (int u = 0; u < 8; ++u) {
+                const int m = m0 + 8 * u;
+                if (m >= row_end || k0 >= p.K) continue;
+                i32x4 v = {0, 0, 0, 0};
                 int img = m / (p.OH * p.OW);
                 int rem = m - img * (p.OH * p.OW);
                 int oh = rem / p.OW, ow = rem - oh * p.OW;
@@ -363,36 +349,33 @@ __global__ __launch_bounds__(256) void act_checksum_kernel(const PreArgs p) {
                         else v[e >> 2] |= (int)(x << (8 * (e & 3)));
                     }
                 }
+                if constexpr (DT == DT_F16) {
+                    f16x8 h = bitcast<f16x8>(v);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) f[e] += (double)(float)h[e];
+                } else if constexpr (DT == DT_BF16) {
+                    bf16x8 h = bitcast<bf16x8>(v);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) f[e] += (double)(float)h[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) f[e] += (int)(signed char)(v[e >> 2] >> (8 * (e & 3)));
+                }
             }
-            if constexpr (DT == DT_F16) {
-                f16x8 h = bitcast<f16x8>(v);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) f[e] += (double)(float)h[e];
-            } else if constexpr (DT == DT_BF16) {
-                bf16x8 h = bitcast<bf16x8>(v);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) f[e] += (double)(float)h[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) f[e] += (int)(signed char)(v[e >> 2] >> (8 * (e & 3)));
-            }
+            for (int e = 0; e < EPC; ++e) s[e] += (Wide)f[e];
         }
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) s[e] += (Wide)f[e];
-    }
-    if (!by_element) {
-#pragma unroll
         for (int e = 0; e < EPC; ++e) red[ty][tx][e] = s[e];
-    }
-    __syncthreads();
-    if (ty == 0 && !by_element) {
-        Wide* out = reinterpret_cast<Wide*>(p.alpha_out);
+        __syncthreads();
+        if (ty == 0) {
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            Wide a = 0;
-            for (int y = 0; y < 8; ++y) a += red[y][tx][e];
-            alpha_s[tx * EPC + e] = (k0 + e < p.K) ? a : (Wide)0;
-            if (out && k0 + e < p.K) out[k0 + e] = a;
+            for (int e = 0; e < EPC; ++e) {
+                Wide a = 0;
+                for (int y = 0; y < 8; ++y) a += red[y][tx][e];
+                alpha_s[tx * EPC + e] = (k0 + e < p.K) ? a : (Wide)0;
+                if (out && k0 + e < p.K) out[k0 + e] = a;
+            }
         }
     }
     if (!p.partial_dots) return;
