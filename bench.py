@@ -514,7 +514,7 @@ def handover_leg(gen, M=2048, widths=(4096, 4096, 4096, 4096, 4096), dtype="f16"
         return best
 
     def brackets():
-        """HIP events right around each layer's product kernel inside the chain (one layer per pass)."""
+        """HIP events right around each layer's product kernel inside the chain (one layer per pass, in a launch of its own)."""
         hip = Hip()
         io = B.PlanIO([rs[0].A] + Cs[:-1], list(widths[:-1]), Cs, ldc)
         out = []
@@ -822,7 +822,8 @@ def main():
     # ---- the timed region: exactly `steps` protected passes, one library call per pass (the
     # library launches every layer's kernels back to back; this is faster than replaying a
     # captured graph of the same pass).  HIP events bracket the dominant layer's GEMM kernel
-    # inside the library, on the stream it is launched on.
+    # inside the library, on the stream it is launched on; a bracketed layer runs in a launch of its own (in a pass
+    # without events it may share one with its neighbours).
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     sp = side.cuda_stream

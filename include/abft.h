@@ -298,7 +298,8 @@ int abft_region_shape(int M, int N, int K, int dtype, int aligned, int *region_m
 int abft_k_ways(int M, int N, int K, int dtype, int aligned, int mode, int *ways, int *step);
 /* Name of the tile configuration a product runs on under `mode` (diagnostics; NULL: a value out of
  * range).  conv != 0: a convolution that is read as an implicit M x K matrix; unprotected ones can
- * run on another configuration than a product of their size. */
+ * run on another configuration than a product of their size.  (Convolutions whose input rows stay in LDS, among them
+ * lowered ones whose name here is that of another tile with the same regions of C, run "R64"'s tiles.) */
 const char *abft_kernel_name(int M, int N, int K, int dtype, int aligned, int mode, int conv);
 
 /* Comparison tolerance (the paper states none; Sec. 2.4 step 4 says "compare").  A comparison
@@ -355,7 +356,9 @@ int abft_plan_run(abft_plan_t *plan, int layer, const void *A, int64_t lda, void
  * writes what another reads or writes: A, B and C of every layer are compared) and run on the same
  * latency-bound tiling may share a kernel launch.
  * event_layer selects the one layer whose product kernel the abft_set_kernel_events hook brackets
- * (-1: none). */
+ * (-1: none).  While a hook is set that layer runs in its place, in a launch of its own, behind all layers before it and
+ * ahead of all after it, so the launches around it are shared differently: what the hook measures is that launch, not
+ * the layer's part in a pass without the hook, and such times do not add up to that pass. */
 int abft_plan_run_all(abft_plan_t *plan, const void *const *A, const int64_t *lda, void *const *C,
                       const int64_t *ldc, uint32_t *fault_flag, int event_layer, void *stream);
 /* Run `count` consecutive layers of the plan, from layer `first`, as a chain (Sec. 2.4 step 4):

@@ -898,6 +898,10 @@ int validate_common(const Problem& pr, int mode, const uint32_t* flag) {
 // kernel (direct-to-LDS configurations) it costs about a tenth of the kernel's time; as a
 // pass of its own over A it costs a launch plus reading A once.  Take the cheaper by estimate
 // (environment variable ABFT_GLOBAL_DOT = fused | pre pins the choice: tuning aid).
+// Unprotected / in the loop / with the pass, us (the estimate takes the faster or one within 3 % of it): 2048 x 4096 x 4096
+// fp16 72 / 80 / 75, bf16 69 / 79 / 72, int8 41 / 45 / 47; 4096 x 4096 x 1024 33 / 37 / 40, 31 / 40 / 39, 26 / 28.5 / 34.7; 4096^3
+// 107 / 119 / 118, 100 / 134 / 114, 60 / 67 / 72; 8192 x 4096 x 4096 int8 117 / 130 / 132; 8192^3 825 / 926 / 852, 787 / 1013 /
+// 814, 443 / 490 / 459; 12544 x 1024 x 512 18.5 / 21.6 / 27, 18 / 22.6 / 26, 22 / 21.5 / 29.
 bool fused_global(const Problem& pr, const CfgInfo& ci) {
     if (!ci.fast) return false;
     if (ci.kways > 1) return true;  // streaming configurations have no other variant
@@ -909,7 +913,7 @@ bool fused_global(const Problem& pr, const CfgInfo& ci) {
     const double t_gemm = 2.0 * pr.M * pr.N * pr.K / (pr.dtype == ABFT_I8 ? 2.0e15 : 1.0e15);
     const double t_pre = 8.0e-6 + (double)pr.M * pr.K * esize(pr.dtype) / 4.5e12;
     // share of the product's time that the in-loop form costs: about a tenth on the 32x32-shape tiles
-    // (matrix-unit form, or vector form on 64 x 64 wavefront tiles) and for int8 everywhere; the vector
+    // (matrix-unit form, or vector form on 64 x 64 wavefront tiles) and for int8 everywhere (9 to 12 %); the vector
     // form of fp16 / bf16 on the 16x16-shape tiles: a tenth for fp16 on the 256 x 256 tile, a quarter for
     // bf16 there (three-piece products), a fifth on the smaller tiles (less work per wavefront to hide it in)
     double in_loop = 0.09;

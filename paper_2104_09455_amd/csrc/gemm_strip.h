@@ -21,7 +21,7 @@
 namespace abft {
 
 // STRIP_RUNS: few channels, p.B in the order (filter row, run of p.strip_seg elements: its KW Cin taps and
-//   zeros up to whole chunks), p.K the whole k tiles of that order; two workgroups per compute unit.
+//   zeros up to whole chunks), p.K the whole k tiles of that order.
 // STRIP_TAPS: a pixel's channels are one k tile (128 bytes).
 template <int FORM>
 struct StripLayout {
