@@ -652,20 +652,20 @@ def tolerance_leg(gen):
             rows.append(tolerance_row(lr, m, label))
         del lr
         torch.cuda.empty_cache()
-    add(wl.Layer("sq64", 64, 64, 64), "f16", "configs[0] 64^3 U[-1,1]", "uniform_pm1", "uniform_pm1", (B.GLOBAL, B.THREAD))
-    add(wl.Layer("sq64", 64, 64, 64), "i8", "configs[0] 64^3 int8", modes=(B.GLOBAL,))
+    add(wl.Layer("sq64", 64, 64, 64), "f16", "64^3 U[-1,1]", "uniform_pm1", "uniform_pm1", (B.GLOBAL, B.THREAD))
+    add(wl.Layer("sq64", 64, 64, 64), "i8", "64^3 int8", modes=(B.GLOBAL,))
     for b in (1, 16, 256):
-        add(wl.dlrm_layers(b)[4], "f16", f"configs[1] DLRM top1 batch {b}")
+        add(wl.dlrm_layers(b)[4], "f16", f"DLRM top1 batch {b}")
     for b in (1, 64):
         layers = wl.resnet50_layers(b)
-        add(layers[0], "f16", f"configs[2] ResNet-50 conv1 batch {b}")
-        add(layers[28], "f16", f"configs[2] ResNet-50 {layers[28].name} batch {b}")
-        add(layers[-2], "f16", f"configs[2] ResNet-50 {layers[-2].name} batch {b}")
+        add(layers[0], "f16", f"ResNet-50 conv1 batch {b}")
+        add(layers[28], "f16", f"ResNet-50 {layers[28].name} batch {b}")
+        add(layers[-2], "f16", f"ResNet-50 {layers[-2].name} batch {b}")
     for n, dts in ((4096, ("f16", "bf16")), (8192, ("f16", "bf16", "i8"))):
         for d in dts:
-            add(wl.Layer(f"sq{n}", n, n, n), d, f"configs[3] {n}^3 N(0,1)", "normal", "normal")
+            add(wl.Layer(f"sq{n}", n, n, n), d, f"{n}^3 N(0,1)", "normal", "normal")
     for m in (1, 256, 512, 8192):
-        add(wl.Layer(f"m{m}", m, 4096, 4096), "f16", f"configs[4] M={m}, N=K=4096 N(0,1)", "normal", "normal")
+        add(wl.Layer(f"m{m}", m, 4096, 4096), "f16", f"M={m}, N=K=4096 N(0,1)", "normal", "normal")
     return rows
 
 
