@@ -366,7 +366,8 @@ int abft_plan_run_all(abft_plan_t *plan, const void *const *A, const int64_t *ld
  * (host arrays, i = 0 .. count - 1) are the layers' outputs, each with the layer's activation
  * function applied and its scheme's checks made on the product.
  * When every layer is fully connected in F16 or BF16 with the same batch M, small enough that a
- * launch of its own would run on 32 x 32 tiles with four wavefronts each (abft_k_ways), weights in ABFT_B_NK
+ * launch of its own would run on 32 x 32 tiles with four wavefronts each (abft_k_ways; more than 16 rows, or scheme
+ * GLOBAL: fewer have a kernel of their own, whose launches are faster), weights in ABFT_B_NK
  * order with 16-byte aligned rows, K a multiple of 64, 16-byte aligned A / C rows, and scheme NONE,
  * GLOBAL or THREAD (and count <= 8), the whole chain runs in ONE kernel launch: the batch is cut into
  * eight slabs of rows, one per die of the GPU, and each die takes its slab through all the layers,

@@ -24,7 +24,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 FLAGS += os.environ.get("ABFT_EXTRA_HIPCC_FLAGS", "").split()   # e.g. -D switches of tuning experiments
 # (the ones that take longest first)
 SOURCES = [f"gemm_{family}_{dt}.hip" for family in ("fast", "generic", "stream", "group") for dt in ("f16", "bf16", "i8")]
-SOURCES += ["gemm_strip_f16.hip", "gemm_strip_bf16.hip", "abft_api.hip"]
+SOURCES += ["gemm_strip_f16.hip", "gemm_strip_bf16.hip", "abft_api.hip"] + [f"gemm_skinny_{dt}.hip" for dt in ("f16", "bf16", "i8")]
 
 
 def _compile(src: str) -> str:

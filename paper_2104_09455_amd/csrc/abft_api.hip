@@ -948,11 +948,31 @@ bool strip_fits(const Problem& pr, int Kp, int segp, int& rows, int& pitch) {
     return true;
 }
 
+// Does the skinny kernel take a product that the tiling `cfg` would take?  At most sixteen rows of 32 x 32 streaming tiles or of
+// the generic kernel's tiles for few rows, both operands contiguous along k in rows of a chunk or more, and at most two
+// workgroups of 16 columns per compute unit.  Injected faults (test hook) land in the accumulators of the tiling itself,
+// and only the global scheme needs its column blocks.  Thread-level, the tiling's kernel / skinny (us, calls of 7 to
+// 7.5 us are the caller's own): 16 x 4096 x 4096 bf16 8.3 / 8.1, 16 x 4096 x 8192 13.1 / 12.8, 12 x 2048 x 8192 11.8 / 9.7,
+// 16 x 64 x 8192 10.5 / 7.9; unaligned 16 x 1000 x 2047 14.9 / 7.1, 16 x 8000 x 4003 25.6 / 16.8, 16 x 64 x 4095 24.8 / 8.2; DLRM's eight
+// layers at batch 1 24.3 / 18.2.  Aligned with more than one workgroup per compute unit and many weights the tiles of 32
+// columns, which read A half as often, are ahead: 16 x 6144 x 2560 8.2 / 8.6, 16 x 8192 x 4096 12.7 / 13.1, 1 x 8192 x 8192 27.7 / 32.
+bool skinny_takes(const Problem& pr, int cfg, int mode) {
+    if (cfg != CFG_S32 && cfg != CFG_S32W && cfg != CFG_G16 && cfg != CFG_G64K) return false;
+    const long long kb = (long long)pr.K * esize(pr.dtype);
+    return pr.M <= SKINNY_ROWS && !pr.conv && pr.b_layout == ABFT_B_NK && mode != ABFT_GLOBAL && mode != ABFT_GLOBAL_WEIGHTED &&
+           kb >= 16 && kb < (1 << 30) && pr.N <= 16 * 512 && (cfg_is_generic(cfg) || pr.N <= 16 * 256 || pr.N * kb <= (16 << 20));
+}
+
+// rows of A or B that do not start at multiples of four bytes
+bool skinny_bytes(const GemmArgs& g, int dt) {
+    return ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B) | (uintptr_t)(g.lda * esize(dt)) | (uintptr_t)(g.ldb * esize(dt))) & 3u) != 0;
+}
+
 // A product ready to be launched
 struct Prepared {
     GemmArgs g;
     int cfg, kmode, dtype;   // kmode: the kernels' scheme index
-    bool inj;
+    bool inj, skinny;
 };
 
 // Everything of a product up to its kernel's launch: checks, tiling, kernel arguments, and the launches that
@@ -1069,6 +1089,7 @@ int prepare_problem(const Problem& pr, int mode, const void* beta, void* workspa
     out.kmode = kmode;
     out.dtype = pr.dtype;
     out.inj = inj;
+    out.skinny = !inj && !g.alpha_out && skinny_takes(pr, cfg, mode);
     return ABFT_OK;
 }
 
@@ -1079,7 +1100,12 @@ int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, 
     if (rc != ABFT_OK) return rc;
     hipError_t e;
     if (g_ev_start && hipEventRecord(g_ev_start, st) != hipSuccess) return ABFT_E_HIP;
-    if (w.dtype == ABFT_F16) e = launch_gemm_f16(w.cfg, w.kmode, w.inj, w.g, st);
+    if (w.skinny) {
+        const int columns = cfg_info_host(w.cfg).wn;
+        e = w.dtype == ABFT_F16    ? launch_skinny_f16(w.kmode, skinny_bytes(w.g, w.dtype), columns, w.g, st)
+            : w.dtype == ABFT_BF16 ? launch_skinny_bf16(w.kmode, skinny_bytes(w.g, w.dtype), columns, w.g, st)
+                                   : launch_skinny_i8(w.kmode, skinny_bytes(w.g, w.dtype), columns, w.g, st);
+    } else if (w.dtype == ABFT_F16) e = launch_gemm_f16(w.cfg, w.kmode, w.inj, w.g, st);
     else if (w.dtype == ABFT_BF16) e = launch_gemm_bf16(w.cfg, w.kmode, w.inj, w.g, st);
     else e = launch_gemm_i8(w.cfg, w.kmode, w.inj, w.g, st);
     if (e != hipSuccess) return ABFT_E_HIP;
@@ -1798,8 +1824,11 @@ struct PassWindow {
     }
 
     // the configuration under which a layer can share a launch, or -1: the streaming kernel on whole
-    // k tiles, with nothing to launch ahead of it
+    // k tiles, with nothing to launch ahead of it; or the skinny kernel
+    static constexpr int SKINNY = CFG_COUNT;
     static int shared_cfg(const abft_plan::Layer& L, const Problem& pr, int mode) {
+        if (pr.M <= SKINNY_ROWS && skinny_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
+            return SKINNY;
         if (!a_vectorisable(pr) || !b_vectorisable(pr) || ((long long)pr.K * esize(pr.dtype)) % 128 != 0) return -1;
         if (pr.conv && conv_lowering(pr).ok) return -1;
         const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, true, mode, pr.conv);
@@ -1839,13 +1868,23 @@ struct PassWindow {
             it.M = g.M; it.N = g.N; it.K = g.K; it.tiles_m = g.tiles_m; it.tiles_n = g.tiles_n; it.act = g.act;
             it.conv = g.conv; it.H = g.H; it.W = g.W; it.Cin = g.Cin; it.KH = g.KH; it.KW = g.KW;
             it.stride = g.stride; it.pad = g.pad; it.OH = g.OH; it.OW = g.OW; it.pix = g.pix;
+            if (slot.cfg == SKINNY) {
+                it.tiles_n = (int)cdiv(g.N, 16);
+                it.bytes = skinny_bytes(g, slot.dtype);
+            }
             a.first[q] = blocks;
-            blocks += g.tiles_m * g.tiles_n;
+            blocks += it.tiles_m * it.tiles_n;
         }
         for (int q = slot.count; q < GROUP_MAX; ++q) a.first[q] = 0x7fffffff;
         a.flag = flag;
         g_shared_launches.fetch_add(1, std::memory_order_relaxed);
         hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+        if (slot.cfg == SKINNY) {
+            const hipError_t e = slot.dtype == ABFT_F16    ? launch_skinny_group_f16(slot.kmode, blocks, a, st)
+                                 : slot.dtype == ABFT_BF16 ? launch_skinny_group_bf16(slot.kmode, blocks, a, st)
+                                                           : launch_skinny_group_i8(slot.kmode, blocks, a, st);
+            return e == hipSuccess ? ABFT_OK : ABFT_E_HIP;
+        }
         const hipError_t e = slot.dtype == ABFT_F16    ? launch_group_f16(slot.cfg, slot.kmode, blocks, a, st)
                              : slot.dtype == ABFT_BF16 ? launch_group_bf16(slot.cfg, slot.kmode, blocks, a, st)
                                                        : launch_group_i8(slot.cfg, slot.kmode, blocks, a, st);
@@ -1941,6 +1980,7 @@ int abft_plan_run_chain(abft_plan_t* plan, int first, int count, const void* A, 
         one_launch = L.chain_beta != nullptr && d.dtype == d0.dtype && d.M == d0.M &&
                      pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode) == CFG_S32 && !L.report && !L.has_fault &&
                      (L.mode == ABFT_NONE || L.mode == ABFT_GLOBAL || L.mode == ABFT_THREAD) && C[i] != nullptr &&
+                     (d.M > SKINNY_ROWS || L.mode == ABFT_GLOBAL) &&   // (else a launch of its own runs on the skinny kernel)
                      aligned16(a_i) && (lda_i * 2) % 16 == 0 && lda_i >= d.K && ldc[i] >= d.N &&
                      (i == 0 || d.K == plan->layers[first + i - 1].desc.N);
         any_check = any_check || L.mode != ABFT_NONE;

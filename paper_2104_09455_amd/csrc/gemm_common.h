@@ -321,6 +321,12 @@ __device__ __forceinline__ i32x4 ld16g(const char* p) {
     return *(const __attribute__((address_space(1))) i32x4*)(const __attribute__((address_space(1))) char*)p;
 }
 
+// 16 bytes shifted down by `bytes` (0 .. 15), zeros at the top
+__device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
+    unsigned __int128 u = bitcast<unsigned __int128>(v);
+    return bitcast<i32x4>(u >> (8 * bytes));
+}
+
 // zeros that stand in for rows beyond the matrix edge and for convolution padding
 __device__ __attribute__((aligned(256))) static const char g_zero_chunk[256] = {0};
 

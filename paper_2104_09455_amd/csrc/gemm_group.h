@@ -11,6 +11,7 @@
 // products and epilogue.
 #pragma once
 #include "gemm_configs.h"
+#include "gemm_skinny.h"
 #include "gemm_stream.h"
 
 namespace abft {
@@ -28,6 +29,7 @@ struct GroupItem {
     double tol_coeff, tol_l1;
     int M, N, K, tiles_m, tiles_n, act;
     int conv, H, W, Cin, KH, KW, stride, pad, OH, OW, pix;
+    int bytes;   // skinny kernel: rows at addresses that are no multiples of four
 };
 
 struct GroupArgs {
@@ -72,9 +74,39 @@ __global__ __launch_bounds__((64 * CfgOf<DT, ID>::KWAYS)) void gemm_group_kernel
     else stream_tile<CFG, NST, KWAYS, MODE, false, false, false, false>(g, tile_m, tile_n, smem);
 }
 
+// Products of at most sixteen rows: the skinny kernel's tile routine, with the loads that each product's rows allow.
+template <int DT, int MODE>
+__global__ __launch_bounds__(64 * SKINNY_WAVES) void gemm_skinny_group_kernel(const GroupArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bid = (int)blockIdx.x;
+    int i = 0;
+#pragma unroll
+    for (int q = 1; q < GROUP_MAX; ++q) i += bid >= a.first[q] ? 1 : 0;
+    const GroupItem& L = a.item[i];
+    GemmArgs g;
+    g.A = L.A; g.B = L.B; g.C = L.C;
+    g.M = L.M; g.N = L.N; g.K = L.K;
+    g.lda = L.lda; g.ldb = L.ldb; g.ldc = L.ldc;
+    g.tol_coeff = L.tol_coeff;
+    g.flag = a.flag; g.report = nullptr;
+    g.act = L.act;
+    int tile_m, tile_n;
+    tile_of_block(bid - a.first[i], 1, L.tiles_n, tile_m, tile_n);
+    if (L.bytes) skinny_tile<DT, 1, MODE, true>(g, tile_n, smem);
+    else skinny_tile<DT, 1, MODE, false>(g, tile_n, smem);
+}
+
 // blocks: workgroups of all products together; mode: MODE_NONE, MODE_GLOBAL or MODE_THREAD
 hipError_t launch_group_f16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 hipError_t launch_group_bf16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 hipError_t launch_group_i8(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+// the skinny kernel: one product (mode: MODE_NONE or wavefront-level; bytes: rows at addresses that are no multiples of four; columns: of the
+// comparisons that a report counts, 16 or 32), several
+hipError_t launch_skinny_f16(int mode, bool bytes, int columns, const GemmArgs& args, hipStream_t stream);
+hipError_t launch_skinny_bf16(int mode, bool bytes, int columns, const GemmArgs& args, hipStream_t stream);
+hipError_t launch_skinny_i8(int mode, bool bytes, int columns, const GemmArgs& args, hipStream_t stream);
+hipError_t launch_skinny_group_f16(int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+hipError_t launch_skinny_group_bf16(int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+hipError_t launch_skinny_group_i8(int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 
 }  // namespace abft

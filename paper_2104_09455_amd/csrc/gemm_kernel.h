@@ -17,12 +17,6 @@
 
 namespace abft {
 
-// 16 bytes shifted down by `bytes` (0 .. 15), zeros at the top
-__device__ __forceinline__ i32x4 shift_down(const i32x4& v, int bytes) {
-    unsigned __int128 u = bitcast<unsigned __int128>(v);
-    return bitcast<i32x4>(u >> (8 * bytes));
-}
-
 // ---------------------------------------------------------------------------
 // The kernel.  KG groups of CFG::THREADS threads each own the whole workgroup tile and take the k
 // tiles t with t % KG == group, each with LDS buffers of its own; at the end the groups' partial

@@ -1,0 +1,79 @@
+"""Products of at most sixteen rows, whose 16-column workgroups share the k loop over sixteen wavefronts: edges of rows,
+columns, k tiles and chunks, rows at any alignment, every wavefront-level scheme, with a report and without."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import DT, c_close, run_gemm
+from paper_2104_09455_amd import binding as B
+from paper_2104_09455_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K in 16-byte chunks, elements more): one chunk, a part of a k tile, one, one per wavefront and one more, the
+# most that is in flight at once, the first loop that runs past it, and by an odd number of tiles
+SHAPES = [(1, 1, 1, 0), (16, 16, 8, 0), (3, 17, 3, 0), (16, 33, 9, 0), (5, 40, 8 * 16, 0), (16, 100, 8 * 17 + 3, 0),
+          (2, 31, 8 * 64, 0), (16, 16, 8 * 129, 0), (7, 70, 8 * 300 + 5, 0),
+          (1, 512, 1, 5), (16, 15, 8, 1), (4, 65, 15, 7), (16, 48, 8 * 16, 3), (9, 33, 8 * 129, 1), (16, 20, 8 * 160 + 7, 7)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_every_scheme_at_the_edges(shape, dtype):
+    M, N, chunks, more = shape
+    K = chunks * (16 if dtype == "i8" else 8) + more
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N, dist_a="uniform_01", dist_b="weights")
+    C_ref = oracle.gemm(A, Bm, dtype)
+    aligned = more == 0
+    ways = {}
+    for mode in (B.NONE, B.THREAD, B.REPLICA, B.THREAD_HALF, B.TWOSIDED):
+        for kw in (dict(), dict(want_report=False), dict(want_report=False, lda_pad=8, ldb_pad=16, ldc_pad=3), dict(misalign=1)):
+            print("case", shape, dtype, mode, kw, flush=True)
+            r = run_gemm(A, Bm, dtype, mode, **kw)
+            assert c_close(r.C, C_ref, dtype) and r.flag == 0
+            if not kw.get("misalign"):
+                ways.setdefault(mode, []).append(r.C)
+            if mode != B.NONE and not kw:
+                tm, tn, _ = B.abft_tile_shape(M, N, K, DT[dtype], aligned)
+                assert r.report.tiles == math.ceil(M / tm) * math.ceil(N / tn) and r.report.worst_ratio == 0.0
+    # one result, whatever the scheme and whether a report is asked for
+    for got in ways.values():
+        assert all(np.array_equal(np.asarray(g).view(np.uint8), np.asarray(ways[B.NONE][0]).view(np.uint8)) for g in got)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K", [64, 1000, 1003])
+def test_what_is_no_number_is_flagged_and_nothing_outside_c_is_touched(K, dtype):
+    import torch
+    t = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    gen = torch.Generator(device="cuda:0").manual_seed(K)
+    M, N, ldc = 9, 41, 50
+    A, W = (torch.randn(s, device="cuda:0", generator=gen).to(t) for s in ((M, K), (N, K)))
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    for value, want in ((None, 0), (float("nan"), 1), (float("inf"), 1), (-3e38 if dtype == "bf16" else -float("inf"), 1)):
+        A2 = A.clone()
+        if value is not None:
+            A2[8, K - 1] = value
+        C = torch.full((M + 2, ldc), 77, dtype=t, device="cuda:0")
+        flag.zero_()
+        B.abft_gemm(M, N, K, A2, K, W, K, B.B_NK, C[1:], ldc, DT[dtype], B.THREAD, fault_flag=flag)
+        torch.cuda.synchronize()
+        assert int(flag.item()) == want, value
+        assert bool((C[0] == 77).all()) and bool((C[M + 1] == 77).all()) and bool((C[:, N:] == 77).all())
+        ref = A2[:8].float() @ W.float().t()
+        assert torch.allclose(C[1:9, :N].float(), ref, rtol=1e-2, atol=1e-2 * float(ref.square().mean().sqrt()))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+def test_layers_of_few_rows_share_a_launch_at_any_alignment(dtype):
+    """Aligned rows, rows of thirteen values and a single column in one launch: bit by bit what they give alone."""
+    import torch
+    from test_gpu_shared_launch import Pass
+    for mode in (B.NONE, B.THREAD):
+        p = Pass(dtype, mode)
+        for M, N, K in ((1, 512, 32), (16, 40, 29), (16, 1, 256), (7, 1024, 1040), (3, 96, 4096), (16, 33, 8400)):
+            p.add((M, N, K), p.rnd(M, K), p.out(M, N, pad=N % 3), relu=N == 40)
+        p.both_ways(shared=1)
+    assert torch.cuda.is_available()
