@@ -89,6 +89,7 @@ __global__ __launch_bounds__(64 * SKINNY_WAVES) void gemm_skinny_group_kernel(co
     g.lda = L.lda; g.ldb = L.ldb; g.ldc = L.ldc;
     g.tol_coeff = L.tol_coeff;
     g.flag = a.flag; g.report = nullptr;
+    g.f_row = -1;
     g.act = L.act;
     int tile_m, tile_n;
     tile_of_block(bid - a.first[i], 1, L.tiles_n, tile_m, tile_n);

@@ -171,6 +171,21 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
             if constexpr (CHECKED) w += red[((KW + q) * TN + wave) * 64 + lane];
         }
         const int col = n0 + 16 * wave + lrow;
+        if (p.f_row >= 0) {
+            // test hook: a flipped bit in a finished sum, p.n_parts == 4 and f_kt == -1 in that of the share of four (k
+            // tiles t % 4) that holds the last k tile
+            const bool mine = col == p.f_col && (p.f_row >> 2) == lgrp;
+            static_assert(KW == 8, "a share of four is two of eight");
+            const int last = (nkt - 1) & 3;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const AccT part = red[(last * TN + wave) * 64 + lane][r] + red[((last + 4) * TN + wave) * 64 + lane][r];
+                const bool share = p.n_parts == 4 && p.f_kt == -1;
+                const unsigned mask = mine && (p.f_row & 3) == r ? 1u << p.f_bit : 0u;
+                const AccT flipped = bitcast<AccT>(bitcast<unsigned>(share ? part : v[r]) ^ mask);
+                if (mask) v[r] = share ? v[r] - part + flipped : flipped;
+            }
+        }
         if (col < N) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
