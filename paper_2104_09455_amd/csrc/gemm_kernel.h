@@ -25,7 +25,11 @@ namespace abft {
 // since the other loaders' registers and branches cost such products a fifth (4000 x 4000 x 1000 fp16
 // unprotected 74 us, so 59; int8 thread-level, K = 4016, 283 / 199; 5 x 5 convolution 40 -> 120 on 100352 rows 76 / 53).
 // ROWS: both contiguous along k, at any alignment; TURN: A so, weights K x N.  These two know their loaders at compile
-// time, and load without a condition per lane (rows outside read the zeros).
+// time; a load is a base that the wavefront shares and 32 bits per lane, without a condition (what lies outside reads the
+// last row or chunk that is inside and becomes zeros on the way to LDS, in the tiles that have such).  64-bit products per
+// load, a condition each, and the loads behind the products / so, thread-level fp16, weights K x N, us: 2048 x 4096 x 4096
+// 113 / 97, 1900 x 4000 x 4000 121 / 115, 16 x 4096 x 4096 25.6 / 21.5, 1 x 1024 x 1024 8.5 / 7.2; 2000 x 600 x 4090 60 / 58.  (Two or three k
+// tiles on their way in registers: 511 x 1000 x 2047 15.4 -> 16.5, 17.5: the tiles read past the end cost more.)
 // ---------------------------------------------------------------------------
 enum { LD_ANY = 0, LD_VEC = 1, LD_ROWS = 2, LD_TURN = 3 };
 template <class CFG, int MODE, bool INJ, bool CONV, int KG, int LD>
@@ -103,16 +107,17 @@ void gemm_kernel(const GemmArgs p) {
     // rows read 16 bytes at a time at any alignment: a chunk that K cuts short is read as the last 16
     // bytes of its row and shifted down when it goes to LDS
     constexpr bool VEC = LD == LD_VEC, STREAM = LD >= LD_ROWS;
+    constexpr bool ROWS = LD == LD_ROWS;
     static_assert(!STREAM || !CONV, "matrices only");
     const bool a_vec = VEC || (!STREAM && p.a_vec), b_vec = VEC || (!STREAM && p.b_vec);
-    const bool a_row = STREAM || (!CONV && !a_vec && K >= EPC);
-    const bool b_row = LD == LD_ROWS || (LD != LD_TURN && !b_vec && p.b_sk == 1 && K >= EPC);
+    const bool a_row = !STREAM && (!CONV && !a_vec && K >= EPC);
+    const bool b_row = !STREAM && !b_vec && p.b_sk == 1 && K >= EPC;
     // weights stored K x N: units of eight k times four bytes of n (four bytes of a row end inside it)
     constexpr int NPD = 4 / ESIZE;                     // columns per four bytes
     constexpr int NGN = BN / NPD;                      // such groups per row of the tile
     constexpr int UNITS = NB / 2;                      // units per thread
     static_assert(NB % 2 == 0 && CFG::THREADS * UNITS == NGN * (BK / 8), "units of the transposing loader");
-    const bool b_turn = LD == LD_TURN || (!STREAM && !b_vec && !b_row && p.b_sn == 1 && N >= NPD);
+    const bool b_turn = !STREAM && !b_vec && !b_row && p.b_sn == 1 && N >= NPD;
     auto load_a = [&](int kt, i32x4(&regs)[NA]) {
         const int k0 = kt * BK + kc * EPC;  // first k of this thread's chunk
         if constexpr (!CONV) {
@@ -121,13 +126,9 @@ void gemm_kernel(const GemmArgs p) {
 #pragma unroll
                 for (int t = 0; t < NA; ++t) {
                     const int m = bm0 + r0 + t * RPP;
-                    if constexpr (STREAM) {
-                        regs[t] = ld16u(m < M && k0 < K ? p.A + ((long long)m * p.lda + ks) * ESIZE : g_zero_chunk);
-                    } else {
-                        i32x4 v = {0, 0, 0, 0};
-                        if (m < M && k0 < K) v = ld16u(p.A + ((long long)m * p.lda + ks) * ESIZE);
-                        regs[t] = v;
-                    }
+                    i32x4 v = {0, 0, 0, 0};
+                    if (m < M && k0 < K) v = ld16u(p.A + ((long long)m * p.lda + ks) * ESIZE);
+                    regs[t] = v;
                 }
             } else if (a_vec) {
 #pragma unroll
@@ -222,13 +223,9 @@ void gemm_kernel(const GemmArgs p) {
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 const int n = bn0 + r0 + t * RPP;
-                if constexpr (STREAM) {
-                    regs[t] = ld16u(n < N && k0 < K ? p.B + ((long long)n * p.ldb + ks) * ESIZE : g_zero_chunk);
-                } else {
-                    i32x4 v = {0, 0, 0, 0};
-                    if (n < N && k0 < K) v = ld16u(p.B + ((long long)n * p.ldb + ks) * ESIZE);
-                    regs[t] = v;
-                }
+                i32x4 v = {0, 0, 0, 0};
+                if (n < N && k0 < K) v = ld16u(p.B + ((long long)n * p.ldb + ks) * ESIZE);
+                regs[t] = v;
             }
         } else if (b_turn) {
             // (rows past K and columns past N read valid elements, dropped on the way to LDS)
@@ -260,6 +257,51 @@ void gemm_kernel(const GemmArgs p) {
             }
         }
     };
+    // units of the transposing loader, turned on the way to LDS
+    auto store_turned = [&](char* bs, int kt, const i32x4(&rb)[NB]) {
+        const bool cut = (kt + 1) * BK > K;
+        const bool edge = cut || bn0 + BN > N;
+#pragma unroll
+        for (int t = 0; t < UNITS; ++t) {
+            const int u = tid + t * CFG::THREADS, nl = (u % NGN) * NPD, kl = (u / NGN) * 8;
+            unsigned d[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d[e] = (unsigned)rb[2 * t + (e >> 2)][e & 3];
+            if (edge) {
+                const int over = bn0 + nl + NPD - N;   // columns of the group beyond N (read early by as many)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (over > 0) d[e] = over >= NPD ? 0u : d[e] >> (8 * ESIZE * over);
+                    if (kt * BK + kl + e >= K) d[e] = 0u;
+                }
+            }
+            if constexpr (ESIZE == 2) {
+                i32x4 c0, c1;   // eight k of column nl, of column nl + 1
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    c0[q] = (int)__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u);
+                    c1[q] = (int)__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u);
+                }
+                *reinterpret_cast<i32x4*>(bs + nl * STRIDE + kl * 2) = c0;
+                *reinterpret_cast<i32x4*>(bs + (nl + 1) * STRIDE + kl * 2) = c1;
+            } else {
+                i32x2 c[4];     // eight k of each of four columns
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const unsigned x01 = __builtin_amdgcn_perm(d[4 * h + 1], d[4 * h], 0x05010400u);
+                    const unsigned x23 = __builtin_amdgcn_perm(d[4 * h + 3], d[4 * h + 2], 0x05010400u);
+                    const unsigned y01 = __builtin_amdgcn_perm(d[4 * h + 1], d[4 * h], 0x07030602u);
+                    const unsigned y23 = __builtin_amdgcn_perm(d[4 * h + 3], d[4 * h + 2], 0x07030602u);
+                    c[0][h] = (int)__builtin_amdgcn_perm(x23, x01, 0x05040100u);
+                    c[1][h] = (int)__builtin_amdgcn_perm(x23, x01, 0x07060302u);
+                    c[2][h] = (int)__builtin_amdgcn_perm(y23, y01, 0x05040100u);
+                    c[3][h] = (int)__builtin_amdgcn_perm(y23, y01, 0x07060302u);
+                }
+#pragma unroll
+                for (int n = 0; n < 4; ++n) *reinterpret_cast<i32x2*>(bs + (nl + n) * STRIDE + kl) = c[n];
+            }
+        }
+    };
     auto store_tiles = [&](int buf, int kt, const i32x4(&ra)[NA], const i32x4(&rb)[NB]) {
         char* as = smem + buf * CFG::STAGE_BYTES;
         char* bs = as + BM * STRIDE;
@@ -277,47 +319,7 @@ void gemm_kernel(const GemmArgs p) {
                 *reinterpret_cast<i32x4*>(as + (r0 + t * RPP) * STRIDE + kc * 16) = ra[t];
         }
         if (b_turn) {
-            const bool edge = cut || bn0 + BN > N;
-#pragma unroll
-            for (int t = 0; t < UNITS; ++t) {
-                const int u = tid + t * CFG::THREADS, nl = (u % NGN) * NPD, kl = (u / NGN) * 8;
-                unsigned d[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) d[e] = (unsigned)rb[2 * t + (e >> 2)][e & 3];
-                if (edge) {
-                    const int over = bn0 + nl + NPD - N;   // columns of the group beyond N (read early by as many)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        if (over > 0) d[e] = over >= NPD ? 0u : d[e] >> (8 * ESIZE * over);
-                        if (kt * BK + kl + e >= K) d[e] = 0u;
-                    }
-                }
-                if constexpr (ESIZE == 2) {
-                    i32x4 c0, c1;   // eight k of column nl, of column nl + 1
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        c0[q] = (int)__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u);
-                        c1[q] = (int)__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u);
-                    }
-                    *reinterpret_cast<i32x4*>(bs + nl * STRIDE + kl * 2) = c0;
-                    *reinterpret_cast<i32x4*>(bs + (nl + 1) * STRIDE + kl * 2) = c1;
-                } else {
-                    i32x2 c[4];     // eight k of each of four columns
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const unsigned x01 = __builtin_amdgcn_perm(d[4 * h + 1], d[4 * h], 0x05010400u);
-                        const unsigned x23 = __builtin_amdgcn_perm(d[4 * h + 3], d[4 * h + 2], 0x05010400u);
-                        const unsigned y01 = __builtin_amdgcn_perm(d[4 * h + 1], d[4 * h], 0x07030602u);
-                        const unsigned y23 = __builtin_amdgcn_perm(d[4 * h + 3], d[4 * h + 2], 0x07030602u);
-                        c[0][h] = (int)__builtin_amdgcn_perm(x23, x01, 0x05040100u);
-                        c[1][h] = (int)__builtin_amdgcn_perm(x23, x01, 0x07060302u);
-                        c[2][h] = (int)__builtin_amdgcn_perm(y23, y01, 0x05040100u);
-                        c[3][h] = (int)__builtin_amdgcn_perm(y23, y01, 0x07060302u);
-                    }
-#pragma unroll
-                    for (int n = 0; n < 4; ++n) *reinterpret_cast<i32x2*>(bs + (nl + n) * STRIDE + kl) = c[n];
-                }
-            }
+            store_turned(bs, kt, rb);
         } else if (b_row && cut) {
 #pragma unroll
             for (int t = 0; t < NB; ++t)
@@ -326,6 +328,78 @@ void gemm_kernel(const GemmArgs p) {
 #pragma unroll
             for (int t = 0; t < NB; ++t)
                 *reinterpret_cast<i32x4*>(bs + (r0 + t * RPP) * STRIDE + kc * 16) = rb[t];
+        }
+    };
+
+    // ---- ROWS and TURN: bases that the workgroup shares, this thread's rows as offsets from them
+    const unsigned kb = (unsigned)K * ESIZE, lda_b = (unsigned)(p.lda * ESIZE), ldb_b = (unsigned)(p.ldb * ESIZE);
+    const char* const a_base = p.A + (long long)bm0 * p.lda * ESIZE;
+    const char* const b_base = ROWS ? p.B + (long long)bn0 * p.ldb * ESIZE : p.B;
+    unsigned a_off[NA], b_off[ROWS ? NB : UNITS], b_col[ROWS ? 1 : UNITS];
+    if constexpr (STREAM) {
+#pragma unroll
+        for (int t = 0; t < NA; ++t) a_off[t] = (unsigned)min(r0 + t * RPP, M - 1 - bm0) * lda_b;
+        if constexpr (ROWS) {
+#pragma unroll
+            for (int t = 0; t < NB; ++t) b_off[t] = (unsigned)min(r0 + t * RPP, N - 1 - bn0) * ldb_b;
+        } else {
+#pragma unroll
+            for (int t = 0; t < UNITS; ++t) {
+                const int u = tid + t * CFG::THREADS;
+                b_col[t] = (unsigned)(min(bn0 + (u % NGN) * NPD, N - NPD) * ESIZE);
+                b_off[t] = (unsigned)((u / NGN) * 8) * ldb_b + b_col[t];
+            }
+        }
+    }
+    auto chunk_from = [&](int kt) { return min((unsigned)kt * BKB + (unsigned)kc * 16, kb - 16); };   // the byte of its row
+    auto stream_load = [&](int kt, i32x4(&ra)[NA], i32x4(&rb)[NB]) {
+        const unsigned from = chunk_from(kt);
+#pragma unroll
+        for (int t = 0; t < NA; ++t) ra[t] = ld16u(a_base + (a_off[t] + from));
+        if constexpr (ROWS) {
+#pragma unroll
+            for (int t = 0; t < NB; ++t) rb[t] = ld16u(b_base + (b_off[t] + from));
+        } else {
+            // (rows past K read the last one, dropped on the way to LDS)
+#pragma unroll
+            for (int t = 0; t < UNITS; ++t) {
+                const unsigned first = (unsigned)(min(kt, nkt - 1) * BK) * ldb_b + b_off[t];
+                const unsigned last = (unsigned)(K - 1) * ldb_b + b_col[t];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) rb[2 * t + (e >> 2)][e & 3] = ld4u(b_base + min(first + e * ldb_b, last));
+            }
+        }
+    };
+    auto stream_store = [&](int buf, int kt, i32x4(&ra)[NA], i32x4(&rb)[NB]) {
+        char* as = smem + buf * CFG::STAGE_BYTES;
+        char* bs = as + BM * STRIDE;
+        const unsigned from = chunk_from(kt);
+        const i32x4 zero = {0, 0, 0, 0};
+        if ((kt + 1) * BK > K) {
+            // (a chunk that K cuts was read early by so many bytes; one beyond K counts as zeros)
+            const int early = (int)((unsigned)kt * BKB + (unsigned)kc * 16 - from);
+#pragma unroll
+            for (int t = 0; t < NA; ++t) ra[t] = early < 16 ? shift_down(ra[t], early) : zero;
+            if constexpr (ROWS) {
+#pragma unroll
+                for (int t = 0; t < NB; ++t) rb[t] = early < 16 ? shift_down(rb[t], early) : zero;
+            }
+        }
+        if (bm0 + BM > M) {
+#pragma unroll
+            for (int t = 0; t < NA; ++t) ra[t] = bm0 + r0 + t * RPP < M ? ra[t] : zero;
+        }
+#pragma unroll
+        for (int t = 0; t < NA; ++t) *reinterpret_cast<i32x4*>(as + (r0 + t * RPP) * STRIDE + kc * 16) = ra[t];
+        if constexpr (ROWS) {
+            if (bn0 + BN > N) {
+#pragma unroll
+                for (int t = 0; t < NB; ++t) rb[t] = bn0 + r0 + t * RPP < N ? rb[t] : zero;
+            }
+#pragma unroll
+            for (int t = 0; t < NB; ++t) *reinterpret_cast<i32x4*>(bs + (r0 + t * RPP) * STRIDE + kc * 16) = rb[t];
+        } else {
+            store_turned(bs, kt, rb);
         }
     };
 
@@ -360,34 +434,30 @@ void gemm_kernel(const GemmArgs p) {
             if constexpr (mode_is_wave_level(MODE)) check_step<CFG, MODE>(a, b, chk);
         }
     };
-    i32x4 ra[NA], rb[NB];
     // (every group goes through the same number of steps: they share the workgroup's barrier)
     const int nsteps = (nkt + KG - 1) / KG;
-    if (grp < nkt) {
-        load_a(grp, ra);
-        load_b(grp, rb);
-        store_tiles(0, grp, ra, rb);
-    }
+    i32x4 ra[NA], rb[NB];
     if constexpr (STREAM) {
         static_assert(!INJ, "injected faults go through the other loaders");
-        // step s: the products of the group's tile s (LDS buffer s % 2); tile s + 1 moves from registers to LDS, and the
-        // loads of tile s + 2 go out, a step and a half before they are waited for
-        if (grp + KG < nkt) {
-            load_a(grp + KG, ra);
-            load_b(grp + KG, rb);
-        }
+        // step s: tile s + 1 of the group moves from registers to LDS, the loads of tile s + 2 go out, the products of tile s
+        // (LDS buffer s % 2) run while they are on their way
+        stream_load(grp, ra, rb);
+        if (grp < nkt) stream_store(0, grp, ra, rb);
+        stream_load(grp + KG, ra, rb);
         __syncthreads();
         for (int s = 0; s < nsteps; ++s) {
             const int kt = s * KG + grp;
+            if (kt + KG < nkt) stream_store((s & 1) ^ 1, kt + KG, ra, rb);
+            if (kt + 2 * KG < nkt) stream_load(kt + 2 * KG, ra, rb);
             if (KG == 1 || kt < nkt) multiply(s & 1);
-            if (kt + KG < nkt) store_tiles((s & 1) ^ 1, kt + KG, ra, rb);
-            if (kt + 2 * KG < nkt) {
-                load_a(kt + 2 * KG, ra);
-                load_b(kt + 2 * KG, rb);
-            }
             __syncthreads();
         }
     } else {
+        if (grp < nkt) {
+            load_a(grp, ra);
+            load_b(grp, rb);
+            store_tiles(0, grp, ra, rb);
+        }
         __syncthreads();
 
         for (int s = 0; s < nsteps; ++s) {

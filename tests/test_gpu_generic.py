@@ -134,3 +134,29 @@ def test_unaligned_operands_take_the_general_path_s_results(shape, layout, dtype
             same = bad.C == r.C
             same[i, j] = True
             assert same.all() and bad.flag == (mode != B.NONE), mode
+
+
+# the four-group tile in halves of 32 rows (at most 128 tiles of 64 x 64): rows that fill one half, both, a half and one row;
+# the first grid that is no longer halved
+HALVES = [(32, 64, 1100), (33, 65, 705), (64, 130, 1024), (97, 70, 4001), (1024, 512, 520), (1025, 512, 520)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("layout", [B.B_NK, B.B_KN], ids=["nk", "kn"])
+@pytest.mark.parametrize("shape", HALVES, ids=str)
+def test_halved_tiles_keep_the_four_group_tile_s_results_and_comparisons(shape, layout, dtype):
+    """Bit for bit what a planted fault's call, on whole tiles, stores everywhere but at the fault; as many comparisons."""
+    M, N, K = shape
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N, dist_a="normal", dist_b="normal")
+    rows = sample_rows(M, 200)
+    C_ref = oracle.gemm(A[rows], Bm, dtype)
+    for mode in (B.NONE, B.THREAD, B.REPLICA):
+        print("case", shape, layout, dtype, mode, flush=True)
+        assert B.abft_kernel_name(M, N, K, DT[dtype], mode, False) == "G64K"
+        r = run_gemm(A, Bm, dtype, mode, layout=layout, misalign=1)
+        assert c_close(r.C[rows], C_ref, dtype) and r.flag == 0
+        assert mode == B.NONE or (r.report.tiles == -(-M // 32) * -(-N // 32) and r.report.worst_ratio < 0.5)
+        bad = run_gemm(A, Bm, dtype, mode, layout=layout, misalign=1, inject=B.Fault(M - 1, N - 1, 30, -2))
+        same = bad.C == r.C
+        same[M - 1, N - 1] = True
+        assert same.all() and bad.flag == (mode != B.NONE)
