@@ -1747,6 +1747,7 @@ struct PassWindow {
     struct Slot {
         int depth;
         int cfg, kmode, dtype;    // of a launch that can take more layers; cfg < 0: one layer, by itself
+        int stages;               // direct-to-LDS kernel: the k tiles that LDS holds at a time
         int count;
         int entry[GROUP_MAX];
     };
@@ -1808,32 +1809,45 @@ struct PassWindow {
         e.depth = 0;
         for (int j = 0; j < n_entries; ++j) {
             const Entry& o = entries[j];
-            if (o.depth >= e.depth && (e.in.meets(o.out) || e.out.meets(o.out) || e.out.meets(o.in) || e.weights.meets(o.out) || e.out.meets(o.weights)))
-                e.depth = o.depth + 1;
+            if (o.depth >= e.depth && ordered(e, o)) e.depth = o.depth + 1;
         }
-        const int cfg = shared_cfg(L, pr, mode);
+        const int cfg = shared_cfg(i, pr, mode);
+        const int stages = cfg >= 0 && cfg < CFG_COUNT && !cfg_is_stream(cfg) ? (int)std::min(cdiv(pr.K * es, 128), 3LL) : 0;
         int s = n_slots;
         if (cfg >= 0) {
             s = 0;
             while (s < n_slots && !(slots[s].depth == e.depth && slots[s].cfg == cfg && slots[s].kmode == mode && slots[s].dtype == d.dtype &&
-                                    slots[s].count < GROUP_MAX))
+                                    slots[s].stages == stages && slots[s].count < GROUP_MAX))
                 ++s;
         }
-        if (s == n_slots) slots[n_slots++] = Slot{e.depth, cfg, mode, d.dtype, 0, {}};
+        if (s == n_slots) slots[n_slots++] = Slot{e.depth, cfg, mode, d.dtype, stages, 0, {}};
         slots[s].entry[slots[s].count++] = n_entries;
         ++n_entries;
         return ABFT_OK;
     }
 
-    // the configuration under which a layer can share a launch, or -1: the streaming kernel on whole
-    // k tiles, with nothing to launch ahead of it; or the skinny kernel
+    // does one of two layers have to wait for the other?
+    static bool ordered(const Entry& e, const Entry& o) {
+        return e.in.meets(o.out) || e.out.meets(o.out) || e.out.meets(o.in) || e.weights.meets(o.out) || e.out.meets(o.weights);
+    }
+
+    // the configuration under which layer i can share a launch, or -1: the streaming kernel on whole
+    // k tiles, with nothing to launch ahead of it; the skinny kernel; or the direct-to-LDS kernel's tiles of 32 x 128 per
+    // wavefront, unprotected or thread-level, for matrices of at most 512 tiles (beyond two rounds of workgroups a launch
+    // of its own is full) that leave no activation checksums to the layer behind them
     static constexpr int SKINNY = CFG_COUNT;
-    static int shared_cfg(const abft_plan::Layer& L, const Problem& pr, int mode) {
+    int shared_cfg(int i, const Problem& pr, int mode) const {
+        const abft_plan::Layer& L = plan->layers[i];
         if (pr.M <= SKINNY_ROWS && skinny_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
             return SKINNY;
         if (!a_vectorisable(pr) || !b_vectorisable(pr) || ((long long)pr.K * esize(pr.dtype)) % 128 != 0) return -1;
         if (pr.conv && conv_lowering(pr).ok) return -1;
         const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, true, mode, pr.conv);
+        if (cfg == CFG_F64T || cfg == CFG_F128T) {
+            const CfgInfo ci = cfg_info_host(cfg);
+            const bool hands_over = i + 1 < (int)plan->layers.size() && A[i + 1] == C[i] && lda[i + 1] == ldc[i] && handover_target(plan, i + 1, C[i], ldc[i]);
+            return mode == ABFT_GLOBAL || pr.conv || hands_over || cdiv(pr.M, ci.bm) * cdiv(pr.N, ci.bn) > 512 ? -1 : cfg;
+        }
         if (!cfg_is_stream(cfg) || (mode == ABFT_GLOBAL && !layer_beta(L, pr))) return -1;
         return cfg;
     }
@@ -1893,13 +1907,36 @@ struct PassWindow {
         return e == hipSuccess ? ABFT_OK : ABFT_E_HIP;
     }
 
+    // A layer that would go out alone joins a later launch of its kind if nothing that goes out until then waits for it
+    // (ResNet-50 at batch 1: a downsampling of 64 -> 256 channels, 4 to 5 us by itself, with the three expansions of its stage)
+    void join_later(Slot& lone) {
+        Entry& e = entries[lone.entry[0]];
+        for (int s = 0; s < n_slots; ++s) {
+            Slot& to = slots[s];
+            if (to.depth <= lone.depth || to.count == 0 || to.count == GROUP_MAX || to.cfg != lone.cfg || to.kmode != lone.kmode ||
+                to.dtype != lone.dtype || to.stages != lone.stages)
+                continue;
+            bool free = true;
+            for (int j = 0; j < n_entries && free; ++j)
+                free = entries[j].depth <= lone.depth || entries[j].depth > to.depth || !ordered(e, entries[j]);
+            if (!free) continue;
+            e.depth = to.depth;
+            to.entry[to.count++] = lone.entry[0];
+            lone.count = 0;
+            return;
+        }
+    }
+
     // what has been added so far goes out; the window is empty again and starts behind it
     int flush() {
         int rc = ABFT_OK;
+        for (int s = 0; s < n_slots; ++s)
+            if (slots[s].count == 1 && slots[s].cfg >= 0) join_later(slots[s]);
         for (int depth = 0, left = n_slots; left > 0 && rc == ABFT_OK; ++depth)
             for (int s = 0; s < n_slots && rc == ABFT_OK; ++s)
                 if (slots[s].depth == depth) {
                     --left;
+                    if (slots[s].count == 0) continue;
                     rc = slots[s].count > 1 ? launch_shared(slots[s]) : run_now(entries[slots[s].entry[0]].layer);
                 }
         advance(n_entries);

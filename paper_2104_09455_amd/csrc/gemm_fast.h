@@ -55,9 +55,9 @@ struct FastLayout {
     static_assert((NSTAGE - 2) * (NQA + NQB) <= 63, "vmcnt range");
 };
 
+// One output tile, by all threads of the workgroup; bid: the workgroup's index among those of the product.
 template <class CFG, int NSTAGE, int MODE, bool INJ, bool CONV>
-__global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(INJ ? 1 : min_waves_per_simd<CFG, MODE>())))
-void gemm_fast_kernel(const GemmArgs p) {
+__device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem) {
     typedef FastLayout<CFG, NSTAGE> LAY;
     constexpr int DT = CFG::DT;
     constexpr int MI = CFG::MI;
@@ -91,14 +91,12 @@ void gemm_fast_kernel(const GemmArgs p) {
     constexpr int EMODE = (MODE == MODE_GLOBAL_PRE || FED) ? MODE_GLOBAL : MODE;  // the epilogue's scheme
     constexpr bool IS_INT = DT == DT_I8;
 
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_m = wave / CFG::WAVES_N, wave_n = wave % CFG::WAVES_N;
 
     int tile_m, tile_n;
-    tile_of_block((int)blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
+    tile_of_block(bid, p.tiles_m, p.tiles_n, tile_m, tile_n);
     const int bm0 = tile_m * BM, bn0 = tile_n * BN;
     const int M = p.M, N = p.N;
     const int nkt = p.K / BK;
@@ -567,6 +565,13 @@ void gemm_fast_kernel(const GemmArgs p) {
         }
     }
     epilogue<CFG, EMODE>(acc, chk, p, tile_m, tile_n, smem, true, -1, (GDOT || FED) ? &dot.total : nullptr, epi);
+}
+
+template <class CFG, int NSTAGE, int MODE, bool INJ, bool CONV>
+__global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(INJ ? 1 : min_waves_per_simd<CFG, MODE>())))
+void gemm_fast_kernel(const GemmArgs p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    fast_tile<CFG, NSTAGE, MODE, INJ, CONV>(p, (int)blockIdx.x, smem);
 }
 
 }  // namespace abft

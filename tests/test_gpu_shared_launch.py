@@ -232,3 +232,32 @@ def test_captured_into_a_graph():
         torch.cuda.synchronize()
         assert all(torch.equal(x[2], w) for x, w in zip(p.io, want)) and int(flag.item()) == 0
     B.abft_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("dtype,shape,name", [("f16", (3136, 256, 64), "F64T"), ("bf16", (3101, 250, 64), "F64T"), ("i8", (3136, 256, 128), "F64T"),
+                                              ("f16", (12544, 256, 64), "F128T"), ("bf16", (6272, 256, 128), "F64T")])
+@pytest.mark.parametrize("mode", [B.NONE, B.GLOBAL, B.THREAD])
+def test_direct_to_lds_tiles_share_a_launch(mode, dtype, shape, name):
+    """Two at once; one that waits for a later one of its kind; one that cannot, since a layer in between reads what it leaves."""
+    M, N, K = shape
+    if mode == B.THREAD:
+        assert B.abft_kernel_name(M, N, K, DT[dtype], mode) == name
+    takes = mode != B.GLOBAL and B.abft_kernel_name(M, N, K, DT[dtype], mode) == name
+    p = Pass(dtype, mode)
+    for rep in range(2):
+        p.add(shape, p.rnd(M, K), p.out(M, N, pad=2 * rep), relu=rep == 1)
+    p.both_ways(shared=1 if takes else 0)
+
+    def later(reads):
+        p = Pass(dtype, mode)
+        first, x, y = p.out(M, N), p.out(M, K), p.out(M, 40)
+        p.add(shape, p.rnd(M, K), first)
+        p.add((M, K, K), p.rnd(M, K), x)
+        if reads:
+            p.add((M, 40, N), first, y)
+            p.add((M, K, 40), y, x)
+        p.add(shape, x, p.out(M, N))
+        return p
+    if dtype != "i8":
+        later(False).both_ways(shared=1 if takes else None)
+        later(True).both_ways()
