@@ -1835,17 +1835,26 @@ struct PassWindow {
     // k tiles, with nothing to launch ahead of it; the skinny kernel; or the direct-to-LDS kernel's tiles of 32 x 128 per
     // wavefront, unprotected or thread-level, for matrices of at most 512 tiles (beyond two rounds of workgroups a launch
     // of its own is full) that leave no activation checksums to the layer behind them
-    static constexpr int SKINNY = CFG_COUNT;
+    static constexpr int SKINNY = CFG_COUNT, SHALLOW = CFG_COUNT + 1;
+    // ... or, in a launch of the streaming kernel with four wavefronts, a product of one 64 x 64 generic tile's k: rows contiguous along k,
+    // of 16 to 128 bytes, at any address
+    static bool shallow(const Problem& pr, int mode) {
+        const long long kb = (long long)pr.K * esize(pr.dtype);
+        return (mode == ABFT_NONE || mode == ABFT_THREAD) && !pr.conv && pr.b_layout == ABFT_B_NK && kb >= 16 && kb <= 128 &&
+               pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode) == CFG_G64;
+    }
+    static bool takes_shallow(int cfg) { return cfg == CFG_S32 || cfg == CFG_S64 || cfg == CFG_S128; }
     int shared_cfg(int i, const Problem& pr, int mode) const {
         const abft_plan::Layer& L = plan->layers[i];
         if (pr.M <= SKINNY_ROWS && skinny_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
             return SKINNY;
+        const bool hands_over = i + 1 < (int)plan->layers.size() && A[i + 1] == C[i] && lda[i + 1] == ldc[i] && handover_target(plan, i + 1, C[i], ldc[i]);
+        if (shallow(pr, mode)) return hands_over ? -1 : (int)SHALLOW;
         if (!a_vectorisable(pr) || !b_vectorisable(pr) || ((long long)pr.K * esize(pr.dtype)) % 128 != 0) return -1;
         if (pr.conv && conv_lowering(pr).ok) return -1;
         const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, true, mode, pr.conv);
         if (cfg == CFG_F64T || cfg == CFG_F128T) {
             const CfgInfo ci = cfg_info_host(cfg);
-            const bool hands_over = i + 1 < (int)plan->layers.size() && A[i + 1] == C[i] && lda[i + 1] == ldc[i] && handover_target(plan, i + 1, C[i], ldc[i]);
             return mode == ABFT_GLOBAL || pr.conv || hands_over || cdiv(pr.M, ci.bm) * cdiv(pr.N, ci.bn) > 512 ? -1 : cfg;
         }
         if (!cfg_is_stream(cfg) || (mode == ABFT_GLOBAL && !layer_beta(L, pr))) return -1;
@@ -1884,6 +1893,7 @@ struct PassWindow {
             it.M = g.M; it.N = g.N; it.K = g.K; it.tiles_m = g.tiles_m; it.tiles_n = g.tiles_n; it.act = g.act;
             it.conv = g.conv; it.H = g.H; it.W = g.W; it.Cin = g.Cin; it.KH = g.KH; it.KW = g.KW;
             it.stride = g.stride; it.pad = g.pad; it.OH = g.OH; it.OW = g.OW; it.pix = g.pix;
+            it.shallow = w.cfg == CFG_G64;
             if (slot.cfg == SKINNY) {
                 it.tiles_n = (int)cdiv(g.N, 16);
                 it.bytes = skinny_bytes(g, slot.dtype);
@@ -1907,14 +1917,14 @@ struct PassWindow {
         return e == hipSuccess ? ABFT_OK : ABFT_E_HIP;
     }
 
-    // A layer that would go out alone joins a later launch of its kind if nothing that goes out until then waits for it
+    // A layer that would go out alone joins a launch that takes it, now or a later one of its kind, if nothing that goes out until then waits for it
     // (ResNet-50 at batch 1: a downsampling of 64 -> 256 channels, 4 to 5 us by itself, with the three expansions of its stage)
-    void join_later(Slot& lone) {
+    void join(Slot& lone) {
         Entry& e = entries[lone.entry[0]];
         for (int s = 0; s < n_slots; ++s) {
             Slot& to = slots[s];
-            if (to.depth <= lone.depth || to.count == 0 || to.count == GROUP_MAX || to.cfg != lone.cfg || to.kmode != lone.kmode ||
-                to.dtype != lone.dtype || to.stages != lone.stages)
+            if (&to == &lone || to.depth < lone.depth || to.count == 0 || to.count == GROUP_MAX || to.kmode != lone.kmode || to.dtype != lone.dtype ||
+                !(lone.cfg == SHALLOW ? takes_shallow(to.cfg) : to.cfg == lone.cfg && to.stages == lone.stages))
                 continue;
             bool free = true;
             for (int j = 0; j < n_entries && free; ++j)
@@ -1931,13 +1941,17 @@ struct PassWindow {
     int flush() {
         int rc = ABFT_OK;
         for (int s = 0; s < n_slots; ++s)
-            if (slots[s].count == 1 && slots[s].cfg >= 0) join_later(slots[s]);
+            if (slots[s].count == 1 && slots[s].cfg >= 0) join(slots[s]);
         for (int depth = 0, left = n_slots; left > 0 && rc == ABFT_OK; ++depth)
             for (int s = 0; s < n_slots && rc == ABFT_OK; ++s)
                 if (slots[s].depth == depth) {
                     --left;
                     if (slots[s].count == 0) continue;
-                    rc = slots[s].count > 1 ? launch_shared(slots[s]) : run_now(entries[slots[s].entry[0]].layer);
+                    if (slots[s].count == 1 || slots[s].cfg == SHALLOW) {
+                        for (int q = 0; q < slots[s].count && rc == ABFT_OK; ++q) rc = run_now(entries[slots[s].entry[q]].layer);
+                    } else {
+                        rc = launch_shared(slots[s]);
+                    }
                 }
         advance(n_entries);
         n_entries = n_slots = 0;

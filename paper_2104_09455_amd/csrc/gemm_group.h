@@ -31,6 +31,7 @@ struct GroupItem {
     int M, N, K, tiles_m, tiles_n, act;
     int conv, H, W, Cin, KH, KW, stride, pad, OH, OW, pix;
     int bytes;   // skinny kernel: rows at addresses that are no multiples of four
+    int shallow; // streaming kernel's launches: a product for shallow_tile
 };
 
 struct GroupArgs {
@@ -41,7 +42,7 @@ struct GroupArgs {
 static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments");
 
 // The product that workgroup bid works on; bid becomes its index among that product's workgroups.
-__device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid) {
+__device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, bool* shallow = nullptr) {
     int i = 0;
 #pragma unroll
     for (int q = 1; q < GROUP_MAX; ++q) i += bid >= a.first[q] ? 1 : 0;
@@ -66,7 +67,59 @@ __device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid) 
     g.tiles_m = L.tiles_m; g.tiles_n = L.tiles_n;
     g.act = L.act;
     g.alpha_out = nullptr; g.ld_alpha_out = 0; g.alpha_in = nullptr;
+    if (shallow) *shallow = L.shallow != 0;
     return g;
+}
+
+// A 64 x 64 tile of a product whose k ends within one k tile (16 to 128 bytes of k, rows at any address): the generic kernel's
+// tile for such products, every wavefront with its 32 x 32 MFMA block straight from memory, in registers, since no wavefront
+// reads a row of A or B more than one other does.  Bound: the latency of one load.  DLRM's first layer (K = 13) so goes out
+// with the first of the other MLP, which takes 32 workgroups beside 256: batch 256 27.0 -> 23.6 us a pass (five launches instead of six).
+template <int DT, int MODE>
+__device__ __forceinline__ void shallow_tile(const GemmArgs& p, int tile_m, int tile_n, char* smem) {
+    typedef typename CfgOf<DT, CFG_G64>::type CFG;
+    typedef Mma<DT, 32> MMA;
+    static_assert(CFG::TM == 1 && CFG::TN == 1 && CFG::MI == 32 && !CFG::INTERLEAVED, "one MFMA block per wavefront");
+    static_assert(MODE == MODE_NONE || MODE == MODE_THREAD, "nothing is compared across wavefronts");
+    constexpr int ES = CFG::ESIZE;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = tile_m * CFG::BM + wave / CFG::WAVES_N * 32 + (lane & 31);
+    const int n = tile_n * CFG::BN + wave % CFG::WAVES_N * 32 + (lane & 31);
+    const int kb = p.K * ES;
+    // (rows outside A and B: another row's address, and zeros in its place)
+    const char* const a = p.A + (long long)min(m, p.M - 1) * p.lda * ES;
+    const char* const b = p.B + (long long)min(n, p.N - 1) * p.ldb * ES;
+    const i32x4 zero = {0, 0, 0, 0};
+    // the chunk at byte c of a row: one that K cuts short is the row's last 16 bytes shifted down, one beyond K zeros
+    i32x4 va[4], vb[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const int off = min(32 * kk + 16 * (lane >> 5), kb - 16);
+        va[kk] = vb[kk] = zero;
+        if (32 * kk < kb) {
+            va[kk] = ld16u(a + off);
+            vb[kk] = ld16u(b + off);
+        }
+    }
+    typename MMA::Acc acc[1][1], chk[CheckRegs<CFG, MODE>::N];
+#pragma unroll
+    for (int r = 0; r < MMA::NACC; ++r) acc[0][0][r] = 0;
+    clear_check<CFG, MODE, true>(chk);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        if (32 * kk >= kb) break;
+        const int c = 32 * kk + 16 * (lane >> 5), early = c - min(c, kb - 16);
+        i32x4 fa[1] = {va[kk]}, fb[1] = {vb[kk]};
+        if (32 * kk + 32 > kb) {
+            fa[0] = early < 16 ? shift_down(fa[0], early & 15) : zero;
+            fb[0] = early < 16 ? shift_down(fb[0], early & 15) : zero;
+        }
+        fa[0] = m < p.M ? fa[0] : zero;
+        fb[0] = n < p.N ? fb[0] : zero;
+        acc[0][0] = MMA::run(fa[0], fb[0], acc[0][0]);
+        if constexpr (MODE == MODE_THREAD) check_step<CFG, MODE>(fa, fb, chk);
+    }
+    epilogue<CFG, MODE>(acc, chk, p, tile_m, tile_n, smem);
 }
 
 template <int DT, int ID, int NST, int MODE>
@@ -75,9 +128,16 @@ __global__ __launch_bounds__((64 * CfgOf<DT, ID>::KWAYS)) void gemm_group_kernel
     constexpr int KWAYS = CfgOf<DT, ID>::KWAYS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int bid = (int)blockIdx.x;
-    const GemmArgs g = group_product(a, bid);
+    bool shallow;
+    const GemmArgs g = group_product(a, bid, &shallow);
     int tile_m, tile_n;
     tile_of_block(bid, g.tiles_m, g.tiles_n, tile_m, tile_n);
+    if constexpr (KWAYS == 4 && MODE != MODE_GLOBAL) {
+        if (shallow) {
+            shallow_tile<DT, MODE>(g, tile_m, tile_n, smem);
+            return;
+        }
+    }
     if (g.conv) stream_tile<CFG, NST, KWAYS, MODE, false, true, false, false>(g, tile_m, tile_n, smem);
     else stream_tile<CFG, NST, KWAYS, MODE, false, false, false, false>(g, tile_m, tile_n, smem);
 }
