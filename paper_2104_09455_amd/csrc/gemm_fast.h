@@ -43,11 +43,11 @@ struct FastLayout {
     static constexpr int EPI_BYTES = 512;
     static constexpr int LDS_BYTES = NSTAGE * STAGE + EPI_BYTES;
     // Activation checksums handed over by the layer before travel in runs of 256 floats, four k
-    // tiles at a time, through a ring of two 1 KB slots per wavefront (its 32-row block's sums) behind the stages
-    // and, with them, 256 floats of the column block's weight checksums through one such ring for the
+    // tiles at a time, through 1 KB per wavefront (its 32-row block's sums) behind the stages
+    // and, with them, 256 floats of the column block's weight checksums through 1 KB for the
     // workgroup (a quarter of the copies that a record per k tile would take)
-    static constexpr int RING_A = NSTAGE * STAGE, RING_B = RING_A + WAVES * 2048;
-    static constexpr int LDS_BYTES_FED = RING_B + 2048 + EPI_BYTES;
+    static constexpr int FED_A = NSTAGE * STAGE, FED_B = FED_A + WAVES * 1024;
+    static constexpr int LDS_BYTES_FED = FED_B + 1024 + EPI_BYTES;
     static constexpr int NQA = CFG::BM / (8 * WAVES);           // 1 KB copies per wave per k tile
     static constexpr int NQB = CFG::BN / (8 * WAVES);
     static_assert(CFG::BM % (8 * WAVES) == 0 && CFG::BN % (8 * WAVES) == 0, "tile rows vs waves");
@@ -101,8 +101,8 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
     const int M = p.M, N = p.N;
     const int nkt = p.K / BK;
     // scratch of the global scheme's epilogue: behind the stages this launch asked for (a k loop
-    // shorter than the pipeline gets no more) or behind the rings of the handed-over sums
-    char* const epi = smem + (FED ? LAY::RING_B + 2048 : (nkt < NSTAGE ? (nkt < 1 ? 1 : nkt) : NSTAGE) * STAGE);
+    // shorter than the pipeline gets no more) or behind the handed-over sums
+    char* const epi = smem + (FED ? LAY::FED_B + 1024 : (nkt < NSTAGE ? (nkt < 1 ? 1 : nkt) : NSTAGE) * STAGE);
     if constexpr (EMODE == MODE_GLOBAL) {
         if (tid == 0) *reinterpret_cast<unsigned*>(epi + 256) = 0u;  // the ticket counter; the barrier after the prologue publishes it
     }
@@ -159,10 +159,11 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
     int rec_turn = 0;  // the wavefront that copies the next record
     if constexpr (BREC) beta_rec = p.beta_r + (long long)tile_n * nkt * 1024 + lane * 16;
     // Handed-over activation checksums.  Group g = k tiles 4 g .. 4 g + 3 = floats 256 g .. 256 g + 255 of
-    // this wavefront's row of sums (lane l copies floats 4 l .. 4 l + 3 of the group) and, by wavefront 0
-    // for everyone, of the column block's weight checksums; group g sits in
-    // slot g % 2 and is copied while group g - 1 is in use.  These copies are older than the operand
-    // copies any later wait counts on, so every such wait covers them too.
+    // this wavefront's row of sums and, by wavefront 0 for everyone, of the column block's weight checksums: lane l
+    // copies floats 4 l .. 4 l + 3 of the group to where it reads them again, one product for each.  The copies go out behind the barrier of tile 4 g - 1,
+    // ahead of that tile's operand copies, so that every wait from tile 4 g on covers them; they are read behind the barrier of
+    // tile 4 g + 2 and so make room before the next group's.  (Two groups in LDS, each lane with a product per k tile, took the 256 x 128 tile's
+    // third stage: four layers of 2048 x 4096 x 4096 bf16 291 us, so 270.)
     const char* fed_alpha = nullptr;
     const char* fed_beta = nullptr;
     // (a row of wavefronts per block: one of them takes it, chosen so that the takers sit on different
@@ -180,13 +181,11 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
             const bool in_k = f0 + 4 <= p.K;                   // (K is a multiple of 64: whole lanes)
             const char* src = (fed_alpha && in_k) ? fed_alpha + (long long)f0 * 4 : zero;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(smem + LAY::RING_A + (wave * 2 + (g & 1)) * 1024),
-                                             16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(smem + LAY::FED_A + wave * 1024), 16, 0, 0);
             if (wave == 0) {
                 const char* srcb = in_k ? fed_beta + (long long)f0 * 4 : zero;
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)srcb,
-                                                 (__attribute__((address_space(3))) void*)(smem + LAY::RING_B + (g & 1) * 1024),
-                                                 16, 0, 0);
+                                                 (__attribute__((address_space(3))) void*)(smem + LAY::FED_B), 16, 0, 0);
             }
         }
     };
@@ -281,19 +280,24 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
     // the MFMAs.  Per k tile the fp32 / int32 partial sums move into a wide accumulator.
     const int beta_off = LAY::AB_STAGE + (IS_INT ? ckc * 16 : 256 + ckc * 32);  // this lane's k chunk in the record
     ChecksumDot<DT> dot;
-    float fed_a = 0.f, fed_b = 0.f;
-    auto fed_tile = [&](const char* st, int kt) {
+    i32x4 fed_a = {0, 0, 0, 0}, fed_b = {0, 0, 0, 0};
+    auto read_group = [&]() {
+        fed_a = *reinterpret_cast<const i32x4*>(smem + LAY::FED_A + wave * 1024 + lane * 16);
+        fed_b = *reinterpret_cast<const i32x4*>(smem + LAY::FED_B + lane * 16);
+    };
+    auto use_group = [&]() {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot.total += (double)bitcast<float>((int)fed_a[e]) * (double)bitcast<float>((int)fed_b[e]);
+    };
+    // behind the barrier of tile kt (the products a tile behind the reads, which have long landed)
+    auto fed_step = [&](int kt) {
         if constexpr (FED) {
             if (!fed_on) return;
-            // lane l: (column sum of the wavefront's 32 rows at k = l of the tile) x (weight checksum
-            // there); the product is taken one tile later, when the two reads have long landed
-            dot.total += (double)fed_a * (double)fed_b;
-            const int off = ((kt >> 2) & 1) * 1024 + ((kt & 3) * 64 + lane) * 4;
-            fed_a = *reinterpret_cast<const float*>(smem + LAY::RING_A + wave * 2048 + off);
-            fed_b = *reinterpret_cast<const float*>(smem + LAY::RING_B + off);
-            // the slot of the group before is free (everyone read its last tile before the barrier
-            // of that tile): the next group goes there
-            if ((kt & 3) == 0 && kt >= 4 && 4 * ((kt >> 2) + 1) < nkt) issue_group((kt >> 2) + 1);
+            if ((kt & 3) == 2) read_group();
+            if ((kt & 3) == 3) {
+                use_group();
+                issue_group((kt >> 2) + 1);
+            }
         }
     };
     auto dot_tile = [&](const char* st) {
@@ -361,10 +365,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
     // copies per wave per tile (the one more of the wavefront whose turn it is to copy the record makes
     // its waits at most one copy stricter than needed)
     constexpr int NL = NQA + NQB;
-    if constexpr (FED) {
-        issue_group(0);
-        if (nkt > 4) issue_group(1);
-    }
+    if constexpr (FED) issue_group(0);
 #pragma unroll
     for (int t = 0; t < NSTAGE; ++t) {
         if (t < nkt) {
@@ -382,7 +383,6 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
         constexpr int CUR = decltype(cur_c)::value;
         const char* st = smem + stage * STAGE;
         dot_tile(st);
-        fed_tile(st, kt);
         {
 #pragma unroll
             for (int kk = 0; kk < 3; ++kk) {
@@ -425,6 +425,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
             if (kt + NSTAGE < nkt) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * NL) & ~0x0F00);
             else __builtin_amdgcn_s_waitcnt(0x0070);  // tail: vmcnt(0) lgkmcnt(0)
             __syncthreads();
+            fed_step(kt);
             if (kt + NSTAGE < nkt) {
                 advance();
                 issue_loads(stage);
@@ -446,7 +447,6 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
     // 2 x 12).  The barrier sits between the two steps, as in the 32x32 form.
     auto tile_step16 = [&](int kt) {
         const char* st = smem + stage * STAGE;
-        fed_tile(st, kt);
         i32x4 b0 = {0, 0, 0, 0}, b1 = {0, 0, 0, 0};
         if constexpr (VDOT) {
             b0 = *reinterpret_cast<const i32x4*>(st + beta_off);
@@ -504,6 +504,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
             if (kt + NSTAGE < nkt) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * NL) & ~0x0F00);
             else __builtin_amdgcn_s_waitcnt(0x0070);  // tail: vmcnt(0) lgkmcnt(0)
             __syncthreads();
+            fed_step(kt);
             if (kt + NSTAGE < nkt) {
                 advance();
                 issue_loads(stage);
@@ -535,7 +536,15 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
         // a fault in the finished accumulator
         if (p.f_kt < 0) inject_fault<CFG>(acc, p, TileCoords<CFG>(tile_m, tile_n));
     }
-    if constexpr (FED) dot.total += (double)fed_a * (double)fed_b;  // the last tile's
+    if constexpr (FED) {
+        // the last group: read in the loop, if it is whole
+        if (nkt & 3) {
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+            __syncthreads();
+            if (fed_on) read_group();
+        }
+        if (fed_on) use_group();
+    }
     if constexpr (MDOT16) {
         // this lane's share of the dot product: column 0 / 1 of the extra block holds A . (low / high digits)
         int g_lo = 0, g_hi = 0;

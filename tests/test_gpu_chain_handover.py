@@ -406,3 +406,37 @@ def test_handover_between_layers_on_the_256x256_tile(dtype, M, region):
     finally:
         B.abft_plan_set_diagnostics(ch.plan, 1)
         ch.close()
+
+
+@pytest.mark.parametrize("M,width,name", [(100000, 64, "F256S"), (65500, 128, "F128"), (65536, 192, "F256W"), (65536, 256, "F256W"), (16384, 320, "F128"),
+                                          (16384, 384, "F256N"), (16384, 448, "F256N"), (16300, 512, "F256N"), (8192, 576, "F256N"),
+                                          (65536, 576, "F256W"), (8192, 192, "F128"), (4090, 192, "F64T")])
+def test_handed_over_sums_at_every_length_of_the_last_group_of_k_tiles(M, width, name):
+    """Sums travel four k tiles at a time: k loops of one to nine tiles.  Same C and, within the fp32 roundings of the
+    handed-over sums, the same right-hand side of the comparison as the layer run alone; a planted fault is seen."""
+    import torch
+    from gpu_util import read_report
+    assert B.abft_kernel_name(M, width, width, B.F16, B.GLOBAL) == name
+    ch = Chain(M, [width] * 3, "f16", seed=1700, modes=[B.GLOBAL] * 2)
+    try:
+        reps = _reports(ch)
+        _, dx = ch.input(seed=1701)
+        before = B.abft_handover_launches()
+        ch.run(dx)
+        torch.cuda.synchronize()
+        assert B.abft_handover_launches() - before == 1 and int(ch.flag.item()) == 0
+        chained, got = ch.Cs[1].clone(), read_report(reps[1])
+        reps[1].zero_()
+        B.abft_plan_run(ch.plan, 1, ch.Cs[0], width, ch.Cs[1], width, ch.flag)
+        torch.cuda.synchronize()
+        alone = read_report(reps[1])
+        assert torch.equal(ch.Cs[1], chained) and int(ch.flag.item()) == 0
+        assert got.tiles == alone.tiles and got.worst_ratio < 0.5
+        if alone.region == got.region:
+            assert alone.lhs == got.lhs and abs(alone.rhs - got.rhs) <= 0.1 * alone.tau
+        B.abft_plan_set_diagnostics(ch.plan, 1, report=reps[1], inject=B.Fault(M - 3, width - 5, 30, -1))
+        ch.run(dx)
+        torch.cuda.synchronize()
+        assert int(ch.flag.item()) == 1
+    finally:
+        ch.close()
