@@ -28,6 +28,19 @@ namespace abft {
 // vmcnt(n) with expcnt / lgkmcnt left open (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
+// The workgroup's barrier among copies in flight: what a wavefront has read from LDS or written there is done, the copies it waits
+// for itself, by their number.  Ahead of __syncthreads() the compiler waits for all copies, at the first such barrier or at every one:
+// the prologue held every wavefront until its last stage had landed (global, two runs each in turn, us: 2048 x 4096 x 4096 bf16
+// 74.3-75.3 -> 72.2-73.2, 2048^3 fp16 25.9-26.3 -> 25.2-25.4, 1024 x 4096 x 4096 50.2-51.4 -> 49.8-50.0; four layers of 2048 x 4096 x 4096
+// with handed-over sums 270.3 -> 268.5).  Unprotected the late start costs nothing (1024 x 4096 x 4096 43.6-44.3 against
+// 44.6-45.1, others level), with two stages neither (int8 4096^3 global 68.0 / 68.2), and around the instruction the compiler moves the reads of the loops that are not hand-placed (32x32
+// shapes) together (third-stage block of 64 images 71.0 -> 72.2).
+template <class CFG, int NSTAGE, int MODE>
+__device__ __forceinline__ void copies_barrier() {
+    if constexpr (CFG::MI == 16 && NSTAGE > 2 && MODE != MODE_NONE) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else __syncthreads();
+}
+
 template <class CFG, int NSTAGE>
 struct FastLayout {
     static constexpr int ROWB = 128;                            // bytes per LDS row
@@ -375,7 +388,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
     }
     if (nkt >= NSTAGE) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 1) * NL));  // tile 0 has landed
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __syncthreads();
+    copies_barrier<CFG, NSTAGE, MODE>();
     int stage = 0;
     // one k tile; CUR is the fragment buffer that holds the step multiplied after the barrier
     // (a compile-time constant, so that the fragment arrays stay in registers)
@@ -424,7 +437,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
             // every wave is done reading this stage, which the copies of tile kt+NSTAGE overwrite
             if (kt + NSTAGE < nkt) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * NL) & ~0x0F00);
             else __builtin_amdgcn_s_waitcnt(0x0070);  // tail: vmcnt(0) lgkmcnt(0)
-            __syncthreads();
+            copies_barrier<CFG, NSTAGE, MODE>();
             fed_step(kt);
             if (kt + NSTAGE < nkt) {
                 advance();
@@ -503,7 +516,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs& p, int bid, char* smem
         if (kt + 1 < nkt) {
             if (kt + NSTAGE < nkt) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * NL) & ~0x0F00);
             else __builtin_amdgcn_s_waitcnt(0x0070);  // tail: vmcnt(0) lgkmcnt(0)
-            __syncthreads();
+            copies_barrier<CFG, NSTAGE, MODE>();
             fed_step(kt);
             if (kt + NSTAGE < nkt) {
                 advance();
