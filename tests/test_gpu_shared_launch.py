@@ -239,16 +239,26 @@ def test_captured_into_a_graph():
 def test_products_of_one_k_tile_at_any_address_beside_streaming_ones(mode, dtype):
     """k of 16 to 128 bytes: whole and cut chunks and k steps, tiles that C cuts, with and without a launch that takes them."""
     elements = (9, 13, 15, 17, 33, 47, 63) if dtype != "i8" else (17, 19, 33, 65, 97, 113, 127)
-    for host in (None, KINDS["S32"], KINDS["S64"], KINDS["S128"]):
-        p = Pass(dtype, mode)
-        for i, K in enumerate(elements):
-            M, N = (17, 64, 65, 250)[i % 4], (1, 31, 64, 100, 130)[i % 5]
+    for i, K in enumerate(elements):
+        for h, host in enumerate((None, KINDS["S32"], KINDS["S64"], KINDS["S128"])):
+            M, N = (17, 64, 65, 250)[(i + h) % 4], (1, 31, 64, 100, 130)[(i + 2 * h) % 5]
             assert B.abft_kernel_name(M, N, K, DT[dtype], mode, False) == "G64"
+            p = Pass(dtype, mode, seed=K)
             p.add((M, N, K), p.rnd(M, K), p.out(M, N, pad=i % 3), relu=i % 2 == 0)
-        for _ in range(2 if host else 0):
-            M, N, K = host[0], host[1], host[2] * (2 if dtype == "i8" else 1)
-            p.add((M, N, K), p.rnd(M, K), p.out(M, N))
-        p.both_ways(shared=1 if host else 0)
+            if host:
+                m, n, k = host[0], host[1], host[2] * (2 if dtype == "i8" else 1)
+                p.add((m, n, k), p.rnd(m, k), p.out(m, n))
+            p.both_ways(shared=1 if host else 0)
+    # one that waits for the only launch of its depth's kind, and one whose output that launch reads
+    K = elements[2]
+    p = Pass(dtype, mode)
+    k = 512 if dtype == "i8" else 256
+    x = p.out(64, k)
+    p.add((64, k, K), p.rnd(64, K), x)
+    p.add((64, 96, k), x, p.out(64, 96))
+    p.both_ways(shared=0)
+    p.add((33, 50, K), p.rnd(33, K), p.out(33, 50))
+    p.both_ways(shared=0)   # (two of them at one depth, none with a launch to join)
 
 
 @pytest.mark.parametrize("dtype,shape,name", [("f16", (3136, 256, 64), "F64T"), ("bf16", (3101, 250, 64), "F64T"), ("i8", (3136, 256, 128), "F64T"),
