@@ -950,8 +950,7 @@ bool strip_fits(const Problem& pr, int Kp, int segp, int& rows, int& pitch) {
 
 // Does the skinny kernel take a product that the tiling `cfg` would take?  At most sixteen rows of 32 x 32 streaming tiles or of
 // the generic kernel's tiles for few rows, both operands contiguous along k in rows of a chunk or more, and at most two
-// workgroups of 16 columns per compute unit.  Faults injected into running sums (test hook) land in the accumulators of the
-// tiling itself, and only the global scheme needs its column blocks.  Thread-level, the tiling's kernel / skinny (us, calls of 7 to
+// workgroups of 16 columns per compute unit; only the global scheme needs the tiling's column blocks.  Thread-level, the tiling's kernel / skinny (us, calls of 7 to
 // 7.5 us are the caller's own): 16 x 4096 x 4096 bf16 8.3 / 8.1, 16 x 4096 x 8192 13.1 / 12.8, 12 x 2048 x 8192 11.8 / 9.7,
 // 16 x 64 x 8192 10.5 / 7.9; unaligned 16 x 1000 x 2047 14.9 / 7.1, 16 x 8000 x 4003 25.6 / 16.8, 16 x 64 x 4095 24.8 / 8.2; DLRM's eight
 // layers at batch 1 24.3 / 18.2.  Aligned with more than one workgroup per compute unit and many weights the tiles of 32
@@ -1089,9 +1088,13 @@ int prepare_problem(const Problem& pr, int mode, const void* beta, void* workspa
     out.kmode = kmode;
     out.dtype = pr.dtype;
     out.inj = inj;
-    // (the generic kernel's loaders store the same whether a fault is planted or not: one in a finished sum stays here)
-    out.skinny = (!inj || (cfg_is_generic(cfg) && g.f_kt < 0)) && !g.alpha_out && skinny_takes(pr, cfg, mode);
-    if (out.skinny) g.n_parts = ci.kways;
+    out.skinny = !g.alpha_out && skinny_takes(pr, cfg, mode);
+    if (out.skinny) {
+        // (its k tiles are of 128 bytes; a planted fault lands in the share of the tiling's shares that it names)
+        if (g.f_kt >= 0) g.f_kt = (g.f_kt + 1) * (ci.bk_bytes / 128) - 1;
+        if (g.f_kt == -1 && ci.kways == 1) g.f_kt = -2;
+        g.n_parts = ci.kways;
+    }
     return ABFT_OK;
 }
 

@@ -169,19 +169,18 @@ __global__ __launch_bounds__(64 * SKINNY_WAVES) void gemm_skinny_group_kernel(co
     g.lda = L.lda; g.ldb = L.ldb; g.ldc = L.ldc;
     g.tol_coeff = L.tol_coeff;
     g.flag = a.flag; g.report = nullptr;
-    g.f_row = -1;
     g.act = L.act;
     int tile_m, tile_n;
     tile_of_block(bid - a.first[i], 1, L.tiles_n, tile_m, tile_n);
-    if (L.bytes) skinny_tile<DT, 1, MODE, true>(g, tile_n, smem);
-    else skinny_tile<DT, 1, MODE, false>(g, tile_n, smem);
+    if (L.bytes) skinny_tile<DT, 1, MODE, true, false>(g, tile_n, smem);
+    else skinny_tile<DT, 1, MODE, false, false>(g, tile_n, smem);
 }
 
 // blocks: workgroups of all products together; mode: MODE_NONE, MODE_GLOBAL or MODE_THREAD (direct-to-LDS kernel: not MODE_GLOBAL)
 hipError_t launch_group_f16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 hipError_t launch_group_bf16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 hipError_t launch_group_i8(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
-// the skinny kernel: one product (mode: MODE_NONE or wavefront-level; bytes: rows at addresses that are no multiples of four; columns: of the
+// the skinny kernel: one product (mode: MODE_NONE or wavefront-level; args.f_row >= 0: with a planted fault; bytes: rows at addresses that are no multiples of four; columns: of the
 // comparisons that a report counts, 16 or 32), several
 hipError_t launch_skinny_f16(int mode, bool bytes, int columns, const GemmArgs& args, hipStream_t stream);
 hipError_t launch_skinny_bf16(int mode, bool bytes, int columns, const GemmArgs& args, hipStream_t stream);

@@ -24,8 +24,11 @@ constexpr int SKINNY_ROWS = 16, SKINNY_WAVES = 8, SKINNY_AHEAD = 2;
 // columns of a workgroup: 16; with a report 32, the columns of the comparisons that it counts on 32 x 32 tiles
 constexpr int skinny_lds_bytes(int tn) { return SKINNY_WAVES * (1 + tn) * 2048; }
 
-// Rows of at least 16 bytes.  BYTES: rows at any address; else at multiples of four bytes.
-template <int DT, int TN, int MODE, bool BYTES>
+// Rows of at least 16 bytes.  BYTES: rows at any address; else at multiples of four bytes.  INJ: with a planted fault (test
+// hook): in the sum of those of the eight shares that the tiling whose place this kernel takes has in one (p.n_parts shares, k tile t in
+// share t % p.n_parts), as it stands once that share has taken all its k tiles up to p.f_kt (-1: up to the last), or in the finished sum (-2).
+// The loop and the comparison are those of a call without one, and so is every other element.
+template <int DT, int TN, int MODE, bool BYTES, bool INJ>
 __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char* smem) {
     typedef Mma<DT, 16> MMA;
     typedef typename MMA::Acc Acc;
@@ -102,7 +105,13 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
             acc[j][r] = 0;
             chk[j][r] = r == 0 ? zero : 0;
         }
-    auto multiply = [&](int u, int cut) {
+    const int upto = INJ && p.f_kt >= 0 ? p.f_kt : nkt - 1;
+    Acc then[INJ ? TN : 1];   // this wavefront's part of the share's sum up to there
+    if constexpr (INJ) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) then[j] = acc[j];
+    }
+    auto multiply = [&](int u, int i, int cut) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             i32x4 x = v_[u][q];
@@ -124,6 +133,12 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
                 if constexpr (CHECKED) chk[j] = MMA::run(a, b, chk[j]);
             }
         }
+        if constexpr (INJ) {
+            if (wave + KW * i <= upto) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) then[j] = acc[j];
+            }
+        }
     };
     int i = 0;
     if (n_own > 2 * U) {
@@ -134,7 +149,7 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
         for (; i + 2 * U < n_own; i += U)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                multiply(u, 0);
+                multiply(u, i + u, 0);
                 load_whole(u, i + U + u);
             }
     } else {
@@ -148,7 +163,7 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
         for (int u = 0; u < U; ++u)
             if (i + u < n_own) {
                 const int left = kb - (wave + KW * (i + u)) * 128;
-                multiply(u, left < 128 && (left & 15) ? left : 0);   // (bytes of a tile whose last chunk K cuts)
+                multiply(u, i + u, left < 128 && (left & 15) ? left : 0);   // (bytes of a tile whose last chunk K cuts)
                 if (i + U + u < n_own) load(u, i + U + u);
             }
 
@@ -159,6 +174,7 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
     for (int j = 0; j < TN; ++j) {
         red[(wave * TN + j) * 64 + lane] = acc[j];
         if constexpr (CHECKED) red[((KW + wave) * TN + j) * 64 + lane] = chk[j];
+        if constexpr (INJ) red[((2 * KW + wave) * TN + j) * 64 + lane] = then[j];
     }
     __syncthreads();
     Acc v, w;
@@ -171,19 +187,19 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
             if constexpr (CHECKED) w += red[((KW + q) * TN + wave) * 64 + lane];
         }
         const int col = n0 + 16 * wave + lrow;
-        if (p.f_row >= 0) {
-            // test hook: a flipped bit in a finished sum, p.n_parts == 4 and f_kt == -1 in that of the share of four (k
-            // tiles t % 4) that holds the last k tile
-            const bool mine = col == p.f_col && (p.f_row >> 2) == lgrp;
-            static_assert(KW == 8, "a share of four is two of eight");
-            const int last = (nkt - 1) & 3;
+        if constexpr (INJ) {
+            Acc part = v;
+            if (p.f_kt != -2) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) part[r] = 0;
+#pragma unroll
+                for (int q = 0; q < KW; ++q)
+                    if (((q ^ upto) & (p.n_parts - 1)) == 0) part += red[((2 * KW + q) * TN + wave) * 64 + lane];
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const AccT part = red[(last * TN + wave) * 64 + lane][r] + red[((last + 4) * TN + wave) * 64 + lane][r];
-                const bool share = p.n_parts == 4 && p.f_kt == -1;
-                const unsigned mask = mine && (p.f_row & 3) == r ? 1u << p.f_bit : 0u;
-                const AccT flipped = bitcast<AccT>(bitcast<unsigned>(share ? part : v[r]) ^ mask);
-                if (mask) v[r] = share ? v[r] - part + flipped : flipped;
+                const AccT flipped = bitcast<AccT>(bitcast<unsigned>(part[r]) ^ (1u << p.f_bit));
+                if (col == p.f_col && p.f_row == 4 * lgrp + r) v[r] = p.f_kt == -2 ? flipped : v[r] - part[r] + flipped;
             }
         }
         if (col < N) {
@@ -255,12 +271,12 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
     }
 }
 
-template <int DT, int TN, int MODE, bool BYTES>
+template <int DT, int TN, int MODE, bool BYTES, bool INJ>
 __global__ __launch_bounds__(64 * SKINNY_WAVES) void gemm_skinny_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tile_m, tile_n;
     tile_of_block((int)blockIdx.x, 1, (int)gridDim.x, tile_m, tile_n);   // (a run of columns per die: whole lines of C and A once)
-    skinny_tile<DT, TN, MODE, BYTES>(p, tile_n, smem);
+    skinny_tile<DT, TN, MODE, BYTES, INJ>(p, tile_n, smem);
 }
 
 }  // namespace abft

@@ -77,3 +77,44 @@ def test_layers_of_few_rows_share_a_launch_at_any_alignment(dtype):
             p.add((M, N, K), p.rnd(M, K), p.out(M, N, pad=N % 3), relu=N == 40)
         p.both_ways(shared=1)
     assert torch.cuda.is_available()
+
+
+# a tiling of four shares (32 x 32 streaming tiles, the four-group tile), of eight, of one (16 x 64): aligned rows, rows at multiples of
+# four bytes, rows at any address
+FAULTS = [(16, 100, 1920, "S32", 4), (3, 33, 1000, "S32", 4), (16, 40, 8192, "S32W", 8), (9, 64, 4096 + 16, "S32W", 8),
+          (9, 70, 2050, "G64K", 4), (16, 33, 4099, "G64K", 4), (7, 40, 402, "G16", 1), (16, 70, 211, "G16", 1)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("shape", FAULTS, ids=str)
+def test_a_planted_fault_changes_its_element_and_no_other_and_is_seen(shape, dtype):
+    """Faults of every kind run on the kernel of the call without one: every other element is that call's bit by bit, int8
+    carries exactly the flip of the sum that the tiling's shares make of it, and the flag is raised with a report and without."""
+    M, N, K, name, ways = shape
+    K = 2 * K + K % 2 if dtype == "i8" else K
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N + K, dist_a="normal", dist_b="normal")
+    C_ref = oracle.gemm(A, Bm, dtype)
+    aligned = name[0] == "S"
+    ks = B.abft_tile_shape(M, N, K, DT[dtype], aligned)[2]
+    last = (K - 1) // ks * ks
+    rng = np.random.default_rng(K)
+    for mode in (B.NONE, B.THREAD, B.REPLICA, B.THREAD_HALF, B.TWOSIDED):
+        assert B.abft_kernel_name(M, N, K, DT[dtype], mode, aligned) == name
+        parts = B.abft_k_parts(M, N, K, DT[dtype], mode, aligned)
+        assert len(parts) == ways
+        for report in (False, True) if mode != B.NONE else (False,):
+            kw = dict(want_report=report, misalign=K % 2 if dtype == "i8" else 0)
+            clean = run_gemm(A, Bm, dtype, mode, **kw)
+            assert c_close(clean.C, C_ref, dtype) and clean.flag == 0
+            for k_after in (-1, -2, ks, 6 * ks if 6 * ks < K else ks, last):
+                i, j = int(rng.integers(M)), int(rng.integers(N))
+                print("case", shape, dtype, mode, report, k_after, i, j, flush=True)
+                bad = run_gemm(A, Bm, dtype, mode, inject=B.Fault(i, j, 30, k_after), **kw)
+                same = bad.C == clean.C
+                assert not same[i, j]
+                same[i, j] = True
+                assert same.all() and bad.flag == (mode != B.NONE), (mode, report, k_after)
+                if dtype == "i8":
+                    part = {} if k_after == -2 else dict(k_after=k_after, k_set=parts[oracle.part_of(parts, (K if k_after < 0 else k_after) - 1)])
+                    want = oracle.inject(A, Bm, C_ref, dtype, i, j, 30, **part)
+                    assert np.array_equal(bad.C, ((want + 2 ** 31) % 2 ** 32) - 2 ** 31), (mode, report, k_after)
