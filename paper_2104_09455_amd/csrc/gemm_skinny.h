@@ -217,12 +217,15 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
         }
     }
     if constexpr (CHECKED) {
-        // comparison (Sec. 5.2.2): the sum of the workgroup's blocks against that of their checksum blocks
+        // comparison (Sec. 5.2.2): the sum of a 16 x 16 block against that of its checksum block.  A report counts
+        // comparisons of 32 columns where the tiling's tiles are that wide, and so gets the sums of two blocks, but the larger of their
+        // ratios: what raises the flag is the same with a report and without.
         static_assert(TN <= 2, "the second block's sums go through LDS");
         Wide s = 0, c = 0;
-        float f2 = 0.f;
+        double F2 = 0.0, ratio = 0.0;
         if (wave < TN) {
             int differ = 0;
+            float f2 = 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 differ |= bitcast<int>(v[r]) ^ bitcast<int>(w[r]);
@@ -237,37 +240,36 @@ __device__ __forceinline__ void skinny_tile(const GemmArgs& p, int tile_n, char*
             }
             s = wave_sum(s);
             c = wave_sum(c);
-            if constexpr (!IS_INT) f2 = wave_sum(f2);
+            bool bad = s != c;
+            ratio = bad ? __builtin_huge_val() : 0.0;
+            if constexpr (!IS_INT) {
+                F2 = (double)wave_sum(f2);
+                const double tau = p.tol_coeff * __builtin_sqrt(F2), res = __builtin_fabs(s - c);
+                // a sum of squares beyond the fp32 range cannot come from a fault-free tile
+                const bool finite = __builtin_isfinite(s) && __builtin_isfinite(c) && __builtin_isfinite(F2);
+                bad = !finite || !(res <= tau);
+                ratio = !finite ? __builtin_huge_val() : (tau > 0.0 ? res / tau : (res > 0.0 ? __builtin_huge_val() : 0.0));
+            }
+            if (lane == 0 && bad) atomicOr(p.flag, 1u);
         }
         if constexpr (TN == 2) {
             __syncthreads();   // everyone has read the partial tiles
             Wide* const sums = reinterpret_cast<Wide*>(smem);
+            double* const norms = reinterpret_cast<double*>(sums + 2);
             if (wave == 1 && lane == 0) {
                 sums[0] = s;
                 sums[1] = c;
-                *reinterpret_cast<float*>(sums + 2) = f2;
+                norms[0] = F2;
+                norms[1] = ratio;
             }
             __syncthreads();
             s += sums[0];
             c += sums[1];
-            f2 += *reinterpret_cast<const float*>(sums + 2);
+            F2 += norms[0];
+            ratio = __builtin_fmax(ratio, norms[1]);
         }
-        if (tid == 0) {
-            if constexpr (IS_INT) {
-                const bool bad = s != c;
-                if (bad) atomicOr(p.flag, 1u);
-                if (p.report) report_update(p.report, bad ? __builtin_huge_val() : 0.0, (double)s, (double)c, 0.0, 0.0, 0.0, (unsigned)tile_n);
-            } else {
-                const double F2 = (double)f2, tau = p.tol_coeff * __builtin_sqrt(F2), res = __builtin_fabs(s - c);
-                // a sum of squares beyond the fp32 range cannot come from a fault-free tile
-                const bool finite = __builtin_isfinite(s) && __builtin_isfinite(c) && __builtin_isfinite(F2);
-                const bool bad = !finite || !(res <= tau);
-                if (bad) atomicOr(p.flag, 1u);
-                if (p.report)
-                    report_update(p.report, !finite ? __builtin_huge_val() : (tau > 0.0 ? res / tau : (res > 0.0 ? __builtin_huge_val() : 0.0)),
-                                  s, c, tau, __builtin_sqrt(F2), 0.0, (unsigned)tile_n);
-            }
-        }
+        if (tid == 0 && p.report)
+            report_update(p.report, ratio, (double)s, (double)c, IS_INT ? 0.0 : p.tol_coeff * __builtin_sqrt(F2), __builtin_sqrt(F2), 0.0, (unsigned)tile_n);
     }
 }
 

@@ -118,3 +118,35 @@ def test_a_planted_fault_changes_its_element_and_no_other_and_is_seen(shape, dty
                     part = {} if k_after == -2 else dict(k_after=k_after, k_set=parts[oracle.part_of(parts, (K if k_after < 0 else k_after) - 1)])
                     want = oracle.inject(A, Bm, C_ref, dtype, i, j, 30, **part)
                     assert np.array_equal(bad.C, ((want + 2 ** 31) % 2 ** 32) - 2 ** 31), (mode, report, k_after)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K,misalign", [(256, 0), (4096, 0), (2050, 0), (4099, 1)])
+def test_the_verdict_does_not_depend_on_a_report(K, misalign, dtype):
+    """Sixteen columns of small sums beside sixteen of large ones: a fault among the small ones that is beyond the tolerance of
+    its own columns and within that of all 32 raises the flag with a report (whose ratio says so) and without."""
+    M, N = 11, 64
+    assert B.abft_tile_shape(M, N, K, DT[dtype], K % 8 == 0)[1] == 32
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=K, dist_a="uniform_01", dist_b="uniform_01")
+    large = np.ones(N, dtype=bool)
+    large[32:48] = False
+    # (times 32: exact in both types, whose values here are all normal numbers or zero)
+    Bm[:, large] = Bm[:, large] * np.float16(32) if dtype == "f16" else np.where(Bm[:, large] != 0, Bm[:, large] + (5 << 7), 0)
+    C_ref = oracle.gemm(A, Bm, dtype)
+    i, j = M - 2, 37
+    seen = set()
+    for bit in range(2, 23):
+        C_bad = oracle.inject(A, Bm, C_ref, dtype, i, j, bit)
+        own, both = (oracle.tile_check(A, Bm, C_bad, dtype, 0, M, c0, c1) for c0, c1 in ((32, 48), (32, 64)))
+        beyond = abs(own.residual) >= 2 * own.tau
+        within = abs(own.residual) <= own.tau / 2
+        if not (beyond or within) or (beyond and abs(both.residual) > both.tau / 2):
+            continue
+        print("case", K, misalign, dtype, bit, own.residual, own.tau, both.tau, flush=True)
+        seen.add(beyond)
+        for report in (False, True):
+            r = run_gemm(A, Bm, dtype, B.THREAD, misalign=misalign, want_report=report, inject=B.Fault(i, j, bit, -2))
+            assert r.flag == beyond, (bit, report)
+            if report:
+                assert (r.report.worst_ratio > 1) == beyond
+    assert True in seen
