@@ -288,3 +288,26 @@ def test_direct_to_lds_tiles_share_a_launch(mode, dtype, shape, name):
     if dtype != "i8":
         later(False).both_ways(shared=1 if takes else None)
         later(True).both_ways()
+
+
+# layers that share a launch of the skinny kernel (rows at any alignment), of the direct-to-LDS kernel's two tiles, of a streaming
+# tiling with a product of less than one k tile
+FLAGGED = {"skinny": [(16, 96, 4096), (3, 33, 37), (9, 40, 1030)], "F64T": [(3136, 256, 64), (3101, 250, 64)],
+           "F128T": [(12544, 256, 64), (12500, 256, 64)], "shallow": [KINDS["S32"], (70, 100, 13), (64, 64, 64)],
+           "shallow beside S64": [KINDS["S64"], (70, 100, 33)], "shallow beside S128": [KINDS["S128"], (33, 50, 15)]}
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("kind", FLAGGED)
+def test_what_is_no_number_in_any_member_of_a_shared_launch_raises_the_flag(kind, dtype):
+    """In the last row and the last k of one layer's input: the launch's workgroups all know the flag, and compare."""
+    for bad in range(len(FLAGGED[kind])):
+        p = Pass(dtype, B.THREAD, seed=bad)
+        for i, (M, N, K) in enumerate(FLAGGED[kind]):
+            if kind in ("F64T", "F128T"):
+                assert B.abft_kernel_name(M, N, K, DT[dtype], B.THREAD) == kind
+            A = p.rnd(M, K)
+            if i == bad:
+                A[M - 1, K - 1] = float("nan")
+            p.add((M, N, K), A, p.out(M, N))
+        p.both_ways(shared=1, flag=1)
