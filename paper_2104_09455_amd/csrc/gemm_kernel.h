@@ -24,14 +24,17 @@ namespace abft {
 // LD: how the operands are read.  VEC: both in aligned 16-byte chunks (a_vec and b_vec); an instance of its own,
 // since the other loaders' registers and branches cost such products a fifth (4000 x 4000 x 1000 fp16
 // unprotected 74 us, so 59; int8 thread-level, K = 4016, 283 / 199; 5 x 5 convolution 40 -> 120 on 100352 rows 76 / 53).
-// ROWS: both contiguous along k, at any alignment; TURN: A so, weights K x N.  These two know their loaders at compile
+// ROWS: both contiguous along k, at any alignment; TURN: A so, weights K x N.  These know their loaders at compile
 // time; a load is a base that the wavefront shares and 32 bits per lane, without a condition (what lies outside reads the
 // last row or chunk that is inside and becomes zeros on the way to LDS, in the tiles that have such).  64-bit products per
 // load, a condition each, and the loads behind the products / so, thread-level fp16, weights K x N, us: 2048 x 4096 x 4096
 // 113 / 97, 1900 x 4000 x 4000 121 / 115, 16 x 4096 x 4096 25.6 / 21.5, 1 x 1024 x 1024 8.5 / 7.2; 2000 x 600 x 4090 60 / 58.  (Two or three k
 // tiles on their way in registers: 511 x 1000 x 2047 15.4 -> 16.5, 17.5: the tiles read past the end cost more.)
+// TURN_RUNS: weights K x N of 2 GiB and more, whose offsets start again with every run of k.  ANY / 64-bit products / so, us:
+// 64 x 65536 x 20000 fp16 thread-level 774 / 740 / 648, unprotected 652 / 579 / 508, 8 x 152064 x 8192 bf16 495 / 456 / 456.  (For all weights:
+// the four-group tile 128 x 2048 x 4096 18.1 -> 19.3, 16 x 4096 x 4096 19.8 -> 20.6.)
 // ---------------------------------------------------------------------------
-enum { LD_ANY = 0, LD_VEC = 1, LD_ROWS = 2, LD_TURN = 3 };
+enum { LD_ANY = 0, LD_VEC = 1, LD_ROWS = 2, LD_TURN = 3, LD_TURN_RUNS = 4 };
 template <class CFG, int MODE, bool INJ, bool CONV, int KG, int LD>
 __global__ __launch_bounds__(CFG::THREADS * KG) __attribute__((amdgpu_waves_per_eu(INJ || KG > 1 ? 1 : min_waves_per_simd<CFG, MODE>())))
 void gemm_kernel(const GemmArgs p) {
@@ -351,6 +354,8 @@ void gemm_kernel(const GemmArgs p) {
             }
         }
     }
+    // rows of weights K x N whose offsets stay in 31 bits: a power of two, whole k tiles
+    const int b_run = LD == LD_TURN_RUNS ? 1 << (31 - __builtin_clz(0x7fffffffu / ldb_b)) : 0;
     auto chunk_from = [&](int kt) { return min((unsigned)kt * BKB + (unsigned)kc * 16, kb - 16); };   // the byte of its row
     auto stream_load = [&](int kt, i32x4(&ra)[NA], i32x4(&rb)[NB]) {
         const unsigned from = chunk_from(kt);
@@ -361,12 +366,15 @@ void gemm_kernel(const GemmArgs p) {
             for (int t = 0; t < NB; ++t) rb[t] = ld16u(b_base + (b_off[t] + from));
         } else {
             // (rows past K read the last one, dropped on the way to LDS)
+            const int k0 = min(kt, nkt - 1) * BK;
+            const int from_k = LD == LD_TURN_RUNS ? k0 & -b_run : 0, rows = LD == LD_TURN_RUNS ? min(K - from_k, b_run) : K;
+            const char* const run = b_base + (long long)from_k * p.ldb * ESIZE;
 #pragma unroll
             for (int t = 0; t < UNITS; ++t) {
-                const unsigned first = (unsigned)(min(kt, nkt - 1) * BK) * ldb_b + b_off[t];
-                const unsigned last = (unsigned)(K - 1) * ldb_b + b_col[t];
+                const unsigned first = (unsigned)(k0 - from_k) * ldb_b + b_off[t];
+                const unsigned last = (unsigned)(rows - 1) * ldb_b + b_col[t];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) rb[2 * t + (e >> 2)][e & 3] = ld4u(b_base + min(first + e * ldb_b, last));
+                for (int e = 0; e < 8; ++e) rb[2 * t + (e >> 2)][e & 3] = ld4u(run + min(first + e * ldb_b, last));
             }
         }
     };

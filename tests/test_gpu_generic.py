@@ -160,3 +160,47 @@ def test_halved_tiles_keep_the_four_group_tile_s_results_and_comparisons(shape, 
         same = bad.C == r.C
         same[M - 1, N - 1] = True
         assert same.all() and bad.flag == (mode != B.NONE)
+
+
+# (M, N, K, pitch of A, of B, which operand's pitch is large): weights K x N of more than 2 GiB, whose k loops take several runs of
+# 32-bit offsets (the last one cut) on every tile of the generic kernel; k loops far shorter than the k tile, on either side of the
+# pitch where a k tile's offsets leave 31 bits; rows of A, of B whose tile does
+WIDE = [("kn", 9, 70, 600, 600, 4_000_000), ("kn", 40, 66, 777, 777, 4_000_000), ("kn", 70, 130, 130, 130, 16_000_000),
+        ("kn", 1500, 1400, 130, 131, 16_000_000), ("kn", 4, 9, 17, 17, 8_000_000), ("kn", 4, 9, 17, 17, 40_000_000),
+        ("nk", 33, 40, 41, 35_000_000, 41), ("nk", 33, 40, 41, 41, 35_000_000), ("nk", 33, 40, 41, 30_000_000, 20_000_000)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("case", WIDE, ids=str)
+def test_pitches_beyond_32_bit_offsets(case, dtype):
+    """Bit for bit what the operands without their pitches give; what lies between the rows is no number (int8: large)."""
+    import torch
+    from gpu_util import DEV, to_dev
+    layout, M, N, K, lda, ldb = case
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N, dist_a="normal", dist_b="normal")
+    t, c_t, gap = (torch.int8, torch.int32, 77) if dtype == "i8" else (torch.float16, torch.float16, float("nan"))
+    order, W = (B.B_NK, Bm.T) if layout == "nk" else (B.B_KN, Bm)
+
+    def spread(x, pitch):
+        rows, cols = x.shape
+        buf = torch.full(((rows - 1) * pitch + cols,), gap, dtype=t, device=DEV)
+        torch.as_strided(buf, (rows, cols), (pitch, 1)).copy_(to_dev(np.ascontiguousarray(x), dtype))
+        return buf, pitch
+
+    C_ref = oracle.gemm(A, Bm, dtype)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    stored = {}
+    for a_pitch, b_pitch in ((K + 1, W.shape[1] + 1), (lda, ldb)):
+        (dA, a_pitch), (dB, b_pitch) = spread(A, a_pitch), spread(W, b_pitch)
+        for mode in (B.NONE, B.GLOBAL, B.THREAD):
+            print("case", case, dtype, mode, a_pitch, b_pitch, flush=True)
+            need = max(B.abft_workspace_bytes(M, N, K, DT[dtype], mode), 256)
+            ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
+            C = torch.zeros((M, N), dtype=c_t, device=DEV)
+            B.abft_gemm(M, N, K, dA, a_pitch, dB, b_pitch, order, C, N, DT[dtype], mode, workspace=ws, workspace_bytes=need, fault_flag=flag)
+            torch.cuda.synchronize()
+            assert int(flag.item()) == 0
+            assert torch.equal(C, stored.setdefault(mode, C))
+        del dA, dB
+    got = stored[B.THREAD].cpu().numpy()
+    assert c_close(got.astype(np.int64) if dtype == "i8" else got.astype(np.float64), C_ref, dtype)
