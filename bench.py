@@ -410,9 +410,10 @@ def clock_context(lr, secs=1.5):
 def chain_leg(gen, batch=256, steps=300):
     """DLRM's two MLPs as chains (Sec. 2.4 step 4): ReLU fused into the store of every layer but
     each MLP's last, layer l's output handed to layer l + 1 as its input.  Two forms, both timed as
-    device time of a whole pass replayed from a graph: one kernel launch per layer
-    (abft_plan_run_all), and one launch per chain (abft_plan_run_chain: bottom MLP behind its K = 13
-    layer, top MLP), each with the selector's schemes, all-global and unprotected."""
+    device time of a whole pass replayed from a graph: one call for all layers (abft_plan_run_all), and one
+    call per chain (abft_plan_run_chain: bottom MLP behind its K = 13 layer, top MLP), which is one launch where
+    the chain qualifies (chains_in_one_launch of the two: not at 16 rows or fewer but under the global
+    scheme), each with the selector's schemes, all-global and unprotected."""
     layers = wl.dlrm_layers(batch)
     rs = [LayerRun(l, "f16", gen) for l in layers]
     plan = B.abft_plan_create([B.Layer(r.layer.M, r.layer.N, r.layer.K, r.dt, B.B_NK, 0, B.Conv(), r.B.data_ptr(),
@@ -460,11 +461,15 @@ def chain_leg(gen, batch=256, steps=300):
         return 1e6 * (time.perf_counter() - t0) / steps
 
     res = {"batch": batch, "layers": [r.layer.name for r in rs], "relu_after": [r.layer.name for i, r in enumerate(rs) if i not in last]}
+    chains = res["chains_in_one_launch"] = {}
     try:
         for label, mode in (("selector", B.AUTO), ("global", B.GLOBAL), ("none", B.NONE)):
             for i in range(len(rs)):
                 B.abft_plan_set_mode(plan, i, mode)
             res["us_" + label] = round(pass_us(per_layer), 2)
+            before = B.abft_chain_launches()
+            one_launch(side.cuda_stream)
+            chains[label] = B.abft_chain_launches() - before
             res["us_" + label + "_one_launch_per_chain"] = round(pass_us(one_launch), 2)
         for form in ("", "_one_launch_per_chain"):
             res["ovh_selector_pct" + form] = round(100 * (res["us_selector" + form] / res["us_none" + form] - 1), 2)

@@ -366,8 +366,8 @@ int abft_plan_run_all(abft_plan_t *plan, const void *const *A, const int64_t *ld
  * (host arrays, i = 0 .. count - 1) are the layers' outputs, each with the layer's activation
  * function applied and its scheme's checks made on the product.
  * When every layer is fully connected in F16 or BF16 with the same batch M, small enough that a
- * launch of its own would run on 32 x 32 tiles with four wavefronts each (abft_k_ways; more than 16 rows, or scheme
- * GLOBAL: fewer have a kernel of their own, whose launches are faster), weights in ABFT_B_NK
+ * launch of its own would run on 32 x 32 tiles with four wavefronts each (abft_k_ways; at most 16 rows only where every layer is
+ * under GLOBAL: such products have a kernel of their own under the other schemes, whose launches are faster), weights in ABFT_B_NK
  * order with 16-byte aligned rows, K a multiple of 64, 16-byte aligned A / C rows, and scheme NONE,
  * GLOBAL or THREAD (and count <= 8), the whole chain runs in ONE kernel launch: the batch is cut into
  * eight slabs of rows, one per die of the GPU, and each die takes its slab through all the layers,
@@ -404,6 +404,8 @@ int abft_plan_set_diagnostics(abft_plan_t *plan, int layer, abft_report_t *repor
 /* How many product launches of this process so far took their activation checksums from the
  * layer before (abft_plan_run_chain, layer by layer); lets a caller see that a chain qualified. */
 long long abft_handover_launches(void);
+/* How many chains of this process so far went out as one launch (abft_plan_run_chain). */
+long long abft_chain_launches(void);
 /* How many launches of this process so far carried several layers of an abft_plan_run_all pass. */
 long long abft_shared_launches(void);
 /* Override the scheme of a layer (abft_mode_t; ABFT_AUTO re-applies abft_select). */

@@ -60,7 +60,7 @@ EXPORTS = [
     "abft_plan_run_all", "abft_plan_set_mode", "abft_k_ways", "abft_beta_bytes", "abft_conv_workspace_bytes",
     "abft_plan_set_activation", "abft_plan_activation", "abft_gemm_static", "abft_static_scratch_bytes",
     "abft_tolerance_half_coeff", "abft_plan_run_chain", "abft_plan_chain_status", "abft_plan_chain_reset",
-    "abft_plan_set_diagnostics", "abft_kernel_name", "abft_handover_launches", "abft_shared_launches", "abft_mfma_probe", "abft_mfma_probe_bytes",
+    "abft_plan_set_diagnostics", "abft_kernel_name", "abft_handover_launches", "abft_chain_launches", "abft_shared_launches", "abft_mfma_probe", "abft_mfma_probe_bytes",
 ]
 
 _lib = None
@@ -132,6 +132,8 @@ def lib() -> ctypes.CDLL:
     L.abft_kernel_name.argtypes = [ctypes.c_int] * 7
     L.abft_handover_launches.restype = ctypes.c_longlong
     L.abft_handover_launches.argtypes = []
+    L.abft_chain_launches.restype = ctypes.c_longlong
+    L.abft_chain_launches.argtypes = []
     L.abft_shared_launches.restype = ctypes.c_longlong
     L.abft_shared_launches.argtypes = []
     L.abft_mfma_probe_bytes.restype = ctypes.c_size_t
@@ -364,6 +366,10 @@ def abft_plan_chain_reset(plan, spin_limit=-1, stream=None) -> None:
 
 def abft_handover_launches() -> int:
     return int(lib().abft_handover_launches())
+
+
+def abft_chain_launches() -> int:
+    return int(lib().abft_chain_launches())
 
 
 def abft_shared_launches() -> int:

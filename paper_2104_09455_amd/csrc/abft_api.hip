@@ -69,6 +69,8 @@ constexpr size_t STATIC_SCRATCH_BYTES = 8u << 20;
 __device__ __align__(256) unsigned char g_static_scratch[STATIC_SCRATCH_BYTES];
 // product launches so far that took their activation checksums from the layer before (diagnostics)
 std::atomic<long long> g_handover_launches{0};
+// chains of layers so far that went out as one launch (diagnostics)
+std::atomic<long long> g_chain_launches{0};
 constexpr int MAX_DEVICES = 64;
 void* g_scratch_ptr[MAX_DEVICES] = {nullptr};
 std::mutex g_scratch_mutex;
@@ -2036,7 +2038,10 @@ int abft_plan_run_chain(abft_plan_t* plan, int first, int count, const void* A, 
         one_launch = L.chain_beta != nullptr && d.dtype == d0.dtype && d.M == d0.M &&
                      pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode) == CFG_S32 && !L.report && !L.has_fault &&
                      (L.mode == ABFT_NONE || L.mode == ABFT_GLOBAL || L.mode == ABFT_THREAD) && C[i] != nullptr &&
-                     (d.M > SKINNY_ROWS || L.mode == ABFT_GLOBAL) &&   // (else a launch of its own runs on the skinny kernel)
+                     // (else a launch of its own runs on the skinny kernel, and layer by layer is faster: 16 x 512 -> 1024 -> 1024
+                     // -> 512 -> 256 -> 1 fp16 thread-level 16.0 us, in one launch 21.5; 1 x 512 -> 256 -> 64 5.8 / 8.5; so, too, where
+                     // that kernel leaves a layer of more weights to 32 x 32 tiles: 16 x 2048 -> 8192 -> 2048 18.9 / 77)
+                     (d.M > SKINNY_ROWS || L.mode == ABFT_GLOBAL) &&
                      aligned16(a_i) && (lda_i * 2) % 16 == 0 && lda_i >= d.K && ldc[i] >= d.N &&
                      (i == 0 || d.K == plan->layers[first + i - 1].desc.N);
         any_check = any_check || L.mode != ABFT_NONE;
@@ -2087,6 +2092,7 @@ int abft_plan_run_chain(abft_plan_t* plan, int first, int count, const void* A, 
         c.tol_coeff = tol_coeff(d.K, d.dtype, L.mode);
         c.tol_l1 = tol_bias_coeff(d.K, d.dtype, L.mode);
     }
+    g_chain_launches.fetch_add(1, std::memory_order_relaxed);
     const hipError_t e = d0.dtype == ABFT_F16 ? launch_mlp_chain_f16(a, st) : launch_mlp_chain_bf16(a, st);
     return e == hipSuccess ? ABFT_OK : ABFT_E_HIP;
 }
@@ -2112,6 +2118,7 @@ int abft_plan_chain_reset(abft_plan_t* plan, int spin_limit, void* stream) {
 }
 
 long long abft_handover_launches(void) { return g_handover_launches.load(std::memory_order_relaxed); }
+long long abft_chain_launches(void) { return g_chain_launches.load(std::memory_order_relaxed); }
 long long abft_shared_launches(void) { return g_shared_launches.load(std::memory_order_relaxed); }
 
 int abft_plan_set_diagnostics(abft_plan_t* plan, int layer, abft_report_t* report, const abft_fault_t* inject) {

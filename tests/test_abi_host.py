@@ -127,6 +127,7 @@ def test_argument_validation_without_a_gpu(lib):
     assert lib.abft_plan_set_diagnostics(None, 0, None, None) == -8
     assert lib.abft_plan_run_chain(None, 0, 1, p, 4, None, None, p, None) == -8
     assert lib.abft_handover_launches() == 0   # nothing has run in this process
+    assert lib.abft_chain_launches() == 0
     assert lib.abft_shared_launches() == 0
     # the measurement aid checks its arguments before it touches the device
     ops = ctypes.c_double(0.0)

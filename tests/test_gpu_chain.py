@@ -79,18 +79,22 @@ BOTTOM = [512, 256, 64]                     # DLRM bottom MLP behind its first (
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("kind", ["none", "global", "thread", "mixed"])
-@pytest.mark.parametrize("M,widths", [(1, TOP), (16, TOP), (256, TOP), (256, BOTTOM), (200, [128, 320, 64]),
+@pytest.mark.parametrize("M,widths", [(1, TOP), (16, TOP), (17, TOP), (256, TOP), (256, BOTTOM), (200, [128, 320, 64]),
                                       (1024, [256, 192, 64])])
 def test_chain_in_one_launch_matches_the_oracle(M, widths, kind, dtype):
-    """DLRM's MLPs at batch 1 / 16 / 256, a ragged batch and one of several tile rows per die."""
+    """DLRM's MLPs at batch 1 / 16 / 256, a ragged batch and one of several tile rows per die.  One launch, but for at most
+    sixteen rows with a layer that is not under the global scheme: such a layer has a kernel of its own, and the chain runs
+    layer by layer."""
     import torch
     ch = Chain(M, widths, dtype, seed=500 + M, modes=_modes(kind, len(widths) - 1))
     try:
         for call in range(2):          # the second call reads new inputs through the same buffers
             x, dx = ch.input(seed=600 + M + call)
             print(f"case chain M={M} widths={widths} modes={kind} dtype={dtype} call={call}", flush=True)
+            before = B.abft_chain_launches()
             ch.run(dx)
             torch.cuda.synchronize()
+            assert B.abft_chain_launches() - before == (1 if M > 16 or kind == "global" else 0)
             assert B.abft_plan_chain_status(ch.plan) == 0
             assert int(ch.flag.item()) == 0
             ch.check(x)
@@ -161,8 +165,10 @@ def test_chain_that_does_not_qualify_runs_layer_by_layer():
     ch = Chain(64, [13, 512, 256, 64], "f16", seed=710, modes=_modes("thread", 3))
     try:
         x, dx = ch.input(seed=711)
+        before = B.abft_chain_launches()
         ch.run(dx)
         torch.cuda.synchronize()
+        assert B.abft_chain_launches() == before
         assert int(ch.flag.item()) == 0
         ch.check(x)
     finally:
