@@ -71,7 +71,7 @@ struct FastLayout {
 // One output tile, by all threads of the workgroup; bid: the workgroup's index among those of the product.  (p by value: through a
 // reference the compiler takes the kernel's arguments for memory that may change, and loses the selects of a convolution's copies.)
 template <class CFG, int NSTAGE, int MODE, bool INJ, bool CONV>
-__device__ __forceinline__ void fast_tile(const GemmArgs p, int bid, char* smem) {
+__device__ __forceinline__ void fast_tile(const GemmArgs p, int bid) {
     typedef FastLayout<CFG, NSTAGE> LAY;
     constexpr int DT = CFG::DT;
     constexpr int MI = CFG::MI;
@@ -104,6 +104,12 @@ __device__ __forceinline__ void fast_tile(const GemmArgs p, int bid, char* smem)
     static_assert(!FED || (DT != DT_I8 && (!FED_PER_ROW || CFG::WM == 32)), "a 32-row block per wavefront or per row of wavefronts");
     constexpr int EMODE = (MODE == MODE_GLOBAL_PRE || FED) ? MODE_GLOBAL : MODE;  // the epilogue's scheme
     constexpr bool IS_INT = DT == DT_I8;
+
+    // (LDS by its own pointers in the copies: one that may be null costs them a comparison and a select)
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    typedef __attribute__((address_space(3))) char LdsByte;
+    typedef const __attribute__((address_space(1))) void* From;
+    LdsByte* const lds = (LdsByte*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -194,12 +200,10 @@ __device__ __forceinline__ void fast_tile(const GemmArgs p, int bid, char* smem)
             const int f0 = 256 * g + 4 * lane;                 // first of this lane's four floats
             const bool in_k = f0 + 4 <= p.K;                   // (K is a multiple of 64: whole lanes)
             const char* src = (fed_alpha && in_k) ? fed_alpha + (long long)f0 * 4 : zero;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(smem + LAY::FED_A + wave * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((From)src, lds + LAY::FED_A + wave * 1024, 16, 0, 0);
             if (wave == 0) {
                 const char* srcb = in_k ? fed_beta + (long long)f0 * 4 : zero;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)srcb,
-                                                 (__attribute__((address_space(3))) void*)(smem + LAY::FED_B), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((From)srcb, lds + LAY::FED_B, 16, 0, 0);
             }
         }
     };
@@ -213,8 +217,8 @@ __device__ __forceinline__ void fast_tile(const GemmArgs p, int bid, char* smem)
     }
 
     auto issue_loads = [&](int stage) {
-        char* abase = smem + stage * STAGE + wave * 1024;
-        char* bbase = abase + A_STAGE;
+        LdsByte* const abase = lds + stage * STAGE + wave * 1024;
+        LdsByte* const bbase = abase + A_STAGE;
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
             const char* src = aptr[q];
@@ -227,18 +231,14 @@ __device__ __forceinline__ void fast_tile(const GemmArgs p, int bid, char* smem)
                 const bool ok = in_m & in_h & in_w;
                 src = ok ? aptr[q] + tap_off : zero;
             }
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(abase + q * WAVES * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((From)src, abase + q * WAVES * 1024, 16, 0, 0);
         }
 #pragma unroll
         for (int q = 0; q < NQB; ++q)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)bptr[q],
-                                             (__attribute__((address_space(3))) void*)(bbase + q * WAVES * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((From)bptr[q], bbase + q * WAVES * 1024, 16, 0, 0);
         if constexpr (BREC) {
             // (the wavefronts take turns, so that none carries the extra copy every tile)
-            if (rec_turn == wave)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)beta_rec,
-                                                 (__attribute__((address_space(3))) void*)(smem + stage * STAGE + LAY::AB_STAGE), 16, 0, 0);
+            if (rec_turn == wave) __builtin_amdgcn_global_load_lds((From)beta_rec, lds + stage * STAGE + LAY::AB_STAGE, 16, 0, 0);
             rec_turn = rec_turn + 1 == WAVES ? 0 : rec_turn + 1;
         }
     };
@@ -596,8 +596,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs p, int bid, char* smem)
 template <class CFG, int NSTAGE, int MODE, bool INJ, bool CONV>
 __global__ __launch_bounds__(CFG::THREADS) __attribute__((amdgpu_waves_per_eu(INJ ? 1 : min_waves_per_simd<CFG, MODE>())))
 void gemm_fast_kernel(const GemmArgs p) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    fast_tile<CFG, NSTAGE, MODE, INJ, CONV>(p, (int)blockIdx.x, smem);
+    fast_tile<CFG, NSTAGE, MODE, INJ, CONV>(p, (int)blockIdx.x);
 }
 
 }  // namespace abft

@@ -148,10 +148,9 @@ __global__ __launch_bounds__((64 * CfgOf<DT, ID>::KWAYS)) void gemm_group_kernel
 template <int DT, int ID, int MODE>
 __global__ __launch_bounds__((CfgOf<DT, ID>::type::THREADS)) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<typename CfgOf<DT, ID>::type, MODE>())))
 void gemm_fast_group_kernel(const GroupArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     int bid = (int)blockIdx.x;
     const GemmArgs g = group_product(a, bid);
-    fast_tile<typename CfgOf<DT, ID>::type, CfgOf<DT, ID>::NSTAGE, MODE, false, false>(g, bid, smem);
+    fast_tile<typename CfgOf<DT, ID>::type, CfgOf<DT, ID>::NSTAGE, MODE, false, false>(g, bid);
 }
 
 // Products of at most sixteen rows: the skinny kernel's tile routine, with the loads that each product's rows allow.
