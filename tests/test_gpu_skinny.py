@@ -1,4 +1,4 @@
-"""Products of at most sixteen rows, whose 16-column workgroups share the k loop over sixteen wavefronts: edges of rows,
+"""Products of at most sixteen rows, whose 16-column workgroups share the k loop over eight wavefronts: edges of rows,
 columns, k tiles and chunks, rows at any alignment, every wavefront-level scheme, with a report and without."""
 import math
 
@@ -12,11 +12,14 @@ from paper_2104_09455_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K in 16-byte chunks, elements more): one chunk, a part of a k tile, one, one per wavefront and one more, the
-# most that is in flight at once, the first loop that runs past it, and by an odd number of tiles
-SHAPES = [(1, 1, 1, 0), (16, 16, 8, 0), (3, 17, 3, 0), (16, 33, 9, 0), (5, 40, 8 * 16, 0), (16, 100, 8 * 17 + 3, 0),
-          (2, 31, 8 * 64, 0), (16, 16, 8 * 129, 0), (7, 70, 8 * 300 + 5, 0),
-          (1, 512, 1, 5), (16, 15, 8, 1), (4, 65, 15, 7), (16, 48, 8 * 16, 3), (9, 33, 8 * 129, 1), (16, 20, 8 * 160 + 7, 7)]
+# (M, N, K in 16-byte chunks, elements more): one chunk, a part of a k tile, one, one per wavefront and one more, two (the most
+# that is in flight at once) and a part of a third, the k loops in which one, seven and all wavefronts take the loop without
+# conditions (their fifth own tile: 33, 39, 40 k tiles, the last one whole or cut), longer ones, by an odd number of tiles too
+SHAPES = [(1, 1, 1, 0), (16, 16, 8, 0), (3, 17, 3, 0), (16, 33, 9, 0), (8, 24, 8 * 8, 0), (8, 24, 8 * 9, 0), (5, 40, 8 * 16, 0), (16, 100, 8 * 17 + 3, 0),
+          (16, 34, 8 * 32, 0), (16, 34, 8 * 33, 0), (5, 18, 8 * 32 + 1, 0), (11, 40, 8 * 39, 0), (16, 16, 8 * 39 + 7, 0), (2, 31, 8 * 64, 0),
+          (16, 16, 8 * 129, 0), (7, 70, 8 * 300 + 5, 0),
+          (1, 512, 1, 5), (16, 15, 8, 1), (4, 65, 15, 7), (16, 48, 8 * 16, 3), (16, 34, 8 * 32, 1), (3, 20, 8 * 33, 5), (16, 17, 8 * 39 + 7, 7),
+          (9, 33, 8 * 129, 1), (16, 20, 8 * 160 + 7, 7)]
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
