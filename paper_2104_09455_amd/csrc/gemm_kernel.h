@@ -25,8 +25,8 @@ namespace abft {
 // since the other loaders' registers and branches cost such products a fifth (4000 x 4000 x 1000 fp16
 // unprotected 74 us, so 59; int8 thread-level, K = 4016, 283 / 199; 5 x 5 convolution 40 -> 120 on 100352 rows 76 / 53).
 // ROWS: both contiguous along k, at any alignment; TURN: A so, weights K x N.  These know their loaders at compile
-// time; a load is a base that the wavefront shares and 32 bits per lane, without a condition (what lies outside reads the
-// last row or chunk that is inside and becomes zeros on the way to LDS, in the tiles that have such).  64-bit products per
+// time; a load is a base that the wavefront shares and 32 bits per lane, without a condition (what lies outside reads
+// something that is inside and becomes zeros on the way to LDS, in the tiles that have such).  64-bit products per
 // load, a condition each, and the loads behind the products / so, thread-level fp16, weights K x N, us: 2048 x 4096 x 4096
 // 113 / 97, 1900 x 4000 x 4000 121 / 115, 16 x 4096 x 4096 25.6 / 21.5, 1 x 1024 x 1024 8.5 / 7.2; 2000 x 600 x 4090 60 / 58.  (Two or three k
 // tiles on their way in registers: 511 x 1000 x 2047 15.4 -> 16.5, 17.5: the tiles read past the end cost more.)
@@ -340,11 +340,16 @@ void gemm_kernel(const GemmArgs p) {
     const char* const b_base = ROWS ? p.B + (long long)bn0 * p.ldb * ESIZE : p.B;
     unsigned a_off[NA], b_off[ROWS ? NB : UNITS], b_col[ROWS ? 1 : UNITS];
     if constexpr (STREAM) {
+        // (rows outside read chunks of 16 aligned bytes near the first row's, the same ones for all: off the dword, a row each costs
+        // the vector memory path four times as much; up to 15 bytes behind the first row's, so only where there is a second)
+        auto outside = [](const char* base, int rows) { return rows > 1 ? (unsigned)(-reinterpret_cast<uintptr_t>(base) & 15u) : 0u; };
+        const unsigned a_out = outside(a_base, M - bm0);
 #pragma unroll
-        for (int t = 0; t < NA; ++t) a_off[t] = (unsigned)min(r0 + t * RPP, M - 1 - bm0) * lda_b;
+        for (int t = 0; t < NA; ++t) a_off[t] = r0 + t * RPP < M - bm0 ? (unsigned)(r0 + t * RPP) * lda_b : a_out;
         if constexpr (ROWS) {
+            const unsigned b_out = outside(b_base, N - bn0);
 #pragma unroll
-            for (int t = 0; t < NB; ++t) b_off[t] = (unsigned)min(r0 + t * RPP, N - 1 - bn0) * ldb_b;
+            for (int t = 0; t < NB; ++t) b_off[t] = r0 + t * RPP < N - bn0 ? (unsigned)(r0 + t * RPP) * ldb_b : b_out;
         } else {
 #pragma unroll
             for (int t = 0; t < UNITS; ++t) {
@@ -451,7 +456,7 @@ void gemm_kernel(const GemmArgs p) {
         // (LDS buffer s % 2) run while they are on their way
         stream_load(grp, ra, rb);
         if (grp < nkt) stream_store(0, grp, ra, rb);
-        stream_load(grp + KG, ra, rb);
+        if (grp + KG < nkt) stream_load(grp + KG, ra, rb);
         __syncthreads();
         for (int s = 0; s < nsteps; ++s) {
             const int kt = s * KG + grp;
