@@ -965,15 +965,24 @@ bool skinny_takes(const Problem& pr, int cfg, int mode) {
 }
 
 // rows of A or B that do not start at multiples of four bytes
-bool skinny_bytes(const GemmArgs& g, int dt) {
+bool rows_off_dwords(const GemmArgs& g, int dt) {
     return ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B) | (uintptr_t)(g.lda * esize(dt)) | (uintptr_t)(g.ldb * esize(dt))) & 3u) != 0;
+}
+
+// Does shallow_tile take a product that the tiling `cfg` would take?  One 64 x 64 generic tile's k: rows contiguous along k, of 16 to 128
+// bytes, at any address; results and comparisons are that tile's.  By itself: up to 96 bytes and two rounds of workgroups, off dwords one
+// round beyond 64 bytes.  Fp16, N x K, in LDS / so, us: 250 x 1000 rows of 26 bytes unprotected 3.5 / 2.9, 62 bytes thread-level 4.0 / 3.6, 92
+// 3.9 / 3.5, 94 4.0 / 3.8, 110 4.0 / 4.1, 124 3.8 / 4.1; 1000 x 2040 62 bytes 4.8 / 4.5, 92 4.6 / 4.2, 74 4.7 / 4.9; 2000 x 2040 60 bytes 7.2 / 7.3.
+bool shallow_takes(const Problem& pr, int cfg, int mode) {
+    const long long kb = (long long)pr.K * esize(pr.dtype);
+    return cfg == CFG_G64 && (mode == ABFT_NONE || mode == ABFT_THREAD) && !pr.conv && pr.b_layout == ABFT_B_NK && kb >= 16 && kb <= 128;
 }
 
 // A product ready to be launched
 struct Prepared {
     GemmArgs g;
     int cfg, kmode, dtype;   // kmode: the kernels' scheme index
-    bool inj, skinny;
+    bool inj, skinny, shallow;
 };
 
 // Everything of a product up to its kernel's launch: checks, tiling, kernel arguments, and the launches that
@@ -1090,6 +1099,9 @@ int prepare_problem(const Problem& pr, int mode, const void* beta, void* workspa
     out.kmode = kmode;
     out.dtype = pr.dtype;
     out.inj = inj;
+    const long long blocks = (long long)g.tiles_m * g.tiles_n;
+    out.shallow = !inj && !g.alpha_out && shallow_takes(pr, cfg, mode) && blocks <= 512 &&
+                  (long long)pr.K * esize(pr.dtype) <= (blocks > 256 && rows_off_dwords(g, pr.dtype) ? 64 : 96);
     out.skinny = !g.alpha_out && skinny_takes(pr, cfg, mode);
     if (out.skinny) {
         // (its k tiles are of 128 bytes; a planted fault lands in the share of the tiling's shares that it names)
@@ -1109,9 +1121,13 @@ int run_problem(const Problem& pr, int mode, const void* beta, void* workspace, 
     if (g_ev_start && hipEventRecord(g_ev_start, st) != hipSuccess) return ABFT_E_HIP;
     if (w.skinny) {
         const int columns = cfg_info_host(w.cfg).wn;
-        e = w.dtype == ABFT_F16    ? launch_skinny_f16(w.kmode, skinny_bytes(w.g, w.dtype), columns, w.g, st)
-            : w.dtype == ABFT_BF16 ? launch_skinny_bf16(w.kmode, skinny_bytes(w.g, w.dtype), columns, w.g, st)
-                                   : launch_skinny_i8(w.kmode, skinny_bytes(w.g, w.dtype), columns, w.g, st);
+        e = w.dtype == ABFT_F16    ? launch_skinny_f16(w.kmode, rows_off_dwords(w.g, w.dtype), columns, w.g, st)
+            : w.dtype == ABFT_BF16 ? launch_skinny_bf16(w.kmode, rows_off_dwords(w.g, w.dtype), columns, w.g, st)
+                                   : launch_skinny_i8(w.kmode, rows_off_dwords(w.g, w.dtype), columns, w.g, st);
+    } else if (w.shallow) {
+        e = w.dtype == ABFT_F16    ? launch_shallow_f16(w.kmode, rows_off_dwords(w.g, w.dtype), w.g, st)
+            : w.dtype == ABFT_BF16 ? launch_shallow_bf16(w.kmode, rows_off_dwords(w.g, w.dtype), w.g, st)
+                                   : launch_shallow_i8(w.kmode, rows_off_dwords(w.g, w.dtype), w.g, st);
     } else if (w.dtype == ABFT_F16) e = launch_gemm_f16(w.cfg, w.kmode, w.inj, w.g, st);
     else if (w.dtype == ABFT_BF16) e = launch_gemm_bf16(w.cfg, w.kmode, w.inj, w.g, st);
     else e = launch_gemm_i8(w.cfg, w.kmode, w.inj, w.g, st);
@@ -1841,20 +1857,15 @@ struct PassWindow {
     // wavefront, unprotected or thread-level, for matrices of at most 512 tiles (beyond two rounds of workgroups a launch
     // of its own is full) that leave no activation checksums to the layer behind them
     static constexpr int SKINNY = CFG_COUNT, SHALLOW = CFG_COUNT + 1;
-    // ... or, in a launch of the streaming kernel with four wavefronts, a product of one 64 x 64 generic tile's k: rows contiguous along k,
-    // of 16 to 128 bytes, at any address
-    static bool shallow(const Problem& pr, int mode) {
-        const long long kb = (long long)pr.K * esize(pr.dtype);
-        return (mode == ABFT_NONE || mode == ABFT_THREAD) && !pr.conv && pr.b_layout == ABFT_B_NK && kb >= 16 && kb <= 128 &&
-               pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode) == CFG_G64;
-    }
+    // ... or, in a launch of the streaming kernel with four wavefronts, a product for shallow_tile
     static bool takes_shallow(int cfg) { return cfg == CFG_S32 || cfg == CFG_S64 || cfg == CFG_S128; }
     int shared_cfg(int i, const Problem& pr, int mode) const {
         const abft_plan::Layer& L = plan->layers[i];
         if (pr.M <= SKINNY_ROWS && skinny_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
             return SKINNY;
         const bool hands_over = i + 1 < (int)plan->layers.size() && A[i + 1] == C[i] && lda[i + 1] == ldc[i] && handover_target(plan, i + 1, C[i], ldc[i]);
-        if (shallow(pr, mode)) return hands_over ? -1 : (int)SHALLOW;
+        if (shallow_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
+            return hands_over ? -1 : (int)SHALLOW;
         if (!a_vectorisable(pr) || !b_vectorisable(pr) || ((long long)pr.K * esize(pr.dtype)) % 128 != 0) return -1;
         if (pr.conv && conv_lowering(pr).ok) return -1;
         const int cfg = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, true, mode, pr.conv);
@@ -1898,10 +1909,10 @@ struct PassWindow {
             it.M = g.M; it.N = g.N; it.K = g.K; it.tiles_m = g.tiles_m; it.tiles_n = g.tiles_n; it.act = g.act;
             it.conv = g.conv; it.H = g.H; it.W = g.W; it.Cin = g.Cin; it.KH = g.KH; it.KW = g.KW;
             it.stride = g.stride; it.pad = g.pad; it.OH = g.OH; it.OW = g.OW; it.pix = g.pix;
-            it.shallow = w.cfg == CFG_G64;
+            it.shallow = w.cfg != CFG_G64 ? 0 : rows_off_dwords(g, slot.dtype) ? 2 : 1;
             if (slot.cfg == SKINNY) {
                 it.tiles_n = (int)cdiv(g.N, 16);
-                it.bytes = skinny_bytes(g, slot.dtype);
+                it.bytes = rows_off_dwords(g, slot.dtype);
             }
             a.first[q] = blocks;
             blocks += it.tiles_m * it.tiles_n;

@@ -31,7 +31,7 @@ struct GroupItem {
     int M, N, K, tiles_m, tiles_n, act;
     int conv, H, W, Cin, KH, KW, stride, pad, OH, OW, pix;
     int bytes;   // skinny kernel: rows at addresses that are no multiples of four
-    int shallow; // streaming kernel's launches: a product for shallow_tile
+    int shallow; // streaming kernel's launches: a product for shallow_tile (2: rows at such addresses)
 };
 
 struct GroupArgs {
@@ -42,7 +42,7 @@ struct GroupArgs {
 static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments");
 
 // The product that workgroup bid works on; bid becomes its index among that product's workgroups.
-__device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, bool* shallow = nullptr) {
+__device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, int* shallow = nullptr) {
     int i = 0;
 #pragma unroll
     for (int q = 1; q < GROUP_MAX; ++q) i += bid >= a.first[q] ? 1 : 0;
@@ -67,7 +67,7 @@ __device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, 
     g.tiles_m = L.tiles_m; g.tiles_n = L.tiles_n;
     g.act = L.act;
     g.alpha_out = nullptr; g.ld_alpha_out = 0; g.alpha_in = nullptr;
-    if (shallow) *shallow = L.shallow != 0;
+    if (shallow) *shallow = L.shallow;
     return g;
 }
 
@@ -75,7 +75,8 @@ __device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, 
 // tile for such products, every wavefront with its 32 x 32 MFMA block straight from memory, in registers, since no wavefront
 // reads a row of A or B more than one other does.  Bound: the latency of one load.  DLRM's first layer (K = 13) so goes out
 // with the first of the other MLP, which takes 32 workgroups beside 256: batch 256 27.0 -> 23.6 us a pass (five launches instead of six).
-template <int DT, int MODE>
+// BYTES: rows off multiples of four bytes, in whole dwords shifted down (gemm_skinny.h says why, and why that leaves no row's dwords).
+template <int DT, int MODE, bool BYTES>
 __device__ __forceinline__ void shallow_tile(const GemmArgs& p, int tile_m, int tile_n, char* smem) {
     typedef typename CfgOf<DT, CFG_G64>::type CFG;
     typedef Mma<DT, 32> MMA;
@@ -92,13 +93,32 @@ __device__ __forceinline__ void shallow_tile(const GemmArgs& p, int tile_m, int 
     const i32x4 zero = {0, 0, 0, 0};
     // the chunk at byte c of a row: one that K cuts short is the row's last 16 bytes shifted down, one beyond K zeros
     i32x4 va[4], vb[4];
+    int more_a[4], more_b[4];
+    auto fetch = [](const char* from, i32x4& v, int& more) {
+        if constexpr (BYTES) {
+            const int off = (int)(reinterpret_cast<uintptr_t>(from) & 3u);
+            v = ld16u(from - off);
+            more = ld4u(from - off + (off ? 16 : 12));
+        } else {
+            v = ld16u(from);
+        }
+    };
+    auto whole = [](const char* from, const i32x4& v, int more) {
+        if constexpr (!BYTES) return v;
+        const unsigned off = (unsigned)(reinterpret_cast<uintptr_t>(from) & 3u);
+        i32x4 x;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) x[d] = (int)__builtin_amdgcn_alignbyte((unsigned)(d < 3 ? v[d + 1] : more), (unsigned)v[d], off);
+        return x;
+    };
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         const int off = min(32 * kk + 16 * (lane >> 5), kb - 16);
         va[kk] = vb[kk] = zero;
+        more_a[kk] = more_b[kk] = 0;
         if (32 * kk < kb) {
-            va[kk] = ld16u(a + off);
-            vb[kk] = ld16u(b + off);
+            fetch(a + off, va[kk], more_a[kk]);
+            fetch(b + off, vb[kk], more_b[kk]);
         }
     }
     typename MMA::Acc acc[1][1], chk[CheckRegs<CFG, MODE>::N];
@@ -108,8 +128,8 @@ __device__ __forceinline__ void shallow_tile(const GemmArgs& p, int tile_m, int 
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         if (32 * kk >= kb) break;
-        const int c = 32 * kk + 16 * (lane >> 5), early = c - min(c, kb - 16);
-        i32x4 fa[1] = {va[kk]}, fb[1] = {vb[kk]};
+        const int c = 32 * kk + 16 * (lane >> 5), off = min(c, kb - 16), early = c - off;
+        i32x4 fa[1] = {whole(a + off, va[kk], more_a[kk])}, fb[1] = {whole(b + off, vb[kk], more_b[kk])};
         if (32 * kk + 32 > kb) {
             fa[0] = early < 16 ? shift_down(fa[0], early & 15) : zero;
             fb[0] = early < 16 ? shift_down(fb[0], early & 15) : zero;
@@ -122,19 +142,28 @@ __device__ __forceinline__ void shallow_tile(const GemmArgs& p, int tile_m, int 
     epilogue<CFG, MODE>(acc, chk, p, tile_m, tile_n, smem);
 }
 
+// One such product by itself, its tiles in the generic kernel's order.
+template <int DT, int MODE, bool BYTES>
+__global__ __launch_bounds__((CfgOf<DT, CFG_G64>::type::THREADS)) void gemm_shallow_kernel(const GemmArgs p) {
+    int tile_m, tile_n;
+    generic_tile_of_block((int)blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
+    shallow_tile<DT, MODE, BYTES>(p, tile_m, tile_n, nullptr);
+}
+
 template <int DT, int ID, int NST, int MODE>
 __global__ __launch_bounds__((64 * CfgOf<DT, ID>::KWAYS)) void gemm_group_kernel(const GroupArgs a) {
     typedef typename CfgOf<DT, ID>::type CFG;
     constexpr int KWAYS = CfgOf<DT, ID>::KWAYS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int bid = (int)blockIdx.x;
-    bool shallow;
+    int shallow;
     const GemmArgs g = group_product(a, bid, &shallow);
     int tile_m, tile_n;
     tile_of_block(bid, g.tiles_m, g.tiles_n, tile_m, tile_n);
     if constexpr (KWAYS == 4 && MODE != MODE_GLOBAL) {
         if (shallow) {
-            shallow_tile<DT, MODE>(g, tile_m, tile_n, smem);
+            if (shallow == 2) shallow_tile<DT, MODE, true>(g, tile_m, tile_n, smem);
+            else shallow_tile<DT, MODE, false>(g, tile_m, tile_n, smem);
             return;
         }
     }
@@ -179,6 +208,10 @@ __global__ __launch_bounds__(64 * SKINNY_WAVES) void gemm_skinny_group_kernel(co
 hipError_t launch_group_f16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 hipError_t launch_group_bf16(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
 hipError_t launch_group_i8(int cfg, int mode, int blocks, const GroupArgs& args, hipStream_t stream);
+// one product for shallow_tile (mode: MODE_NONE or MODE_THREAD; bytes: rows at addresses that are no multiples of four)
+hipError_t launch_shallow_f16(int mode, bool bytes, const GemmArgs& args, hipStream_t stream);
+hipError_t launch_shallow_bf16(int mode, bool bytes, const GemmArgs& args, hipStream_t stream);
+hipError_t launch_shallow_i8(int mode, bool bytes, const GemmArgs& args, hipStream_t stream);
 // the skinny kernel: one product (mode: MODE_NONE or wavefront-level; args.f_row >= 0: with a planted fault; bytes: rows at addresses that are no multiples of four; columns: of the
 // comparisons that a report counts, 16 or 32), several
 hipError_t launch_skinny_f16(int mode, bool bytes, int columns, const GemmArgs& args, hipStream_t stream);

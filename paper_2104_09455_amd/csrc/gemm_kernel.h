@@ -60,16 +60,8 @@ void gemm_kernel(const GemmArgs p) {
     const int wave_m = wave / CFG::WAVES_N, wave_n = wave % CFG::WAVES_N;
     const int lrow = lane % MI, lgrp = lane / MI;
 
-    // workgroup -> tile: more tile columns than rows: every die its own run of them (tile_of_block); else consecutive
-    // workgroups walk down M within a band of tile columns, which gives it rows of A of its own.  (300 x 3000 x 1001
-    // fp16 11.1 -> 9.6 us, 37 x 4001 x 2000 8.6 -> 7.1, 1900 x 4000 x 4000 87 -> 82; 2000 x 600 x 4090 43 walking, 45 in runs)
     int tile_m, tile_n;
-    if (p.tiles_n > p.tiles_m) {
-        tile_of_block((int)blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    } else {
-        tile_n = (int)blockIdx.x / p.tiles_m;
-        tile_m = (int)blockIdx.x - tile_n * p.tiles_m;
-    }
+    generic_tile_of_block((int)blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
     const int bm0 = tile_m * BM, bn0 = tile_n * BN;
 
     const int M = p.M, N = p.N, K = p.K;

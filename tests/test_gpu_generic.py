@@ -204,3 +204,35 @@ def test_pitches_beyond_32_bit_offsets(case, dtype):
         del dA, dB
     got = stored[B.THREAD].cpu().numpy()
     assert c_close(got.astype(np.int64) if dtype == "i8" else got.astype(np.float64), C_ref, dtype)
+
+
+# (M, N, K in bytes): one chunk, the whole k tile, between; one tile and one row or column more, many tiles more wide than high
+# and more high than wide
+SHALLOW = [(17, 1, 16), (64, 64, 128), (65, 63, 18), (33, 130, 58), (41, 157, 34), (129, 200, 112), (700, 70, 126), (70, 1500, 98), (488, 276, 106)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("shape", SHALLOW, ids=str)
+def test_products_of_one_k_tile_straight_from_memory_are_those_of_the_tile_in_lds(shape, dtype):
+    """Rows of 16 to 128 bytes, unprotected and thread-level, go without LDS; a planted fault's call does not: the same
+    elements bit by bit, as many comparisons, and NaN in an input is flagged."""
+    M, N, K = shape[0], shape[1], shape[2] // (1 if dtype == "i8" else 2)
+    A, Bm = wl.gemm_operands(M, N, K, dtype, seed=M + N + K, dist_a="normal", dist_b="normal")
+    C_ref = oracle.gemm(A, Bm, dtype)
+    i, j = M - 1, N - 1
+    for mode in (B.NONE, B.THREAD):
+        for kw in (dict(misalign=1), dict(lda_pad=3, ldb_pad=1, ldc_pad=5, want_report=False)):
+            assert B.abft_kernel_name(M, N, K, DT[dtype], mode, False) == "G64"
+            print("case", shape, dtype, mode, kw, flush=True)
+            r = run_gemm(A, Bm, dtype, mode, **kw)
+            assert c_close(r.C, C_ref, dtype) and r.flag == 0
+            bad = run_gemm(A, Bm, dtype, mode, inject=B.Fault(i, j, 30, -1), **kw)
+            if r.report and mode != B.NONE:
+                assert r.report.tiles == bad.report.tiles == -(-M // 32) * -(-N // 32) and r.report.worst_ratio == 0.0
+            same = bad.C == r.C
+            same[i, j] = True
+            assert same.all() and bad.flag == (mode != B.NONE)
+            if dtype != "i8":
+                lost = A.copy()
+                lost[i, K - 1] = np.float16("nan") if dtype == "f16" else 0x7fc0
+                assert run_gemm(lost, Bm, dtype, mode, **kw).flag == (mode != B.NONE)
