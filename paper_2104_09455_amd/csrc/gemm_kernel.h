@@ -330,16 +330,16 @@ void gemm_kernel(const GemmArgs p) {
     const unsigned kb = (unsigned)K * ESIZE, lda_b = (unsigned)(p.lda * ESIZE), ldb_b = (unsigned)(p.ldb * ESIZE);
     const char* const a_base = p.A + (long long)bm0 * p.lda * ESIZE;
     const char* const b_base = ROWS ? p.B + (long long)bn0 * p.ldb * ESIZE : p.B;
-    unsigned a_off[NA], b_off[ROWS ? NB : UNITS], b_col[ROWS ? 1 : UNITS];
+    unsigned a_off[NA], b_off[ROWS ? NB : UNITS], b_col[ROWS ? 1 : UNITS], a_out = 0, b_out = 0;
     if constexpr (STREAM) {
         // (rows outside read chunks of 16 aligned bytes near the first row's, the same ones for all: off the dword, a row each costs
         // the vector memory path four times as much; up to 15 bytes behind the first row's, so only where there is a second)
         auto outside = [](const char* base, int rows) { return rows > 1 ? (unsigned)(-reinterpret_cast<uintptr_t>(base) & 15u) : 0u; };
-        const unsigned a_out = outside(a_base, M - bm0);
+        a_out = outside(a_base, M - bm0);
 #pragma unroll
         for (int t = 0; t < NA; ++t) a_off[t] = r0 + t * RPP < M - bm0 ? (unsigned)(r0 + t * RPP) * lda_b : a_out;
         if constexpr (ROWS) {
-            const unsigned b_out = outside(b_base, N - bn0);
+            b_out = outside(b_base, N - bn0);
 #pragma unroll
             for (int t = 0; t < NB; ++t) b_off[t] = r0 + t * RPP < N - bn0 ? (unsigned)(r0 + t * RPP) * ldb_b : b_out;
         } else {
@@ -354,13 +354,15 @@ void gemm_kernel(const GemmArgs p) {
     // rows of weights K x N whose offsets stay in 31 bits: a power of two, whole k tiles
     const int b_run = LD == LD_TURN_RUNS ? 1 << (31 - __builtin_clz(0x7fffffffu / ldb_b)) : 0;
     auto chunk_from = [&](int kt) { return min((unsigned)kt * BKB + (unsigned)kc * 16, kb - 16); };   // the byte of its row
-    auto stream_load = [&](int kt, i32x4(&ra)[NA], i32x4(&rb)[NB]) {
+    // first: chunks beyond K as rows outside (where there is one k tile, most of its chunks may be such)
+    auto stream_load = [&](int kt, i32x4(&ra)[NA], i32x4(&rb)[NB], auto first) {
         const unsigned from = chunk_from(kt);
+        const bool beyond = decltype(first)::value && (unsigned)kt * BKB + (unsigned)kc * 16 >= kb;
 #pragma unroll
-        for (int t = 0; t < NA; ++t) ra[t] = ld16u(a_base + (a_off[t] + from));
+        for (int t = 0; t < NA; ++t) ra[t] = ld16u(a_base + (beyond ? a_out : a_off[t] + from));
         if constexpr (ROWS) {
 #pragma unroll
-            for (int t = 0; t < NB; ++t) rb[t] = ld16u(b_base + (b_off[t] + from));
+            for (int t = 0; t < NB; ++t) rb[t] = ld16u(b_base + (beyond ? b_out : b_off[t] + from));
         } else {
             // (rows past K read the last one, dropped on the way to LDS)
             const int k0 = min(kt, nkt - 1) * BK;
@@ -446,14 +448,14 @@ void gemm_kernel(const GemmArgs p) {
         static_assert(!INJ, "injected faults go through the other loaders");
         // step s: tile s + 1 of the group moves from registers to LDS, the loads of tile s + 2 go out, the products of tile s
         // (LDS buffer s % 2) run while they are on their way
-        stream_load(grp, ra, rb);
+        stream_load(grp, ra, rb, std::true_type{});
         if (grp < nkt) stream_store(0, grp, ra, rb);
-        if (grp + KG < nkt) stream_load(grp + KG, ra, rb);
+        if (grp + KG < nkt) stream_load(grp + KG, ra, rb, std::false_type{});
         __syncthreads();
         for (int s = 0; s < nsteps; ++s) {
             const int kt = s * KG + grp;
             if (kt + KG < nkt) stream_store((s & 1) ^ 1, kt + KG, ra, rb);
-            if (kt + 2 * KG < nkt) stream_load(kt + 2 * KG, ra, rb);
+            if (kt + 2 * KG < nkt) stream_load(kt + 2 * KG, ra, rb, std::false_type{});
             if (KG == 1 || kt < nkt) multiply(s & 1);
             __syncthreads();
         }
