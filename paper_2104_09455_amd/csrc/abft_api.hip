@@ -950,18 +950,30 @@ bool strip_fits(const Problem& pr, int Kp, int segp, int& rows, int& pitch) {
     return true;
 }
 
-// Does the skinny kernel take a product that the tiling `cfg` would take?  At most sixteen rows of 32 x 32 streaming tiles or of
+// Can the skinny kernel run a product that the tiling `cfg` would take?  At most sixteen rows of 32 x 32 streaming tiles or of
 // the generic kernel's tiles for few rows, both operands contiguous along k in rows of a chunk or more, and at most two
-// workgroups of 16 columns per compute unit; only the global scheme needs the tiling's column blocks.  Thread-level, the tiling's kernel / skinny (us, calls of 7 to
-// 7.5 us are the caller's own): 16 x 4096 x 4096 bf16 8.3 / 8.1, 16 x 4096 x 8192 13.1 / 12.8, 12 x 2048 x 8192 11.8 / 9.7,
-// 16 x 64 x 8192 10.5 / 7.9; unaligned 16 x 1000 x 2047 14.9 / 7.1, 16 x 8000 x 4003 25.6 / 16.8, 16 x 64 x 4095 24.8 / 8.2; DLRM's eight
-// layers at batch 1 24.3 / 18.2.  Aligned with more than one workgroup per compute unit and many weights the tiles of 32
-// columns, which read A half as often, are ahead: 16 x 6144 x 2560 8.2 / 8.6, 16 x 8192 x 4096 12.7 / 13.1, 1 x 8192 x 8192 27.7 / 32.
-bool skinny_takes(const Problem& pr, int cfg, int mode) {
+// workgroups of 16 columns per compute unit; only the global scheme needs the tiling's column blocks.
+bool skinny_fits(const Problem& pr, int cfg, int mode) {
     if (cfg != CFG_S32 && cfg != CFG_S32W && cfg != CFG_G16 && cfg != CFG_G64K) return false;
     const long long kb = (long long)pr.K * esize(pr.dtype);
     return pr.M <= SKINNY_ROWS && !pr.conv && pr.b_layout == ABFT_B_NK && mode != ABFT_GLOBAL && mode != ABFT_GLOBAL_WEIGHTED &&
-           kb >= 16 && kb < (1 << 30) && pr.N <= 16 * 512 && (cfg_is_generic(cfg) || pr.N <= 16 * 256 || pr.N * kb <= (16 << 20));
+           kb >= 16 && kb < (1 << 30) && pr.N <= 16 * 512;
+}
+
+// Does it?  Thread-level, the tiling's kernel / skinny (us a call of many in a graph; the first three alone):
+// 16 x 4096 x 4096 bf16 8.3 / 8.0, 16 x 4096 x 8192 13.1 / 12.8, 12 x 2048 x 8192 11.8 / 9.7; 16 x 5120 x 1024 fp16 4.60 / 4.20, 16 x
+// 8192 x 1024 4.65 / 4.28, 8 x 8192 x 2048 int8 4.50 / 4.18; unaligned 16 x 1000 x 2047 14.9 / 7.1, 16 x 8000 x 4003 25.6 / 16.8.
+// Aligned with more than one workgroup per compute unit and many weights the tiles of 32 columns, which read A half
+// as often, are ahead: 16 x 6144 x 2560 8.2 / 8.6, 16 x 8192 x 4096 12.7 / 13.1, 1 x 8192 x 8192 27.7 / 32; unprotected they are with
+// few, too: 16 x 8192 x 256 bytes 2.79 / 3.05, 1 KB 3.24 / 3.36, 16 x 5120 x 1024 fp16 level.  So is, unaligned, the 16 x 64 tile on one of
+// its k tiles (256 bytes): 1 x 5760 x 61 fp16 unprotected 2.83 / 3.13, thread-level 3.20 / 3.46, on two 1 x 5760 x 189 thread-level 3.79 / 3.46; with at
+// most one workgroup per compute unit it is not (unprotected 1 x 2048 x 253 int8 2.82 / 2.65; thread-level 16 x 512 x 61 fp16 3.21 / 3.01).
+bool skinny_takes(const Problem& pr, int cfg, int mode) {
+    if (!skinny_fits(pr, cfg, mode)) return false;
+    const long long kb = (long long)pr.K * esize(pr.dtype);
+    const bool one_round = pr.N <= 16 * 256, checked = mode != ABFT_NONE;
+    if (cfg_is_generic(cfg)) return kb > 256 || one_round;
+    return one_round || (checked && pr.N * kb <= (16 << 20));
 }
 
 // rows of A or B that do not start at multiples of four bytes
@@ -1861,8 +1873,11 @@ struct PassWindow {
     static bool takes_shallow(int cfg) { return cfg == CFG_S32 || cfg == CFG_S64 || cfg == CFG_S128; }
     int shared_cfg(int i, const Problem& pr, int mode) const {
         const abft_plan::Layer& L = plan->layers[i];
-        if (pr.M <= SKINNY_ROWS && skinny_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
-            return SKINNY;
+        if (pr.M <= SKINNY_ROWS) {
+            // (also where it would be slower alone, if its results are the tiling's bit by bit: the 16 x 64 tile's on one k tile, whose sums nobody shares)
+            const int alone = pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv);
+            if (skinny_takes(pr, alone, mode) || (alone == CFG_G16 && skinny_fits(pr, alone, mode) && (long long)pr.K * esize(pr.dtype) <= 128)) return SKINNY;
+        }
         const bool hands_over = i + 1 < (int)plan->layers.size() && A[i + 1] == C[i] && lda[i + 1] == ldc[i] && handover_target(plan, i + 1, C[i], ldc[i]);
         if (shallow_takes(pr, pick_cfg(pr.M, pr.N, pr.K, pr.dtype, a_vectorisable(pr) && b_vectorisable(pr), mode, pr.conv), mode))
             return hands_over ? -1 : (int)SHALLOW;
@@ -2049,7 +2064,7 @@ int abft_plan_run_chain(abft_plan_t* plan, int first, int count, const void* A, 
         one_launch = L.chain_beta != nullptr && d.dtype == d0.dtype && d.M == d0.M &&
                      pick_cfg(d.M, d.N, d.K, d.dtype, true, L.mode) == CFG_S32 && !L.report && !L.has_fault &&
                      (L.mode == ABFT_NONE || L.mode == ABFT_GLOBAL || L.mode == ABFT_THREAD) && C[i] != nullptr &&
-                     // (else a launch of its own runs on the skinny kernel, and layer by layer is faster: 16 x 512 -> 1024 -> 1024
+                     // (else most layers' own launches run on the skinny kernel, and layer by layer is faster: 16 x 512 -> 1024 -> 1024
                      // -> 512 -> 256 -> 1 fp16 thread-level 16.0 us, in one launch 21.5; 1 x 512 -> 256 -> 64 5.8 / 8.5; so, too, where
                      // that kernel leaves a layer of more weights to 32 x 32 tiles: 16 x 2048 -> 8192 -> 2048 18.9 / 77)
                      (d.M > SKINNY_ROWS || L.mode == ABFT_GLOBAL) &&

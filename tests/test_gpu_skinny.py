@@ -76,7 +76,9 @@ def test_layers_of_few_rows_share_a_launch_at_any_alignment(dtype):
     from test_gpu_shared_launch import Pass
     for mode in (B.NONE, B.THREAD):
         p = Pass(dtype, mode)
-        for M, N, K in ((1, 512, 32), (16, 40, 29), (16, 1, 256), (7, 1024, 1040), (3, 96, 4096), (16, 33, 8400)):
+        # (rows of one k tile, 16 to 128 bytes, of many columns: by themselves on the 16 x 64 tile)
+        for M, N, K in ((1, 512, 32), (16, 40, 29), (16, 1, 256), (7, 1024, 1040), (3, 96, 4096), (16, 33, 8400),
+                        (16, 5000, 17), (2, 7001, 61), (11, 20, 128 if dtype == "i8" else 63)):
             p.add((M, N, K), p.rnd(M, K), p.out(M, N, pad=N % 3), relu=N == 40)
         p.both_ways(shared=1)
     assert torch.cuda.is_available()
