@@ -148,6 +148,9 @@ typedef struct {
 /* What the checksum comparisons saw; optional diagnostics written by the device.
  * Both schemes make one comparison per region of C: GLOBAL per workgroup tile
  * (abft_region_shape), THREAD per wavefront register tile (abft_tile_shape).
+ * (Products of at most 16 rows may be compared per 16 columns instead, with the tolerance of those 16, with a report and
+ * without; the report still counts regions of abft_tile_shape, gives the sums of a whole region and, as worst_ratio, the
+ * larger ratio of its two halves.)
  * lhs = output summation of the region with the largest |lhs - rhs| / tau seen,
  * rhs = its checksum product, tau = its tolerance, worst_ratio = that ratio (0 when
  * tau = 0 and both sides are equal, +inf when they differ or are not finite); ties go to
@@ -294,12 +297,17 @@ int abft_region_shape(int M, int N, int K, int dtype, int aligned, int *region_m
  * register tile, wavefront w multiplying the k with (k / step) % ways == w; their partial
  * tiles are added in wavefront order at the end (bit-reproducible) and every scheme makes its
  * comparison on the added-up tile, so the split only matters for where an injected fault
- * lands (abft_fault_t).  ways = 1: not split. */
+ * lands (abft_fault_t).  ways = 1: not split.  Products of at most 16 rows may run on a kernel that
+ * splits k eight ways, 128 bytes at a time; a fault there still lands in the sum that this
+ * says, which that kernel puts together from its shares. */
 int abft_k_ways(int M, int N, int K, int dtype, int aligned, int mode, int *ways, int *step);
 /* Name of the tile configuration a product runs on under `mode` (diagnostics; NULL: a value out of
  * range).  conv != 0: a convolution that is read as an implicit M x K matrix; unprotected ones can
  * run on another configuration than a product of their size.  (Convolutions whose input rows stay in LDS, among them
- * lowered ones whose name here is that of another tile with the same regions of C, run "R64"'s tiles.) */
+ * lowered ones whose name here is that of another tile with the same regions of C, run "R64"'s tiles.  The name stands for
+ * the regions and the split of k; three kernels take products in other configurations' place, with these: at most 16 rows
+ * in that of "S32", "S32W", "G16" and "G64K" (16 columns per workgroup), k of at most 128 bytes in that of "G64" (straight from
+ * memory), unaligned products of at most 128 tiles of 64 x 64 in that of "G64K" (32 x 64 per workgroup).) */
 const char *abft_kernel_name(int M, int N, int K, int dtype, int aligned, int mode, int conv);
 
 /* Comparison tolerance (the paper states none; Sec. 2.4 step 4 says "compare").  A comparison

@@ -6,7 +6,8 @@
 // workgroup takes 16 columns (a 16 x 16 MFMA shape: no rows of zeros beside them), eight wavefronts share its k tiles (128
 // bytes; wavefront w those with t % 8 == w).  A wavefront's rows travel through registers, two k tiles ahead, and through
 // its own 4 KB of LDS into fragments; no barrier before the sums.  (Sixteen wavefronts, or three tiles ahead: DLRM at
-// batch 1 19.6 and 18.5 us, so 18.2, start of the 32 x 32 tiles' kernel 24.3; 16 x 4096 x 4096 bf16 8.6 and 8.4, so 8.1.)
+// batch 1 19.6 and 18.5 us, so 18.2, in one run on one card; 16 x 4096 x 4096 bf16 8.6 and 8.4, so 8.1.  Against the 32 x 32 tiles'
+// kernel, in turn, several cards: DLRM at batch 1 25.7-26.0 -> 22.3-22.6, 16 x 4096 x 4096 bf16 8.31 -> 8.02.)
 // The partial tiles meet in LDS; one wavefront per 16 x 16 block adds them in wavefront order, its checksum blocks
 // likewise, compares and stores.  On a clean tile both are the same bit for bit, which is all that is looked at without a
 // report: sums over the lanes are formed only where they differ.
