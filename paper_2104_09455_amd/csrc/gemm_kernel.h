@@ -354,7 +354,8 @@ void gemm_kernel(const GemmArgs p) {
     // rows of weights K x N whose offsets stay in 31 bits: a power of two, whole k tiles
     const int b_run = LD == LD_TURN_RUNS ? 1 << (31 - __builtin_clz(0x7fffffffu / ldb_b)) : 0;
     auto chunk_from = [&](int kt) { return min((unsigned)kt * BKB + (unsigned)kc * 16, kb - 16); };   // the byte of its row
-    // first: chunks beyond K as rows outside (where there is one k tile, most of its chunks may be such)
+    // first: chunks beyond K as rows outside (where there is one k tile, most of its chunks may be such).  (Zeros by address there, and no
+    // selects behind them: products of one k tile gain 0.05 us, 511 x 1000 x 2047 K x N loses 0.3.)
     auto stream_load = [&](int kt, i32x4(&ra)[NA], i32x4(&rb)[NB], auto first) {
         const unsigned from = chunk_from(kt);
         const bool beyond = decltype(first)::value && (unsigned)kt * BKB + (unsigned)kc * 16 >= kb;
@@ -370,10 +371,10 @@ void gemm_kernel(const GemmArgs p) {
             const char* const run = b_base + (long long)from_k * p.ldb * ESIZE;
 #pragma unroll
             for (int t = 0; t < UNITS; ++t) {
-                const unsigned first = (unsigned)(k0 - from_k) * ldb_b + b_off[t];
+                const unsigned row0 = (unsigned)(k0 - from_k) * ldb_b + b_off[t];
                 const unsigned last = (unsigned)(rows - 1) * ldb_b + b_col[t];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) rb[2 * t + (e >> 2)][e & 3] = ld4u(run + min(first + e * ldb_b, last));
+                for (int e = 0; e < 8; ++e) rb[2 * t + (e >> 2)][e & 3] = ld4u(run + min(row0 + e * ldb_b, last));
             }
         }
     };
