@@ -1924,7 +1924,7 @@ struct PassWindow {
             it.M = g.M; it.N = g.N; it.K = g.K; it.tiles_m = g.tiles_m; it.tiles_n = g.tiles_n; it.act = g.act;
             it.conv = g.conv; it.H = g.H; it.W = g.W; it.Cin = g.Cin; it.KH = g.KH; it.KW = g.KW;
             it.stride = g.stride; it.pad = g.pad; it.OH = g.OH; it.OW = g.OW; it.pix = g.pix;
-            it.shallow = w.cfg != CFG_G64 ? 0 : rows_off_dwords(g, slot.dtype) ? 2 : 1;
+            it.shallow = w.cfg == CFG_G64;
             if (slot.cfg == SKINNY) {
                 it.tiles_n = (int)cdiv(g.N, 16);
                 it.bytes = rows_off_dwords(g, slot.dtype);

@@ -31,7 +31,7 @@ struct GroupItem {
     int M, N, K, tiles_m, tiles_n, act;
     int conv, H, W, Cin, KH, KW, stride, pad, OH, OW, pix;
     int bytes;   // skinny kernel: rows at addresses that are no multiples of four
-    int shallow; // streaming kernel's launches: a product for shallow_tile (2: rows at such addresses)
+    int shallow; // streaming kernel's launches: a product for shallow_tile
 };
 
 struct GroupArgs {
@@ -42,7 +42,7 @@ struct GroupArgs {
 static_assert(sizeof(GroupArgs) <= 4096, "kernel arguments");
 
 // The product that workgroup bid works on; bid becomes its index among that product's workgroups.
-__device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, int* shallow = nullptr) {
+__device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, bool* shallow = nullptr) {
     int i = 0;
 #pragma unroll
     for (int q = 1; q < GROUP_MAX; ++q) i += bid >= a.first[q] ? 1 : 0;
@@ -67,7 +67,7 @@ __device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, 
     g.tiles_m = L.tiles_m; g.tiles_n = L.tiles_n;
     g.act = L.act;
     g.alpha_out = nullptr; g.ld_alpha_out = 0; g.alpha_in = nullptr;
-    if (shallow) *shallow = L.shallow;
+    if (shallow) *shallow = L.shallow != 0;
     return g;
 }
 
@@ -75,7 +75,8 @@ __device__ __forceinline__ GemmArgs group_product(const GroupArgs& a, int& bid, 
 // tile for such products, every wavefront with its 32 x 32 MFMA block straight from memory, in registers, since no wavefront
 // reads a row of A or B more than one other does.  Bound: the latency of one load.  DLRM's first layer (K = 13) so goes out
 // with the first of the other MLP, which takes 32 workgroups beside 256: batch 256 27.0 -> 23.6 us a pass (five launches instead of six).
-// BYTES: rows off multiples of four bytes, in whole dwords shifted down (gemm_skinny.h says why, and why that leaves no row's dwords).
+// BYTES (a product by itself): rows off multiples of four bytes, in whole dwords shifted down (gemm_skinny.h says why, and why that leaves
+// no row's dwords).
 template <int DT, int MODE, bool BYTES>
 __device__ __forceinline__ void shallow_tile(const GemmArgs& p, int tile_m, int tile_n, char* smem) {
     typedef typename CfgOf<DT, CFG_G64>::type CFG;
@@ -156,14 +157,15 @@ __global__ __launch_bounds__((64 * CfgOf<DT, ID>::KWAYS)) void gemm_group_kernel
     constexpr int KWAYS = CfgOf<DT, ID>::KWAYS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int bid = (int)blockIdx.x;
-    int shallow;
+    bool shallow;
     const GemmArgs g = group_product(a, bid, &shallow);
     int tile_m, tile_n;
     tile_of_block(bid, g.tiles_m, g.tiles_n, tile_m, tile_n);
     if constexpr (KWAYS == 4 && MODE != MODE_GLOBAL) {
         if (shallow) {
-            if (shallow == 2) shallow_tile<DT, MODE, true>(g, tile_m, tile_n, smem);
-            else shallow_tile<DT, MODE, false>(g, tile_m, tile_n, smem);
+            // (off dwords too without whole dwords: a second body's 6 KB of code cost launches that hold no such product, too: ResNet-50 at
+            // batch 1 89.5 -> 91.2 us, DLRM at 256 23.55 -> 23.8)
+            shallow_tile<DT, MODE, false>(g, tile_m, tile_n, smem);
             return;
         }
     }
